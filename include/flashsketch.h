@@ -191,9 +191,12 @@ fs_status fs_sketch_apply_static(fs_sketch_t h, const void* A, int64_t lda, int6
  *    than 128 rows in 128-row slices) and smaller Br input-stationary in groups of 128/Br
  *    wiring slots (G is read once per group).  Also needs 130*ldg*sizeof(elt) < 2^31 (input-stationary: 34*ldg*sizeof(elt));
  *    any Bc, and d need not be a multiple of it.
+ *    When there are too few blocks and examples for the chip, the stages of a work-group are
+ *    split over grid.z in both forms.
  *    Fastest when G, ldg*sizeof(elt) and Bc*sizeof(elt) are multiples of 16
- *    bytes (128-bit loads; otherwise four dword loads or, for an odd ldg of a 16-bit type,
- *    eight element loads per piece).  A row stride that is a large power of two maps the
+ *    bytes; a piece that starts on an odd 16-bit entry is loaded as the five dwords that hold
+ *    it (up to 2 bytes before G's first and after its last entry, inside the same dword, are
+ *    then loaded and discarded).  A row stride that is a large power of two maps the
  *    rows of a tile to one HBM channel: prefer ldg = d + 64 elements.
  *  - general: every other valid sketch (more than 128 padded rows of blocks whose padded
  *    height is 128 or more, with Br not a power of two or kappa > 128);
@@ -201,9 +204,11 @@ fs_status fs_sketch_apply_static(fs_sketch_t h, const void* A, int64_t lda, int6
  * Forcing FS_VARIANT_MFMA on a call the matrix-core kernel cannot take returns
  * FS_ERR_UNSUPPORTED (nothing is launched).
  * n == 0 is FS_OK.  Errors: NULL handle/G/out, n < 0, ldg < d, ldo < k, unknown dtype.
- * Workspace (matrix cores, input-stationary shapes only): kappa (times a row split) sets of
- * n x k floats, grown or attached as for fs_sketch_apply; fs_sketch_rows_workspace_bytes gives its size for
- * a well-aligned call.  The first call of a handle also uploads the 8*M-byte orbit table. */
+ * Workspace (matrix cores): kappa (times a row split) sets of n x k floats for input-stationary
+ * shapes, one set per split for output-stationary ones that are split; grown or attached as for
+ * fs_sketch_apply.  fs_sketch_rows_workspace_bytes gives the size a well-aligned call is fastest
+ * with; a smaller attached workspace is accepted when a coarser split fits (output-stationary
+ * calls run with none).  The first call of a handle also builds the 8*M-byte orbit table. */
 fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_t n, void* out,
                                int64_t ldo, fs_dtype dtype, void* stream);
 fs_status fs_sketch_rows_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dtype, size_t* bytes);
@@ -218,7 +223,8 @@ fs_status fs_sketch_rows_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dtyp
  * fs_sketch_set_variant choice is honoured.  Errors as for the apply it describes
  * (FS_ERR_INVALID_ARG, FS_ERR_UNSUPPORTED); any result pointer may be NULL. */
 typedef enum {
-  FS_PLAN_ELEMENT_LOADS = 1, /* A / G not aligned for vector loads: narrower loads, slower    */
+  FS_PLAN_ELEMENT_LOADS = 1, /* A / G not aligned for vector loads: narrower or unaligned
+                                loads, slower                                                  */
   FS_PLAN_ROW_SLICES = 2,    /* output blocks higher than 128 rows, served in 128-row slices   */
   FS_PLAN_SLOT_GROUPS = 4,   /* more than 128 stacked rows of small blocks: input read once
                                 per group of wiring slots                                      */
@@ -254,7 +260,8 @@ fs_status fs_sketch_prepare(fs_sketch_t h, void* stream);
  * what the most recent apply launched. */
 fs_status fs_sketch_info(fs_sketch_t h, fs_info* out);
 
-/* Bytes of device workspace an apply of n columns of `dtype` needs at most with the
+/* (A handle's own workspace starts at FS_STATIC_SCRATCH_BYTES when a call first needs one.)
+ * Bytes of device workspace an apply of n columns of `dtype` needs at most with the
  * handle's current variant setting (0 if none).  The workspace holds the fp32 partial results
  * of the cross-block accumulation (Section 5.3: each output tile is owned by one work-group and
  * summed without global atomics) when the work is split by INPUT block: kappa (times a row

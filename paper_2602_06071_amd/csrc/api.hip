@@ -106,6 +106,23 @@ fs_status ensure_workspace(fs_sketch_t h, size_t need) {
   return FS_OK;
 }
 
+// Workspace for a call that runs with `w.floor` bytes and is fastest with `w.want`.  An attached
+// workspace is taken as it is if it holds the floor.  The handle's own grows to `want`, except while
+// `st` is being captured into a graph: there nothing may be allocated, and a call that the present
+// size can serve is served by it.  Its first allocation is kSplitScratch at least, and `want` exceeds
+// the floor only up to that size: later calls free and replace it only for a larger floor, not
+// because a smaller problem is split into more pieces (captured graphs hold its address).
+fs_status ensure_workspace(fs_sketch_t h, const fs::Workspace& w, hipStream_t st) {
+  if (w.want <= h->ws_bytes) return FS_OK;
+  if (w.floor <= h->ws_bytes) {
+    if (h->ws && !h->ws_owned) return FS_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+    else if (cap != hipStreamCaptureStatusNone) return FS_OK;
+  }
+  return ensure_workspace(h, w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch);
+}
+
 // pos2blk[q] = f^q(0), blk2pos = its inverse: allocated once per handle and filled by a small
 // kernel enqueued on `st` (no copy, no synchronisation).
 fs_status ensure_orbit(fs_sketch_t h, hipStream_t st) {
@@ -430,7 +447,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   if (h->variant == FS_VARIANT_MFMA && !can) return FS_ERR_UNSUPPORTED;
   const bool use_mfma = can && h->variant != FS_VARIANT_GENERIC;
   hipStream_t st = (hipStream_t)stream;
-  fs_status rc = use_mfma ? ensure_workspace(h, fs::rows_workspace_bytes(h->p, G, ldg, n, dt)) : FS_OK;
+  fs_status rc = use_mfma ? ensure_workspace(h, fs::rows_workspace(h->p, G, ldg, n, dt), st) : FS_OK;
   if (rc != FS_OK) return rc;
   const ProfSet prof = next_events(h, st);
   const fs::EventPair ev = prof.kernel;
@@ -445,7 +462,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   }
   rc = ensure_orbit(h, st);  // the gather-reduction walks the wiring through this table
   if (rc != FS_OK) return rc;
-  const hipError_t e = fs::launch_rows(h->p, G, ldg, n, out, ldo, dt, h->ws, h->orbit, st, ev);
+  const hipError_t e = fs::launch_rows(h->p, G, ldg, n, out, ldo, dt, h->ws, h->ws_bytes, h->orbit, st, ev);
   if (prof.end) (void)hipEventRecord(prof.end, st);
   snprintf(h->last_kernel, sizeof(h->last_kernel), "rows_kernel");
   h->last_variant = FS_VARIANT_MFMA;
@@ -461,7 +478,7 @@ fs_status fs_sketch_rows_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dt, 
   const size_t esz = dt == FS_F32 ? 4 : 2;
   const int64_t ld = (h->p.d + 7) & ~(int64_t)7;  // a well-aligned call: packed rows rounded to 16 bytes
   if (34 * ld * (int64_t)esz >= ((int64_t)1 << 31)) return FS_OK;
-  *bytes = fs::rows_workspace_bytes(h->p, (const void*)(uintptr_t)256, ld, n, dt);
+  *bytes = fs::rows_workspace(h->p, (const void*)(uintptr_t)256, ld, n, dt).want;
   return FS_OK;
 }
 

@@ -68,6 +68,14 @@ fs_status apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, void*
 // Records a failed HIP call in the handle, clears the sticky error, returns FS_ERR_HIP.
 fs_status hip_fail(fs_sketch_t h, hipError_t e);
 
+// Device workspace of one call: `floor` bytes it must have, `want` (>= floor) what its fastest split
+// uses, more than the floor only up to kSplitScratch.  With less than `want` the planner takes a
+// split that fits.
+constexpr size_t kSplitScratch = (size_t)FS_STATIC_SCRATCH_BYTES;
+struct Workspace {
+  size_t floor = 0, want = 0;
+};
+
 // Each launcher validates nothing: api.hip has already checked every argument
 // and that the shape fits the kernel.  They return the launch's hipError_t.
 
@@ -118,9 +126,10 @@ hipError_t launch_stacked(const SketchParams& p, const void* A, int64_t lda, int
 bool rows_supported(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt);
 bool rows_describe(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, int* mode,
                    int* flags, size_t* workspace);
-size_t rows_workspace_bytes(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt);
+Workspace rows_workspace(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt);
+// ws_bytes: what ws holds; the row split is the best one that fits.
 hipError_t launch_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
-                       int64_t ldo, fs_dtype dt, void* ws, const uint32_t* orbit, hipStream_t st,
+                       int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev);
 
 // Plain SJLT, global float atomics.  ws: k*n floats for bf16 output, unused for fp32.

@@ -25,8 +25,7 @@
 //
 // Shapes: power-of-two Br (kappa*Br <= 128: tile height 32, 64 or 128, rows above kappa*Br idle;
 // more: Br < 32 in groups of wiring slots, Br in {32, 64, 128} output-stationary), any Bc and
-// alignment (128-bit loads need G, ldg and Bc to be multiples of 16 bytes).  Inputs must be finite (a dense
-// product also multiplies by the zeros).
+// alignment.  Inputs must be finite (a dense product also multiplies by the zeros).
 #include <type_traits>
 
 #include "handle.h"
@@ -47,8 +46,9 @@ struct RowsArgs {
   void* out;              // OUT mode: the result itself
   int64_t ldg, ldo;
   int n;        // examples
-  int stages;   // 64-row stages per work-group
-  int zsplit;       // IN: row splits of an input block
+  int stages;       // 64-entry stages per work-group (the last row split may have fewer)
+  int total;        // stages of an input block (IN) or of the kappa blocks an output block reads (OUT)
+  int zsplit;       // row splits: split z takes the stages [z*stages, min((z+1)*stages, total))
   int group_slots;  // IN: wiring slots one work-group stacks (grid.z = zsplit * slot groups)
   int nsub;         // OUT, Br > 128: 128-row slices of an output block (grid.y = example tiles * nsub)
   uint32_t log2_br;
@@ -61,14 +61,28 @@ struct RowsArgs {
 // fp32 with 64 stacked rows and every type with 128 get the whole register file of a SIMD (one
 // wave): with two waves fp32 spills its accumulators and split operands, and a 128-row tile with
 // four example tiles (256 accumulators, in AGPRs) reuses every Phi^T operand twice as often.
-// UNAL = 1: rows are only 4-byte aligned (G or ldg*sizeof(T) not a multiple of 16): every 16-byte
-// piece is loaded as four dwords.  UNAL = 2 (16-bit types): rows are only 2-byte aligned (odd
-// ldg): eight element loads per piece, and a ring of two example tiles.
+// ET: 32-example tiles per wave.  4 reuses a Phi^T tile over 128 examples; a call with fewer examples
+// takes 1 or 2, so that the wave neither multiplies nor stages tiles without an example.
+// A row split (grid.z) fills the chip when blocks x example tiles are few: the splits are whole
+// stages, ceil(total / zsplit) each, so any Bc can be split.  Split OUT work-groups (kOutSplit, a
+// variant of its own: both epilogues in one kernel cost the unsplit one 2 %) store unscaled records
+// like IN ones, and the same reduction adds them.
+// UNAL (16-bit types): pieces start on an odd element (G, an odd ldg or an odd Bc).  The 16-byte
+// load itself needs dword alignment only, so such a piece is loaded as the five dwords that hold
+// it and shifted into place by half a dword.  (Eight element loads per piece, the alternative,
+// took 2.5-3.5 times as long on the gradient workload.)
 // BIG (input-stationary only): rows so long that 128 of them span 2^31 bytes get one buffer
 // descriptor per 32-example tile instead of one per wave (2 % slower on the gradient workload).
-template <typename T, int MT, int ET, bool OUT, int UNAL = 0, bool BIG = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu((sizeof(T) == 4 && MT >= 2) || MT == 4 ? 1 : 2)))
+constexpr int rows_waves_per_simd(int esz, int mt, int et) {
+  if (et == 4) return (esz == 4 && mt >= 2) || mt == 4 ? 1 : 2;
+  if (et == 2) return esz == 4 && mt == 4 ? 1 : 2;
+  return mt == 4 ? 2 : mt == 2 ? (esz == 4 ? 2 : 3) : 3;
+}
+enum RowsMode { kIn, kOut, kOutSplit };
+template <typename T, int MT, int ET, RowsMode MODE, bool UNAL = false, bool BIG = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(rows_waves_per_simd(sizeof(T), MT, ET))))
 void rows_kernel(RowsArgs a) {
+  constexpr bool OUT = MODE != kIn;
   constexpr int RWV = 32 * MT;         // tile height: kappa * Br stacked output rows, rounded up
   constexpr int TILE = RWV * PHI_LD;   // bf16 elements of the Phi tile
   constexpr int ROWB = KC * (int)sizeof(T);   // bytes of a row per stage: 128 / 256
@@ -112,10 +126,11 @@ void rows_kernel(RowsArgs a) {
   const int ex0 = (int)ey * (32 * ET);
   // IN with kappa*Br above the tile height: grid.z also numbers groups of `group_slots` wiring
   // slots; a work-group serves the slots [slot0, slot0 + kap) and G is read once per group
-  const int z = OUT ? 0 : (int)(blockIdx.z % (uint32_t)a.zsplit);
+  const int z = OUT ? (int)blockIdx.z : (int)(blockIdx.z % (uint32_t)a.zsplit);
   const uint32_t slot0 = OUT ? 0u : (blockIdx.z / (uint32_t)a.zsplit) * (uint32_t)a.group_slots;
   const uint32_t kap = OUT ? p.kappa : min(p.kappa - slot0, (uint32_t)a.group_slots);
-  const int T_stages = a.stages;
+  const int t_first = z * a.stages;
+  const int T_stages = min(a.stages, a.total - t_first);  // >= 1: the host picks zsplit = ceil(total / stages)
   const uint32_t lbr = a.log2_br;
 
   // slot tables and an empty tile
@@ -147,21 +162,22 @@ void rows_kernel(RowsArgs a) {
   // K-values of k-step j in lane half kg: 16 j + 8 kg.
   const int64_t row_bytes = a.ldg * (int64_t)sizeof(T);
   const int rows_valid = min(32 * ET, a.n - ex0);
-  const int64_t last_row_bytes =
-      // (the last row's end rounded up to a dword: range checks are per dword, and the dword that
-      // holds entry d-1 must not count as outside; its other half lies in the same aligned word,
-      // hence in mapped memory, and is cleared with the rest of the tail.  Element loads, UNAL = 2,
-      // are checked per element and get the exact end: their rows need not start on a dword.)
-      UNAL == 2 ? p.d * (int64_t)sizeof(T) : (p.d * (int64_t)sizeof(T) + 3) & ~(int64_t)3;
+  // UNAL: the descriptors start at the dword that holds G's first entry; `mis` is what it adds to
+  // every offset.
+  const uint32_t mis = UNAL ? (uint32_t)((uintptr_t)a.G & 2) : 0u;
   constexpr int ND = BIG ? ET : 1;      // descriptors
   constexpr int DR = BIG ? 32 : 32 * ET;  // example rows each covers
   __amdgpu_buffer_rsrc_t rs_t[ND];
 #pragma unroll
   for (int c = 0; c < ND; ++c) {
     const int valid = min(DR, rows_valid - DR * c);
-    const int64_t range = valid > 0 ? (int64_t)(valid - 1) * row_bytes + last_row_bytes : 0;
+    // (the last row's end rounded up to a dword: range checks are per dword, and the dword that
+    // holds entry d-1 must not count as outside; its other half lies in the same aligned word,
+    // hence in mapped memory, and is cleared with the rest of the tail)
+    const int64_t end = (int64_t)mis + (int64_t)(valid - 1) * row_bytes + p.d * (int64_t)sizeof(T);
+    const int64_t range = valid > 0 ? (end + 3) & ~(int64_t)3 : 0;
     rs_t[c] = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char*>(reinterpret_cast<const char*>(a.G) + (int64_t)(ex0 + DR * c) * row_bytes), 0,
+        const_cast<char*>(reinterpret_cast<const char*>(a.G) - mis + (int64_t)(ex0 + DR * c) * row_bytes), 0,
         (int)(uint32_t)range, 0x00020000);
   }
   // Byte offset in a row of a stage's first K-value.  IN: the wave's own K-range.  OUT: stage t
@@ -170,9 +186,9 @@ void rows_kernel(RowsArgs a) {
   // stages per input block; the last one may reach past the block (Bc not a multiple of 64):
   // Phi^T gets no nonzeros for those K-values, so the neighbouring block's entries count as 0
   const uint32_t spb = (p.Bc + KC - 1) / KC;
-  uint32_t sl_n = 0, st_n = 0;
-  uint32_t kb_c = OUT ? (uint32_t)__builtin_amdgcn_readfirstlane(s_blk[0]) * p.Bc * (uint32_t)sizeof(T)
-                      : (uint32_t)(((int64_t)blk * p.Bc + (int64_t)z * T_stages * KC) * (int64_t)sizeof(T));
+  uint32_t sl_n = OUT ? (uint32_t)t_first / spb : 0u, st_n = OUT ? (uint32_t)t_first % spb : 0u;
+  uint32_t kb_c = OUT ? ((uint32_t)__builtin_amdgcn_readfirstlane(s_blk[sl_n]) * p.Bc + st_n * KC) * (uint32_t)sizeof(T)
+                      : (uint32_t)(((int64_t)blk * p.Bc + (int64_t)t_first * KC) * (int64_t)sizeof(T));
   uint32_t kb_n = kb_c;
   auto step_next = [&]() {  // (sl_n, st_n, kb_n) <- the stage after the one they describe
     if constexpr (OUT) {
@@ -183,7 +199,7 @@ void rows_kernel(RowsArgs a) {
       kb_n += ROWB;
     }
   };
-  const uint32_t voff = (uint32_t)((int64_t)(lane / LPR) * row_bytes + (lane % LPR) * 16);
+  const uint32_t voff = mis + (uint32_t)((int64_t)(lane / LPR) * row_bytes + (lane % LPR) * 16);
   unsigned char* g_wr = s_g + (lane / LPR) * GLD + (lane % LPR) * 16;
   const unsigned char* g_rd = s_g + m * GLD + kg * (8 * (int)sizeof(T));
   const int phi_k = kg * 8;  // + 16 j
@@ -191,29 +207,28 @@ void rows_kernel(RowsArgs a) {
   // Prefetch ring of R example tiles, a whole stage of each: the lines of a tile are requested
   // back to back, once.  (Requesting them one k-step at a time, a stage apart, re-fetched every
   // line four times.)
-  constexpr int R = sizeof(T) == 2 && UNAL != 2 ? ET : 2;
+  // (UNAL pieces are five dwords each: with 64 or more stacked rows a full ring would spill)
+  constexpr int R = ET == 1 ? 1 : sizeof(T) == 2 ? (UNAL && MT >= 2 ? ET / 2 : ET) : 2;
   static_assert(ET % R == 0, "the ring divides a stage");
+  static_assert(!UNAL || sizeof(T) == 2, "only 16-bit entries can start inside a dword");
   uint4 ld[R][NLD];
-  auto issue_tile = [&](uint32_t kb, int c, uint4 (&dst)[NLD]) {
+  uint32_t ld5[UNAL ? R : 1][UNAL ? NLD : 1];  // UNAL: the fifth dword of each piece
+  // UNAL: whether the pieces of this lane's rows start in the upper half of a dword, for a stage at
+  // row offset kb.  RPI rows further on (an even number) they start in the same half.
+  static_assert(RPI % 2 == 0, "rows of one lane share their parity");
+  auto odd = [&](uint32_t kb) -> uint32_t { return (voff + kb) & 2u; };
+  auto issue_tile = [&](uint32_t kb, int slot, int c) {
+    uint4(&dst)[NLD] = ld[slot];
+    // (UNAL: the half-dword of kb, if any, moves from the scalar to the lane offset, which is then
+    // rounded down to a dword)
+    const uint32_t vo = UNAL ? (voff + (kb & 2u)) & ~3u : voff;
+    const uint32_t kq = UNAL ? kb & ~2u : kb;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const __amdgpu_buffer_rsrc_t rs = rs_t[BIG ? c : 0];
-      const uint32_t so = (uint32_t)((BIG ? 0 : c * 32) + i * RPI) * (uint32_t)row_bytes + kb;
-      if constexpr (UNAL == 2) {
-        typedef unsigned short us8 __attribute__((ext_vector_type(8)));
-        us8 e;
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-          e[c] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, voff + 2u * c, so, 0);
-        dst[i] = __builtin_bit_cast(uint4, e);
-      } else if constexpr (UNAL == 1) {
-        dst[i].x = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff, so, 0);
-        dst[i].y = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 4u, so, 0);
-        dst[i].z = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 8u, so, 0);
-        dst[i].w = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 12u, so, 0);
-      } else {
-        dst[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, so, 0));
-      }
+      const uint32_t so = (uint32_t)((BIG ? 0 : c * 32) + i * RPI) * (uint32_t)row_bytes + kq;
+      dst[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, 0));
+      if constexpr (UNAL) ld5[slot][i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, vo + 16u, so, 0);
     }
   };
 
@@ -249,7 +264,7 @@ void rows_kernel(RowsArgs a) {
       }
       return;
     }
-    const uint32_t u = (uint32_t)(z * T_stages + t) * KC + lane;
+    const uint32_t u = (uint32_t)(t_first + t) * KC + lane;
     if (u >= p.Bc) return;  // past the block
     if (!p.br_pow2) {  // (wave-uniform) slots of 2^lbr >= Br rows; the general row hash, wrap by compare
       for (uint32_t slot = part; slot < kap; slot += KSTEPS) {
@@ -304,6 +319,16 @@ void rows_kernel(RowsArgs a) {
         for (int part = c * KSTEPS / ET; part < (c + 1) * KSTEPS / ET; ++part) produce(t + 1, part);
       }
       uint4(&cur)[NLD] = ld[c % R];
+      if constexpr (UNAL) {
+        const uint32_t sh = odd(kb_c) << 3;  // 0 or 16 bits
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+          cur[i].x = __builtin_amdgcn_alignbit(cur[i].y, cur[i].x, sh);
+          cur[i].y = __builtin_amdgcn_alignbit(cur[i].z, cur[i].y, sh);
+          cur[i].z = __builtin_amdgcn_alignbit(cur[i].w, cur[i].z, sh);
+          cur[i].w = __builtin_amdgcn_alignbit(ld5[c % R][i], cur[i].w, sh);
+        }
+      }
       if (tail) {  // wave-uniform: only the stages of a partly filled last block that reach entry d
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
@@ -321,7 +346,7 @@ void rows_kernel(RowsArgs a) {
       // refill the slot with the tile R places further on: same stage, or the next one
       const int CN = (c + R) % ET;  // compile-time after unrolling
       const bool wrap = c + R >= ET;
-      if (!(LAST && wrap)) issue_tile(wrap ? kb_n : kb_c, CN, cur);
+      if (!(LAST && wrap)) issue_tile(wrap ? kb_n : kb_c, c % R, CN);
 #pragma unroll
       for (int i = 0; i < NLD; ++i)
         g[i] = *reinterpret_cast<const uint4*>(g_rd + (i / NV) * (16 * (int)sizeof(T)) + (i % NV) * 16);
@@ -356,7 +381,7 @@ void rows_kernel(RowsArgs a) {
 
   if (rows_valid > 0) {
 #pragma unroll
-    for (int c = 0; c < R; ++c) issue_tile(kb_c, c, ld[c]);
+    for (int c = 0; c < R; ++c) issue_tile(kb_c, c, c);
 #pragma unroll
     for (int part = 0; part < KSTEPS; ++part) produce(0, part);
     for (int t = 0; t + 1 < T_stages; ++t) stage(t, std::false_type{});
@@ -365,7 +390,25 @@ void rows_kernel(RowsArgs a) {
 
   // ---- epilogue: accumulator v of tile (c, rt) is example ex0 + 32 c + 8 (v/4) + 4 kg + v%4,
   // stacked row 32 rt + m.
-  if constexpr (OUT) {  // the finished block: scale, convert, 32 consecutive columns per half-wave
+  if constexpr (OUT) {
+    if constexpr (MODE == kOutSplit) {  // a partial sum: the record of the block, at the place the reduction looks for
+      const uint32_t pos = a.orbit ? __builtin_amdgcn_readfirstlane(a.orbit[p.M + blk]) : 0u;
+      const uint32_t rec = a.orbit ? (pos + 1u == p.M ? 0u : pos + 1u) : wire_next(blk, p.a, p.b, p.M);
+      float* base = a.ws + (((int64_t)z * a.n + ex0) * p.M + rec) * p.Br + row_lo + m;
+      const int64_t ex_stride = (int64_t)p.M * p.Br;
+#pragma unroll
+      for (int c = 0; c < ET; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int ex = c * 32 + 8 * (v >> 2) + 4 * kg + (v & 3);
+          if (ex < rows_valid) {
+#pragma unroll
+            for (int rt = 0; rt < MT; ++rt) base[ex * ex_stride + rt * 32] = acc[c][rt][v];
+          }
+        }
+      return;
+    }
+    // the finished block: scale, convert, 32 consecutive columns per half-wave
     T* base = reinterpret_cast<T*>(a.out) + (int64_t)ex0 * a.ldo + (int64_t)blk * p.Br + row_lo + m;
 #pragma unroll
     for (int c = 0; c < ET; ++c)
@@ -409,17 +452,28 @@ void rows_kernel(RowsArgs a) {
 // position of f from block 0, then the inverse) threads are numbered by the orbit position pos of
 // their output block and the records are those at positions pos+1 .. pos+kappa: a sliding window
 // of contiguous memory.  Without it records are indexed by block and f is evaluated directly.
-template <typename T, int VEC>
+//
+// PARTS > 1, for calls with few outputs and many addends (narrow batches split into many pieces): a
+// work-group serves 256/PARTS outputs, each through PARTS threads that add a contiguous share of
+// the addends; the shares are then added in order through LDS.  One thread per output would wait
+// for memory once per 8 addends with most of the chip idle (24 examples of 10^6 entries in 8
+// splits, k = 2048: 64 addends for 12288 threads).
+template <typename T, int VEC, int PARTS>
 __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restrict__ part, int zsplit, int n,
                                                           SketchParams p, uint32_t lbr, uint32_t rw,
                                                           uint32_t group_slots,
                                                           const uint32_t* __restrict__ orbit,
                                                           T* __restrict__ out, int64_t ldo) {
+  constexpr int OPW = 256 / PARTS;  // outputs per work-group
+  constexpr int UN = 8;             // loads issued together
+  using Vec = std::conditional_t<VEC == 4, float4, float>;
+  const int share = PARTS > 1 ? (int)threadIdx.x / OPW : 0;
   const int64_t q = p.k / VEC;
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (int64_t)n * q) return;
-  const int64_t ex = idx / q;
-  const uint32_t col0 = (uint32_t)(idx % q) * VEC;
+  const int64_t idx = (int64_t)blockIdx.x * OPW + (int)threadIdx.x % OPW;
+  const bool valid = idx < (int64_t)n * q;
+  if (PARTS == 1 && !valid) return;
+  const int64_t ex = valid ? idx / q : 0;
+  const uint32_t col0 = valid ? (uint32_t)(idx % q) * VEC : 0u;
   // orbit position (or block) and row in block; lbr = log2 of the rows a slot takes in a record
   // (Br, or the next power of two when Br is not one)
   const uint32_t bi = p.br_pow2 ? col0 >> lbr : col0 / p.Br;
@@ -430,38 +484,54 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restric
   float s[VEC];
 #pragma unroll
   for (int c = 0; c < VEC; ++c) s[c] = 0.f;
-  // The kappa * zsplit addends in the order (slot l, row split z), four at a time: their loads are
+  // The kappa * zsplit addends in the order (slot l, row split z), UN at a time: their loads are
   // issued together, then added in that order.  (One load per pass of a loop made the kernel wait
   // for memory once per addend.)
-  using Vec = std::conditional_t<VEC == 4, float4, float>;
-  const uint32_t total = p.kappa * (uint32_t)zsplit;
-  uint32_t rec = bi, l = 0, zc = 0, lg = 0, grp = 0;  // record of slot l; l = grp * group_slots + lg
-  rec = orbit ? (rec + 1 == p.M ? 0u : rec + 1) : wire_next(rec, p.a, p.b, p.M);
-  for (uint32_t t0 = 0; t0 < total; t0 += 4) {
-    Vec v[4];
+  const uint32_t all = p.kappa * (uint32_t)zsplit;
+  const uint32_t per = (all + PARTS - 1) / PARTS;
+  const uint32_t first = (uint32_t)share * per, total = min(first + per, all);
+  uint32_t l = first / (uint32_t)zsplit, zc = first - l * (uint32_t)zsplit;
+  uint32_t grp = l / group_slots, lg = l - grp * group_slots;  // l = grp * group_slots + lg
+  uint32_t rec = bi;  // record of slot l
+  if (orbit) {
+    rec = (uint32_t)(((uint64_t)bi + 1u + l) % p.M);
+  } else {
+    for (uint32_t i = 0; i <= l; ++i) rec = wire_next(rec, p.a, p.b, p.M);
+  }
+  for (uint32_t t0 = first; t0 < total; t0 += UN) {
+    Vec v[UN];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < UN; ++j) {
       // (past the last addend the cursor stays on it: the load is valid and ignored)
       const float* ph = src + ((int64_t)grp * zsplit + zc) * z_stride + (int64_t)rec * rw + (lg << lbr);
       v[j] = *reinterpret_cast<const Vec*>(ph);
       if (t0 + j + 1 < total) {
         if (++zc == (uint32_t)zsplit) {
           zc = 0;
-          ++l;
           if (++lg == group_slots) { lg = 0; ++grp; }
           rec = orbit ? (rec + 1 == p.M ? 0u : rec + 1) : wire_next(rec, p.a, p.b, p.M);
         }
       }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < UN; ++j) {
       if (t0 + j < total) {
         if constexpr (VEC == 4) { s[0] += v[j].x; s[1] += v[j].y; s[2] += v[j].z; s[3] += v[j].w; }
         else s[0] += v[j];
       }
     }
   }
-  (void)l;
+  if constexpr (PARTS > 1) {
+    __shared__ float sh[PARTS][OPW][VEC];
+#pragma unroll
+    for (int c = 0; c < VEC; ++c) sh[share][threadIdx.x % OPW][c] = s[c];
+    __syncthreads();
+    if (share > 0 || !valid) return;
+#pragma unroll
+    for (int i = 1; i < PARTS; ++i)
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) s[c] += sh[i][threadIdx.x][c];
+  }
   T* dst = out + ex * ldo + (int64_t)g * p.Br + r;
 #pragma unroll
   for (int c = 0; c < VEC; ++c) s[c] *= p.scale;
@@ -482,15 +552,48 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restric
 
 struct RowsPlan {
   bool ok = false;
-  int mt = 0, et = 0, zsplit = 1, stages = 0, planes = 0, groups = 1, group_slots = 0;
+  int mt = 0, et = 4, zsplit = 1, stages = 0, total = 0, groups = 1, group_slots = 0;
   bool out_stat = false;
-  int unal = 0;  // 0: 128-bit loads, 1: dword loads, 2: element loads (16-bit types)
-  int nsub = 1;  // OUT: 128-row slices of an output block
-  bool big = false;  // IN: one descriptor per 32-example tile (very long rows)
+  bool vec = true;       // every piece starts on 16 bytes
+  bool unal = false;     // some pieces start inside a dword (16-bit types)
+  int nsub = 1;          // OUT: 128-row slices of an output block
+  bool big = false;      // IN: one descriptor per 32-example tile (very long rows)
+  int waves_per_simd = 1;
   size_t lds = 0;
+  size_t ws = 0;         // bytes of partial records of this plan
+  size_t ws_floor = 0;   // bytes a call must find (an attached workspace below this is refused)
 };
 
-RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt) {
+// Row split of `units` work-groups (one wave each) with `total` stages of work each.  Every split
+// adds a set of partial records; fewer splits than the chip has room for waves leave it idle.  The
+// model: the longest of (1) what the waves issue, spread over 1024 SIMDs, (2) rounds of resident
+// waves, each stage of a wave costing a memory latency on top, (3) the stream of G, plus the
+// records written at 3.4 and read back at 6 TB/s (rates measured on this kernel pair) and, where
+// without a split there would be no reduction, its launch.  Measured (fp32, 24 examples of 1000003
+// entries, kappa*Br = 64, M = 256): 1 split 94 us, 8 splits 36 us.
+int pick_rows_split(double units, int total, double stage_us, double slots, double stream_us,
+                    double set_bytes, bool has_reduce, double max_bytes) {
+  int best_z = 1, last_s = 0;
+  double best = 0;
+  for (int zc = 1; zc <= total && zc <= 256; ++zc) {
+    const int st = (total + zc - 1) / zc;
+    if (st == last_s || (total + st - 1) / st != zc) continue;  // the same stages per work-group as before
+    last_s = st;
+    if (zc > 1 && set_bytes * zc > max_bytes) break;
+    const double waves = units * zc;
+    const double rounds = waves <= slots ? 1.0 : waves / slots;
+    double t = rounds * st * (stage_us + 1.0);
+    if (waves * st * stage_us / 1024 > t) t = waves * st * stage_us / 1024;
+    if (stream_us > t) t = stream_us;
+    if (has_reduce || zc > 1) t += set_bytes * zc * (1 / 3.4e6 + 1 / 6e6);
+    if (!has_reduce && zc > 1) t += 4.0;
+    if (zc == 1 || t < best) { best = t; best_z = zc; }
+  }
+  return best_z;
+}
+
+// `limit`: bytes of workspace the call can have at most.
+RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t limit) {
   RowsPlan pl;
   const size_t esz = dt == FS_F32 ? 4 : 2;
   if (n < 1) return pl;
@@ -507,48 +610,81 @@ RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64
   if (p.kappa == 1 && br_tile) {  // nothing is re-read: output-stationary stores the result directly
     pl.out_stat = true;
     pl.mt = out_mt; pl.nsub = out_nsub;
-    pl.et = 4;
-  } else if (rw <= 32) { pl.mt = 1; pl.et = 4; }   // the smallest tile that holds the stacked rows
-  else if (rw <= 64) { pl.mt = 2; pl.et = 4; }
-  else if (rw <= 128) { pl.mt = 4; pl.et = 4; }
+  } else if (rw <= 32) pl.mt = 1;  // the smallest tile that holds the stacked rows
+  else if (rw <= 64) pl.mt = 2;
+  else if (rw <= 128) pl.mt = 4;
   else if (br_tile) {  // too many stacked rows: output-stationary
     pl.out_stat = true;
     pl.mt = out_mt; pl.nsub = out_nsub;
-    pl.et = 4;
   } else if (brp <= 64) {  // ... and no OUT for them (small blocks, Br not a power of two, kappa > 128):
-    pl.mt = 4; pl.et = 4;  // groups of 128/Br slots, G read once per group
+    pl.mt = 4;             // groups of 128/Br slots, G read once per group
     pl.group_slots = (int)(128 / brp);
     pl.groups = (int)((p.kappa + pl.group_slots - 1) / pl.group_slots);
   } else return pl;
   if ((uintptr_t)G % esz) return pl;
   // what every piece address G + example*ldg + block*Bc + 64*stage (in bytes) is a multiple of
   const int64_t bc_bytes = (int64_t)p.Bc * (int64_t)esz;
-  if ((uintptr_t)G % 4 || (ldg * (int64_t)esz) % 4 || bc_bytes % 4) pl.unal = 2;         // element loads
-  else if ((uintptr_t)G % 16 || (ldg * (int64_t)esz) % 16 || bc_bytes % 16) pl.unal = 1;  // four dwords each
+  pl.unal = (uintptr_t)G % 4 || (ldg * (int64_t)esz) % 4 || bc_bytes % 4;
+  pl.vec = !((uintptr_t)G % 16 || (ldg * (int64_t)esz) % 16 || bc_bytes % 16);
   // 32-bit offsets: within the wave's 128 examples, or (input-stationary only) within a 32-example tile
   if (34 * ldg * (int64_t)esz >= ((int64_t)1 << 31)) return pl;
-  pl.big = 130 * ldg * (int64_t)esz >= ((int64_t)1 << 31);
-  if (pl.big && pl.out_stat) return pl;
+  const bool big = 130 * ldg * (int64_t)esz >= ((int64_t)1 << 31);
+  if (big && pl.out_stat) return pl;
+  const int64_t tiles128 = (n + 127) / 128;
+  if (tiles128 * pl.nsub > 65535) return pl;
+  if (pl.group_slots == 0) pl.group_slots = (int)p.kappa;
+
+  // What a call must be able to hold whatever the split: for IN the records of the split that a
+  // traffic model alone picks (G at 6 TB/s once 1024 waves exist, records as above; splits that
+  // divide the block evenly).  Callers size and attach workspaces by this figure.
+  const double set_bytes = pl.out_stat ? (double)n * (double)p.k * 4.0
+                                       : (double)pl.groups * (double)n * p.M * (32.0 * pl.mt) * 4.0;
+  if (!pl.out_stat) {
+    int zf = 1;
+    double best = 0;
+    for (int zc = 1; zc <= 16; zc *= 2) {
+      if (zc > 1 && p.Bc % (uint32_t)(zc * KC) != 0) break;
+      const double waves = (double)p.M * tiles128 * zc * pl.groups;
+      const double plane_bytes = (double)zc * p.kappa * (double)p.k * (double)n * 4.0;
+      const double t = (double)p.d * (double)n * esz * pl.groups / (6e12 * (waves < 1024 ? waves / 1024 : 1.0)) +
+                       plane_bytes / 3.4e12 + plane_bytes / 6e12;
+      if (zc == 1 || t < best) { best = t; zf = zc; }
+    }
+    pl.ws_floor = (size_t)set_bytes * zf;
+  }
+  if (limit < pl.ws_floor) limit = pl.ws_floor;  // (the call is refused before it gets here)
+
+  // Examples per wave: the tiles a wave processes without a single example against making Phi^T
+  // once per wave.  Microseconds of one SIMD per 64-entry stage: one 32-example tile (loads, LDS
+  // turn, MFMAs; fp32 also the split), and Phi^T (a hash and s stores per slot, the clear).
+  const double tile_us = esz == 4 ? 0.25 + 0.16 * pl.mt : 0.15 + 0.06 * pl.mt;
+  const double phi_us = 0.15 + 0.07 * (pl.out_stat ? 1 : pl.group_slots < (int)p.kappa ? pl.group_slots : (int)p.kappa);
+  double best_cost = 0;
+  for (int et = 4; et >= 1; et /= 2) {
+    if (et == 2 && 66 * ldg * (int64_t)esz >= ((int64_t)1 << 31)) continue;
+    const double cost = (double)((n + 32 * et - 1) / (32 * et)) * (phi_us + et * tile_us);
+    if (et == 4 || cost < 0.95 * best_cost) { best_cost = cost; pl.et = et; }
+  }
+  pl.big = big && pl.et == 4;
   const int64_t ex_tiles = (n + 32 * pl.et - 1) / (32 * pl.et);
   if (ex_tiles * pl.nsub > 65535) return pl;
-  // row split: the traffic model of the column layout (G at ~6 TB/s once 1024 waves exist,
-  // planes written at ~3.4 TB/s and read back at ~6 TB/s)
-  if (pl.group_slots == 0) pl.group_slots = (int)p.kappa;
-  const double g_bytes = (double)p.d * (double)n * esz * pl.groups;
-  double best = 0;
-  for (int zc = 1; zc <= 16; zc *= 2) {
-    if (zc > 1 && p.Bc % (uint32_t)(zc * KC) != 0) break;  // splits are whole stages
-    const double waves = (double)p.M * ex_tiles * zc * pl.groups;
-    const double plane_bytes = (double)zc * p.kappa * (double)p.k * (double)n * 4.0;
-    const double t = g_bytes / (6e12 * (waves < 1024 ? waves / 1024 : 1.0)) + plane_bytes / 3.4e12 +
-                     plane_bytes / 6e12;
-    if (zc == 1 || t < best) { best = t; pl.zsplit = zc; }
-  }
-  if (pl.out_stat) pl.zsplit = 1;
-  pl.stages = pl.out_stat ? (int)(p.kappa * blk_stages) : (int)(blk_stages / pl.zsplit);
-  pl.planes = pl.out_stat ? 0 : pl.zsplit * (int)p.kappa;
+
   // slot tables, the Phi^T tile and the transposition tile
   pl.lds = 2 * MAX_KAPPA * 4 + (size_t)(32 * pl.mt) * PHI_LD * 2 + 32 * (KC * esz + 16);
+  pl.waves_per_simd = rows_waves_per_simd((int)esz, pl.mt, pl.et);
+  const int by_lds = (int)((160 * 1024) / pl.lds);
+  const double slots = 256.0 * (4 * pl.waves_per_simd < by_lds ? 4 * pl.waves_per_simd : by_lds);
+  pl.total = pl.out_stat ? (int)(p.kappa * blk_stages) : (int)blk_stages;
+  const double g_us = (double)p.d * (double)n * esz / 5.5e6;
+  const double stream_us = pl.out_stat ? g_us * (1.0 + 0.3 * (p.kappa - 1)) : g_us * pl.groups;
+  double max_bytes = (double)(pl.ws_floor > kSplitScratch ? pl.ws_floor : kSplitScratch);
+  if ((double)limit < max_bytes) max_bytes = (double)limit;
+  const int zmax = 65535 / pl.groups;
+  pl.zsplit = pick_rows_split((double)p.M * ex_tiles * pl.nsub * pl.groups, pl.total, phi_us + pl.et * tile_us, slots,
+                              stream_us, set_bytes, !pl.out_stat, max_bytes);
+  if (pl.zsplit > zmax) pl.zsplit = 1;
+  pl.stages = (pl.total + pl.zsplit - 1) / pl.zsplit;
+  if (!pl.out_stat || pl.zsplit > 1) pl.ws = (size_t)set_bytes * pl.zsplit;
   pl.ok = true;
   return pl;
 }
@@ -559,40 +695,74 @@ hipError_t go(K kernel, dim3 grid, size_t lds, hipStream_t st, const RowsArgs& a
   return hipGetLastError();
 }
 
+template <typename T, int MT, int ET, bool UNAL>
+hipError_t launch_mode(const RowsPlan& pl, dim3 grid, hipStream_t st, const RowsArgs& a) {
+  if (pl.out_stat)
+    return pl.zsplit > 1 ? go(rows_kernel<T, MT, ET, kOutSplit, UNAL>, grid, pl.lds, st, a)
+                         : go(rows_kernel<T, MT, ET, kOut, UNAL>, grid, pl.lds, st, a);
+  if constexpr (ET == 4) {
+    if (pl.big) return go(rows_kernel<T, MT, ET, kIn, UNAL, true>, grid, pl.lds, st, a);
+  }
+  return go(rows_kernel<T, MT, ET, kIn, UNAL>, grid, pl.lds, st, a);
+}
+
+template <typename T, int MT, bool UNAL>
+hipError_t launch_shape(const RowsPlan& pl, dim3 grid, hipStream_t st, const RowsArgs& a) {
+  return pl.et == 1   ? launch_mode<T, MT, 1, UNAL>(pl, grid, st, a)
+         : pl.et == 2 ? launch_mode<T, MT, 2, UNAL>(pl, grid, st, a)
+                      : launch_mode<T, MT, 4, UNAL>(pl, grid, st, a);
+}
+
+template <typename T, bool UNAL>
+hipError_t launch_mt(const RowsPlan& pl, dim3 grid, hipStream_t st, const RowsArgs& a) {
+  return pl.mt == 1   ? launch_shape<T, 1, UNAL>(pl, grid, st, a)
+         : pl.mt == 2 ? launch_shape<T, 2, UNAL>(pl, grid, st, a)
+                      : launch_shape<T, 4, UNAL>(pl, grid, st, a);
+}
+
+template <typename T, int VEC>
+void launch_reduce(int64_t outputs, uint32_t addends, hipStream_t st, const RowsArgs& a, const SketchParams& p,
+                   uint32_t rw, uint32_t group_slots) {
+#define FS_RED(PARTS)                                                                                            \
+  hipLaunchKernelGGL((reduce_rows_kernel<T, VEC, PARTS>), dim3((unsigned)((outputs + 256 / PARTS - 1) / (256 / PARTS))), \
+                     dim3(256), 0, st, a.ws, a.zsplit, a.n, p, a.log2_br, rw, group_slots, a.orbit, (T*)a.out, a.ldo)
+  // (65536 threads are one per lane of a SIMD on every SIMD)
+  if (addends >= 16 && outputs < 65536) FS_RED(8); else FS_RED(1);
+#undef FS_RED
+}
+
 }  // namespace
 
 bool rows_supported(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt) {
-  return make_rows_plan(p, G, ldg, n, dt).ok;
+  return make_rows_plan(p, G, ldg, n, dt, SIZE_MAX).ok;
 }
 
 bool rows_describe(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, int* mode,
                    int* flags, size_t* workspace) {
-  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt);
+  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, SIZE_MAX);
   if (!pl.ok) return false;
   *mode = pl.out_stat ? 1 : 2;
-  *flags = (pl.unal ? FS_PLAN_ELEMENT_LOADS : 0) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
+  *flags = (pl.vec ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
            (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (pl.zsplit > 1 ? FS_PLAN_SPLIT : 0);
-  *workspace = rows_workspace_bytes(p, G, ldg, n, dt);
+  *workspace = pl.ws > pl.ws_floor ? pl.ws : pl.ws_floor;
   return true;
 }
 
-size_t rows_workspace_bytes(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt) {
-  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt);
-  if (!pl.ok) return 0;
-  // [z][example][block][tile height]
-  return pl.out_stat ? 0 : (size_t)pl.groups * (size_t)pl.zsplit * (size_t)n * (size_t)p.M * (size_t)(32 * pl.mt) *
-                               sizeof(float);
+Workspace rows_workspace(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt) {
+  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, SIZE_MAX);
+  if (!pl.ok) return {0, 0};
+  return {pl.ws_floor, pl.ws > pl.ws_floor ? pl.ws : pl.ws_floor};
 }
 
 hipError_t launch_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
-                       int64_t ldo, fs_dtype dt, void* ws, const uint32_t* orbit, hipStream_t st,
+                       int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev) {
-  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt);
-  if (!pl.ok) return hipErrorInvalidValue;
+  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, ws_bytes);
+  if (!pl.ok || pl.ws > ws_bytes) return hipErrorInvalidValue;
   RowsArgs a;
   a.p = p; a.G = G; a.ws = (float*)ws; a.orbit = orbit; a.out = out;
   a.ldg = ldg; a.ldo = ldo; a.n = (int)n;
-  a.stages = pl.stages;
+  a.stages = pl.stages; a.total = pl.total;
   a.log2_br = 0;
   while ((1u << a.log2_br) < p.Br) ++a.log2_br;
   a.zsplit = pl.zsplit; a.group_slots = pl.group_slots; a.nsub = pl.nsub;
@@ -600,33 +770,25 @@ hipError_t launch_rows(const SketchParams& p, const void* G, int64_t ldg, int64_
 
   if (ev.start) (void)hipEventRecord(ev.start, st);
   hipError_t e;
-#define FS_ROWS_U(T, MT, ET, U)                                                   \
-  (pl.out_stat ? go(rows_kernel<T, MT, ET, true, U>, grid, pl.lds, st, a)         \
-   : pl.big    ? go(rows_kernel<T, MT, ET, false, U, true>, grid, pl.lds, st, a)  \
-               : go(rows_kernel<T, MT, ET, false, U>, grid, pl.lds, st, a))
-// (U2: what pl.unal == 2 selects -- element loads exist for the 16-bit types only; fp32 rows are
-// always dword aligned)
-#define FS_ROWS(T, MT, ET, U2) \
-  (pl.unal == 0 ? FS_ROWS_U(T, MT, ET, 0) : pl.unal == 1 ? FS_ROWS_U(T, MT, ET, 1) : FS_ROWS_U(T, MT, ET, U2))
-  if (dt == FS_BF16)
-    e = pl.mt == 1 ? FS_ROWS(uint16_t, 1, 4, 2) : pl.mt == 2 ? FS_ROWS(uint16_t, 2, 4, 2) : FS_ROWS(uint16_t, 4, 4, 2);
-  else if (dt == FS_F16)
-    e = pl.mt == 1 ? FS_ROWS(f16, 1, 4, 2) : pl.mt == 2 ? FS_ROWS(f16, 2, 4, 2) : FS_ROWS(f16, 4, 4, 2);
-  else
-    e = pl.mt == 1 ? FS_ROWS(float, 1, 4, 1) : pl.mt == 2 ? FS_ROWS(float, 2, 4, 1) : FS_ROWS(float, 4, 4, 1);
-#undef FS_ROWS
-#undef FS_ROWS_U
+  if (dt == FS_F32) e = launch_mt<float, false>(pl, grid, st, a);
+  else if (dt == FS_BF16) e = pl.unal ? launch_mt<uint16_t, true>(pl, grid, st, a) : launch_mt<uint16_t, false>(pl, grid, st, a);
+  else e = pl.unal ? launch_mt<f16, true>(pl, grid, st, a) : launch_mt<f16, false>(pl, grid, st, a);
   if (ev.stop) (void)hipEventRecord(ev.stop, st);
-  if (e != hipSuccess || pl.out_stat) return e;
+  if (e != hipSuccess || (pl.out_stat && pl.zsplit == 1)) return e;
   const int vec = p.Br % 4 == 0 ? 4 : 1;
-  const int64_t work = n * (p.k / vec);
-  const dim3 rgrid((unsigned)((work + 255) / 256));
-#define FS_RED(T, VEC)                                                                                   \
-  hipLaunchKernelGGL((reduce_rows_kernel<T, VEC>), rgrid, dim3(256), 0, st, a.ws, pl.zsplit, (int)n, p, \
-                     a.log2_br, (uint32_t)(32 * pl.mt), (uint32_t)pl.group_slots, orbit, (T*)out, ldo)
-  if (dt == FS_BF16)     { if (vec == 4) FS_RED(uint16_t, 4); else FS_RED(uint16_t, 1); }
-  else if (dt == FS_F16) { if (vec == 4) FS_RED(f16, 4); else FS_RED(f16, 1); }
-  else                   { if (vec == 4) FS_RED(float, 4); else FS_RED(float, 1); }
+  const int64_t outputs = n * (p.k / vec);
+  // (OUT: one record per output block and split, as if kappa were 1)
+  SketchParams rp = p;
+  if (pl.out_stat) rp.kappa = 1;
+  const uint32_t rw = pl.out_stat ? p.Br : (uint32_t)(32 * pl.mt);
+  const uint32_t slots = pl.out_stat ? 1u : (uint32_t)pl.group_slots;
+  const uint32_t addends = rp.kappa * (uint32_t)pl.zsplit;
+#define FS_RED(T)                                                           \
+  (vec == 4 ? launch_reduce<T, 4>(outputs, addends, st, a, rp, rw, slots)   \
+            : launch_reduce<T, 1>(outputs, addends, st, a, rp, rw, slots))
+  if (dt == FS_BF16) FS_RED(uint16_t);
+  else if (dt == FS_F16) FS_RED(f16);
+  else FS_RED(float);
 #undef FS_RED
   return hipGetLastError();
 }

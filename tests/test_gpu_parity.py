@@ -953,6 +953,50 @@ def test_apply_rows_matches_oracle(case, dtype, variant):
     check(colwise.t(), ref, dtype, "column layout on the transpose")
 
 
+# Few blocks and few examples: the stages of a block are split over grid.z (unevenly: Bc is no multiple
+# of a split), a wave takes 32, 64 or 128 examples, pieces may start on an odd entry.
+ROWS_SPLIT = [
+    # params (d,k,Bc,Br,kappa,s), n, ldg pad, first column of the view
+    ((15990, 128, 4000, 32, 2, 4), 1, 0, 0),       # input-stationary, 63 stages, one example
+    ((15990, 128, 4000, 32, 2, 4), 32, 1, 1),      # one full 32-example tile, odd row stride, odd first entry
+    ((15990, 128, 4000, 32, 2, 4), 33, 2, 1),      # two tiles, the second with one example
+    ((15990, 128, 4000, 32, 2, 4), 65, 3, 2),
+    ((15990, 128, 4000, 32, 2, 4), 129, 1, 0),
+    ((16000, 256, 4001, 64, 4, 4), 2, 0, 1),       # output-stationary, split; odd Bc: a block starts on either half
+    ((16000, 256, 4001, 64, 4, 4), 40, 1, 0),
+    ((6000, 1024, 1501, 256, 2, 8), 20, 1, 0),     # 128-row slices, split
+    ((5000, 128, 2500, 64, 1, 4), 3, 1, 1),        # M = 2: no orbit table
+    ((9000, 48, 2250, 12, 3, 5), 7, 1, 0),         # Br not a power of two
+    ((6000, 512, 1501, 128, 4, 32), 100, 0, 1),    # 128 stacked rows, s = 32
+]
+
+
+@DTYPES
+@pytest.mark.parametrize("case", ROWS_SPLIT, ids=lambda c: f"{c[0]}-n{c[1]}")
+def test_apply_rows_split_over_few_blocks_matches_oracle(case, dtype):
+    params, n, pg, first = case
+    print("rows split", params, n, dtype, flush=True)
+    d, k = params[0], params[1]
+    g = torch.Generator(device=DEV).manual_seed(n + k)
+    Gbuf = torch.randn((n + 1, first + d + pg), generator=g, device=DEV).to(dtype)
+    Gbuf[n:] = float("nan")         # what surrounds the examples must never reach the result
+    Gbuf[:, :first] = float("nan")
+    Gbuf[:, first + d:] = float("nan")
+    G = Gbuf[:n, first:first + d]
+    sk = make_sketch(params, 9, B.VARIANT_MFMA)
+    plan = sk.plan(n, dtype, ld=G.stride(0), rows=True, address=G.data_ptr())
+    assert plan["flags"] & B.PLAN_SPLIT, plan
+    out = sk.apply_rows(G)
+    ref = O.apply_rows(oracle_csc(params, 9), host64(G))
+    check(out, ref, dtype, "apply_rows, split")
+    assert torch.equal(sk.apply_rows(G), out)     # fixed summation order
+    if plan["mode"] == 1:                         # output-stationary calls need no workspace: with 256 bytes they run unsplit
+        ws = torch.empty(512, dtype=torch.uint8, device=DEV)
+        off = (-ws.data_ptr()) % 256
+        sk.set_workspace(ws[off:off + 256])
+        check(sk.apply_rows(G), ref, dtype, "apply_rows, unsplit")
+
+
 def test_apply_rows_one_hot_rows_reproduce_columns_exactly():
     params = (32768, 64, 4096, 8, 8, 2)  # kappa*s = 16: the scale is a power of two
     d, k = params[0], params[1]
