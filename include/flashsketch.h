@@ -26,14 +26,17 @@
  *   Pointers   A, out, rows, signs, S_dense and workspaces are DEVICE pointers
  *              owned by the caller.  Handles and fs_info are HOST objects.
  *   Alignment  A and out must be aligned to their element size.  The matrix-core
- *              kernels load 4 columns per lane as one vector when A and lda are
- *              aligned to 4 elements; otherwise they load element by element,
- *              about half as fast (never an error).  With vector loads and n not
- *              a multiple of 4, up to 3 elements of a row's own padding (columns
- *              n .. lda-1, inside the aligned 4-element group of the row's last
- *              valid element) are loaded and discarded; their values, NaN
- *              included, never reach the result.  Element loads read nothing
- *              beyond column n-1.  Stores to out are vectors when out and ldo are
+ *              kernels load 4 columns per lane as one vector; rows of a 16-bit
+ *              type that start inside a dword (A or lda odd) as the three dwords
+ *              that hold them, which is slower (never an error).  With n not
+ *              a multiple of 4, up to 3 elements behind column n-1 (the row's
+ *              padding, or the start of the next row; behind the last row only
+ *              inside the aligned 4-element group, or without such alignment the
+ *              dword, of its last valid element) and up to one before the first
+ *              element, inside its dword, are loaded and discarded; their values, NaN
+ *              included, never reach the result.  Calls of up to 64 columns load
+ *              element by element and read nothing beyond column n-1.  Stores to
+ *              out are vectors when out and ldo are
  *              aligned to 4 elements, else element by element.
  *   Streams    `stream` is a hipStream_t passed as void* (NULL = default
  *              stream).  Calls enqueue work and return; they never synchronise.
@@ -100,8 +103,8 @@ typedef enum {
                              (other Br while its kappa slots, each padded to the next
                              power of two rows, fit 128 tile rows, or padded Br <= 64),
                              any Bc, kappa <= 128 (more when Br <= 64),
-                             64*ceil(Bc/64)*lda*sizeof(elt) < 2^31; about twice as fast
-                             when A and lda are aligned to 4 columns (vector loads)  */
+                             64*ceil(Bc/64)*lda*sizeof(elt) < 2^31; fastest
+                             when A and lda are aligned to 4 columns                */
 } fs_variant;
 
 typedef struct {
@@ -228,7 +231,8 @@ typedef enum {
   FS_PLAN_ROW_SLICES = 2,    /* output blocks higher than 128 rows, served in 128-row slices   */
   FS_PLAN_SLOT_GROUPS = 4,   /* more than 128 stacked rows of small blocks: input read once
                                 per group of wiring slots                                      */
-  FS_PLAN_SPLIT = 8,         /* the rows of a work-group's input are split over grid.z         */
+  FS_PLAN_SPLIT = 8,         /* the rows of a work-group's input are split over grid.z, or over
+                                all its waves                                                  */
   FS_PLAN_STACKED = 16       /* output-stationary with several output blocks, consecutive on
                                 the orbit of the wiring, per wave (mode 1, no workspace)       */
 } fs_plan_flags;
@@ -270,7 +274,8 @@ fs_status fs_sketch_info(fs_sketch_t h, fs_info* out);
 fs_status fs_sketch_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dtype, size_t* bytes);
 
 /* Attach a caller-owned device workspace (256-byte aligned); applies then never grow a
- * workspace and fail with FS_ERR_ALLOC if it is too small (after fs_sketch_prepare they
+ * workspace: a call takes the row split that fits (results then differ in the last bits: another
+ * summation order), and fails with FS_ERR_ALLOC if not even the coarsest it accepts does (after fs_sketch_prepare they
  * allocate nothing at all).  Its contents need not be kept between calls.
  * (NULL, 0) detaches it and returns to the internal, lazily grown one. */
 fs_status fs_sketch_set_workspace(fs_sketch_t h, void* dev_ptr, size_t bytes);

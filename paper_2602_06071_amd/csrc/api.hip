@@ -62,15 +62,15 @@ bool is_pow2(uint32_t x) { return x && !(x & (x - 1)); }
 
 bool valid_dtype(fs_dtype dt) { return dt == FS_F32 || dt == FS_BF16 || dt == FS_F16; }
 
-// Bytes of workspace the variant that would run needs.  exact_orbit < 0: an upper bound that
+// Workspace of the variant that would run.  exact_orbit < 0: an upper bound that
 // holds whether or not the orbit table will be there; 0 / 1: the size of exactly this call,
 // without / with the table.
 fs_status needed_workspace(fs_sketch_t h, const void* A, int64_t lda, int64_t n, const void* out,
-                           int64_t ldo, fs_dtype dt, int* variant_out, size_t* bytes, int exact_orbit = -1) {
-  *bytes = 0;
+                           int64_t ldo, fs_dtype dt, int* variant_out, fs::Workspace* need, int exact_orbit = -1) {
+  *need = {};
   *variant_out = FS_VARIANT_GENERIC;
   if (h->kind == FS_KIND_SJLT_SCATTER) {
-    *bytes = fs::scatter_workspace_bytes(h->p, n, dt);
+    need->floor = need->want = fs::scatter_workspace_bytes(h->p, n, dt);
     return FS_OK;
   }
   if (h->kind == FS_KIND_GAUSS_DENSE)
@@ -81,11 +81,8 @@ fs_status needed_workspace(fs_sketch_t h, const void* A, int64_t lda, int64_t n,
   if (v == FS_VARIANT_AUTO) v = can ? FS_VARIANT_MFMA : FS_VARIANT_GENERIC;
   if (v == FS_VARIANT_MFMA) {
     if (!can) return FS_ERR_UNSUPPORTED;
-    *bytes = fs::mfma_workspace_bytes(h->p, n, dt);
-    if (exact_orbit >= 0) {
-      int mode = 0, flags = 0;
-      if (!fs::mfma_describe(h->p, A, lda, n, dt, exact_orbit != 0, &mode, &flags, bytes)) return FS_ERR_UNSUPPORTED;
-    }
+    if (exact_orbit >= 0) *need = fs::mfma_workspace(h->p, A, lda, n, dt, exact_orbit != 0);
+    else need->floor = need->want = fs::mfma_workspace_bytes(h->p, n, dt);
   }
   *variant_out = v;
   return FS_OK;
@@ -328,8 +325,10 @@ fs_status fs_sketch_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dt, size_
   const int64_t ld = (n + 7) & ~(int64_t)7;
   int v;
   const void* aligned = (const void*)(uintptr_t)256;
-  fs_status st = needed_workspace(h, aligned, ld, n, aligned, ld, dt, &v, bytes);
-  if (st == FS_ERR_UNSUPPORTED) { *bytes = 0; return FS_OK; }
+  fs::Workspace need;
+  fs_status st = needed_workspace(h, aligned, ld, n, aligned, ld, dt, &v, &need);
+  if (st == FS_ERR_UNSUPPORTED) return FS_OK;
+  *bytes = need.want;
   return st;
 }
 
@@ -363,20 +362,22 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
   const bool with_orbit = h->kind == FS_KIND_BLOCKPERM && fs::mfma_wants_orbit(h->p) &&
                           (!src.external || 2 * (size_t)h->p.M * sizeof(uint32_t) <= src.orbit_bytes);
   int variant;
-  size_t need;
+  fs::Workspace need;
   fs_status rc = needed_workspace(h, A, lda, n, out, ldo, dt, &variant, &need, with_orbit ? 1 : 0);
   if (rc != FS_OK) return rc;
   void* ws = nullptr;
+  size_t ws_bytes = 0;
   const uint32_t* orbit = nullptr;
-  if (src.external && need > src.plane_bytes) return FS_ERR_ALLOC;  // beyond the supplied memory: nothing is launched
+  if (src.external && need.floor > src.plane_bytes) return FS_ERR_ALLOC;  // beyond the supplied memory: nothing is launched
   if (!src.external) {
-    rc = ensure_workspace(h, need);
+    rc = ensure_workspace(h, need, st);
     if (rc != FS_OK) return rc;
   }
   const ProfSet prof = next_events(h, st);
   const fs::EventPair ev = prof.kernel;
   if (src.external) {
     ws = src.planes;
+    ws_bytes = src.plane_bytes;
     // such memory is shared between handles: the table of this handle's wiring is rebuilt on every
     // call (a wiring too long for the table's room runs without one: the kernels then skip the
     // orbit-ordered modes)
@@ -391,6 +392,7 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
       if (rc != FS_OK) return rc;
     }
     ws = h->ws;
+    ws_bytes = h->ws_bytes;
     orbit = h->orbit;
   }
 
@@ -407,7 +409,7 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
     e = fs::launch_blockrow(h->p, A, lda, n, out, ldo, dt, st, ev);
     what = "blockrow_kernel";
   } else if (variant == FS_VARIANT_MFMA) {
-    e = fs::launch_mfma(h->p, A, lda, n, out, ldo, dt, ws, orbit, st, ev, &mode, h->last_kernel,
+    e = fs::launch_mfma(h->p, A, lda, n, out, ldo, dt, ws, ws_bytes, orbit, st, ev, &mode, h->last_kernel,
                         sizeof(h->last_kernel));
   } else {
     e = fs::launch_generic(h->p, A, lda, n, out, ldo, dt, st, ev);
@@ -500,8 +502,10 @@ fs_status fs_sketch_plan(fs_sketch_t h, const void* A, int64_t ld, int64_t n, fs
     if (can && h->variant != FS_VARIANT_GENERIC) { v = FS_VARIANT_MFMA; m = mm; f = ff; ws = w; }
   } else if (n > 0) {
     int vv;
-    const fs_status rc = needed_workspace(h, A, ld, n, A, n, dt, &vv, &ws);
+    fs::Workspace need;
+    const fs_status rc = needed_workspace(h, A, ld, n, A, n, dt, &vv, &need);
     if (rc != FS_OK) return rc;
+    ws = need.want;
   }
   if (variant) *variant = v;
   if (mode) *mode = m;

@@ -92,6 +92,9 @@ hipError_t launch_generic_rows(const SketchParams& p, const void* G, int64_t ldg
 // Matrix-core path.  ws holds the per-slot partial tiles.
 bool mfma_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n, const void* out,
                     int64_t ldo, fs_dtype dt);
+// Workspace of one call with or without the orbit table, and an upper bound over alignments and the
+// presence of the table.
+Workspace mfma_workspace(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit);
 size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt);
 // orbit: device array of 2*M words (block at each orbit position of the wiring map
 // starting from block 0, then the inverse), or NULL.
@@ -100,14 +103,16 @@ bool mfma_wants_orbit(const SketchParams& p);
 // input-stationary, 3 the same with orbit runs; flags as in fs_plan_flags.  False: unsupported.
 bool mfma_describe(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt,
                    bool have_orbit, int* mode, int* flags, size_t* workspace);
+// ws_bytes: what ws holds; the row split is the best one that fits.
 hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
-                       int64_t ldo, fs_dtype dt, void* ws, const uint32_t* orbit, hipStream_t st,
+                       int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev, int* mode, char* desc, size_t desc_cap);
 
 // Output-stationary matrix-core kernel with Phi tiles shared by a work-group (16-bit types, blocks
 // exactly 32, 64 or 128 rows high): whether it takes the call with a given row split, and its
 // launch.  Without a row split it stores the result itself; with one, work-group z writes plane z
 // of the workspace and the caller runs the plane reduction.
+inline int64_t outs_stages(int64_t total, int zsplit) { return ((total + zsplit - 1) / zsplit + 1) / 2 * 2; }
 bool outs_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, int zsplit);
 hipError_t launch_outs(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out, int64_t ldo,
                        fs_dtype dt, const uint32_t* orbit, int zsplit, float* ws, int64_t ldw, hipStream_t st,

@@ -1,0 +1,446 @@
+// BlockPerm-SJLT apply on the matrix cores for calls that leave most of the chip idle when a wave
+// owns a (block, 128 columns) pair: few columns, few blocks, or both.
+//
+// The waves of a work-group share the block and the columns and split the K dimension: wave w
+// walks its own contiguous share of the work-group's 64-row stages with accumulators of its own,
+// and the shares are added through LDS in a fixed order before anything leaves the CU.  Compared with
+// splitting the rows over grid.z alone this writes and reads back NW times fewer partial planes.
+//
+// What bounds such calls: a wave needs a memory latency (1-2 us) per stage it waits for, so the time
+// is the number of dependent stages per wave, and for narrow inputs the matrix work spent on
+// columns that do not exist plus making Phi (one hash per row and slot, whatever the width).  Hence
+//  * tiles of 32, 64 or 128 columns (CPL accumulator columns per lane).  32 and 64 load element by
+//    element, lane = column, so any alignment and any n do; 128 as in mfma_kernel, 4 consecutive
+//    columns per lane by one vector load, which needs dword alignment;
+//  * narrow tiles keep one Phi tile per wave (all operands of a stage are read first, the tile is
+//    cleared and refilled behind those reads), so that twice as many waves fit in LDS;
+//  * the loads of A are under way before the slot tables and the first Phi tile are made.
+// Measured times of both kernels stand beside the planner's rule in k_mfma.hip.
+//
+// Modes as in mfma_kernel: IN-stationary stacks the destination blocks of one input block and leaves
+// partial planes; OUT-stationary owns an output block and stores it, or one plane per row split.
+// Inputs must be finite (a dense product also multiplies by the zeros of Phi).
+#pragma once
+#include <type_traits>
+
+#include "handle.h"
+#include "mfma_common.h"
+#include "mfma_plan.h"
+#include "spec.h"
+
+namespace fs {
+namespace {
+
+using namespace mm;
+
+// What a lane holds of one row of A until it is used: NR registers.
+template <typename T, int CPL, bool UNAL> struct KsRow {
+  static constexpr int NR = CPL == 4 ? (sizeof(T) == 4 ? 4 : UNAL ? 3 : 2) : CPL;
+};
+
+// UNAL (16-bit, CPL = 4): rows may start inside a dword; a lane's 4 columns are loaded as the three
+// dwords that hold them and shifted into place at the point of use.
+template <typename T, int MT, int CPL, bool IN_STAT, bool UNAL>
+__global__ __launch_bounds__(64 * ks_waves(MT, CPL)) __attribute__((amdgpu_waves_per_eu(ks_waves_per_simd(MT, CPL))))
+void ksplit_kernel(MfmaArgs a) {
+  constexpr int NW = ks_waves(MT, CPL);
+  constexpr int WC = 32 * CPL;          // columns of the work-group
+  constexpr int RWV = 32 * MT;          // stacked Phi rows
+  constexpr int TILE = RWV * PHI_LD;
+  constexpr int TILES = ks_tiles(CPL);  // Phi tiles per wave
+  constexpr int NR = KsRow<T, CPL, UNAL>::NR;
+  // ring depth in k-steps
+  constexpr int PFD = (NR >= 4 && MT <= 2) || MT * CPL == 8 ? 2 : 4;
+  static_assert(!UNAL || (sizeof(T) == 2 && CPL == 4), "");
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const SketchParams& p = a.p;
+  const int tid = (int)threadIdx.x, lane = tid & 63, kg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t* s_bk = reinterpret_cast<uint32_t*>(smem);  // block keys per slot
+  uint32_t* s_blk = s_bk + MAX_KAPPA;                  // IN: destination block; OUT: source block
+  uint16_t* s_phi = reinterpret_cast<uint16_t*>(smem + 2 * MAX_KAPPA * 4) + (size_t)wave * TILES * TILE;
+
+  // Which (block, column tile): as in mfma_kernel.  OUT: neighbours on the orbit side by side on one
+  // XCD, each visiting its inputs in the order of their orbit position modulo kappa.
+  uint32_t blk = blockIdx.x, jt = blockIdx.y, opos = 0;
+  const bool table = a.pos2blk != nullptr;
+  if (!IN_STAT && table) {
+    const uint32_t total = gridDim.x * gridDim.y;
+    uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+    if (total % 8 == 0) id = (id % 8) * (total / 8) + id / 8;
+    opos = id % gridDim.x;
+    jt = id / gridDim.x;
+    blk = __builtin_amdgcn_readfirstlane(a.pos2blk[opos]);
+  }
+  const int z = (int)(blockIdx.z % (uint32_t)a.zsplit);
+  const uint32_t slot0 = IN_STAT ? (blockIdx.z / (uint32_t)a.zsplit) * (uint32_t)a.group_slots : 0u;
+  const uint32_t kap = IN_STAT ? min(p.kappa - slot0, (uint32_t)a.group_slots) : p.kappa;
+  const uint32_t lbr = a.log2_br;
+  // stages [z*stages, ..) of this work-group, [t_lo, t_lo + t_n) of this wave (none, possibly)
+  const int wg_lo = z * a.stages, wg_n = min(a.stages, a.total - wg_lo);
+  const int per = (wg_n + NW - 1) / NW;
+  const int t_lo = wg_lo + wave * per;
+  const int t_n = max(0, min(per, wg_lo + wg_n - t_lo));
+  const uint32_t spb = (p.Bc + KC - 1) / KC;  // stages per input block
+
+  // ---- loads of A ---------------------------------------------------------------------------
+  const uint32_t mis = UNAL ? (uint32_t)((uintptr_t)a.A & 2) : 0u;  // A's first element inside its dword
+  const char* Abase = reinterpret_cast<const char*>(a.A) - mis;
+  const int64_t row_bytes = a.lda * (int64_t)sizeof(T);
+  const int col0 = CPL == 4 ? (int)jt * WC + 4 * (lane & 31) : (int)jt * WC + (lane & 31);
+  // A lane whose columns all lie at or beyond n gets an offset outside every descriptor range.
+  constexpr int NV = CPL == 4 ? 1 : CPL;  // lane offsets
+  uint32_t voff[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+    voff[v] = col0 + 32 * v < a.n ? mis + (uint32_t)(((int64_t)(kg * 8) * a.lda + col0 + 32 * v) * (int64_t)sizeof(T))
+                                  : 0x80000000u;
+  // UNAL: rows of one parity start in the same half of a dword (a block's first row may start in
+  // either); what the dword rounding of the offset adds is shifted out when the row is used.
+  // Range: the rows of block hb, ending with column n-1 of the last valid one (vector loads: rounded
+  // up to a dword, which lies in mapped memory).  Rows at or beyond Bc or d read as 0 -- but for UNAL,
+  // where the row behind the last valid one can share a dword with it: such rows are zeroed where
+  // they are used.
+  // What a lane's vector reads at or beyond column n feeds only accumulators that are never stored.
+  auto make_rsrc = [&](uint32_t hb, uint32_t* par) {
+    const int64_t first = (int64_t)hb * p.Bc;
+    const int64_t valid = min((int64_t)p.Bc, p.d - first);
+    const int64_t off = first * row_bytes;
+    const uint32_t odd = UNAL ? (uint32_t)(off & 2) : 0u;
+    *par = odd;
+    int64_t bytes = valid > 0 ? (int64_t)mis + odd + (valid - 1) * row_bytes + (int64_t)a.n * (int64_t)sizeof(T) : 0;
+    if (CPL == 4) bytes = (bytes + 3) & ~(int64_t)3;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Abase + (off - odd)), 0, (int)bytes, 0x00020000);
+  };
+  uint32_t ld[PFD][8][NR];
+  uint32_t f_par = 0;  // UNAL: 2 when the block's first row lies half a dword further on
+  __amdgpu_buffer_rsrc_t f_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Abase), 0, 0, 0x00020000);
+  uint32_t f_kr = 0, f_l = 0;           // k-step within the block, slot (OUT) of the next load
+  const uint32_t per_blk_k = spb * KSTEPS;
+  auto issue = [&](int slot) {
+    const uint32_t so = f_kr * 16u * (uint32_t)row_bytes;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t soj = so + (uint32_t)j * (uint32_t)row_bytes;
+      uint32_t(&dst)[NR] = ld[slot][j];
+      if constexpr (CPL == 4 && sizeof(T) == 4) {
+        const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(f_rs, voff[0], soj, 0));
+        dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+      } else if constexpr (UNAL) {
+        const uint32_t odd = (f_par + soj) & 2u;
+        const auto v = __builtin_amdgcn_raw_buffer_load_b96(f_rs, (voff[0] + odd) & ~3u, soj + f_par - odd, 0);
+        dst[0] = (uint32_t)v[0]; dst[1] = (uint32_t)v[1]; dst[2] = (uint32_t)v[2];
+      } else if constexpr (CPL == 4) {
+        const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(f_rs, voff[0], soj, 0));
+        dst[0] = v.x; dst[1] = v.y;
+      } else {
+#pragma unroll
+        for (int v = 0; v < CPL; ++v) {
+          if constexpr (sizeof(T) == 4)
+            dst[v] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(f_rs, voff[v], soj, 0);
+          else
+            dst[v] = (uint32_t)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(f_rs, voff[v], soj, 0);
+        }
+      }
+    }
+  };
+  auto advance = [&]() {  // wave-uniform; the branch is taken once per input block
+    ++f_kr;
+    if constexpr (!IN_STAT) {
+      if (f_kr == per_blk_k) {
+        f_kr = 0;
+        if (++f_l < p.kappa) f_rs = make_rsrc(__builtin_amdgcn_readfirstlane(s_blk[f_l]), &f_par);
+      }
+    }
+  };
+  // IN: the block is known, so the first loads leave before anything else
+  if (IN_STAT && t_n > 0) {
+    f_rs = make_rsrc(blk, &f_par);
+    f_kr = (uint32_t)t_lo * KSTEPS;
+#pragma unroll
+    for (int i = 0; i < PFD; ++i) { issue(i); advance(); }
+  }
+
+  // ---- slot tables and empty tiles -------------------------------------------------------------
+  // work-group barrier that orders LDS traffic only (the loads in flight stay in flight)
+  auto lds_barrier = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  auto clear_tile = [&](int buf) {
+    uint4* z4 = reinterpret_cast<uint4*>(s_phi + buf * TILE);
+#pragma unroll
+    for (int i = 0; i < (TILE / 8 + 63) / 64; ++i)
+      if (TILE / 8 % 64 == 0 || lane + i * 64 < TILE / 8) z4[lane + i * 64] = make_uint4(0, 0, 0, 0);
+  };
+  for (int sl = tid; sl < (int)kap; sl += 64 * NW) {
+    uint32_t x = blk;
+    if (table) {
+      if (IN_STAT) {  // f^-(slot0+sl+1)(blk)
+        const uint32_t pos = a.pos2blk[p.M + blk], back = (slot0 + (uint32_t)sl + 1u) % p.M;
+        x = a.pos2blk[(pos + p.M - back) % p.M];
+      } else {
+        const uint32_t l = (sl + p.kappa - (opos + 1) % p.kappa) % p.kappa;
+        x = a.pos2blk[(opos + 1 + l) % p.M];
+      }
+    } else {
+      for (int l = 0; l <= (int)slot0 + sl; ++l)
+        x = IN_STAT ? wire_prev(x, p.a_inv, p.b, p.M) : wire_next(x, p.a, p.b, p.M);
+    }
+    s_blk[sl] = x;
+    s_bk[sl] = IN_STAT ? block_key(p.key1, x, blk, p.M) : block_key(p.key1, blk, x, p.M);
+  }
+#pragma unroll
+  for (int i = 0; i < TILES; ++i) clear_tile(i);
+  lds_barrier();
+  if (!IN_STAT && t_n > 0) {
+    f_l = (uint32_t)t_lo / spb;
+    f_kr = ((uint32_t)t_lo - f_l * spb) * KSTEPS;
+    f_rs = make_rsrc(__builtin_amdgcn_readfirstlane(s_blk[f_l]), &f_par);
+#pragma unroll
+    for (int i = 0; i < PFD; ++i) { issue(i); advance(); }
+  }
+
+  // ---- Phi -------------------------------------------------------------------------------------
+  // Stage (p_l, p_us) of the next tile: its slot (OUT) and stage within the block.  One lane per
+  // input row.
+  uint32_t p_l = IN_STAT ? 0u : (uint32_t)t_lo / spb;
+  uint32_t p_us = IN_STAT ? (uint32_t)t_lo : (uint32_t)t_lo - p_l * spb;
+  auto scatter = [&](uint16_t* phi, uint32_t key, uint32_t u, uint32_t row0) {
+    RowHash rh;
+    if (!IN_STAT || p.br_pow2) rh = row_hash_pow2(key, u, p.Br);
+    else rh = row_hash_any(key, u, p.Br);
+    uint32_t r = rh.shift;
+    for (uint32_t i = 0; i < p.s; ++i) {
+      phi[__umul24(row0 + r, (uint32_t)PHI_LD) + lane] = (uint16_t)(((rh.signs >> i) << 15) | Fmt<T>::one);
+      r += rh.stride;
+      if (!IN_STAT || p.br_pow2) r &= p.Br - 1;
+      else if (r >= p.Br) r -= p.Br;
+    }
+  };
+  auto produce = [&](int buf, int part) {
+    uint16_t* phi = s_phi + buf * TILE;
+    const uint32_t u = p_us * KC + lane;
+    if constexpr (IN_STAT) {
+      for (uint32_t slot = part; slot < kap; slot += KSTEPS) scatter(phi, s_bk[slot], u, slot << lbr);
+    } else if (part == 0) {
+      scatter(phi, s_bk[p_l], u, 0u);
+    }
+  };
+  auto next_phi = [&]() {
+    ++p_us;
+    if constexpr (!IN_STAT) {
+      if (p_us == spb) { p_us = 0; ++p_l; }
+    }
+  };
+
+  f32x16 acc[MT][CPL];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int c = 0; c < CPL; ++c)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[mt][c][i] = 0.f;
+
+  // ---- main loop ---------------------------------------------------------------------------------
+  // UNAL, for the stage being used: which half of a dword the block's first row starts in (f_par may
+  // already belong to the next block), and how many of its rows lie in the block and before row d
+  uint32_t c_par = 0;
+  int c_rows = KC;
+  auto stage = [&](int t, auto last_tag) {
+    constexpr bool LAST = decltype(last_tag)::value;
+    const int cur_buf = TILES == 2 ? (t & 1) : 0, fill_buf = TILES == 2 ? 1 - cur_buf : 0;
+    const uint16_t* phi = s_phi + cur_buf * TILE;
+    if constexpr (UNAL) {  // (p_l, p_us) still is the stage being used
+      const int64_t hb = IN_STAT ? (int64_t)blk : (int64_t)__builtin_amdgcn_readfirstlane(s_blk[p_l]);
+      c_par = (uint32_t)((hb * p.Bc * row_bytes) & 2);
+      c_rows = (int)(min((int64_t)p.Bc, p.d - hb * p.Bc) - (int64_t)p_us * KC);
+    }
+    uint4 pa[TILES == 1 ? KSTEPS : 1][MT];
+    auto read_pa = [&](int ks, uint4 (&dst)[MT]) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        dst[mt] = *reinterpret_cast<const uint4*>(phi + (mt * 32 + (lane & 31)) * PHI_LD + ks * 16 + kg * 8);
+    };
+    if constexpr (TILES == 1) {
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) read_pa(ks, pa[ks]);
+      if constexpr (!LAST) clear_tile(0);
+    }
+    if constexpr (!LAST) next_phi();
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+      uint4(&pk)[MT] = pa[TILES == 1 ? ks : 0];
+      if constexpr (TILES == 2) read_pa(ks, pk);
+      if constexpr (!LAST) produce(fill_buf, ks);
+      uint32_t(&cur)[8][NR] = ld[ks % PFD];
+      const bool fetch = !LAST || ks + PFD < KSTEPS;  // compile-time
+      if constexpr (sizeof(T) == 2) {
+        uint4 op[CPL];
+        if constexpr (CPL == 4) {
+          uint2 r[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            if constexpr (UNAL) {
+              const uint32_t sh = ((mis + c_par + (uint32_t)j * (uint32_t)row_bytes) & 2u) << 3;
+              r[j].x = __builtin_amdgcn_alignbit(cur[j][1], cur[j][0], sh);
+              r[j].y = __builtin_amdgcn_alignbit(cur[j][2], cur[j][1], sh);
+            } else {
+              r[j].x = cur[j][0]; r[j].y = cur[j][1];
+            }
+          }
+          if (UNAL && c_rows < KC) {  // wave-uniform
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              if (ks * 16 + kg * 8 + j >= c_rows) r[j].x = r[j].y = 0u;
+          }
+          make_ops(r, op);
+        } else {
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) {
+            uint32_t* o = reinterpret_cast<uint32_t*>(&op[c]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] = perm(cur[2 * q + 1][c], cur[2 * q][c], 0x05040100u);
+          }
+        }
+        if (fetch) issue(ks % PFD);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pk[mt], op[c], acc[mt][c]);
+      } else {
+        // two columns at a time, piece by piece (an accumulator is reused after 2*MT other MFMAs)
+        constexpr int CG = CPL >= 2 ? 2 : 1;
+#pragma unroll
+        for (int c = 0; c < CPL; c += CG) {
+          uint4 pc[CG][3];
+#pragma unroll
+          for (int cc = 0; cc < CG; ++cc) {
+            uint32_t xs[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) xs[j] = cur[j][c + cc];
+            split_ops(xs, pc[cc][0], pc[cc][1], pc[cc][2]);
+          }
+#pragma unroll
+          for (int piece = 0; piece < 3; ++piece)
+#pragma unroll
+            for (int cc = 0; cc < CG; ++cc)
+#pragma unroll
+              for (int mt = 0; mt < MT; ++mt) acc[mt][c + cc] = mfma<T>(pk[mt], pc[cc][piece], acc[mt][c + cc]);
+        }
+        if (fetch) issue(ks % PFD);
+      }
+      if (fetch) advance();
+      __builtin_amdgcn_sched_barrier(0);  // keep k-steps apart: bounds register pressure
+    }
+    if constexpr (TILES == 2 && !LAST) clear_tile(cur_buf);
+  };
+  if (t_n > 0) {
+#pragma unroll
+    for (int part = 0; part < KSTEPS; ++part) produce(0, part);
+    for (int t = 0; t + 1 < t_n; ++t) stage(t, std::false_type{});
+    stage(t_n - 1, std::true_type{});
+  }
+
+  // ---- sum of the waves' shares, in wave order, and store --------------------------------------------
+  // 32 rows at a time: every wave puts its tile into LDS as [row][WC], then all threads add the
+  // tiles of the waves that had stages and store, four columns of a row each.  (Adding in registers
+  // and storing from one wave: 250 accumulators and their addresses spilled.)
+  // Register i of tile (mt, c) holds stacked row 32 mt + 8 (i/4) + 4 kg + i%4 of column 4 (lane%32) + c
+  // (CPL = 4) or 32 c + lane%32.
+  float* mbuf = reinterpret_cast<float*>(smem + 2 * MAX_KAPPA * 4);
+  const int active = (wg_n + per - 1) / per;  // waves that had stages
+  constexpr int UNITS = 32 * WC / 4;          // float4 per 32-row tile
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    lds_barrier();  // the Phi tiles, or the tiles of the 32 rows before, have been read
+    if (wave < active) {
+      float* dst = mbuf + (size_t)wave * 32 * WC;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int row = 8 * (i >> 2) + 4 * kg + (i & 3);
+        if constexpr (CPL == 4) {
+          *reinterpret_cast<float4*>(dst + row * WC + 4 * (lane & 31)) =
+              make_float4(acc[mt][0][i], acc[mt][1][i], acc[mt][2][i], acc[mt][3][i]);
+        } else {
+#pragma unroll
+          for (int c = 0; c < CPL; ++c) dst[row * WC + 32 * c + (lane & 31)] = acc[mt][c][i];
+        }
+      }
+    }
+    lds_barrier();
+    for (int e = tid; e < UNITS; e += 64 * NW) {
+      const uint32_t row_s = (uint32_t)(mt * 32 + e / (WC / 4));
+      const int col = (int)jt * WC + (e % (WC / 4)) * 4;
+      if (col >= a.n) continue;
+      const float4* src = reinterpret_cast<const float4*>(mbuf) + e;
+      float4 v = src[0];
+      for (int w = 1; w < active; ++w) {
+        const float4 o = src[(size_t)w * UNITS];
+        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+      }
+      if (IN_STAT) {
+        const uint32_t slot = row_s >> lbr, r = row_s & ((1u << lbr) - 1u);
+        if (slot >= kap || r >= p.Br) continue;  // idle rows: above the stacked slots, or above Br in a slot
+        float* dst = a.ws + (((int64_t)z * p.kappa + slot0 + slot) * p.k + (int64_t)s_blk[slot] * p.Br + r) * a.ldw + col;
+        *reinterpret_cast<float4*>(dst) = v;
+      } else if (a.zsplit > 1) {
+        float* dst = a.ws + ((int64_t)z * p.k + (int64_t)blk * p.Br + row_s) * a.ldw + col;
+        *reinterpret_cast<float4*>(dst) = v;
+      } else {
+        T* dst = reinterpret_cast<T*>(a.out) + ((int64_t)blk * p.Br + row_s) * a.ldo + col;
+        const float sv[4] = {v.x * p.scale, v.y * p.scale, v.z * p.scale, v.w * p.scale};
+        if (a.out_vec && col + 3 < a.n) {
+          if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2*>(dst) = pack4<T>(sv);
+          else *reinterpret_cast<float4*>(dst) = make_float4(sv[0], sv[1], sv[2], sv[3]);
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (col + c < a.n) Elt<T>::store(dst + c, sv[c]);
+        }
+      }
+    }
+  }
+}
+
+template <auto kernel>
+hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const MfmaArgs& a) {
+  static size_t raised = 64 * 1024;  // the dynamic-LDS limit set for this kernel so far
+  if (lds > raised) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    raised = lds;
+  }
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
+  return hipGetLastError();
+}
+
+template <typename T, int MT, int CPL, bool UNAL>
+hipError_t launch_mode(const Plan& pl, const MfmaArgs& a, dim3 grid, hipStream_t st) {
+  constexpr unsigned threads = 64 * ks_waves(MT, CPL);
+  return pl.in_stat ? go<ksplit_kernel<T, MT, CPL, true, UNAL>>(grid, threads, pl.lds, st, a)
+                    : go<ksplit_kernel<T, MT, CPL, false, UNAL>>(grid, threads, pl.lds, st, a);
+}
+
+template <typename T, int MT>
+hipError_t launch_cpl(const Plan& pl, const MfmaArgs& a, dim3 grid, hipStream_t st) {
+  if (pl.cpl == 1) return launch_mode<T, MT, 1, false>(pl, a, grid, st);
+  if (pl.cpl == 2) return launch_mode<T, MT, 2, false>(pl, a, grid, st);
+  if constexpr (sizeof(T) == 2) {
+    if (pl.unal) return launch_mode<T, MT, 4, true>(pl, a, grid, st);
+  }
+  return launch_mode<T, MT, 4, false>(pl, a, grid, st);
+}
+
+template <typename T>
+hipError_t launch_ksplit(const Plan& pl, const MfmaArgs& a, dim3 grid, hipStream_t st) {
+  return pl.mt == 1   ? launch_cpl<T, 1>(pl, a, grid, st)
+         : pl.mt == 2 ? launch_cpl<T, 2>(pl, a, grid, st)
+                      : launch_cpl<T, 4>(pl, a, grid, st);
+}
+
+}  // namespace
+}  // namespace fs

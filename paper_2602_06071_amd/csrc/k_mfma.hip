@@ -50,9 +50,11 @@ namespace fs {
 hipError_t launch_mfma_f32(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
 hipError_t launch_mfma_bf16(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
 hipError_t launch_mfma_f16(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
-hipError_t launch_mfma_f32_unal(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
 hipError_t launch_mfma_bf16_unal(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
 hipError_t launch_mfma_f16_unal(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
+hipError_t launch_ksplit_f32(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
+hipError_t launch_ksplit_bf16(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
+hipError_t launch_ksplit_f16(const mm::Plan& pl, const mm::MfmaArgs& a, dim3 grid, hipStream_t st);
 
 namespace {
 
@@ -76,8 +78,50 @@ size_t lds_bytes(int mt, int nrg, int ncg, int run, size_t merge) {
   return tables + (tiles > merge ? tiles : merge);
 }
 
+// ---- row splits -----------------------------------------------------------------------------------
+// Modelled time (us) of a launch in which `units` work-groups of `nw` waves share `total` stages each
+// in `z` row splits: the longest of (1) what the waves issue, spread over the 1024 SIMDs, (2) rounds of
+// resident waves, where each stage of a wave costs most of a memory latency on top of its
+// instructions (two where the ring holds half a stage), (3) the stream of A; then the merge of the waves' shares, the partial planes (written
+// at 3.4, read back at 6 TB/s: rates measured on this kernel pair; about half that price while they stay in
+// the Infinity Cache) and, where only the split makes
+// one necessary, the launch of the reduction.
+struct SplitCost {
+  double units, stage_us, latency_us, slots, stream_us, plane_bytes, merge_us;  // plane_bytes: of one split
+  int nw, total;
+  bool has_reduce;
+  double at(int z) const {
+    const int per_wg = (total + z - 1) / z, per_wave = (per_wg + nw - 1) / nw;
+    const double waves = units * z * nw;
+    double t = (waves <= slots ? 1.0 : waves / slots) * per_wave * (stage_us + latency_us);
+    const double work = units * z * nw * per_wave * stage_us / 1024;
+    if (work > t) t = work;
+    if (stream_us > t) t = stream_us;
+    t += merge_us;
+    if (has_reduce || z > 1) t += plane_bytes * z * (1 / 3.4e6 + 1 / 6e6) * (plane_bytes * z < 40e6 ? 0.5 : 1.0);
+    if (!has_reduce && z > 1) t += 4.0;
+    return t;
+  }
+  // Smallest modelled time over the splits whose planes fit max_bytes.
+  int best(double max_bytes, int zmax, double* t_best) const {
+    int bz = 1, last = 0;
+    double bt = at(1);
+    for (int z = 2; z <= total && z <= zmax; ++z) {
+      const int st = (total + z - 1) / z;
+      if (st == last || (total + st - 1) / st != z) continue;
+      last = st;
+      if (plane_bytes * z > max_bytes) break;
+      const double t = at(z);
+      if (t < bt * 0.98) { bt = t; bz = z; }
+    }
+    *t_best = bt;
+    return bz;
+  }
+};
+
+// `limit`: bytes of workspace the call can have at most.
 Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt,
-               bool have_orbit) {
+               bool have_orbit, size_t limit) {
   Plan pl;
   const size_t esz = dt == FS_F32 ? 4 : 2;
   if (n < 1) return pl;
@@ -87,7 +131,8 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   if (!p.br_pow2 && brp > 128) return pl;
   const int64_t blk_stages = ((int64_t)p.Bc + KC - 1) / KC;  // the last one may be partly filled
   if ((uintptr_t)A % esz) return pl;
-  pl.unal = (uintptr_t)A % (4 * esz) || (lda * esz) % (4 * esz);  // no 4-column vector loads
+  pl.vec4 = !((uintptr_t)A % (4 * esz) || (lda * esz) % (4 * esz));
+  pl.unal = (uintptr_t)A % 4 || (lda * esz) % 4;  // vector loads need dword alignment
   if ((16 * lda + n) * (int64_t)esz >= ((int64_t)1 << 31)) return pl;     // 32-bit lane offsets
   if (blk_stages * KC * lda * (int64_t)esz >= ((int64_t)1 << 31)) return pl;  // 32-bit row offsets in a block
   pl.ncg = n > WCOLS ? 2 : 1;
@@ -109,39 +154,49 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   if (!can_in && !can_out) return pl;
   const int group_slots = grouped ? (int)(128 / brp) : (int)p.kappa;
   const int groups = (int)((p.kappa + group_slots - 1) / group_slots);
+  pl.ldw = (n + 3) & ~(int64_t)3;
+  const double plane = (double)p.k * (double)pl.ldw * 4.0;  // bytes of one partial plane
 
-  // IN-stationary row split: more work-groups fill the chip better, but every split adds kappa
-  // partial planes.  Pick the split with the smallest modelled time: A streamed at ~6 TB/s once
-  // there is a wave per SIMD (1024 of them), planes written at ~3.4 TB/s and read back at ~6 TB/s
-  // (rates measured on this kernel pair).
-  int zs = 1;
+  // IN-stationary row split of the 128-column waves: more work-groups fill the chip better, but every
+  // split adds kappa partial planes.  Pick the split with the smallest modelled time: A streamed at
+  // ~6 TB/s once there is a wave per SIMD (1024 of them), planes written at ~3.4 TB/s and read back at
+  // ~6 TB/s (rates measured on this kernel pair).
+  int zs = 1, zs_even = 1;  // zs_even: only splits that divide the block evenly
   {
     const double a_bytes = (double)p.d * (double)n * esz * groups;
     const double waves_per_wg = pl.ncg * (can_in ? nrg_i : 1);
-    double best = 0;
+    double best = 0, best_even = 0;
+    bool divides = true;
     for (int zc = 1; zc <= 16; zc *= 2) {
-      if (zc > 1 && p.Bc % (uint32_t)(zc * KC) != 0) break;  // splits are whole stages
       const double waves = (double)p.M * col_tiles * zc * waves_per_wg * groups;
       const double plane_bytes = (double)zc * p.kappa * (double)p.k * (double)n * 4.0;
       const double t = a_bytes / (6e12 * (waves < 1024 ? waves / 1024 : 1.0)) + plane_bytes / 3.4e12 +
                        plane_bytes / 6e12;
-      if (zc == 1 || t < best) { best = t; zs = zc; }
+      if (zc == 1 || (divides && p.Bc % (uint32_t)(zc * KC) == 0)) {
+        if (zc == 1 || t < best_even) { best_even = t; zs_even = zc; }
+      } else {
+        divides = false;
+      }
+      if (zc == 1 || (zc <= blk_stages && t < best)) { best = t; zs = zc; }
     }
   }
   // workspace traffic (write + read of the partial planes) relative to reading A once
-  const double rho = 2.0 * zs * p.kappa * (double)p.k * 4.0 / ((double)p.d * esz);
+  const double rho = 2.0 * zs_even * p.kappa * (double)p.k * 4.0 / ((double)p.d * esz);
   const bool out_starved = (int64_t)p.M * col_tiles < 256;  // fewer output tiles than CUs
   // IN pays for its partial planes (rho, written at about half the read rate), OUT for kappa-1
   // re-reads of A that mostly hit L2 (about 0.3 of an HBM read each): measured cross-over
   // rho ~ 0.23 (kappa - 1).  With kappa = 1 there is nothing to re-read and OUT stores directly.
   pl.in_stat = can_in && (!can_out || (p.kappa > 1 && (out_starved || rho <= 0.23 * (p.kappa - 1))));
+  // 16-bit shapes of the kernel with work-group-shared Phi tiles, were the rows aligned for it
+  const bool shared_shape = !pl.in_stat && nsub == 1 &&
+                            outs_supported(p, (const void*)(uintptr_t)256, (lda + 3) & ~(int64_t)3, n, dt, 1);
+  int floor_planes = 0;  // what a call must be able to hold whatever the split
   if (pl.in_stat) {
     pl.mt = mt_i; pl.nrg = nrg_i; pl.zsplit = zs;
-    pl.stages = (int)(blk_stages / zs);
-    pl.ldw = (n + 3) & ~(int64_t)3;
-    pl.planes = zs * (int)p.kappa;
+    pl.total = (int)blk_stages;
     pl.groups = groups; pl.group_slots = group_slots;
     if (zs * groups > 65535) return pl;
+    floor_planes = zs_even * (int)p.kappa;
     // orbit runs of 4: the 64-row / 256-column shape, enough blocks for one work-group
     // per CU, and a merge buffer that fits beside nothing else in LDS
     constexpr int R = 4;
@@ -150,48 +205,121 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
         p.M % R == 0 && (int64_t)(p.M / R) * col_tiles >= 256 && merge <= 100 * 1024) {
       pl.run = R;
       pl.planes = (int)((p.kappa + R - 2) / R) + 1;
+      if (pl.vec4) floor_planes = pl.planes;
     }
   } else {
     // split the kappa*Bc rows of a work-group over grid.z when there are too few output tiles to
     // fill the chip (small n), as long as the extra plane traffic stays below that of reading A
-    const int total_stages = (int)((int64_t)p.kappa * blk_stages);
-    int zo = 1;
-    // 16-bit shapes of the kernel with work-group-shared Phi tiles: its work-groups cover 512
+    pl.total = (int)((int64_t)p.kappa * blk_stages);
+    int zo = 1, zo_even = 1;
+    // The kernel with work-group-shared Phi tiles: its work-groups cover 512
     // columns and hold a CU each, so it wants a row split that brings their number to between
     // five eighths of the CUs and all of them (measured on wide: n = 2560 and 3072 whole, 0.20 ms
     // against 0.25 and 0.26 ms split; n = 1536 in 2 splits, n = 1024 in 4)
     const int64_t shared_wgs = (int64_t)p.M * ((n + 511) / 512);
-    const bool shared_phi = nsub == 1 && !pl.unal && outs_supported(p, A, lda, n, dt, 1);
     auto enough = [&](int z) {
-      return shared_phi ? shared_wgs * z >= 160 : (int64_t)p.M * col_tiles * nsub * z >= 512;
+      return shared_shape ? shared_wgs * z >= 160 : (int64_t)p.M * col_tiles * nsub * z >= 512;
     };
-    // (the split must divide the stages; the shared-Phi kernel wants an even number per work-group)
-    while (!enough(zo) && zo < 8 && total_stages % (zo * 2 * (shared_phi ? 2 : 1)) == 0 &&
-           2.0 * (zo * 2) * (double)p.k * 4.0 / ((double)p.d * esz) <= 1.0)
-      zo *= 2;
+    auto cheap = [&](int z) { return 2.0 * z * (double)p.k * 4.0 / ((double)p.d * esz) <= 1.0; };
+    while (!enough(zo_even) && zo_even < 8 && pl.total % (zo_even * 2 * (shared_shape && pl.vec4 ? 2 : 1)) == 0 && cheap(zo_even * 2))
+      zo_even *= 2;
+    floor_planes = zo_even > 1 ? zo_even : 0;
+    // any split whose pieces are whole pairs of stages (the shared-Phi kernel and the deep ring want
+    // even numbers); beyond 8 only while a piece keeps 8 stages
+    while (!enough(zo) && cheap(zo * 2) && (zo < 8 ? pl.total / (zo * 2) >= 2 : zo < 32 && pl.total / (zo * 2) >= 8)) zo *= 2;
     pl.mt = mt_o; pl.nrg = nrg_o; pl.zsplit = zo; pl.nsub = nsub;
     if (col_tiles * nsub > 65535) return pl;
-    pl.stages = total_stages / zo;
-    if (zo > 1) { pl.ldw = (n + 3) & ~(int64_t)3; pl.planes = zo; }
   }
-  // bf16 with one wave per SIMD (128-row tiles) has the registers for a ring twice as deep, and
-  // with a single wave nothing else hides the latency of A; the two-stage ring needs an even
-  // stage count.  (For fp32 the deeper ring measured no gain.)
-  if (pl.mt == 4 && dt != FS_F32 && pl.stages % 2 == 0 && !pl.unal) pl.pfx = 2;
-  // 16-bit output-stationary shapes without row splits or slices go to the kernel whose work-group
-  // shares its Phi tiles (measured on the "wide" workload: 0.445 against 0.52 ms)
-  pl.outs = !pl.in_stat && pl.nsub == 1 && !pl.unal && outs_supported(p, A, lda, n, dt, pl.zsplit);
+  pl.ws_floor = (size_t)floor_planes * (size_t)p.k * (size_t)pl.ldw * sizeof(float);
+  if (limit < pl.ws_floor) limit = pl.ws_floor;  // (the call is refused before it gets here)
+  double max_bytes = (double)(pl.ws_floor > kSplitScratch ? pl.ws_floor : kSplitScratch);
+  if ((double)limit < max_bytes) max_bytes = (double)limit;
+  const double per_split = pl.in_stat ? plane * p.kappa : plane;
+  if (pl.run == 1)
+    while (pl.zsplit > 1 && per_split * pl.zsplit > max_bytes) pl.zsplit /= 2;
+
   // Shapes the kernel with several output blocks per wave takes go there (it loads A from L2
   // (kappa+S-1)/S times per output block, not kappa times; measured on "mid": kappa = 4, 0.365
   // against 0.395 ms, kappa = 8, 0.63 against 0.74 ms).  It stores the result itself.
   if (stacked_supported(p, A, lda, n, dt, have_orbit)) {
-    pl.stacked = true; pl.unal = false; pl.outs = false; pl.in_stat = false; pl.run = 1; pl.planes = 0;
-    pl.zsplit = 1; pl.nsub = 1; pl.groups = 1;
+    pl.stacked = true; pl.unal = false; pl.in_stat = false; pl.run = 1; pl.planes = 0;
+    pl.zsplit = 1; pl.nsub = 1; pl.groups = 1; pl.ws_floor = 0;
+    pl.ok = true;
+    return pl;
   }
+  // whole pairs of stages for the shared-Phi kernel and for 16-bit 128-row tiles (their ring spans
+  // two stages)
+  auto settle = [&](bool pairs) {
+    pl.stages = pairs ? (int)outs_stages(pl.total, pl.zsplit) : (pl.total + pl.zsplit - 1) / pl.zsplit;
+    pl.zsplit = (pl.total + pl.stages - 1) / pl.stages;
+  };
+  // 16-bit output-stationary shapes without slices go to the kernel whose work-group
+  // shares its Phi tiles (measured on the "wide" workload: 0.445 against 0.52 ms)
+  if (shared_shape) settle(true);
+  pl.outs = shared_shape && pl.vec4 && outs_supported(p, A, lda, n, dt, pl.zsplit);
+
+  // The K-split kernel: few columns, or too few (block, column tile) pairs (k_ksplit_kernel.h).  Up to 64
+  // columns always; beyond, both kernels are priced by the model above, and the K-split one has to
+  // promise a fifth less.  Measured (us per call, mfma_kernel with its evenly dividing splits -> this plan):
+  // fp32 262144 x 1, k = 4096, kappa = 4: 40 -> 17; fp32 1923840 x 48, kappa = 8: 632 -> 118; half
+  // 1575567 x 7 with eight 98473-row blocks: 3166 -> 107; fp32 262144 x 256 ("tall"): 77 -> 72; half 1728
+  // columns of eight 3520-row blocks: 104 -> 32; where the 128-column waves fill the chip they stay.  (Decided without looking at the alignment, so that an
+  // unaligned view sums in the same order as a packed copy of it; and input-stationary calls
+  // of up to four 256-column chunks, where one chunk leaves CUs without a work-group, are planned as if n were 256:
+  // they sum in the same order as their chunks.)
+  if (!shared_shape && nsub == 1 && pl.run == 1) {
+    const int kap = pl.in_stat ? (group_slots < (int)p.kappa ? group_slots : (int)p.kappa) : 1;
+    const double phi_us = 0.12 + 0.07 * kap;
+    const double mfma_us = pl.mt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0;  // per 32 columns and stage
+    const double conv_us = esz == 4 ? 0.16 : 0.03;
+    const int64_t nr = pl.in_stat && n % 256 == 0 && n <= 1024 && (int64_t)p.M * groups * 2 < 256 ? 256 : n;
+    const double a_us = (double)p.d * (double)nr * esz / 5.5e6, split_bytes = per_split * (double)nr / (double)n;
+    const double stream = pl.in_stat ? a_us * groups : a_us * (1 + 0.3 * (p.kappa - 1));
+    const int zmax = 65535 / groups;
+    // (the waves of mfma_kernel are column groups: they do not share the stages)
+    const SplitCost old{(double)p.M * ((nr + WCOLS - 1) / WCOLS) * groups, phi_us + 4 * (mfma_us + conv_us),
+                        esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : 0.8, pl.mt == 4 ? 1024.0 : 2048.0, stream, split_bytes, 0.0, 1, pl.total, pl.in_stat};
+    // (a split with kappa = 1 adds the planes and a launch to a call that streams A once: only for a clear gain)
+    if (old.at(1) < old.at(pl.zsplit) * (p.kappa == 1 ? 1.15 : 1.0)) pl.zsplit = 1;
+    const double t_old = old.at(pl.zsplit);
+    const int cpl = n <= 32 ? 1 : n <= 64 ? 2 : 4;
+    const int nw = ks_waves(pl.mt, cpl);
+    const size_t lds = ks_lds_bytes(pl.mt, cpl);
+    const int64_t ct = (n + 32 * cpl - 1) / (32 * cpl);
+    int per_cu = (int)(kLdsBudget / lds);
+    const int by_regs = 4 * ks_waves_per_simd(pl.mt, cpl) / nw;
+    if (by_regs < per_cu) per_cu = by_regs;
+    const SplitCost ks{(double)p.M * ((nr + 32 * cpl - 1) / (32 * cpl)) * groups, phi_us + cpl * (mfma_us + conv_us),
+                       esz == 4 && cpl == 4 && pl.mt <= 2 ? 1.6 : 0.8, 256.0 * per_cu * nw, stream, split_bytes, 1.0 + 0.25 * pl.mt * cpl, nw, pl.total, pl.in_stat};
+    double t_ks = 0;
+    int z = ks.best(max_bytes, zmax, &t_ks);
+    while (z > 1 && per_split * z > max_bytes) --z;
+    if (ct <= 65535 && (cpl < 4 || t_ks < 0.8 * t_old)) {
+      pl.ks = true;
+      pl.cpl = cpl; pl.lds = lds;
+      pl.zsplit = z;
+      settle(false);
+      pl.planes = pl.in_stat ? pl.zsplit * (int)p.kappa : pl.zsplit > 1 ? pl.zsplit : 0;
+      pl.ok = true;
+      return pl;
+    }
+  }
+
+  const bool pairs = pl.mt == 4 && dt != FS_F32 && pl.total % 2 == 0 && !pl.unal;
+  settle(pairs || shared_shape);
+  if (pl.run == 1) pl.planes = pl.in_stat ? pl.zsplit * (int)p.kappa : pl.zsplit > 1 ? pl.zsplit : 0;
+  // bf16 with one wave per SIMD (128-row tiles) has the registers for a ring twice as deep, and
+  // with a single wave nothing else hides the latency of A; the two-stage ring needs an even
+  // stage count.  (For fp32 the deeper ring measured no gain.)
+  if (pairs) pl.pfx = 2;
   pl.lds = lds_bytes(pl.mt, pl.nrg, pl.ncg, pl.run,
                      pl.run > 1 ? (size_t)(p.kappa + pl.run - 1) * p.Br * 256 * 4 : 0);
-  pl.ok = pl.stacked || pl.lds <= kLdsBudget;
+  pl.ok = pl.lds <= kLdsBudget;
   return pl;
+}
+
+size_t plan_bytes(const SketchParams& p, const Plan& pl) {
+  return (size_t)pl.planes * (size_t)p.k * (size_t)pl.ldw * sizeof(float);
 }
 
 }  // namespace
@@ -199,18 +327,29 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
 bool mfma_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n, const void* out,
                     int64_t ldo, fs_dtype dt) {
   (void)out; (void)ldo;
-  return make_plan(p, A, lda, n, dt, false).ok;
+  return make_plan(p, A, lda, n, dt, false, SIZE_MAX).ok;
+}
+
+Workspace mfma_workspace(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit) {
+  const Plan pl = make_plan(p, A, lda, n, dt, have_orbit, SIZE_MAX);
+  Workspace w;
+  if (!pl.ok) return w;
+  w.floor = pl.ws_floor;
+  w.want = plan_bytes(p, pl);
+  if (w.want < w.floor) w.want = w.floor;
+  return w;
 }
 
 bool mfma_describe(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt,
                    bool have_orbit, int* mode, int* flags, size_t* workspace) {
-  const Plan pl = make_plan(p, A, lda, n, dt, have_orbit);
+  const Plan pl = make_plan(p, A, lda, n, dt, have_orbit, SIZE_MAX);
   if (!pl.ok) return false;
   *mode = !pl.in_stat ? 1 : pl.run > 1 ? 3 : 2;
-  *flags = (pl.unal ? FS_PLAN_ELEMENT_LOADS : 0) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
-           (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (pl.zsplit > 1 ? FS_PLAN_SPLIT : 0) |
+  const bool split = pl.zsplit > 1 || (pl.ks && pl.stages >= ks_waves(pl.mt, pl.cpl));  // every wave has a share
+  *flags = (pl.vec4 ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
+           (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (split ? FS_PLAN_SPLIT : 0) |
            (pl.stacked ? FS_PLAN_STACKED : 0);
-  *workspace = (size_t)pl.planes * (size_t)p.k * (size_t)pl.ldw * sizeof(float);
+  *workspace = mfma_workspace(p, A, lda, n, dt, have_orbit).want;
   return true;
 }
 
@@ -219,11 +358,14 @@ bool mfma_wants_orbit(const SketchParams& p) {
 }
 
 size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt) {
-  // sized without the orbit-run saving, so it holds for either mode
+  // the largest over aligned and odd row strides, with and without the orbit table
   const int64_t ld = (n + 7) & ~(int64_t)7;
-  const Plan pl = make_plan(p, (const void*)(uintptr_t)256, ld, n, dt, false);
-  if (!pl.ok || pl.planes == 0) return 0;
-  return (size_t)pl.planes * (size_t)p.k * (size_t)pl.ldw * sizeof(float);
+  size_t most = 0;
+  for (int i = 0; i < 4; ++i) {
+    const Workspace w = mfma_workspace(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0);
+    if (w.want > most) most = w.want;
+  }
+  return most;
 }
 
 // The fixed-order sum of the partial planes into the output, scaled and converted.
@@ -232,28 +374,26 @@ static hipError_t launch_reduce(const SketchParams& p, const Plan& pl, int64_t n
   const size_t esz = dt == FS_F32 ? 4 : 2;
   const int out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
   const int64_t work = p.k * (pl.ldw / 4);
-  const unsigned blocks = (unsigned)((work + 255) / 256);
+  // (65536 threads are one per lane of a SIMD on every SIMD)
+  const bool parts = pl.planes >= 16 && work < 65536;
+  const int64_t opw = parts ? 32 : 256;
+  const unsigned blocks = (unsigned)((work + opw - 1) / opw);
   const uint32_t* blk2pos = orbit ? orbit + p.M : nullptr;
-  if (dt == FS_BF16)
-    hipLaunchKernelGGL(reduce_planes_kernel<uint16_t>, dim3(blocks), dim3(256), 0, st, ws, pl.planes,
-                       p.k, pl.ldw, (int)n, (uint16_t*)out, ldo, p.scale, out_vec, pl.run, blk2pos,
-                       p.Br, p.kappa);
-  else if (dt == FS_F16)
-    hipLaunchKernelGGL(reduce_planes_kernel<f16>, dim3(blocks), dim3(256), 0, st, ws, pl.planes,
-                       p.k, pl.ldw, (int)n, (f16*)out, ldo, p.scale, out_vec, pl.run, blk2pos,
-                       p.Br, p.kappa);
-  else
-    hipLaunchKernelGGL(reduce_planes_kernel<float>, dim3(blocks), dim3(256), 0, st, ws, pl.planes,
-                       p.k, pl.ldw, (int)n, (float*)out, ldo, p.scale, out_vec, pl.run, blk2pos,
-                       p.Br, p.kappa);
+#define FS_RED(T, PARTS)                                                                                          \
+  hipLaunchKernelGGL((reduce_planes_kernel<T, PARTS>), dim3(blocks), dim3(256), 0, st, ws, pl.planes, p.k, pl.ldw, \
+                     (int)n, (T*)out, ldo, p.scale, out_vec, pl.run, blk2pos, p.Br, p.kappa)
+  if (dt == FS_BF16)     { if (parts) FS_RED(uint16_t, 8); else FS_RED(uint16_t, 1); }
+  else if (dt == FS_F16) { if (parts) FS_RED(f16, 8); else FS_RED(f16, 1); }
+  else                   { if (parts) FS_RED(float, 8); else FS_RED(float, 1); }
+#undef FS_RED
   return hipGetLastError();
 }
 
 hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
-                       int64_t ldo, fs_dtype dt, void* ws, const uint32_t* orbit, hipStream_t st,
+                       int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev, int* mode, char* desc, size_t desc_cap) {
-  const Plan pl = make_plan(p, A, lda, n, dt, orbit != nullptr);
-  if (!pl.ok) return hipErrorInvalidValue;
+  const Plan pl = make_plan(p, A, lda, n, dt, orbit != nullptr, ws_bytes);
+  if (!pl.ok || plan_bytes(p, pl) > ws_bytes) return hipErrorInvalidValue;
   *mode = !pl.in_stat ? 1 : pl.run > 1 ? 3 : 2;
   if (pl.stacked) return launch_stacked(p, A, lda, n, out, ldo, dt, orbit, st, ev, desc, desc_cap);
   hipError_t e;
@@ -262,7 +402,12 @@ hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_
     if (e != hipSuccess || pl.planes == 0) return e;
     return launch_reduce(p, pl, n, out, ldo, dt, (float*)ws, orbit, st);
   }
-  if (desc && desc_cap)  // the template arguments of the instantiation launched below, in order
+  if (pl.ks) {
+    if (desc && desc_cap)
+      snprintf(desc, desc_cap, "ksplit_kernel<%s,%d,%d,%s,%s>%s", dt == FS_F32 ? "f32" : dt == FS_BF16 ? "bf16" : "f16",
+               pl.mt, pl.cpl, pl.in_stat ? "in" : "out", pl.unal && pl.cpl == 4 ? "unal" : "-",
+               pl.planes ? "+reduce_planes" : "");
+  } else if (desc && desc_cap)  // the template arguments of the instantiation launched below, in order
     snprintf(desc, desc_cap, "mfma_kernel<%s,%d,%d,%d,%s,%d,%d,%d,%s,%s>%s",
              dt == FS_F32 ? "f32" : dt == FS_BF16 ? "bf16" : "f16", pl.mt, pl.nrg, pl.ncg,
              pl.in_stat ? "in" : "out", pl.run, pl.cpl, pl.unal ? 1 : pl.pfx, pl.nsub > 1 ? "sub" : "-",
@@ -272,20 +417,25 @@ hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_
   a.p = p; a.A = A; a.out = out; a.ws = (float*)ws;
   a.pos2blk = orbit;
   a.lda = lda; a.ldo = ldo; a.ldw = pl.ldw; a.n = (int)n;
-  a.zsplit = pl.zsplit; a.stages = pl.stages;
+  a.zsplit = pl.zsplit; a.stages = pl.stages; a.total = pl.total;
+  a.vec4 = pl.vec4 ? 1 : 0;
   a.group_slots = pl.in_stat ? pl.group_slots : (int)p.kappa;
   a.nsub = pl.nsub;
   a.out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
   a.log2_br = 0;
   while ((1u << a.log2_br) < p.Br) ++a.log2_br;
-  const int tnw = 32 * pl.cpl * pl.ncg;
+  const int tnw = 32 * pl.cpl * (pl.ks ? 1 : pl.ncg);
   const unsigned col_tiles = (unsigned)((n + tnw - 1) / tnw);
   dim3 grid(p.M / pl.run, col_tiles * pl.nsub, pl.zsplit * pl.groups);
 
   if (ev.start) (void)hipEventRecord(ev.start, st);
-  if (dt == FS_BF16) e = pl.unal ? launch_mfma_bf16_unal(pl, a, grid, st) : launch_mfma_bf16(pl, a, grid, st);
+  if (pl.ks)
+    e = dt == FS_BF16  ? launch_ksplit_bf16(pl, a, grid, st)
+        : dt == FS_F16 ? launch_ksplit_f16(pl, a, grid, st)
+                       : launch_ksplit_f32(pl, a, grid, st);
+  else if (dt == FS_BF16) e = pl.unal ? launch_mfma_bf16_unal(pl, a, grid, st) : launch_mfma_bf16(pl, a, grid, st);
   else if (dt == FS_F16) e = pl.unal ? launch_mfma_f16_unal(pl, a, grid, st) : launch_mfma_f16(pl, a, grid, st);
-  else e = pl.unal ? launch_mfma_f32_unal(pl, a, grid, st) : launch_mfma_f32(pl, a, grid, st);
+  else e = launch_mfma_f32(pl, a, grid, st);
   if (ev.stop) (void)hipEventRecord(ev.stop, st);
   if (e != hipSuccess || pl.planes == 0) return e;
 

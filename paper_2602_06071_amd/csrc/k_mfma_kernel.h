@@ -6,45 +6,10 @@
 
 #include "handle.h"
 #include "mfma_common.h"
+#include "mfma_plan.h"
 #include "spec.h"
 
 namespace fs {
-namespace mm {
-
-
-struct MfmaArgs {
-  SketchParams p;
-  const void* A;
-  void* out;
-  float* ws;
-  const uint32_t* pos2blk;  // orbit order of the blocks (RUN > 1 only)
-  int64_t lda, ldo, ldw;
-  int n;
-  int zsplit;       // IN: row splits of an input block; OUT: splits of the kappa*Bc rows
-  int group_slots;  // IN: wiring slots one work-group stacks (grid.z = zsplit * slot groups)
-  int nsub;         // OUT, Br > 128: 128-row slices of an output block (grid.y = column tiles * nsub)
-  int stages;       // stages per work-group
-  int out_vec;      // out rows allow 4-column vector stores
-  uint32_t log2_br;
-};
-
-// What the host decided for one launch (make_plan in k_mfma.hip).
-struct Plan {
-  bool ok = false;
-  bool in_stat = false;
-  int mt = 0, nrg = 0, ncg = 0, zsplit = 1, stages = 0, run = 1, cpl = 4, pfx = 1;
-  int groups = 1, group_slots = 0;  // IN: slot groups (A is read once per group)
-  int nsub = 1;                     // OUT: 128-row slices of an output block
-  bool unal = false;                // A or lda not aligned to 4 columns: element-wise loads
-  bool stacked = false;             // several output blocks per wave: the kernel of k_stacked.hip
-  bool outs = false;                // OUT, 16-bit: the kernel of k_outs.hip (work-group-shared Phi tiles)
-  int64_t ldw = 0;
-  int planes = 0;
-  size_t lds = 0;
-};
-
-}  // namespace mm
-
 namespace {
 
 using namespace mm;
@@ -53,15 +18,19 @@ using namespace mm;
 // stage (bf16, PFX = 2: 8 k-steps) needs an even number of stages, which the host checks.
 // SUB (OUT, Br > 128): a work-group owns one 128-row slice of its output block; it walks the same
 // input blocks and keeps only the nonzeros that fall into its slice.
-// UNAL: A or lda is not a multiple of 4 columns, so a lane's 4 columns are not one aligned
-// vector: they are loaded element by element (same registers afterwards, four times the load
-// instructions).
+// UNAL (16-bit types): A or lda is odd, so a row may start inside a dword.  A vector load needs dword
+// alignment only, so a lane's 4 columns are then loaded as the three dwords that hold them and
+// shifted into place by half a dword where they are used.  (Four element loads instead: 1.9 times
+// the time on the gradient workload.)
 template <typename T, int MT, int NRG, int NCG, bool IN_STAT, int RUN, int CPL, int PFX = 1, bool SUB = false,
           bool UNAL = false>
 __global__ __launch_bounds__(64 * NRG * NCG * RUN) __attribute__((amdgpu_waves_per_eu(MT > 2 ? 1 : 2)))
 void mfma_kernel(MfmaArgs a) {
   using V = typename LdN<T, CPL>::V;
-  // (element loads hold four registers per row until they are packed: half the ring)
+  struct V3 { uint32_t x, y, z; };
+  using VR = std::conditional_t<UNAL, V3, V>;  // what the ring holds
+  static_assert(!UNAL || sizeof(T) == 2, "only 16-bit elements can start inside a dword");
+  // (three registers per row instead of two: half the ring)
   constexpr int PFD = UNAL ? 2 : LdN<T, CPL>::PFD * PFX;
   static_assert(PFD <= KSTEPS || PFD == 2 * KSTEPS, "ring depth: within a stage, or exactly two stages");
   constexpr int WC = 32 * CPL;                 // columns per wave
@@ -116,7 +85,9 @@ void mfma_kernel(MfmaArgs a) {
   const int z = (int)(blockIdx.z % (uint32_t)a.zsplit);
   const uint32_t slot0 = IN_STAT ? (blockIdx.z / (uint32_t)a.zsplit) * (uint32_t)a.group_slots : 0u;
   const uint32_t kap = IN_STAT ? min(p.kappa - slot0, (uint32_t)a.group_slots) : p.kappa;
-  const int T_stages = a.stages;
+  // (the last row split may have fewer stages; the host picks zsplit = ceil(total / stages))
+  const int t_first = z * a.stages;
+  const int T_stages = min(a.stages, a.total - t_first);
   // stages per input block (OUT).  Bc need not be a multiple of the stage: the rows of the last
   // stage at or beyond Bc lie outside the block's buffer range and read as 0.
   const uint32_t rows_per_blk_stage = (p.Bc + KC - 1) / KC;
@@ -149,12 +120,14 @@ void mfma_kernel(MfmaArgs a) {
     __syncthreads();
   };
 
-  const char* Abase = reinterpret_cast<const char*>(a.A);
+  // UNAL: A's first element may lie half a dword behind a dword boundary, from where offsets count
+  const uint32_t mis = UNAL ? (uint32_t)((uintptr_t)a.A & 2) : 0u;
+  const char* Abase = reinterpret_cast<const char*>(a.A) - mis;
   // per-lane byte offset of its first row inside a 16-row k-step (fits 32 bits: checked on
   // the host); the other 7 rows are reached through the scalar base
   // (a lane whose columns all lie at or beyond n gets an offset outside every descriptor range
   // instead, 2^31: its loads return 0 and move no data)
-  const uint32_t voff = col0 < a.n ? (uint32_t)(((int64_t)(kg * 8) * a.lda + col0) * (int64_t)sizeof(T))
+  const uint32_t voff = col0 < a.n ? mis + (uint32_t)(((int64_t)(kg * 8) * a.lda + col0) * (int64_t)sizeof(T))
                                    : 0x80000000u;
   const int64_t row_bytes = a.lda * (int64_t)sizeof(T);
 
@@ -216,14 +189,14 @@ void mfma_kernel(MfmaArgs a) {
   auto produce = [&](int t, int buf, int part) {
     uint16_t* phi = s_phi + buf * TILE;
     if (IN_STAT) {
-      const uint32_t u = (uint32_t)(z * T_stages + t) * KC + lane;
+      const uint32_t u = (uint32_t)(t_first + t) * KC + lane;
       const uint32_t slot_lo = row_lo >> lbr;
       const uint32_t slot_hi = min(kap, ((row_lo + RWV - 1) >> lbr) + 1);
       const bool whole = p.Br <= (uint32_t)RWV;  // power-of-two Br: slots tile the wave's rows
       for (uint32_t slot = slot_lo + part; slot < slot_hi; slot += KSTEPS)
         scatter(phi, s_bk[slot], u, slot << lbr, whole);
     } else if (part == 0) {
-      const uint32_t tg = (uint32_t)(z * T_stages + t);  // stage among all kappa blocks
+      const uint32_t tg = (uint32_t)(t_first + t);  // stage among all kappa blocks
       const uint32_t l = tg / rows_per_blk_stage;
       const uint32_t u = (tg % rows_per_blk_stage) * KC + lane;
       scatter(phi, s_bk[l], u, 0u, p.Br <= (uint32_t)RWV);
@@ -234,22 +207,27 @@ void mfma_kernel(MfmaArgs a) {
   // vector loads, masked at the point of use); the choice is uniform per work-group.
   auto body = [&](auto ragged_tag) {
     constexpr bool RAGGED = decltype(ragged_tag)::value;
-    V ld[PFD][8];
+    VR ld[PFD][8];
     // Buffer descriptor over the rows this work-group reads from one input block
     // (dword 3 = 32-bit data format for gfx9-family raw buffers).  The scalar offset
     // walks the rows, the lane offset (voff) selects row-in-k-step and column.
     // Rows at or beyond d (the zero padding of a partly filled last input block) lie outside
     // the descriptor's range, and out-of-range buffer loads return 0 without touching memory.
-    // The range ends with the last valid row's columns, rounded up to the 4-column vector: in the
-    // ragged tile a lane's vector may straddle column n; what it reads beyond n (the row's own
-    // padding, inside the same aligned 8/16-byte granule as a valid element) is masked to zero.
+    // The range ends with the last valid row's columns.  Rows aligned to 4 columns: rounded up to the
+    // 4-column vector; else to the dword.  In the ragged tile a lane's vector may straddle column n;
+    // what it reads beyond n (the row's own padding, or the start of the next row) is masked to zero.
+    // UNAL: the row behind the last valid one can share a dword with it, so rows past the block or
+    // past d are zeroed where they are used.  f_par: 2 when the first row starts in the upper half
+    // of a dword.
+    uint32_t f_par = 0;
     auto make_rsrc = [&](int64_t first_row, int64_t nrows) {
       const int64_t valid = min(nrows, p.d - first_row);
-      // (element loads, UNAL, never reach past column n-1 of the last valid row)
-      const int64_t ncols = UNAL ? (int64_t)a.n : ((int64_t)a.n + 3) & ~(int64_t)3;
-      const int64_t bytes = valid > 0 ? (valid - 1) * row_bytes + ncols * (int64_t)sizeof(T) : 0;
-      return __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<char*>(Abase + first_row * row_bytes), 0, (int)bytes, 0x00020000);
+      const int64_t off = first_row * row_bytes;
+      if constexpr (UNAL) f_par = (uint32_t)(off & 2);
+      const int64_t end = (int64_t)mis + f_par + (valid - 1) * row_bytes +
+                          (a.vec4 ? ((int64_t)a.n + 3) & ~(int64_t)3 : (int64_t)a.n) * (int64_t)sizeof(T);
+      const int64_t bytes = valid > 0 ? (end + 3) & ~(int64_t)3 : 0;
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Abase + (off - f_par)), 0, (int)bytes, 0x00020000);
     };
     // Fetch cursor.  k-steps are issued strictly in order, so the OUT mode
     // keeps (descriptor of the current input block, byte offset, k-step within the block) in
@@ -259,10 +237,10 @@ void mfma_kernel(MfmaArgs a) {
     const uint32_t per_blk_k = rows_per_blk_stage * KSTEPS;
     auto cursor_init = [&]() {
       if (IN_STAT) {
-        const int64_t row0 = (int64_t)z * T_stages * KC;  // the range ends with the block's last row
+        const int64_t row0 = (int64_t)t_first * KC;  // the range ends with the block's last row
         f_rs = make_rsrc((int64_t)blk * p.Bc + row0, min((int64_t)T_stages * KC, (int64_t)p.Bc - row0));
       } else {
-        const uint32_t kg0 = (uint32_t)(z * T_stages * KSTEPS);
+        const uint32_t kg0 = (uint32_t)(t_first * KSTEPS);
         f_l = kg0 / per_blk_k;
         f_kr = kg0 % per_blk_k;
         const uint32_t hb = __builtin_amdgcn_readfirstlane(s_blk[f_l]);
@@ -286,27 +264,16 @@ void mfma_kernel(MfmaArgs a) {
         }
       }
     };
-    auto issue = [&](int kk, V (&dst)[8]) {
+    auto issue = [&](int kk, VR (&dst)[8]) {
       const __amdgpu_buffer_rsrc_t rs = f_rs;
       const uint32_t so = IN_STAT ? (uint32_t)kk * 16u * (uint32_t)row_bytes : f_so;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const uint32_t soj = so + (uint32_t)j * (uint32_t)row_bytes;
-        if constexpr (UNAL && sizeof(V) == 8) {
-          // (written as 16-bit vector inserts so that the halves of a register are loaded in
-          // place, without a packing step)
-          typedef unsigned short us4 __attribute__((ext_vector_type(4)));
-          us4 e;
-          e.x = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, voff, soj, 0);
-          e.y = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, voff + 2u, soj, 0);
-          e.z = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, voff + 4u, soj, 0);
-          e.w = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, voff + 6u, soj, 0);
-          dst[j] = __builtin_bit_cast(V, e);
-        } else if constexpr (UNAL) {
-          uint32_t* e = reinterpret_cast<uint32_t*>(&dst[j]);
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            e[c] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, voff + 4u * c, soj, 0);
+        if constexpr (UNAL) {
+          const uint32_t odd = (f_par + soj) & 2u;  // moves from the scalar to the lane offset
+          const auto e = __builtin_amdgcn_raw_buffer_load_b96(rs, (voff + odd) & ~3u, soj + f_par - odd, 0);
+          dst[j].x = (uint32_t)e[0]; dst[j].y = (uint32_t)e[1]; dst[j].z = (uint32_t)e[2];
         } else if constexpr (sizeof(V) == 8)
           dst[j] = __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soj, 0));
         else
@@ -327,6 +294,37 @@ void mfma_kernel(MfmaArgs a) {
         cmask.w = vc >= 4 ? 0xFFFFFFFFu : 0u;
       }
     }
+    // UNAL: the rows of a stage out of their three dwords; c_par as f_par, for the stage being used,
+    // c_rows its rows inside the block and before row d (>= KC: all)
+    uint32_t c_par = 0;
+    int c_rows = KC;
+    auto stage_par = [&](int t) {
+      if constexpr (UNAL) {
+        const uint32_t tg = (uint32_t)(t_first + t), l = IN_STAT ? 0u : tg / rows_per_blk_stage;
+        const int64_t hb = IN_STAT ? (int64_t)blk : (int64_t)__builtin_amdgcn_readfirstlane(s_blk[l]);
+        c_par = IN_STAT ? f_par : (uint32_t)((hb * p.Bc * row_bytes) & 2);
+        c_rows = (int)(min((int64_t)p.Bc, p.d - hb * p.Bc) - (int64_t)(tg - l * rows_per_blk_stage) * KC);
+      }
+    };
+    auto aligned_rows = [&](VR (&ring)[8], V (&cur)[8], int ks) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        if constexpr (UNAL) {
+          const uint32_t sh = ((mis + c_par + (uint32_t)j * (uint32_t)row_bytes) & 2u) << 3;
+          cur[j].x = __builtin_amdgcn_alignbit(ring[j].y, ring[j].x, sh);
+          cur[j].y = __builtin_amdgcn_alignbit(ring[j].z, ring[j].y, sh);
+        } else {
+          cur[j] = ring[j];
+        }
+      }
+      if constexpr (UNAL) {
+        if (c_rows < KC) {  // wave-uniform: the last stage of a block, where it is partly filled
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (ks * 16 + kg * 8 + j >= c_rows) cur[j].x = cur[j].y = 0u;
+        }
+      }
+    };
     auto mask_cur = [&](V (&cur)[8]) {
       if constexpr (RAGGED) {
 #pragma unroll
@@ -352,6 +350,7 @@ void mfma_kernel(MfmaArgs a) {
       constexpr bool LAST = !decltype(fill_tag)::value;
       const uint16_t* phi = s_phi + (t & 1) * TILE;
       const int fill_buf = (t + 1) & 1;
+      stage_par(t);
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) {
         uint4 pa[MT];
@@ -361,13 +360,15 @@ void mfma_kernel(MfmaArgs a) {
               phi + (mt * 32 + (lane & 31)) * PHI_LD + ks * 16 + kg * 8);
         if constexpr (!LAST) produce(t + 1, fill_buf, ks);
 
-        V(&cur)[8] = ld[(PAR * KSTEPS + ks) % PFD];
+        VR(&ring)[8] = ld[(PAR * KSTEPS + ks) % PFD];
+        V cur[8];
+        aligned_rows(ring, cur, ks);
         const bool fetch = FETCH == 2 || (FETCH == 1 && ks + PFD < KSTEPS);  // compile-time
         mask_cur(cur);
         if constexpr (sizeof(T) == 2) {
           uint4 op[4];
           make_ops(cur, op);
-          if (fetch) issue(t * KSTEPS + ks + PFD, cur);
+          if (fetch) issue(t * KSTEPS + ks + PFD, ring);
 #pragma unroll
           for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -394,7 +395,7 @@ void mfma_kernel(MfmaArgs a) {
                 for (int mt = 0; mt < MT; ++mt)
                   acc[mt][c + cc] = mfma<T>(pa[mt], pc[cc][piece], acc[mt][c + cc]);
           }
-          if (fetch) issue(t * KSTEPS + ks + PFD, cur);
+          if (fetch) issue(t * KSTEPS + ks + PFD, ring);
         }
         if (fetch) advance();
         __builtin_amdgcn_sched_barrier(0);  // keep k-steps apart: bounds register pressure
@@ -429,7 +430,7 @@ void mfma_kernel(MfmaArgs a) {
     };
     auto fill_part = [&](int t1, uint16_t* tile, int ks) {
       if (ks == 0) {
-        const uint32_t tg = (uint32_t)(z * T_stages + t1);  // stage among all kappa blocks
+        const uint32_t tg = (uint32_t)(t_first + t1);  // stage among all kappa blocks
         const uint32_t l = tg / rows_per_blk_stage;
         prh = row_hash_pow2(s_bk[l], (tg % rows_per_blk_stage) * KC + lane, p.Br);
         pr = prh.shift;
@@ -450,9 +451,12 @@ void mfma_kernel(MfmaArgs a) {
       constexpr bool FILL = decltype(fill_tag)::value;
       uint16_t* cur_tile = s_phi + (t & 1) * TILE;
       uint16_t* fill_tile = s_phi + ((t + 1) & 1) * TILE;
+      stage_par(t);
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) {
-        V(&cur)[8] = ld[(PAR * KSTEPS + ks) % PFD];
+        VR(&ring)[8] = ld[(PAR * KSTEPS + ks) % PFD];
+        V cur[8];
+        aligned_rows(ring, cur, ks);
         const bool fetch = FETCH == 2 || (FETCH == 1 && ks + PFD < KSTEPS);  // compile-time
         mask_cur(cur);
         uint4(&pa)[MT] = pa2[ks & 1];
@@ -466,7 +470,7 @@ void mfma_kernel(MfmaArgs a) {
         if constexpr (sizeof(T) == 2) {
           uint4 op[4];
           make_ops(cur, op);
-          if (fetch) issue(t * KSTEPS + ks + PFD, cur);
+          if (fetch) issue(t * KSTEPS + ks + PFD, ring);
 #pragma unroll
           for (int c = 0; c < 4; ++c)
 #pragma unroll
@@ -502,7 +506,7 @@ void mfma_kernel(MfmaArgs a) {
                 for (int mt = 0; mt < MT; ++mt)
                   acc[mt][c + cc] = mfma<T>(pa[mt], pc[cc][piece], acc[mt][c + cc]);
           }
-          if (fetch) issue(t * KSTEPS + ks + PFD, cur);
+          if (fetch) issue(t * KSTEPS + ks + PFD, ring);
         }
         if (fetch) advance();
         __builtin_amdgcn_sched_barrier(0);
@@ -662,28 +666,35 @@ void mfma_kernel(MfmaArgs a) {
   }
 }
 
-// out[row][col] = scale * sum_p ws[p][row][col], planes added in index order.
+// out[row][col] = scale * sum_p ws[p][row][col], planes added in index order (PARTS > 1: PARTS
+// contiguous shares of them, added in order).
 // RUN > 1: plane c of the output block at orbit position pos holds a tile only when
 // delta = c*RUN + (pos%RUN + kappa)%RUN - kappa <= RUN-2 (the writer's relative position).
-template <typename T>
+// PARTS: a work-group serves 256/PARTS outputs through PARTS threads each; used when outputs are few
+// and planes many (one thread per output then waits for memory once per 8 planes on a chip that is
+// mostly idle).
+template <typename T, int PARTS>
 __global__ __launch_bounds__(256) void reduce_planes_kernel(const float* __restrict__ ws, int planes,
                                                             int64_t k, int64_t ldw, int n,
                                                             T* __restrict__ out, int64_t ldo,
                                                             float scale, int out_vec, int run,
                                                             const uint32_t* __restrict__ blk2pos,
                                                             uint32_t Br, uint32_t kappa) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;  // over k * ldw/4
+  constexpr int OPW = 256 / PARTS;
+  constexpr int UN = PARTS > 1 ? 8 : 4;  // loads issued together (with many outputs, the waves of a SIMD hide the rest)
+  const int share = PARTS > 1 ? (int)threadIdx.x / OPW : 0;
+  const int64_t idx = (int64_t)blockIdx.x * OPW + (int)threadIdx.x % OPW;  // over k * ldw/4
   const int64_t q = ldw / 4;
-  if (idx >= k * q) return;
-  const int64_t row = idx / q;
-  const int col0 = (int)(idx % q) * 4;
-  if (col0 >= n) return;
+  const bool valid = idx < k * q;
+  if (PARTS == 1 && !valid) return;
+  const int64_t row = valid ? idx / q : 0;
+  const int col0 = valid ? (int)(idx % q) * 4 : 0;
   uint32_t rho_k = 0;
   if (run > 1) rho_k = (blk2pos[row / Br] % (uint32_t)run + kappa) % (uint32_t)run;
   const float* src = ws + row * ldw + col0;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   // The planes that count are planes 0 .. nvalid-1 (RUN > 1: once a plane is empty the later ones
-  // are too).  Four at a time: their loads are issued together, then added in index order; past
+  // are too).  UN at a time: their loads are issued together, then added in index order; past
   // the last one the load repeats it (a cache hit) and is ignored.  One load per pass of a loop
   // made this kernel wait for memory once per plane.
   int nvalid = planes;
@@ -691,14 +702,27 @@ __global__ __launch_bounds__(256) void reduce_planes_kernel(const float* __restr
     nvalid = 0;
     while (nvalid < planes && (int)(nvalid * run + rho_k) - (int)kappa <= run - 2) ++nvalid;
   }
-  for (int p0 = 0; p0 < nvalid; p0 += 4) {
-    float4 v[4];
+  const int per = (nvalid + PARTS - 1) / PARTS;
+  const int first = share * per, last = min(first + per, nvalid);
+  for (int p0 = first; p0 < last; p0 += UN) {
+    float4 v[UN];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      v[j] = *reinterpret_cast<const float4*>(src + (int64_t)min(p0 + j, nvalid - 1) * k * ldw);
+    for (int j = 0; j < UN; ++j)
+      v[j] = *reinterpret_cast<const float4*>(src + (int64_t)min(p0 + j, last - 1) * k * ldw);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (p0 + j < nvalid) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
+    for (int j = 0; j < UN; ++j)
+      if (p0 + j < last) { s.x += v[j].x; s.y += v[j].y; s.z += v[j].z; s.w += v[j].w; }
+  }
+  if constexpr (PARTS > 1) {
+    __shared__ float4 sh[PARTS][OPW];
+    sh[share][threadIdx.x % OPW] = s;
+    __syncthreads();
+    if (share > 0 || !valid) return;
+#pragma unroll
+    for (int i = 1; i < PARTS; ++i) {
+      const float4 v = sh[i][threadIdx.x];
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
   }
   float v[4] = {s.x * scale, s.y * scale, s.z * scale, s.w * scale};
   T* dst = out + row * ldo + col0;
@@ -730,7 +754,7 @@ hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const Mfm
   return hipGetLastError();
 }
 
-// Element-wise loads (Plan::unal): one ring depth, no orbit runs.
+// Rows that start inside a dword (Plan::unal): one ring depth, no orbit runs.
 template <typename T, bool IN_STAT>
 hipError_t launch_shape_unal(const Plan& pl, const MfmaArgs& a, dim3 grid, hipStream_t st) {
 #define FS_GO(MT, NCG) \

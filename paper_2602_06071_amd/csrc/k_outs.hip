@@ -50,8 +50,8 @@ struct OutsArgs {
   int n;
   int spb;      // stages per input block: ceil(Bc / KC)
   int out_vec;  // out rows allow 4-column vector stores
-  // row split: work-group z (grid.z) takes the stages [z*stages, (z+1)*stages) of the kappa*spb
-  // stages of its output block and, when there is more than one, stores its unscaled fp32 sums to
+  // row split: work-group z (grid.z) takes the stages [z*stages, min((z+1)*stages, kappa*spb)) of
+  // its output block (an even number of them) and, when there is more than one, stores its unscaled fp32 sums to
   // plane z of ws (k x ldw floats each) for the fixed-order reduction kernel
   int zsplit, stages;
   float* ws;
@@ -299,7 +299,7 @@ void outs_kernel(OutsArgs a) {
   read_pa(s_phi, 0, pa2[0]);
   using P0 = std::integral_constant<int, 0>;
   using P1 = std::integral_constant<int, 1>;
-  const int n_stages = a.stages;  // even, >= 2 (checked on the host)
+  const int n_stages = min(a.stages, (int)(spb * p.kappa - t0));  // even, >= 2 (checked on the host)
   for (int t = 0; t + 2 < n_stages; t += 2) {
     stage(P0{}, std::true_type{}, std::true_type{});
     stage(P1{}, std::true_type{}, std::true_type{});
@@ -379,7 +379,11 @@ bool outs_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n
   const int64_t spb = ((int64_t)p.Bc + KC - 1) / KC;
   const int64_t T = spb * p.kappa;
   if (T < 4 || T % 2) return false;
-  if (zsplit < 1 || T % zsplit || (T / zsplit) % 2) return false;  // an even number of stages per work-group
+  // an even number of stages per work-group, ceil(T / zsplit) rounded up to even (the last one takes
+  // what is left, even too): zsplit must be what that gives
+  if (zsplit < 1) return false;
+  const int64_t per = outs_stages(T, zsplit);
+  if ((T + per - 1) / per != zsplit) return false;
   if ((16 * lda + n) * 2 >= ((int64_t)1 << 31)) return false;
   if (spb * KC * lda * 2 >= ((int64_t)1 << 31)) return false;
   const int nw = n > 2 * WCOLS ? 4 : 2;
@@ -395,7 +399,7 @@ hipError_t launch_outs(const SketchParams& p, const void* A, int64_t lda, int64_
   a.lda = lda; a.ldo = ldo; a.n = (int)n;
   a.spb = (int)(((int64_t)p.Bc + KC - 1) / KC);
   a.out_vec = ((uintptr_t)out % 8 == 0 && (ldo * 2) % 8 == 0) ? 1 : 0;
-  a.zsplit = zsplit; a.stages = (int)((int64_t)a.spb * p.kappa / zsplit); a.ws = ws; a.ldw = ldw;
+  a.zsplit = zsplit; a.stages = (int)outs_stages((int64_t)a.spb * p.kappa, zsplit); a.ws = ws; a.ldw = ldw;
   if (zsplit > 1 && (!ws || ldw % 4 || ldw < n)) return hipErrorInvalidValue;
   const int nw = n > 2 * WCOLS ? 4 : 2;
   const int mt = (int)p.Br / 32;

@@ -1,0 +1,58 @@
+// What the planner of the column-layout matrix-core kernels (k_mfma.hip) decides and hands over.
+#pragma once
+#include "handle.h"
+
+namespace fs {
+namespace mm {
+
+struct MfmaArgs {
+  SketchParams p;
+  const void* A;
+  void* out;
+  float* ws;
+  const uint32_t* pos2blk;  // orbit order of the blocks (RUN > 1 only)
+  int64_t lda, ldo, ldw;
+  int n;
+  int zsplit;       // IN: row splits of an input block; OUT: splits of the kappa*Bc rows
+  int group_slots;  // IN: wiring slots one work-group stacks (grid.z = zsplit * slot groups)
+  int nsub;         // OUT, Br > 128: 128-row slices of an output block (grid.y = column tiles * nsub)
+  int stages;       // stages per work-group
+  int total;        // K-split kernel: stages of an input block (IN) or of all kappa blocks (OUT)
+  int out_vec;      // out rows allow 4-column vector stores
+  int vec4;         // rows of A are aligned to 4 columns
+  uint32_t log2_br;
+};
+
+// What the host decided for one launch (make_plan in k_mfma.hip).
+struct Plan {
+  bool ok = false;
+  bool in_stat = false;
+  int mt = 0, nrg = 0, ncg = 0, zsplit = 1, stages = 0, run = 1, cpl = 4, pfx = 1;
+  int groups = 1, group_slots = 0;  // IN: slot groups (A is read once per group)
+  int nsub = 1;                     // OUT: 128-row slices of an output block
+  bool vec4 = true;                 // A and lda aligned to 4 columns
+  bool unal = false;                // 16-bit rows that may start inside a dword
+  bool stacked = false;             // several output blocks per wave: the kernel of k_stacked.hip
+  bool outs = false;                // OUT, 16-bit: the kernel of k_outs.hip (work-group-shared Phi tiles)
+  bool ks = false;                  // the kernel of k_ksplit_kernel.h (waves of a work-group share the columns)
+  int total = 0;                    // ... its stages of a block (IN) or of the kappa blocks (OUT)
+  int64_t ldw = 0;
+  int planes = 0;
+  size_t lds = 0;
+  size_t ws_floor = 0;              // bytes of workspace a call must find (an attached one below this is refused)
+};
+
+// ---- the K-split kernel (k_ksplit_kernel.h): MT 32-row tiles x 32*CPL columns per work-group ----
+// waves per work-group: 8, or one per SIMD where the accumulators take the whole register file
+constexpr int ks_waves(int mt, int cpl) { return mt * cpl >= 16 ? 4 : 8; }
+constexpr int ks_waves_per_simd(int mt, int cpl) { return mt * cpl >= 16 ? 1 : cpl >= 2 || mt == 4 ? 2 : 4; }
+// Phi tiles per wave
+constexpr int ks_tiles(int cpl) { return cpl == 4 ? 2 : 1; }
+constexpr size_t ks_lds_bytes(int mt, int cpl) {
+  const size_t tiles = (size_t)ks_waves(mt, cpl) * ks_tiles(cpl) * (32 * mt) * (64 + 8) * 2;
+  const size_t merge = (size_t)ks_waves(mt, cpl) * cpl * 4096;
+  return 2 * 128 * 4 + (tiles > merge ? tiles : merge);
+}
+
+}  // namespace mm
+}  // namespace fs

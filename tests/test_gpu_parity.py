@@ -341,6 +341,79 @@ def test_shared_phi_kernel_one_hot_columns_are_exact():
     assert np.array_equal(host64(out), oracle_csc(params, 0)[:, cols].toarray())
 
 
+# ------------------- waves of a work-group that split the rows ------------
+KSPLIT = [
+    # params (d,k,Bc,Br,kappa,s), n, lda pad, first column of the view: few columns or few blocks.  Tiles of
+    # 32, 64 and 128 columns, each stacked height, uneven shares (63 stages), rows that start inside a dword.
+    ((15990, 128, 4000, 32, 2, 4), 1, 0, 0),       # 64 stacked rows, one packed column, a partly filled last block
+    ((15990, 128, 4000, 32, 2, 4), 32, 1, 1),      # one full 32-column tile, odd stride, odd first element
+    ((15990, 128, 4000, 32, 2, 4), 33, 0, 0),      # 64-column tile
+    ((15990, 128, 4000, 32, 2, 4), 64, 3, 0),
+    ((15990, 128, 4000, 32, 2, 4), 65, 0, 0),      # 128-column tile, odd packed rows: three dwords per four columns
+    ((15990, 128, 4000, 32, 2, 4), 127, 0, 1),
+    ((15991, 128, 4001, 32, 2, 4), 129, 0, 1),     # two column tiles; odd Bc: blocks start in either half of a dword
+    ((15990, 128, 4000, 32, 2, 4), 130, 2, 0),     # dword-aligned, not aligned to four columns
+    ((16000, 64, 4000, 16, 2, 4), 100, 0, 0),      # 32 stacked rows
+    ((16000, 256, 2000, 32, 4, 4), 30, 0, 0),      # 128 stacked rows
+    ((16000, 256, 2000, 32, 4, 4), 61, 0, 1),
+    ((16000, 256, 2000, 32, 4, 4), 127, 0, 0),
+    ((16000, 256, 4001, 64, 4, 4), 3, 0, 1),       # output-stationary
+    ((16000, 512, 4001, 128, 4, 20), 63, 0, 0),
+    ((16001, 512, 4001, 128, 4, 8), 125, 0, 0),
+    ((16001, 128, 4001, 32, 1, 8), 255, 1, 0),     # kappa = 1
+    ((5000, 128, 2500, 64, 1, 4), 7, 0, 0),        # M = 2: no orbit table
+    ((9000, 48, 2250, 12, 3, 5), 66, 0, 0),        # Br not a power of two
+    ((5120, 256, 640, 32, 8, 2), 5, 0, 0),         # kappa = M
+    ((20480, 512, 640, 16, 16, 3), 40, 0, 0),       # slot groups
+]
+
+
+@DTYPES
+@pytest.mark.parametrize("case", KSPLIT, ids=lambda c: f"{c[0]}-n{c[1]}")
+def test_ksplit_kernel_matches_oracle(case, dtype):
+    params, n, pa, first = case
+    print("ksplit", params, n, dtype, flush=True)
+    d, k = params[0], params[1]
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    flat = torch.full(((d + 2) * (n + pa) + 8,), float("nan"), device=DEV, dtype=dtype)
+    A = flat[4 + first:4 + first + d * (n + pa)].view(d, n + pa)   # NaN right before and behind
+    A[:, :n] = torch.randn((d, n), generator=g, device=DEV).to(dtype)
+    A = A[:, :n]
+    sk = make_sketch(params, 9, B.VARIANT_MFMA)
+    plan = sk.plan(n, dtype, ld=A.stride(0), address=A.data_ptr())
+    obuf = torch.full((k, n + 1), float("nan"), device=DEV, dtype=dtype)
+    out = sk.apply(A, obuf[:, :n])
+    torch.cuda.synchronize()
+    i = sk.info()
+    if n <= 64:
+        assert i.last_kernel.decode().startswith("ksplit_kernel"), i.last_kernel
+    assert (plan["variant"], plan["mode"]) == (i.last_variant, i.last_mode)
+    ref = O.apply(oracle_csc(params, 9), host64(A))
+    check(out, ref, dtype, "K-split kernel")
+    diff = np.abs(host64(out) - ref)
+    assert (diff <= ETOL[dtype] * (np.abs(ref) + np.sqrt((ref ** 2).mean()))).all()
+    assert torch.isnan(obuf[:, n:].float()).all(), "wrote outside the n output columns"
+    assert torch.equal(sk.apply(A), out)          # fixed summation order
+
+
+def test_smaller_workspace_takes_a_coarser_split():
+    """A call that wants a finer row split than the workspace attached to its handle has room for
+    runs with a coarser one; output-stationary calls run with none at all."""
+    params, n = (16000, 256, 4001, 64, 3, 4), 24
+    A = torch.randn((params[0], n), device=DEV)
+    sk = B.Sketch(*params, seed=3)
+    ref = O.apply(oracle_csc(params, 3), host64(A))
+    plan = sk.plan(n, torch.float32)
+    assert plan["mode"] == 1 and plan["workspace_bytes"] >= 2 * 256 * 24 * 4
+    ws = torch.empty(plan["workspace_bytes"] + 256, dtype=torch.uint8, device=DEV)
+    off = (-ws.data_ptr()) % 256
+    for size in (plan["workspace_bytes"], plan["workspace_bytes"] // 2, 256):
+        ws.fill_(0xFF)
+        sk.set_workspace(ws[off:off + size])
+        check(sk.apply(A), ref, torch.float32, f"workspace of {size} bytes")
+        assert (ws[off + size:] == 0xFF).all()
+
+
 # ---------------------------------------------------------- one-hot -------
 @pytest.mark.parametrize("variant", VARIANTS, ids=lambda v: VNAME[v])
 @DTYPES
