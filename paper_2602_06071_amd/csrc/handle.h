@@ -147,12 +147,15 @@ hipError_t launch_blockrow(const SketchParams& p, const void* A, int64_t lda, in
                            int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev);
 hipError_t launch_blockrow_export(const SketchParams& p, int32_t* cols, int8_t* signs, hipStream_t st);
 
-// Dense Gaussian sketch.  `storage` holds the k x d matrix as fp32, then four bf16
-// copies (rounded, and the exact split hi / mid / lo): gauss_bytes(k, d) bytes.
+// Dense Gaussian sketch.  `storage` holds the k x d matrix as fp32, then five 16-bit copies (bf16
+// rounded, the exact bf16 split hi / mid / lo, half), then kGaussScratch bytes for the partial
+// planes of applies that split d: gauss_bytes(k, d) bytes.  (Room of its own, so that the applies of
+// this kind need no workspace, under capture and through fs_sketch_apply_static alike.)
+constexpr size_t kGaussScratch = (size_t)64 << 20;
 size_t gauss_bytes(int64_t k, int64_t d);
 hipError_t gauss_fill(void* storage, int64_t k, int64_t d, uint32_t key1, hipStream_t st);
 bool gauss_supported(int64_t k, int64_t d, const void* A, int64_t lda, int64_t n, fs_dtype dt);
-hipError_t launch_gauss(const void* storage, int64_t k, int64_t d, const void* A, int64_t lda,
+hipError_t launch_gauss(void* storage, int64_t k, int64_t d, const void* A, int64_t lda,
                         int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev);
 
 }  // namespace fs

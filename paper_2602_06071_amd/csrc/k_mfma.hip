@@ -43,6 +43,7 @@
 #include <stdio.h>
 
 #include "k_mfma_kernel.h"
+#include "reduce_planes.h"
 
 namespace fs {
 
@@ -371,22 +372,10 @@ size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt) {
 // The fixed-order sum of the partial planes into the output, scaled and converted.
 static hipError_t launch_reduce(const SketchParams& p, const Plan& pl, int64_t n, void* out, int64_t ldo,
                                 fs_dtype dt, float* ws, const uint32_t* orbit, hipStream_t st) {
-  const size_t esz = dt == FS_F32 ? 4 : 2;
-  const int out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
-  const int64_t work = p.k * (pl.ldw / 4);
-  // (65536 threads are one per lane of a SIMD on every SIMD)
-  const bool parts = pl.planes >= 16 && work < 65536;
-  const int64_t opw = parts ? 32 : 256;
-  const unsigned blocks = (unsigned)((work + opw - 1) / opw);
   const uint32_t* blk2pos = orbit ? orbit + p.M : nullptr;
-#define FS_RED(T, PARTS)                                                                                          \
-  hipLaunchKernelGGL((reduce_planes_kernel<T, PARTS>), dim3(blocks), dim3(256), 0, st, ws, pl.planes, p.k, pl.ldw, \
-                     (int)n, (T*)out, ldo, p.scale, out_vec, pl.run, blk2pos, p.Br, p.kappa)
-  if (dt == FS_BF16)     { if (parts) FS_RED(uint16_t, 8); else FS_RED(uint16_t, 1); }
-  else if (dt == FS_F16) { if (parts) FS_RED(f16, 8); else FS_RED(f16, 1); }
-  else                   { if (parts) FS_RED(float, 8); else FS_RED(float, 1); }
-#undef FS_RED
-  return hipGetLastError();
+  return dt == FS_BF16  ? launch_reduce_planes<uint16_t>(ws, pl.planes, p.k, pl.ldw, n, out, ldo, p.scale, pl.run, blk2pos, p.Br, p.kappa, st)
+         : dt == FS_F16 ? launch_reduce_planes<f16>(ws, pl.planes, p.k, pl.ldw, n, out, ldo, p.scale, pl.run, blk2pos, p.Br, p.kappa, st)
+                        : launch_reduce_planes<float>(ws, pl.planes, p.k, pl.ldw, n, out, ldo, p.scale, pl.run, blk2pos, p.Br, p.kappa, st);
 }
 
 hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,

@@ -593,6 +593,32 @@ def test_dense_gaussian_matches_oracle(k, d, n, pad, dtype):
     assert err <= {torch.float32: 1e-5, torch.bfloat16: 4e-3, torch.float16: 1e-3}[dtype], f"dense gaussian: {err:.3e}"
 
 
+@DTYPES
+@pytest.mark.parametrize("k,d,n,pad", [(128, 64, 1, 3), (384, 4160, 127, 1), (128, 20480, 129, 3), (256, 8256, 257, 3),
+                                       (256, 16448, 512, 4)])
+def test_dense_gaussian_split_over_few_tiles(k, d, n, pad, dtype):
+    """Few tiles of S: its columns are split (unevenly) over grid.z; one, two and four column waves, a
+    single stage, NaN in the rows' padding and behind the last row.  The entry point on the static
+    device array sums in the same order."""
+    from oracle import gaussian as G
+    print("gauss split", k, d, n, dtype, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(7)
+    buf = torch.full((d + 2, n + pad), float("nan"), device=DEV, dtype=dtype)
+    buf[:d, :n] = torch.randn((d, n), generator=g, device=DEV).to(dtype)
+    A = buf[:d, :n]
+    sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
+    obuf = torch.full((k, n + 1), float("nan"), device=DEV, dtype=dtype)
+    out = sk.apply(A, obuf[:, :n])
+    torch.cuda.synchronize()
+    assert torch.isnan(obuf[:, n:].float()).all(), "wrote outside the n output columns"
+    # fp32: sums of d terms, each off by at most 2^-23 relative (the dropped cross terms) before adding
+    err = O.rel_fro_err(host64(out), G.apply(G.gaussian_matrix(k, d, 2), host64(A)))
+    assert err <= {torch.float32: 1e-5, torch.bfloat16: 4e-3, torch.float16: 1e-3}[dtype], f"dense gaussian: {err:.3e}"
+    again = torch.empty((k, n), device=DEV, dtype=dtype)
+    sk.apply_static(A, again)
+    assert torch.equal(again, out) and torch.equal(sk.apply(A), out)
+
+
 # ------------------------------------------------ full-size configs -------
 def _sampled_parity(cfg, A, out, seed=0):
     """Oracle on a sample of columns of the full-size problem: one column, at a random place, from
