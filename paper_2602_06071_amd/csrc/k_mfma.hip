@@ -198,15 +198,18 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
     pl.groups = groups; pl.group_slots = group_slots;
     if (zs * groups > 65535) return pl;
     floor_planes = zs_even * (int)p.kappa;
-    // orbit runs of 4: the 64-row / 256-column shape, enough blocks for one work-group
-    // per CU, and a merge buffer that fits beside nothing else in LDS
+    // orbit runs of 4: full tiles of 64 rows x 256 or 128 rows x 128 columns, enough blocks for one work-group
+    // per CU (the merge buffer takes the place of the Phi tiles).  Measured (us per
+    // call, every slot a plane of its own -> runs): fp32 65536 x 1024 with kappa = 4, Br = 32: 82 -> 75; bf16
+    // 34496 x 1896 with kappa = 8, Br = 16: 147 -> 127; bf16 32768 x 8192 with kappa = 4, Br = 16: 235 -> 183.
     constexpr int R = 4;
-    const size_t merge = (size_t)(p.kappa + R - 1) * p.Br * (WCOLS * 2) * 4;
-    if (have_orbit && p.br_pow2 && !pl.unal && zs == 1 && rw == 64 && pl.nrg == 1 && pl.ncg == 2 && p.kappa > 1 &&
-        p.M % R == 0 && (int64_t)(p.M / R) * col_tiles >= 256 && merge <= 100 * 1024) {
+    const int run_cols = pl.mt == 2 ? 2 * WCOLS : WCOLS;
+    if (have_orbit && p.br_pow2 && !pl.unal && zs == 1 && (rw == 64 || rw == 128) && pl.nrg == 1 && pl.ncg == 2 && p.kappa > 1 &&
+        p.M % R == 0 && (int64_t)(p.M / R) * ((n + run_cols - 1) / run_cols) >= 256) {
       pl.run = R;
+      if (pl.mt == 4) pl.ncg = 1;
       pl.planes = (int)((p.kappa + R - 2) / R) + 1;
-      if (pl.vec4) floor_planes = pl.planes;
+      if (pl.vec4 && rw == 64 && p.kappa >= 6) floor_planes = pl.planes;
     }
   } else {
     // split the kappa*Bc rows of a work-group over grid.z when there are too few output tiles to
@@ -314,7 +317,7 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   // stage count.  (For fp32 the deeper ring measured no gain.)
   if (pairs) pl.pfx = 2;
   pl.lds = lds_bytes(pl.mt, pl.nrg, pl.ncg, pl.run,
-                     pl.run > 1 ? (size_t)(p.kappa + pl.run - 1) * p.Br * 256 * 4 : 0);
+                     pl.run > 1 ? (size_t)pl.run * (32 * pl.mt) * (64 * pl.ncg) * 4 : 0);
   pl.ok = pl.lds <= kLdsBudget;
   return pl;
 }

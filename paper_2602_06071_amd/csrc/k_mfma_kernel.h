@@ -560,68 +560,47 @@ void mfma_kernel(MfmaArgs a) {
   // accumulator register i of tile (mt, c) holds stacked row (rg*MT+mt)*32 + 8*(i/4) + 4*kg + i%4
   // of column col0 + c; columns are handled four at a time (q).
   if constexpr (RUN > 1) {
-    // Merge in LDS the tiles of the RUN sub-groups that go to the same output block:
-    // sub-group j, slot l-1 lands on relative output position idx = j - l + kappa
-    // (0 .. kappa+RUN-2).  Sub-groups take turns in index order, so the sum order is fixed.
-    constexpr int TNW = WC * NCG;
-    float* mbuf = reinterpret_cast<float*>(smem + kTabBytes);  // [kappa+RUN-1][Br][TNW]
-    const int colw = cg * WC + CPL * (lane & 31);
-    __syncthreads();  // every wave is done with the Phi tiles
-    for (int j = 0; j < RUN; ++j) {
-      if (sg == j) {
+    // Merge the tiles of the RUN sub-groups that go to the same output block: sub-group j, slot l-1
+    // lands on relative output position idx = j - l + kappa (0 .. kappa+RUN-2).  All waves put their
+    // accumulators into LDS, 64 of their 128 columns at a time, and all threads add, in sub-group
+    // order, what belongs together and store the kappa+RUN-1 merged tiles to their partial planes.
+    // (Taking turns on one merge buffer instead leaves three quarters of the waves idle and, with
+    // 128 stacked rows, spilled the accumulators: fp32 65536 x 1024, kappa = 4: 118 against 76 us.)
+    static_assert(NRG == 1, "one row group");
+    constexpr int HC = 64 * NCG;  // columns of the work-group per half
+    constexpr uint32_t LQ = NCG == 2 ? 5 : 4;  // log2 of the float4 per row of a half
+    float* mbuf = reinterpret_cast<float*>(smem + kTabBytes);  // [RUN][RWV][HC]
+    const uint32_t* blk_tab = reinterpret_cast<const uint32_t*>(smem);
+    const uint32_t total = (p.kappa + RUN - 1) << (lbr + LQ);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
+    for (int half = 0; half < 2; ++half) {
+      __syncthreads();  // the Phi tiles, or the first half, have been read
+      if (((lane >> 4) & 1) == half) {
+        float* dst = mbuf + (size_t)sg * RWV * HC + cg * 64 + 4 * (lane & 15);
 #pragma unroll
-          for (int ib = 0; ib < 16; ib += 4) {  // four rows at a time: reads first, then adds
-            float4* d[4];
-            bool first[4];
-            float4 o[4][CPL / 4];
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
-              const int i = ib + ii;
-              const uint32_t row_s = (uint32_t)((rg * MT + mt) * 32 + 8 * (i >> 2) + 4 * kg + (i & 3));
-              const uint32_t slot = row_s >> lbr, r = row_s & (p.Br - 1);
-              const uint32_t idx = (uint32_t)j + p.kappa - 1u - slot;
-              first[ii] = slot == 0 || j == 0;  // no earlier sub-group reaches this tile
-              d[ii] = reinterpret_cast<float4*>(mbuf + ((size_t)((idx << lbr) + r)) * TNW + colw);
-              if (j > 0) {
-#pragma unroll
-                for (int q = 0; q < CPL / 4; ++q) o[ii][q] = d[ii][q];
-              }
-            }
-#pragma unroll
-            for (int ii = 0; ii < 4; ++ii) {
-              const int i = ib + ii;
-#pragma unroll
-              for (int q = 0; q < CPL / 4; ++q) {
-                float4 v = make_float4(acc[mt][4 * q][i], acc[mt][4 * q + 1][i], acc[mt][4 * q + 2][i],
-                                       acc[mt][4 * q + 3][i]);
-                if (j > 0 && !first[ii]) {
-                  v.x += o[ii][q].x; v.y += o[ii][q].y; v.z += o[ii][q].z; v.w += o[ii][q].w;
-                }
-                d[ii][q] = v;
-              }
-            }
-          }
-        }
+          for (int i = 0; i < 16; ++i)
+            *reinterpret_cast<float4*>(dst + (mt * 32 + 8 * (i >> 2) + 4 * kg + (i & 3)) * HC) =
+                make_float4(acc[mt][0][i], acc[mt][1][i], acc[mt][2][i], acc[mt][3][i]);
       }
       __syncthreads();
-    }
-    // cooperative store of the kappa+RUN-1 merged tiles to their partial planes; the
-    // destination block of tile idx is slot j+kappa-1-idx of any sub-group j that feeds it
-    static_assert(TNW / 4 == 64, "index split below assumes 64 float4 per tile row");
-    const uint32_t total = (p.kappa + RUN - 1) << (lbr + 6);
-    const uint32_t* blk_tab = reinterpret_cast<const uint32_t*>(smem);
-    for (uint32_t e = threadIdx.x; e < total; e += NT * RUN) {
-      const uint32_t idx = e >> (lbr + 6), r = (e >> 6) & (p.Br - 1), c4 = e & 63u;
-      const int col = (int)blockIdx.y * TNW + (int)c4 * 4;
-      if (col >= a.n) continue;
-      const uint32_t j = min(idx, (uint32_t)(RUN - 1));
-      const uint32_t g = blk_tab[j * 2 * MAX_KAPPA + MAX_KAPPA + (j + p.kappa - 1 - idx)];
-      const int64_t plane = idx / RUN;
-      float* dst = a.ws + (plane * p.k + ((int64_t)g << lbr) + r) * a.ldw + col;
-      *reinterpret_cast<float4*>(dst) =
-          *reinterpret_cast<const float4*>(mbuf + ((size_t)((idx << lbr) + r)) * TNW + c4 * 4);
+      for (uint32_t e = threadIdx.x; e < total; e += NT * RUN) {
+        const uint32_t idx = e >> (lbr + LQ), r = (e >> LQ) & (p.Br - 1), c4 = e & ((1u << LQ) - 1u);
+        const int col = (int)blockIdx.y * (WC * NCG) + (int)(c4 >> 4) * WC + half * 64 + (int)(c4 & 15u) * 4;
+        if (col >= a.n) continue;
+        // the sub-groups that feed it, and the block: slot j+kappa-1-idx of any of them
+        const uint32_t j0 = idx >= p.kappa ? idx - p.kappa + 1 : 0u, j1 = min(idx, (uint32_t)(RUN - 1));
+        const float* src = mbuf + ((size_t)j0 * RWV + (((j0 + p.kappa - 1 - idx) << lbr) + r)) * HC + c4 * 4;
+        float4 v = *reinterpret_cast<const float4*>(src);
+        for (uint32_t j = j0 + 1; j <= j1; ++j) {
+          src += (RWV + (int)p.Br) * HC;  // next sub-group, next slot
+          const float4 o = *reinterpret_cast<const float4*>(src);
+          v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+        }
+        const uint32_t g = blk_tab[j1 * 2 * MAX_KAPPA + MAX_KAPPA + (j1 + p.kappa - 1 - idx)];
+        *reinterpret_cast<float4*>(a.ws + ((int64_t)(idx / RUN) * p.k + ((int64_t)g << lbr) + r) * a.ldw + col) = v;
+      }
     }
     return;
   }
@@ -724,7 +703,13 @@ hipError_t launch_shape(const Plan& pl, const MfmaArgs& a, dim3 grid, hipStream_
     return go<mfma_kernel<T, 4, 1, NCG, IN_STAT, 1, 4, 1>>(grid, 64 * NCG, pl.lds, st, a);     \
   } while (0)
   if constexpr (IN_STAT) {
-    if (pl.run == 4) FS_GO(2, 1, 2, 4);
+    if (pl.run == 4 && pl.mt == 2) FS_GO(2, 1, 2, 4);
+    if (pl.run == 4) {  // 128 stacked rows: one wave per sub-group
+      if constexpr (sizeof(T) == 2) {
+        if (pl.pfx == 2) return go<mfma_kernel<T, 4, 1, 1, IN_STAT, 4, 4, 2>>(grid, 256, pl.lds, st, a);
+      }
+      return go<mfma_kernel<T, 4, 1, 1, IN_STAT, 4, 4, 1>>(grid, 256, pl.lds, st, a);
+    }
   }
   if (pl.ncg == 1) {
     if (pl.mt == 1) FS_GO(1, 1, 1, 1); else if (pl.mt == 2) FS_GO(2, 1, 1, 1); else FS_GO4(1);

@@ -414,6 +414,33 @@ def test_smaller_workspace_takes_a_coarser_split():
         assert (ws[off + size:] == 0xFF).all()
 
 
+# --------------------------- orbit runs of every tile ----------------------
+@DTYPES
+@pytest.mark.parametrize("params,n", [
+    ((36859, 8192, 72, 16, 8, 4), 260),      # 128 stacked rows, two stages per block, a partly filled last block
+    ((65536, 8192, 128, 16, 4, 3), 300),     # 64 stacked rows, kappa = 4: a ragged second column tile
+    ((49152, 2048, 192, 8, 8, 5), 2500),     # three stages per block
+    ((131072, 4096, 1024, 32, 4, 2), 1024),  # 128 stacked rows, kappa = 4
+    ((131072, 8192, 256, 16, 8, 2), 514),    # rows not aligned to four columns
+])
+def test_orbit_runs_match_oracle(params, n, dtype):
+    """Four consecutive orbit positions per work-group, 64 or 128 stacked rows: sampled columns against
+    the oracle, the wrapped end of the orbit and the ragged column tile among them."""
+    print("orbit runs", params, n, dtype, flush=True)
+    A = torch.randn((params[0], n), generator=torch.Generator(device=DEV).manual_seed(n), device=DEV).to(dtype)
+    sk = B.Sketch(*params, seed=6)
+    out = sk.apply(A)
+    torch.cuda.synchronize()
+    assert sk.info().last_mode == 3, sk.info().last_kernel
+    cols = np.unique(np.r_[0, 63, 64, 127, 128, 255, n - 1, np.random.default_rng(1).integers(0, n, 10)])
+    idx = torch.from_numpy(cols).to(DEV)
+    ref = O.apply(oracle_csc(params, 6), host64(A[:, idx]))
+    check(out[:, idx], ref, dtype, "orbit runs")
+    diff = np.abs(host64(out[:, idx]) - ref)
+    assert (diff <= ETOL[dtype] * (np.abs(ref) + np.sqrt((ref ** 2).mean()))).all()
+    assert torch.equal(sk.apply(A), out)
+
+
 # ---------------------------------------------------------- one-hot -------
 @pytest.mark.parametrize("variant", VARIANTS, ids=lambda v: VNAME[v])
 @DTYPES
