@@ -95,17 +95,21 @@ _DTYPE_CODES = {torch.float32: 0, torch.bfloat16: 1, torch.float16: 2}
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return FS_F32
-    if t.dtype == torch.bfloat16:
-        return FS_BF16
-    if t.dtype == torch.float16:
-        return FS_F16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
+
+
+# The raw handle of the current stream, without building a Stream object around it (3 us per call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream_ptr(stream) -> int:
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream)
 

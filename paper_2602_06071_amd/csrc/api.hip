@@ -7,6 +7,7 @@
 #include <new>
 
 #include "handle.h"
+#include "mfma_plan.h"
 #include "spec.h"
 
 fs_status fs::hip_fail(fs_sketch_t h, hipError_t e) {
@@ -62,31 +63,15 @@ bool is_pow2(uint32_t x) { return x && !(x & (x - 1)); }
 
 bool valid_dtype(fs_dtype dt) { return dt == FS_F32 || dt == FS_BF16 || dt == FS_F16; }
 
-// Workspace of the variant that would run.  exact_orbit < 0: an upper bound that
-// holds whether or not the orbit table will be there; 0 / 1: the size of exactly this call,
-// without / with the table.
-fs_status needed_workspace(fs_sketch_t h, const void* A, int64_t lda, int64_t n, const void* out,
-                           int64_t ldo, fs_dtype dt, int* variant_out, fs::Workspace* need, int exact_orbit = -1) {
+// Whether a call of a kind other than BLOCKPERM runs, and its workspace.
+fs_status other_kind(fs_sketch_t h, const void* A, int64_t lda, int64_t n, fs_dtype dt, fs::Workspace* need) {
   *need = {};
-  *variant_out = FS_VARIANT_GENERIC;
-  if (h->kind == FS_KIND_SJLT_SCATTER) {
-    need->floor = need->want = fs::scatter_workspace_bytes(h->p, n, dt);
-    return FS_OK;
-  }
-  if (h->kind == FS_KIND_GAUSS_DENSE)
-    return fs::gauss_supported(h->p.k, h->p.d, A, lda, n, dt) ? FS_OK : FS_ERR_UNSUPPORTED;
-  if (h->kind == FS_KIND_BLOCKROW) return FS_OK;
-  const bool can = fs::mfma_supported(h->p, A, lda, n, out, ldo, dt);
-  int v = h->variant;
-  if (v == FS_VARIANT_AUTO) v = can ? FS_VARIANT_MFMA : FS_VARIANT_GENERIC;
-  if (v == FS_VARIANT_MFMA) {
-    if (!can) return FS_ERR_UNSUPPORTED;
-    if (exact_orbit >= 0) *need = fs::mfma_workspace(h->p, A, lda, n, dt, exact_orbit != 0);
-    else need->floor = need->want = fs::mfma_workspace_bytes(h->p, n, dt);
-  }
-  *variant_out = v;
+  if (h->kind == FS_KIND_SJLT_SCATTER) need->floor = need->want = fs::scatter_workspace_bytes(h->p, n, dt);
+  if (h->kind == FS_KIND_GAUSS_DENSE && !fs::gauss_supported(h->p.k, h->p.d, A, lda, n, dt)) return FS_ERR_UNSUPPORTED;
   return FS_OK;
 }
+
+size_t rows_want(const fs::mm::RowsPlan& pl) { return !pl.ok ? 0 : pl.ws > pl.ws_floor ? pl.ws : pl.ws_floor; }
 
 fs_status ensure_workspace(fs_sketch_t h, size_t need) {
   if (need <= h->ws_bytes) return FS_OK;
@@ -320,16 +305,10 @@ fs_status fs_sketch_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dt, size_
   if (!h || !bytes || n < 0 || !valid_dtype(dt)) return FS_ERR_INVALID_ARG;
   *bytes = 0;
   if (n == 0) return FS_OK;
-  // Size for the best case of a well-aligned call: an aligned dummy pointer
-  // and packed leading dimensions rounded up to 16 bytes.
-  const int64_t ld = (n + 7) & ~(int64_t)7;
-  int v;
-  const void* aligned = (const void*)(uintptr_t)256;
-  fs::Workspace need;
-  fs_status st = needed_workspace(h, aligned, ld, n, aligned, ld, dt, &v, &need);
-  if (st == FS_ERR_UNSUPPORTED) return FS_OK;
-  *bytes = need.want;
-  return st;
+  if (h->kind == FS_KIND_SJLT_SCATTER) *bytes = fs::scatter_workspace_bytes(h->p, n, dt);
+  // (a bound over alignments; shapes the matrix-core kernels do not take need none)
+  if (h->kind == FS_KIND_BLOCKPERM && h->variant != FS_VARIANT_GENERIC) *bytes = fs::mfma_workspace_bytes(h->p, n, dt);
+  return FS_OK;
 }
 
 fs_status fs_sketch_set_workspace(fs_sketch_t h, void* dev_ptr, size_t bytes) {
@@ -361,23 +340,36 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
   // whether the kernels will get the orbit table of the wiring (it shapes their plan)
   const bool with_orbit = h->kind == FS_KIND_BLOCKPERM && fs::mfma_wants_orbit(h->p) &&
                           (!src.external || 2 * (size_t)h->p.M * sizeof(uint32_t) <= src.orbit_bytes);
-  int variant;
+  int variant = FS_VARIANT_GENERIC;
   fs::Workspace need;
-  fs_status rc = needed_workspace(h, A, lda, n, out, ldo, dt, &variant, &need, with_orbit ? 1 : 0);
-  if (rc != FS_OK) return rc;
+  fs::mm::Plan plan;
+  fs_status rc = FS_OK;
+  if (h->kind != FS_KIND_BLOCKPERM) {
+    rc = other_kind(h, A, lda, n, dt, &need);
+    if (rc != FS_OK) return rc;
+  } else if (h->variant != FS_VARIANT_GENERIC) {
+    plan = fs::plan_mfma(h->p, A, lda, n, dt, with_orbit, SIZE_MAX);
+    if (h->variant == FS_VARIANT_MFMA && !plan.ok) return FS_ERR_UNSUPPORTED;
+    if (plan.ok) {
+      variant = FS_VARIANT_MFMA;
+      need = fs::mfma_workspace(h->p, plan);
+    }
+  }
   void* ws = nullptr;
-  size_t ws_bytes = 0;
+  size_t ws_bytes = src.plane_bytes;
   const uint32_t* orbit = nullptr;
   if (src.external && need.floor > src.plane_bytes) return FS_ERR_ALLOC;  // beyond the supplied memory: nothing is launched
   if (!src.external) {
     rc = ensure_workspace(h, need, st);
     if (rc != FS_OK) return rc;
+    ws_bytes = h->ws_bytes;
   }
+  if (variant == FS_VARIANT_MFMA && need.want > ws_bytes)  // less than it would like: a split that fits
+    plan = fs::plan_mfma(h->p, A, lda, n, dt, with_orbit, ws_bytes);
   const ProfSet prof = next_events(h, st);
   const fs::EventPair ev = prof.kernel;
   if (src.external) {
     ws = src.planes;
-    ws_bytes = src.plane_bytes;
     // such memory is shared between handles: the table of this handle's wiring is rebuilt on every
     // call (a wiring too long for the table's room runs without one: the kernels then skip the
     // orbit-ordered modes)
@@ -392,7 +384,6 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
       if (rc != FS_OK) return rc;
     }
     ws = h->ws;
-    ws_bytes = h->ws_bytes;
     orbit = h->orbit;
   }
 
@@ -409,7 +400,8 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
     e = fs::launch_blockrow(h->p, A, lda, n, out, ldo, dt, st, ev);
     what = "blockrow_kernel";
   } else if (variant == FS_VARIANT_MFMA) {
-    e = fs::launch_mfma(h->p, A, lda, n, out, ldo, dt, ws, ws_bytes, orbit, st, ev, &mode, h->last_kernel,
+    mode = fs::mfma_mode(plan);
+    e = fs::launch_mfma(plan, h->p, A, lda, n, out, ldo, dt, ws, ws_bytes, orbit, st, ev, h->last_kernel,
                         sizeof(h->last_kernel));
   } else {
     e = fs::launch_generic(h->p, A, lda, n, out, ldo, dt, st, ev);
@@ -445,12 +437,17 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   const size_t esz = dt == FS_F32 ? 4 : 2;
   if ((uintptr_t)G % esz || (uintptr_t)out % esz) return FS_ERR_INVALID_ARG;
   if (h->kind != FS_KIND_BLOCKPERM) return FS_ERR_UNSUPPORTED;
-  const bool can = fs::rows_supported(h->p, G, ldg, n, dt);
-  if (h->variant == FS_VARIANT_MFMA && !can) return FS_ERR_UNSUPPORTED;
-  const bool use_mfma = can && h->variant != FS_VARIANT_GENERIC;
+  fs::mm::RowsPlan plan;
+  if (h->variant != FS_VARIANT_GENERIC) plan = fs::plan_rows(h->p, G, ldg, n, dt, SIZE_MAX);
+  if (h->variant == FS_VARIANT_MFMA && !plan.ok) return FS_ERR_UNSUPPORTED;
+  const bool use_mfma = plan.ok;
   hipStream_t st = (hipStream_t)stream;
-  fs_status rc = use_mfma ? ensure_workspace(h, fs::rows_workspace(h->p, G, ldg, n, dt), st) : FS_OK;
-  if (rc != FS_OK) return rc;
+  fs_status rc = FS_OK;
+  if (use_mfma) {
+    rc = ensure_workspace(h, fs::Workspace{plan.ws_floor, rows_want(plan)}, st);
+    if (rc != FS_OK) return rc;
+    if (plan.ws > h->ws_bytes) plan = fs::plan_rows(h->p, G, ldg, n, dt, h->ws_bytes);  // a split that fits
+  }
   const ProfSet prof = next_events(h, st);
   const fs::EventPair ev = prof.kernel;
   if (!use_mfma) {
@@ -464,7 +461,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   }
   rc = ensure_orbit(h, st);  // the gather-reduction walks the wiring through this table
   if (rc != FS_OK) return rc;
-  const hipError_t e = fs::launch_rows(h->p, G, ldg, n, out, ldo, dt, h->ws, h->ws_bytes, h->orbit, st, ev);
+  const hipError_t e = fs::launch_rows(plan, h->p, G, ldg, n, out, ldo, dt, h->ws, h->ws_bytes, h->orbit, st, ev);
   if (prof.end) (void)hipEventRecord(prof.end, st);
   snprintf(h->last_kernel, sizeof(h->last_kernel), "rows_kernel");
   h->last_variant = FS_VARIANT_MFMA;
@@ -480,7 +477,7 @@ fs_status fs_sketch_rows_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dt, 
   const size_t esz = dt == FS_F32 ? 4 : 2;
   const int64_t ld = (h->p.d + 7) & ~(int64_t)7;  // a well-aligned call: packed rows rounded to 16 bytes
   if (34 * ld * (int64_t)esz >= ((int64_t)1 << 31)) return FS_OK;
-  *bytes = fs::rows_workspace(h->p, (const void*)(uintptr_t)256, ld, n, dt).want;
+  *bytes = rows_want(fs::plan_rows(h->p, (const void*)(uintptr_t)256, ld, n, dt, SIZE_MAX));
   return FS_OK;
 }
 
@@ -494,16 +491,29 @@ fs_status fs_sketch_plan(fs_sketch_t h, const void* A, int64_t ld, int64_t n, fs
   int v = FS_VARIANT_GENERIC, m = 0, f = 0;
   size_t ws = 0;
   if (n > 0 && h->kind == FS_KIND_BLOCKPERM) {
-    int mm = 0, ff = 0;
-    size_t w = 0;
-    const bool can = rows ? fs::rows_describe(h->p, A, ld, n, dt, &mm, &ff, &w)
-                          : fs::mfma_describe(h->p, A, ld, n, dt, fs::mfma_wants_orbit(h->p), &mm, &ff, &w);
-    if (h->variant == FS_VARIANT_MFMA && !can) return FS_ERR_UNSUPPORTED;
-    if (can && h->variant != FS_VARIANT_GENERIC) { v = FS_VARIANT_MFMA; m = mm; f = ff; ws = w; }
+    if (rows) {
+      const fs::mm::RowsPlan pl = fs::plan_rows(h->p, A, ld, n, dt, SIZE_MAX);
+      if (h->variant == FS_VARIANT_MFMA && !pl.ok) return FS_ERR_UNSUPPORTED;
+      if (pl.ok && h->variant != FS_VARIANT_GENERIC) {
+        v = FS_VARIANT_MFMA;
+        m = pl.out_stat ? 1 : 2;
+        f = (pl.vec ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
+            (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (pl.zsplit > 1 ? FS_PLAN_SPLIT : 0);
+        ws = rows_want(pl);
+      }
+    } else {
+      const fs::mm::Plan pl = fs::plan_mfma(h->p, A, ld, n, dt, fs::mfma_wants_orbit(h->p), SIZE_MAX);
+      if (h->variant == FS_VARIANT_MFMA && !pl.ok) return FS_ERR_UNSUPPORTED;
+      if (pl.ok && h->variant != FS_VARIANT_GENERIC) {
+        v = FS_VARIANT_MFMA;
+        m = fs::mfma_mode(pl);
+        f = fs::mfma_flags(pl);
+        ws = fs::mfma_workspace(h->p, pl).want;
+      }
+    }
   } else if (n > 0) {
-    int vv;
     fs::Workspace need;
-    const fs_status rc = needed_workspace(h, A, ld, n, A, n, dt, &vv, &need);
+    const fs_status rc = other_kind(h, A, ld, n, dt, &need);
     if (rc != FS_OK) return rc;
     ws = need.want;
   }

@@ -89,24 +89,27 @@ hipError_t launch_generic(const SketchParams& p, const void* A, int64_t lda, int
 hipError_t launch_generic_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
                                int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev);
 
-// Matrix-core path.  ws holds the per-slot partial tiles.
-bool mfma_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n, const void* out,
-                    int64_t ldo, fs_dtype dt);
-// Workspace of one call with or without the orbit table, and an upper bound over alignments and the
-// presence of the table.
-Workspace mfma_workspace(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit);
-size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt);
+// Matrix-core path: what a call would do (pure host work; not ok: unsupported), made once per call and
+// handed to the launch.  ws_bytes: workspace the call can have; the row split is the best one that fits.
 // orbit: device array of 2*M words (block at each orbit position of the wiring map
-// starting from block 0, then the inverse), or NULL.
+// starting from block 0, then the inverse), or NULL; have_orbit: whether the launch will get it.
+namespace mm {
+struct Plan;
+struct RowsPlan;
+}
 bool mfma_wants_orbit(const SketchParams& p);
-// What launch_mfma would do, without launching (pure host work): mode 1 output-stationary, 2
-// input-stationary, 3 the same with orbit runs; flags as in fs_plan_flags.  False: unsupported.
-bool mfma_describe(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt,
-                   bool have_orbit, int* mode, int* flags, size_t* workspace);
-// ws_bytes: what ws holds; the row split is the best one that fits.
-hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
+mm::Plan plan_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit,
+                   size_t ws_bytes);
+Workspace mfma_workspace(const SketchParams& p, const mm::Plan& pl);
+// mode 1 output-stationary, 2 input-stationary, 3 the same with orbit runs; flags as in fs_plan_flags
+int mfma_mode(const mm::Plan& pl);
+int mfma_flags(const mm::Plan& pl);
+// An upper bound over alignments and the presence of the table.
+size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt);
+// ws holds the per-slot partial tiles.
+hipError_t launch_mfma(const mm::Plan& pl, const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
                        int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
-                       EventPair ev, int* mode, char* desc, size_t desc_cap);
+                       EventPair ev, char* desc, size_t desc_cap);
 
 // Output-stationary matrix-core kernel with Phi tiles shared by a work-group (16-bit types, blocks
 // exactly 32, 64 or 128 rows high): whether it takes the call with a given row split, and its
@@ -128,12 +131,8 @@ hipError_t launch_stacked(const SketchParams& p, const void* A, int64_t lda, int
                           size_t desc_cap);
 
 // Matrix-core path for inputs held examples-as-rows: G is n x d (ld = ldg), out is n x k.
-bool rows_supported(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt);
-bool rows_describe(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, int* mode,
-                   int* flags, size_t* workspace);
-Workspace rows_workspace(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt);
-// ws_bytes: what ws holds; the row split is the best one that fits.
-hipError_t launch_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
+mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes);
+hipError_t launch_rows(const mm::RowsPlan& pl, const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
                        int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev);
 

@@ -263,11 +263,8 @@ GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt) {
     // us per stage of a work-group that has its CU to itself
     const double stage_us = dt == FS_F32 ? (ncg == 4 ? 9.2 : ncg == 2 ? 5.2 : 4.0) : (ncg == 4 ? 2.0 : ncg == 2 ? 1.3 : 0.9);
     const int per_cu = dt == FS_F32 || ncg == 4 ? 1 : 2;
-    int last = 0;
-    for (int z = 1; z <= total && z <= 128; ++z) {
-      const int st = (total + z - 1) / z;
-      if (st == last || (total + st - 1) / st != z) continue;
-      last = st;
+    for (int z = 1, st; z <= total && z <= 128; z = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
+      st = (total + z - 1) / z;
       if (z > 1 && plane * z > (double)kGaussScratch) break;
       const double w = (double)wgs * z, rounds = ceil(w / (256 * per_cu));
       double t = rounds * (w > 256 && per_cu > 1 ? 1.7 : 1.0) * (st * stage_us + 3.0);

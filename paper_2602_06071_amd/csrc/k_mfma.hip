@@ -105,13 +105,13 @@ struct SplitCost {
   }
   // Smallest modelled time over the splits whose planes fit max_bytes.
   int best(double max_bytes, int zmax, double* t_best) const {
-    int bz = 1, last = 0;
+    int bz = 1;
     double bt = at(1);
-    for (int z = 2; z <= total && z <= zmax; ++z) {
-      const int st = (total + z - 1) / z;
-      if (st == last || (total + st - 1) / st != z) continue;
-      last = st;
-      if (plane_bytes * z > max_bytes) break;
+    // (from one split to the first one with fewer stages per work-group, while the chip is not full many
+    // times over)
+    for (int z = 2, st; z <= total && z <= zmax; z = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
+      st = (total + z - 1) / z;
+      if (plane_bytes * z > max_bytes || units * z * nw > 16 * slots + units * nw) break;
       const double t = at(z);
       if (t < bt * 0.98) { bt = t; bz = z; }
     }
@@ -328,14 +328,12 @@ size_t plan_bytes(const SketchParams& p, const Plan& pl) {
 
 }  // namespace
 
-bool mfma_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n, const void* out,
-                    int64_t ldo, fs_dtype dt) {
-  (void)out; (void)ldo;
-  return make_plan(p, A, lda, n, dt, false, SIZE_MAX).ok;
+mm::Plan plan_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit,
+                   size_t ws_bytes) {
+  return make_plan(p, A, lda, n, dt, have_orbit, ws_bytes);
 }
 
-Workspace mfma_workspace(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit) {
-  const Plan pl = make_plan(p, A, lda, n, dt, have_orbit, SIZE_MAX);
+Workspace mfma_workspace(const SketchParams& p, const mm::Plan& pl) {
   Workspace w;
   if (!pl.ok) return w;
   w.floor = pl.ws_floor;
@@ -344,17 +342,13 @@ Workspace mfma_workspace(const SketchParams& p, const void* A, int64_t lda, int6
   return w;
 }
 
-bool mfma_describe(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt,
-                   bool have_orbit, int* mode, int* flags, size_t* workspace) {
-  const Plan pl = make_plan(p, A, lda, n, dt, have_orbit, SIZE_MAX);
-  if (!pl.ok) return false;
-  *mode = !pl.in_stat ? 1 : pl.run > 1 ? 3 : 2;
+int mfma_mode(const mm::Plan& pl) { return !pl.in_stat ? 1 : pl.run > 1 ? 3 : 2; }
+
+int mfma_flags(const mm::Plan& pl) {
   const bool split = pl.zsplit > 1 || (pl.ks && pl.stages >= ks_waves(pl.mt, pl.cpl));  // every wave has a share
-  *flags = (pl.vec4 ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
-           (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (split ? FS_PLAN_SPLIT : 0) |
-           (pl.stacked ? FS_PLAN_STACKED : 0);
-  *workspace = mfma_workspace(p, A, lda, n, dt, have_orbit).want;
-  return true;
+  return (pl.vec4 ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
+         (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (split ? FS_PLAN_SPLIT : 0) |
+         (pl.stacked ? FS_PLAN_STACKED : 0);
 }
 
 bool mfma_wants_orbit(const SketchParams& p) {
@@ -366,7 +360,7 @@ size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt) {
   const int64_t ld = (n + 7) & ~(int64_t)7;
   size_t most = 0;
   for (int i = 0; i < 4; ++i) {
-    const Workspace w = mfma_workspace(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0);
+    const Workspace w = mfma_workspace(p, make_plan(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0, SIZE_MAX));
     if (w.want > most) most = w.want;
   }
   return most;
@@ -381,12 +375,10 @@ static hipError_t launch_reduce(const SketchParams& p, const Plan& pl, int64_t n
                         : launch_reduce_planes<float>(ws, pl.planes, p.k, pl.ldw, n, out, ldo, p.scale, pl.run, blk2pos, p.Br, p.kappa, st);
 }
 
-hipError_t launch_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
+hipError_t launch_mfma(const mm::Plan& pl, const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
                        int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
-                       EventPair ev, int* mode, char* desc, size_t desc_cap) {
-  const Plan pl = make_plan(p, A, lda, n, dt, orbit != nullptr, ws_bytes);
+                       EventPair ev, char* desc, size_t desc_cap) {
   if (!pl.ok || plan_bytes(p, pl) > ws_bytes) return hipErrorInvalidValue;
-  *mode = !pl.in_stat ? 1 : pl.run > 1 ? 3 : 2;
   if (pl.stacked) return launch_stacked(p, A, lda, n, out, ldo, dt, orbit, st, ev, desc, desc_cap);
   hipError_t e;
   if (pl.outs) {

@@ -30,6 +30,7 @@
 
 #include "handle.h"
 #include "mfma_common.h"
+#include "mfma_plan.h"
 #include "spec.h"
 
 namespace fs {
@@ -550,20 +551,6 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restric
   for (int c = 0; c < VEC; ++c) Elt<T>::store(dst + c, s[c]);
 }
 
-struct RowsPlan {
-  bool ok = false;
-  int mt = 0, et = 4, zsplit = 1, stages = 0, total = 0, groups = 1, group_slots = 0;
-  bool out_stat = false;
-  bool vec = true;       // every piece starts on 16 bytes
-  bool unal = false;     // some pieces start inside a dword (16-bit types)
-  int nsub = 1;          // OUT: 128-row slices of an output block
-  bool big = false;      // IN: one descriptor per 32-example tile (very long rows)
-  int waves_per_simd = 1;
-  size_t lds = 0;
-  size_t ws = 0;         // bytes of partial records of this plan
-  size_t ws_floor = 0;   // bytes a call must find (an attached workspace below this is refused)
-};
-
 // Row split of `units` work-groups (one wave each) with `total` stages of work each.  Every split
 // adds a set of partial records; fewer splits than the chip has room for waves leave it idle.  The
 // model: the longest of (1) what the waves issue, spread over 1024 SIMDs, (2) rounds of resident
@@ -573,12 +560,10 @@ struct RowsPlan {
 // entries, kappa*Br = 64, M = 256): 1 split 94 us, 8 splits 36 us.
 int pick_rows_split(double units, int total, double stage_us, double slots, double stream_us,
                     double set_bytes, bool has_reduce, double max_bytes) {
-  int best_z = 1, last_s = 0;
+  int best_z = 1;
   double best = 0;
-  for (int zc = 1; zc <= total && zc <= 256; ++zc) {
-    const int st = (total + zc - 1) / zc;
-    if (st == last_s || (total + st - 1) / st != zc) continue;  // the same stages per work-group as before
-    last_s = st;
+  for (int zc = 1, st; zc <= total && zc <= 256; zc = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
+    st = (total + zc - 1) / zc;  // (the next split is the first one with fewer stages per work-group)
     if (zc > 1 && set_bytes * zc > max_bytes) break;
     const double waves = units * zc;
     const double rounds = waves <= slots ? 1.0 : waves / slots;
@@ -733,31 +718,13 @@ void launch_reduce(int64_t outputs, uint32_t addends, hipStream_t st, const Rows
 
 }  // namespace
 
-bool rows_supported(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt) {
-  return make_rows_plan(p, G, ldg, n, dt, SIZE_MAX).ok;
+mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes) {
+  return make_rows_plan(p, G, ldg, n, dt, ws_bytes);
 }
 
-bool rows_describe(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, int* mode,
-                   int* flags, size_t* workspace) {
-  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, SIZE_MAX);
-  if (!pl.ok) return false;
-  *mode = pl.out_stat ? 1 : 2;
-  *flags = (pl.vec ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
-           (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (pl.zsplit > 1 ? FS_PLAN_SPLIT : 0);
-  *workspace = pl.ws > pl.ws_floor ? pl.ws : pl.ws_floor;
-  return true;
-}
-
-Workspace rows_workspace(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt) {
-  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, SIZE_MAX);
-  if (!pl.ok) return {0, 0};
-  return {pl.ws_floor, pl.ws > pl.ws_floor ? pl.ws : pl.ws_floor};
-}
-
-hipError_t launch_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
+hipError_t launch_rows(const mm::RowsPlan& pl, const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
                        int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev) {
-  const RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, ws_bytes);
   if (!pl.ok || pl.ws > ws_bytes) return hipErrorInvalidValue;
   RowsArgs a;
   a.p = p; a.G = G; a.ws = (float*)ws; a.orbit = orbit; a.out = out;

@@ -42,6 +42,21 @@ struct Plan {
   size_t ws_floor = 0;              // bytes of workspace a call must find (an attached one below this is refused)
 };
 
+// The same for the examples-as-rows layout (k_rows.hip).
+struct RowsPlan {
+  bool ok = false;
+  int mt = 0, et = 4, zsplit = 1, stages = 0, total = 0, groups = 1, group_slots = 0;
+  bool out_stat = false;
+  bool vec = true;       // every piece starts on 16 bytes
+  bool unal = false;     // some pieces start inside a dword (16-bit types)
+  int nsub = 1;          // OUT: 128-row slices of an output block
+  bool big = false;      // IN: one descriptor per 32-example tile (very long rows)
+  int waves_per_simd = 1;
+  size_t lds = 0;
+  size_t ws = 0;         // bytes of partial records of this plan
+  size_t ws_floor = 0;   // bytes a call must find (an attached workspace below this is refused)
+};
+
 // ---- the K-split kernel (k_ksplit_kernel.h): MT 32-row tiles x 32*CPL columns per work-group ----
 // waves per work-group: 8, or one per SIMD where the accumulators take the whole register file
 constexpr int ks_waves(int mt, int cpl) { return mt * cpl >= 16 ? 4 : 8; }
