@@ -266,12 +266,15 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   // columns always; beyond, both kernels are priced by the model above, and the K-split one has to
   // promise a fifth less.  Measured (us per call, mfma_kernel with its evenly dividing splits -> this plan):
   // fp32 262144 x 1, k = 4096, kappa = 4: 40 -> 17; fp32 1923840 x 48, kappa = 8: 632 -> 118; half
-  // 1575567 x 7 with eight 98473-row blocks: 3166 -> 107; fp32 262144 x 256 ("tall"): 77 -> 72; half 1728
-  // columns of eight 3520-row blocks: 104 -> 32; where the 128-column waves fill the chip they stay.  (Decided without looking at the alignment, so that an
-  // unaligned view sums in the same order as a packed copy of it; and input-stationary calls
-  // of up to four 256-column chunks, where one chunk leaves CUs without a work-group, are planned as if n were 256:
-  // they sum in the same order as their chunks.)
-  if (!shared_shape && nsub == 1 && pl.run == 1) {
+  // 1575567 x 7 with 98473-row blocks: 3166 -> 107; fp32 262144 x 256 ("tall"): 86 -> 75; half 1728
+  // columns of eight 3520-row blocks: 104 -> 32; in 64-column tiles fp32 4096 x 512 ("tiny"): 14 -> 11.6, fp32
+  // 17856 x 168: 38 -> 14, half 11253 x 729: 31 -> 9.6.  Where the 128-column waves fill the chip they stay.
+  // (Decided without looking at the alignment when n is a multiple of 4, so that an unaligned view sums in the
+  // same order as a packed copy of it; rows of another length have no aligned packed copy, and the calls that would be
+  // the shared-Phi kernel's if they were aligned are priced too.  Input-stationary calls of up to four 256-column
+  // chunks, where one chunk leaves CUs without a work-group, are planned as if n were 256: they sum in the
+  // same order as their chunks.)
+  if (!(shared_shape && (pl.vec4 || n % 4 == 0)) && nsub == 1 && pl.run == 1) {
     const int kap = pl.in_stat ? (group_slots < (int)p.kappa ? group_slots : (int)p.kappa) : 1;
     const double phi_us = 0.12 + 0.07 * kap;
     const double mfma_us = pl.mt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0;  // per 32 columns and stage
@@ -282,25 +285,29 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
     const int zmax = 65535 / groups;
     // (the waves of mfma_kernel are column groups: they do not share the stages)
     const SplitCost old{(double)p.M * ((nr + WCOLS - 1) / WCOLS) * groups, phi_us + 4 * (mfma_us + conv_us),
-                        esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : 0.8, pl.mt == 4 ? 1024.0 : 2048.0, stream, split_bytes, 0.0, 1, pl.total, pl.in_stat};
+                        esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : pl.unal && n % 4 ? 1.6 : 0.8,
+                        pl.mt == 4 ? 1024.0 : 2048.0, stream, split_bytes, 2.0, 1, pl.total, pl.in_stat};
     // (a split with kappa = 1 adds the planes and a launch to a call that streams A once: only for a clear gain)
     if (old.at(1) < old.at(pl.zsplit) * (p.kappa == 1 ? 1.15 : 1.0)) pl.zsplit = 1;
     const double t_old = old.at(pl.zsplit);
-    const int cpl = n <= 32 ? 1 : n <= 64 ? 2 : 4;
-    const int nw = ks_waves(pl.mt, cpl);
-    const size_t lds = ks_lds_bytes(pl.mt, cpl);
-    const int64_t ct = (n + 32 * cpl - 1) / (32 * cpl);
-    int per_cu = (int)(kLdsBudget / lds);
-    const int by_regs = 4 * ks_waves_per_simd(pl.mt, cpl) / nw;
-    if (by_regs < per_cu) per_cu = by_regs;
-    const SplitCost ks{(double)p.M * ((nr + 32 * cpl - 1) / (32 * cpl)) * groups, phi_us + cpl * (mfma_us + conv_us),
-                       esz == 4 && cpl == 4 && pl.mt <= 2 ? 1.6 : 0.8, 256.0 * per_cu * nw, stream, split_bytes, 1.0 + 0.25 * pl.mt * cpl, nw, pl.total, pl.in_stat};
     double t_ks = 0;
-    int z = ks.best(max_bytes, zmax, &t_ks);
+    int cpl = 0, z = 1;
+    for (int c = n <= 32 ? 1 : n <= 64 ? 2 : 4; c >= 1; c /= 2) {  // (narrower tiles: more waves, Phi made more often)
+      const int nw = ks_waves(pl.mt, c);
+      int per_cu = (int)(kLdsBudget / ks_lds_bytes(pl.mt, c));
+      const int by_regs = 4 * ks_waves_per_simd(pl.mt, c) / nw;
+      if (by_regs < per_cu) per_cu = by_regs;
+      const SplitCost ks{(double)p.M * ((nr + 32 * c - 1) / (32 * c)) * groups, phi_us + c * (mfma_us + conv_us),
+                         esz == 4 && c == 4 && pl.mt <= 2 ? 1.6 : 0.8, 256.0 * per_cu * nw,
+                         stream, split_bytes, 1.0 + 0.25 * pl.mt * c, nw, pl.total, pl.in_stat};
+      double t = 0;
+      const int zc = ks.best(max_bytes, zmax, &t);
+      if ((n + 32 * c - 1) / (32 * c) <= 65535 && (cpl == 0 || t < 0.9 * t_ks)) { t_ks = t; cpl = c; z = zc; }
+    }
     while (z > 1 && per_split * z > max_bytes) --z;
-    if (ct <= 65535 && (cpl < 4 || t_ks < 0.8 * t_old)) {
+    if (cpl && (n <= 64 || t_ks < 0.8 * t_old)) {
       pl.ks = true;
-      pl.cpl = cpl; pl.lds = lds;
+      pl.cpl = cpl; pl.lds = ks_lds_bytes(pl.mt, cpl);
       pl.zsplit = z;
       settle(false);
       pl.planes = pl.in_stat ? pl.zsplit * (int)p.kappa : pl.zsplit > 1 ? pl.zsplit : 0;
