@@ -285,7 +285,7 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
     const int zmax = 65535 / groups;
     // (the waves of mfma_kernel are column groups: they do not share the stages)
     const SplitCost old{(double)p.M * ((nr + WCOLS - 1) / WCOLS) * groups, phi_us + 4 * (mfma_us + conv_us),
-                        esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : pl.unal && n % 4 ? 1.6 : 0.8,
+                        esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : 0.8,
                         pl.mt == 4 ? 1024.0 : 2048.0, stream, split_bytes, 2.0, 1, pl.total, pl.in_stat};
     // (a split with kappa = 1 adds the planes and a launch to a call that streams A once: only for a clear gain)
     if (old.at(1) < old.at(pl.zsplit) * (p.kappa == 1 ? 1.15 : 1.0)) pl.zsplit = 1;
