@@ -304,6 +304,29 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
       const int zc = ks.best(max_bytes, zmax, &t);
       if ((n + 32 * c - 1) / (32 * c) <= 65535 && (cpl == 0 || t < 0.9 * t_ks)) { t_ks = t; cpl = c; z = zc; }
     }
+    // 128 stacked rows under a few columns: what a wave does per stage is mostly making Phi, and its tile
+    // leaves room for one work-group per CU.  Two groups of half the slots read A twice, but are twice as
+    // many work-groups of half the work: taken unless the model, which does not see the idle slots of a
+    // lone work-group, prices them far higher (fp32 262144 columns of 1 and 40, kappa = 4, 32-row blocks:
+    // 18.9 -> 17.6 and 26.1 -> 24.0 us; bf16 65536 x 64: 14.4 -> 13.6).
+    if (n <= 64 && pl.in_stat && pl.mt == 4 && groups == 1 && p.kappa >= 2) {
+      const int half_slots = ((int)p.kappa + 1) / 2, hmt = half_slots * (int)brp <= 32 ? 1 : 2;
+      if (half_slots * (int)brp <= 64) {
+        const int nw = ks_waves(hmt, cpl);
+        int per_cu = (int)(kLdsBudget / ks_lds_bytes(hmt, cpl));
+        const int by_regs = 4 * ks_waves_per_simd(hmt, cpl) / nw;
+        if (by_regs < per_cu) per_cu = by_regs;
+        const SplitCost hs{(double)p.M * ((n + 32 * cpl - 1) / (32 * cpl)) * 2,
+                           0.12 + 0.07 * half_slots + cpl * (hmt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0 + conv_us), 0.8,
+                           256.0 * per_cu * nw, 2 * a_us, split_bytes, 1.0 + 0.25 * hmt * cpl, nw, pl.total, true};
+        double t = 0;
+        const int zc = hs.best(max_bytes, 65535 / 2, &t);
+        if (t < 1.5 * t_ks) {
+          t_ks = t; z = zc;
+          pl.mt = hmt; pl.groups = 2; pl.group_slots = half_slots;
+        }
+      }
+    }
     while (z > 1 && per_split * z > max_bytes) --z;
     if (cpl && (n <= 64 || t_ks < 0.8 * t_old)) {
       pl.ks = true;
