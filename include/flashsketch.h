@@ -229,8 +229,8 @@ typedef enum {
   FS_PLAN_ELEMENT_LOADS = 1, /* A / G not aligned for vector loads: narrower or unaligned
                                 loads, slower                                                  */
   FS_PLAN_ROW_SLICES = 2,    /* output blocks higher than 128 rows, served in 128-row slices   */
-  FS_PLAN_SLOT_GROUPS = 4,   /* more than 128 stacked rows of small blocks: input read once
-                                per group of wiring slots                                      */
+  FS_PLAN_SLOT_GROUPS = 4,   /* input read once per group of wiring slots: more than 128 stacked
+                                rows of small blocks, or more than 64 under at most 64 columns */
   FS_PLAN_SPLIT = 8,         /* the rows of a work-group's input are split over grid.z, or over
                                 all its waves                                                  */
   FS_PLAN_STACKED = 16       /* output-stationary with several output blocks, consecutive on

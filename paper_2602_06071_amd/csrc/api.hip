@@ -102,7 +102,9 @@ fs_status ensure_workspace(fs_sketch_t h, const fs::Workspace& w, hipStream_t st
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
     else if (cap != hipStreamCaptureStatusNone) return FS_OK;
   }
-  return ensure_workspace(h, w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch);
+  const fs_status rc = ensure_workspace(h, w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch);
+  if (rc != FS_ERR_ALLOC || (h->ws && !h->ws_owned)) return rc;
+  return w.floor <= h->ws_bytes ? FS_OK : ensure_workspace(h, w.floor);  // short of memory: what the call must have
 }
 
 // pos2blk[q] = f^q(0), blk2pos = its inverse: allocated once per handle and filled by a small
