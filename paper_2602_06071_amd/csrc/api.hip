@@ -89,22 +89,26 @@ fs_status ensure_workspace(fs_sketch_t h, size_t need) {
 }
 
 // Workspace for a call that runs with `w.floor` bytes and is fastest with `w.want`.  An attached
-// workspace is taken as it is if it holds the floor.  The handle's own grows to `want`, except while
-// `st` is being captured into a graph: there nothing may be allocated, and a call that the present
-// size can serve is served by it.  Its first allocation is kSplitScratch at least, and `want` exceeds
-// the floor only up to that size: later calls free and replace it only for a larger floor, not
-// because a smaller problem is split into more pieces (captured graphs hold its address).
+// workspace is taken as it is if it holds the floor.  The handle's own is allocated by the first call
+// that wants one, with kSplitScratch at least; `want` exceeds the floor only up to that size, so that
+// later calls free and replace it only for a larger floor, not because a smaller problem is split into
+// more pieces.  A call that the present size can serve is served by it where it may not or could not
+// be larger: while `st` is being captured into a graph (nothing may be allocated there) and after the
+// device was too full for kSplitScratch (nothing is freed that a call can run with, and a refused
+// allocation is not tried again for speed alone).
 fs_status ensure_workspace(fs_sketch_t h, const fs::Workspace& w, hipStream_t st) {
   if (w.want <= h->ws_bytes) return FS_OK;
   if (w.floor <= h->ws_bytes) {
-    if (h->ws && !h->ws_owned) return FS_OK;
+    if (h->ws || h->ws_refused) return FS_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
     else if (cap != hipStreamCaptureStatusNone) return FS_OK;
   }
-  const fs_status rc = ensure_workspace(h, w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch);
+  const size_t ask = w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch;
+  const fs_status rc = ensure_workspace(h, ask);
   if (rc != FS_ERR_ALLOC || (h->ws && !h->ws_owned)) return rc;
-  return w.floor <= h->ws_bytes ? FS_OK : ensure_workspace(h, w.floor);  // short of memory: what the call must have
+  h->ws_refused = true;  // short of memory: what the call must have
+  return w.floor == 0 ? FS_OK : ask > w.floor ? ensure_workspace(h, w.floor) : rc;
 }
 
 // pos2blk[q] = f^q(0), blk2pos = its inverse: allocated once per handle and filled by a small
@@ -197,7 +201,7 @@ fs_status fs_sketch_create_kind(fs_sketch_t* out, fs_kind kind, int64_t d, int64
   h->last_hip_error = 0;
   h->last_kernel[0] = 0;
   h->device = -1;
-  h->ws = nullptr; h->ws_bytes = 0; h->ws_owned = true;
+  h->ws = nullptr; h->ws_bytes = 0; h->ws_owned = true; h->ws_refused = false;
   h->dense = nullptr;
   h->profiling = false; h->prof_used = 0; h->prof_scope = 0;
   h->orbit = nullptr;

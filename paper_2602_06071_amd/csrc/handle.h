@@ -31,6 +31,7 @@ struct fs_sketch_s {
   void* ws;
   size_t ws_bytes;
   bool ws_owned;
+  bool ws_refused;  // the device had no room for a workspace that a call can do without
   // optional events of each apply: begin / end around everything it enqueues, start / stop
   // around its dominant kernel
   bool profiling;

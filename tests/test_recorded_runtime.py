@@ -1,0 +1,53 @@
+"""Host code of the library on a recording runtime (hip_recorder.c): what it allocates, frees and
+launches, without a GPU."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.environ.get("FLASHSKETCH_LIB", os.path.join(HERE, "..", "paper_2602_06071_amd", "libflashsketch.so"))
+
+
+@pytest.fixture(scope="module")
+def recorded(tmp_path_factory):
+    """Runs Python source with the names of recorded.py in a process of its own."""
+    cc = shutil.which("gcc")
+    if not cc:
+        pytest.skip("no C compiler")
+    rec = str(tmp_path_factory.mktemp("recorder") / "recorder.so")
+    subprocess.run([cc, "-shared", "-fPIC", "-O1", "-o", rec, os.path.join(HERE, "hip_recorder.c")], check=True)
+
+    def run(source):
+        r = subprocess.run([sys.executable, os.path.join(HERE, "recorded.py"), rec, LIB], input=source, text=True,
+                           capture_output=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return r.stdout
+    return run
+
+
+def test_a_workspace_that_serves_a_call_is_kept_when_memory_is_short(recorded):
+    recorded("""
+s = Sketch(262144, 4096, 2048, 32, 4, 4)
+rec.rec_budget(8 << 20)                       # no room for the usual first size
+assert s.apply_rows(2) == 0                   # input-stationary: it must have one
+held = s.info().workspace_bytes
+assert 0 < held < (8 << 20) and len(lines("malloc-failed")) == 1
+for n in (2, 1):
+    rec.rec_clear()
+    assert s.apply_rows(n) == 0
+    assert not lines("free") and not lines("malloc") and not lines("malloc-failed"), lines()
+rec.rec_budget(1 << 40)
+rec.rec_clear()
+assert s.apply_rows(64) == 0                  # needs more: replaced
+assert len(lines("free")) == 1 and s.info().workspace_bytes > held
+
+s = Sketch(16384, 1024, 1024, 64, 4, 8)       # output-stationary: runs without any
+rec.rec_budget(rec.rec_live() + (1 << 20))
+assert s.apply_rows(4) == 0 and s.info().workspace_bytes == 0
+rec.rec_clear()
+assert s.apply_rows(4) == 0
+assert not lines("malloc-failed"), lines()    # not asked for again on every call
+""")
