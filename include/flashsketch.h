@@ -152,7 +152,9 @@ fs_status fs_sketch_create_kind(fs_sketch_t* out, fs_kind kind, int64_t d, int64
  * matrix-core apply of a handle also allocates a table of 8*M bytes (the orbit
  * of the wiring map) and enqueues the small kernel that fills it, unless fs_sketch_prepare
  * has done so; no call ever copies from the host or synchronises.  Later applies only enqueue
- * kernels (call prepare, or apply once, before capturing applies into a HIP graph). */
+ * kernels (call prepare, or apply once, before capturing applies into a HIP graph).  A workspace
+ * of the handle's own that a captured apply uses stays allocated until fs_sketch_destroy, also when
+ * a later call needs a larger one or fs_sketch_set_workspace replaces it, so the graph stays valid. */
 fs_status fs_sketch_apply(fs_sketch_t h, const void* A, int64_t lda, int64_t n, void* out,
                           fs_dtype dtype, void* stream);
 

@@ -73,14 +73,34 @@ fs_status other_kind(fs_sketch_t h, const void* A, int64_t lda, int64_t n, fs_dt
 
 size_t rows_want(const fs::mm::RowsPlan& pl) { return !pl.ok ? 0 : pl.ws > pl.ws_floor ? pl.ws : pl.ws_floor; }
 
+// Whether `st` is being captured into a graph (the NULL stream cannot be).
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!st) return false;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cap != hipStreamCaptureStatusNone;
+}
+
+// Gives up the handle's own workspace: frees it (which waits for work that may still use it) or, if a
+// graph may still use it, sets it aside until the handle is destroyed.
+fs_status drop_workspace(fs_sketch_t h) {
+  if (!h->ws || !h->ws_owned) return FS_OK;
+  void* p = h->ws;
+  const bool keep = h->ws_captured;
+  h->ws = nullptr; h->ws_bytes = 0; h->ws_captured = false;
+  if (keep) {
+    h->ws_retired.push_back(p);  // (room was reserved when it was marked)
+    return FS_OK;
+  }
+  const hipError_t e = hipFree(p);
+  return e == hipSuccess ? FS_OK : hip_fail(h, e);
+}
+
 fs_status ensure_workspace(fs_sketch_t h, size_t need) {
   if (need <= h->ws_bytes) return FS_OK;
   if (h->ws && !h->ws_owned) return FS_ERR_ALLOC;  // caller-owned and too small
-  if (h->ws) {
-    hipError_t e = hipFree(h->ws);  // waits for work that may still use it
-    h->ws = nullptr; h->ws_bytes = 0;
-    if (e != hipSuccess) return hip_fail(h, e);
-  }
+  const fs_status rc = drop_workspace(h);
+  if (rc != FS_OK) return rc;
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, need);
   if (e != hipSuccess) { hip_fail(h, e); return FS_ERR_ALLOC; }
@@ -97,18 +117,24 @@ fs_status ensure_workspace(fs_sketch_t h, size_t need) {
 // device was too full for kSplitScratch (nothing is freed that a call can run with, and a refused
 // allocation is not tried again for speed alone).
 fs_status ensure_workspace(fs_sketch_t h, const fs::Workspace& w, hipStream_t st) {
-  if (w.want <= h->ws_bytes) return FS_OK;
-  if (w.floor <= h->ws_bytes) {
-    if (h->ws || h->ws_refused) return FS_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
-    else if (cap != hipStreamCaptureStatusNone) return FS_OK;
+  const bool needs_none = w.want == 0 || (h->ws && !h->ws_owned);
+  if (w.floor > h->ws_bytes || (w.want > h->ws_bytes && !h->ws && !h->ws_refused && !capturing(st))) {
+    const size_t ask = w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch;
+    fs_status rc = ensure_workspace(h, ask);
+    if (rc == FS_ERR_ALLOC && !h->ws) {
+      h->ws_refused = true;  // short of memory: what the call must have
+      if (w.floor < ask) rc = ensure_workspace(h, w.floor);
+    }
+    if (rc != FS_OK) return rc;
   }
-  const size_t ask = w.want > fs::kSplitScratch ? w.want : fs::kSplitScratch;
-  const fs_status rc = ensure_workspace(h, ask);
-  if (rc != FS_ERR_ALLOC || (h->ws && !h->ws_owned)) return rc;
-  h->ws_refused = true;  // short of memory: what the call must have
-  return w.floor == 0 ? FS_OK : ask > w.floor ? ensure_workspace(h, w.floor) : rc;
+  if (needs_none || !h->ws || h->ws_captured || !capturing(st)) return FS_OK;
+  try {
+    h->ws_retired.reserve(h->ws_retired.size() + 1);
+  } catch (const std::bad_alloc&) {
+    return FS_ERR_ALLOC;
+  }
+  h->ws_captured = true;
+  return FS_OK;
 }
 
 // pos2blk[q] = f^q(0), blk2pos = its inverse: allocated once per handle and filled by a small
@@ -201,7 +227,7 @@ fs_status fs_sketch_create_kind(fs_sketch_t* out, fs_kind kind, int64_t d, int64
   h->last_hip_error = 0;
   h->last_kernel[0] = 0;
   h->device = -1;
-  h->ws = nullptr; h->ws_bytes = 0; h->ws_owned = true; h->ws_refused = false;
+  h->ws = nullptr; h->ws_bytes = 0; h->ws_owned = true; h->ws_refused = false; h->ws_captured = false;
   h->dense = nullptr;
   h->profiling = false; h->prof_used = 0; h->prof_scope = 0;
   h->orbit = nullptr;
@@ -277,6 +303,8 @@ fs_status fs_sketch_destroy(fs_sketch_t h) {
   fs_status st = FS_OK;
   release_events(h);
   if (h->ws && h->ws_owned && hipFree(h->ws) != hipSuccess) st = FS_ERR_HIP;
+  for (void* p : h->ws_retired)
+    if (hipFree(p) != hipSuccess) st = FS_ERR_HIP;
   if (h->orbit && hipFree(h->orbit) != hipSuccess) st = FS_ERR_HIP;
   if (h->dense && hipFree(h->dense) != hipSuccess) st = FS_ERR_HIP;
   if (st != FS_OK) (void)hipGetLastError();
@@ -321,11 +349,8 @@ fs_status fs_sketch_set_workspace(fs_sketch_t h, void* dev_ptr, size_t bytes) {
   if (!h) return FS_ERR_INVALID_ARG;
   if ((dev_ptr == nullptr) != (bytes == 0)) return FS_ERR_INVALID_ARG;
   if ((uintptr_t)dev_ptr % 256) return FS_ERR_INVALID_ARG;
-  if (h->ws && h->ws_owned) {
-    hipError_t e = hipFree(h->ws);
-    h->ws = nullptr; h->ws_bytes = 0;
-    if (e != hipSuccess) return hip_fail(h, e);
-  }
+  const fs_status rc = drop_workspace(h);
+  if (rc != FS_OK) return rc;
   h->ws = dev_ptr; h->ws_bytes = bytes; h->ws_owned = (dev_ptr == nullptr);
   return FS_OK;
 }

@@ -32,6 +32,8 @@ struct fs_sketch_s {
   size_t ws_bytes;
   bool ws_owned;
   bool ws_refused;  // the device had no room for a workspace that a call can do without
+  bool ws_captured;  // a call recorded into a graph uses it: it stays allocated until destroy
+  std::vector<void*> ws_retired;  // such workspaces after they were replaced
   // optional events of each apply: begin / end around everything it enqueues, start / stop
   // around its dominant kernel
   bool profiling;

@@ -35,24 +35,27 @@ def launches():
     return [Launch(ln[0], *map(int, ln[1:])) for ln in lines("launch")]
 
 
+STREAM = C.c_void_p(64)   # any handle but that of the default stream, which cannot be captured
+
+
 class Sketch:
     def __init__(self, d, k, Bc=1, Br=1, kappa=1, s=1, kind=0, seed=0):
         self.h, self.d, self.k = C.c_void_p(), d, k
         self.status = lib.fs_sketch_create_kind(C.byref(self.h), kind, C.c_int64(d), C.c_int64(k), Bc, Br, kappa, s,
                                                 C.c_uint64(seed))
 
-    def apply(self, n, dtype=F32, ld=None, first=0, ldo=None):
+    def apply(self, n, dtype=F32, ld=None, first=0, ldo=None, stream=None):
         esz = 4 if dtype == F32 else 2
         return lib.fs_sketch_apply_ld(self.h, C.c_void_p((1 << 44) + first * esz), C.c_int64(ld or n), C.c_int64(n),
-                                      C.c_void_p(1 << 45), C.c_int64(ldo or n), dtype, None)
+                                      C.c_void_p(1 << 45), C.c_int64(ldo or n), dtype, stream)
 
     def apply_static(self, n, dtype=F32):
         return lib.fs_sketch_apply_static(self.h, C.c_void_p(1 << 44), C.c_int64(n), C.c_int64(n), C.c_void_p(1 << 45),
                                           C.c_int64(n), dtype, None)
 
-    def apply_rows(self, n, dtype=F32, ld=None):
+    def apply_rows(self, n, dtype=F32, ld=None, stream=None):
         return lib.fs_sketch_apply_rows(self.h, C.c_void_p(1 << 44), C.c_int64(ld or self.d), C.c_int64(n),
-                                        C.c_void_p(1 << 45), C.c_int64(self.k), dtype, None)
+                                        C.c_void_p(1 << 45), C.c_int64(self.k), dtype, stream)
 
     def attach(self, address, size):
         return lib.fs_sketch_set_workspace(self.h, C.c_void_p(address), C.c_size_t(size))

@@ -51,3 +51,23 @@ rec.rec_clear()
 assert s.apply_rows(4) == 0
 assert not lines("malloc-failed"), lines()    # not asked for again on every call
 """)
+
+
+@pytest.mark.parametrize("replace", ["s.apply(512)", "s.attach(1 << 42, 1 << 30)"])
+@pytest.mark.parametrize("captured", [True, False])
+def test_a_workspace_that_a_graph_uses_outlives_its_replacement(recorded, captured, replace):
+    recorded(f"""
+captured = {captured}
+s = Sketch(262144, 4096, 2048, 32, 4, 4)
+assert s.apply_rows(2, stream=STREAM) == 0
+address = lines("malloc")[0][0]               # the workspace (then the wiring's table)
+rec.rec_capturing(int(captured))
+assert s.apply_rows(2, stream=STREAM) == 0
+rec.rec_capturing(0)
+rec.rec_clear()
+assert {replace} == 0                         # a larger one takes its place
+assert lines("free") == ([] if captured else [[address]])
+rec.rec_clear()
+assert s.destroy() == 0
+assert ([address] in lines("free")) == captured and rec.rec_live() == 0
+""")
