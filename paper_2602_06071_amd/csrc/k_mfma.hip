@@ -204,8 +204,9 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
     // 34496 x 1896 with kappa = 8, Br = 16: 147 -> 127; bf16 32768 x 8192 with kappa = 4, Br = 16: 235 -> 183.
     constexpr int R = 4;
     const int run_cols = pl.mt == 2 ? 2 * WCOLS : WCOLS;
+    const int64_t run_tiles = (n + run_cols - 1) / run_cols;  // grid.y: up to twice col_tiles, so bounded again
     if (have_orbit && p.br_pow2 && !pl.unal && zs == 1 && (rw == 64 || rw == 128) && pl.nrg == 1 && pl.ncg == 2 && p.kappa > 1 &&
-        p.M % R == 0 && (int64_t)(p.M / R) * ((n + run_cols - 1) / run_cols) >= 256) {
+        p.M % R == 0 && (int64_t)(p.M / R) * run_tiles >= 256 && run_tiles <= 65535) {
       pl.run = R;
       if (pl.mt == 4) pl.ncg = 1;
       pl.planes = (int)((p.kappa + R - 2) / R) + 1;

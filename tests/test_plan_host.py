@@ -85,6 +85,15 @@ def test_rows_layout_dispatch(params, n, dtype, kw, want):
     assert (p["variant"], p["mode"], p["flags"] & ~SP) == want, p
 
 
+@pytest.mark.parametrize("n,mode", [
+    (65535 * 128, RUNS),       # the last width whose 128-column tiles are a valid grid.y
+    (65535 * 128 + 8, IN),     # one tile more: back to 256-column tiles
+    (14089536, IN),
+])
+def test_orbit_runs_of_128_stacked_rows_stay_within_the_grid(n, mode):
+    assert plan((512, 128, 64, 16, 8, 4), n, torch.bfloat16)["mode"] == mode
+
+
 def test_plan_honours_the_forced_variant_and_reports_errors():
     sk = B.Sketch(4096, 256, 512, 32, 2, 4)
     assert sk.plan(64, torch.float32)["variant"] == MFMA
