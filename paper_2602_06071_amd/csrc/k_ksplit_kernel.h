@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "handle.h"
+#include "lds_limit.h"
 #include "mfma_common.h"
 #include "mfma_plan.h"
 #include "spec.h"
@@ -407,13 +408,8 @@ void ksplit_kernel(MfmaArgs a) {
 
 template <auto kernel>
 hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const MfmaArgs& a) {
-  static size_t raised = 64 * 1024;  // the dynamic-LDS limit set for this kernel so far
-  if (lds > raised) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    raised = lds;
-  }
+  const hipError_t e = allow_lds<kernel>(lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
   return hipGetLastError();
 }

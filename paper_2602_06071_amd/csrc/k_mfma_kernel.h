@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "handle.h"
+#include "lds_limit.h"
 #include "mfma_common.h"
 #include "mfma_plan.h"
 #include "spec.h"
@@ -645,16 +646,10 @@ void mfma_kernel(MfmaArgs a) {
   }
 }
 
-// One instantiation, and so one cached limit, per kernel (the kernel is a template argument).
 template <auto kernel>
 hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const MfmaArgs& a) {
-  static size_t raised = 64 * 1024;  // the dynamic-LDS limit set for this kernel so far
-  if (lds > raised) {  // above the default dynamic-LDS limit: raise it for this kernel
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    raised = lds;
-  }
+  const hipError_t e = allow_lds<kernel>(lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
   return hipGetLastError();
 }

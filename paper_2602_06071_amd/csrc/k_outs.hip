@@ -349,13 +349,6 @@ void outs_kernel(OutsArgs a) {
 
 template <auto kernel>
 hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const OutsArgs& a) {
-  static bool raised = false;
-  if (lds > 64 * 1024 && !raised) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
   hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
   return hipGetLastError();
 }

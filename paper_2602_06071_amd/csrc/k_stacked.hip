@@ -64,6 +64,7 @@
 #include <type_traits>
 
 #include "handle.h"
+#include "lds_limit.h"
 #include "mfma_common.h"
 #include "spec.h"
 
@@ -537,13 +538,8 @@ void stacked_kernel(StackedArgs a) {
 
 template <auto kernel>
 hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const StackedArgs& a) {
-  static bool raised = false;
-  if (lds > 64 * 1024 && !raised) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
+  const hipError_t e = allow_lds<kernel>(lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
   return hipGetLastError();
 }

@@ -71,3 +71,24 @@ rec.rec_clear()
 assert s.destroy() == 0
 assert ([address] in lines("free")) == captured and rec.rec_live() == 0
 """)
+
+
+def test_the_lds_limit_is_raised_on_every_device(recorded):
+    recorded("""
+calls = [((4096, 256, 512, 32, 2, 4), 512, F32, "ksplit_kernel"), ((65536, 8192, 64, 8, 8, 2), 300, BF16, "mfma_kernel"),
+         ((16384, 1024, 1024, 64, 4, 8), 16384, F32, "stacked_kernel")]
+for params, n, dtype, kernel in calls:
+    for device in (0, 1, 0, 70):              # each device has limits of its own, whatever its number
+        rec.rec_device(device)
+        s = Sketch(*params)
+        assert s.apply(n, dtype) == 0 and s.kernel().startswith(kernel), s.kernel()
+    big = [l for l in launches() if l.lds > 64 * 1024]
+    assert {l.device for l in big} == {0, 1, 70}, kernel
+    seen = set()
+    for ln in lines():
+        if ln[0] == "lds-limit":
+            seen.add((ln[1], ln[3], int(ln[2])))
+        elif ln[0] == "launch" and int(ln[6]) > 64 * 1024:
+            assert any(k == ln[1] and dev == ln[7] and limit >= int(ln[6]) for k, dev, limit in seen), ln
+    rec.rec_clear()
+""")
