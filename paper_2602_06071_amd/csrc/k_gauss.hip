@@ -253,7 +253,7 @@ void gauss_kernel(GaussArgs a) {
 // (1.4 PFLOP/s of bf16 products); fp32 41152 x 672, k = 1792: 5190 -> 614; half 42816 x 148, k = 384 (three
 // work-groups with element loads before): 11030 -> 26.
 struct GaussPlan { int ncg = 4, zsplit = 1, stages = 1; };
-GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt) {
+GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratch) {
   GaussPlan pl;
   const int total = (int)(d / KC);
   const double plane = (double)k * (double)((n + 3) & ~(int64_t)3) * 4.0;
@@ -265,7 +265,7 @@ GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt) {
     const int per_cu = dt == FS_F32 || ncg == 4 ? 1 : 2;
     for (int z = 1, st; z <= total && z <= 128; z = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
       st = (total + z - 1) / z;
-      if (z > 1 && plane * z > (double)kGaussScratch) break;
+      if (z > 1 && plane * z > (double)scratch) break;
       const double w = (double)wgs * z, rounds = ceil(w / (256 * per_cu));
       double t = rounds * (w > 256 && per_cu > 1 ? 1.7 : 1.0) * (st * stage_us + 3.0);
       if (z > 1) t += 4.0 + plane * z * (1 / 3.4e6 + 1 / 6e6) * (plane * z < 40e6 ? 0.5 : 1.0);
@@ -288,9 +288,8 @@ hipError_t go(K kernel, dim3 grid, unsigned threads, size_t lds, hipStream_t st,
 
 }  // namespace
 
-// fp32, bf16, three pieces of the exact split, half; then the planes of split applies.
-size_t gauss_matrix_bytes(int64_t k, int64_t d) { return ((size_t)k * (size_t)d * (4 + 5 * 2) + 255) & ~(size_t)255; }
-size_t gauss_bytes(int64_t k, int64_t d) { return gauss_matrix_bytes(k, d) + kGaussScratch; }
+// fp32, bf16, three pieces of the exact split, half.
+size_t gauss_bytes(int64_t k, int64_t d) { return ((size_t)k * (size_t)d * (4 + 5 * 2) + 255) & ~(size_t)255; }
 
 hipError_t gauss_fill(void* storage, int64_t k, int64_t d, uint32_t key1, hipStream_t st) {
   float* S32 = (float*)storage;
@@ -311,17 +310,17 @@ bool gauss_supported(int64_t k, int64_t d, const void* A, int64_t lda, int64_t n
   return (n + 255) / 256 <= 65535;
 }
 
-hipError_t launch_gauss(void* storage, int64_t k, int64_t d, const void* A, int64_t lda,
+hipError_t launch_gauss(void* storage, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
                         int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev) {
   const float* S32 = (const float*)storage;
   const uint16_t* b = (const uint16_t*)(S32 + k * d);
   const size_t esz = dt == FS_F32 ? 4 : 2;
-  const GaussPlan pl = gauss_plan(k, d, n, dt);
+  const GaussPlan pl = gauss_plan(k, d, n, dt, scratch);
   GaussArgs a;
   a.A = A; a.out = out; a.k = k; a.d = d; a.lda = lda; a.ldo = ldo; a.n = (int)n;
   a.total = (int)(d / KC); a.stages = pl.stages; a.zsplit = pl.zsplit;
   a.ldw = (n + 3) & ~(int64_t)3;
-  a.ws = (float*)((char*)storage + gauss_matrix_bytes(k, d));
+  a.ws = (float*)((char*)storage + gauss_bytes(k, d));
   a.out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
   a.S[1] = a.S[2] = nullptr;
   if (dt == FS_F32) { a.S[0] = b + k * d; a.S[1] = b + 2 * k * d; a.S[2] = b + 3 * k * d; }

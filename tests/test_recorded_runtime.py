@@ -92,3 +92,20 @@ for params, n, dtype, kernel in calls:
             assert any(k == ln[1] and dev == ln[7] and limit >= int(ln[6]) for k, dev, limit in seen), ln
     rec.rec_clear()
 """)
+
+
+def test_a_dense_sketch_that_just_fits_is_created_and_does_not_split(recorded):
+    recorded("""
+k, d, n = 256, 4096, 64
+matrix = 14 * k * d                           # fp32 and five 16-bit copies
+for room, status, splits in ((matrix + (128 << 20), 0, True), (matrix + (1 << 20), 0, False), (matrix - 1, 3, None)):
+    rec.rec_budget(rec.rec_live() + room)
+    s = Sketch(d, k, kind=2)
+    assert s.status == status, room
+    if status == 0:
+        rec.rec_clear()
+        assert s.apply(n) == 0
+        assert ([l.z > 1 for l in launches()] == [splits] + [False] * splits), launches()
+        assert s.destroy() == 0
+    assert rec.rec_live() == 0
+""")
