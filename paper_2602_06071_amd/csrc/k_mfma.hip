@@ -288,8 +288,12 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
     const SplitCost old{(double)p.M * ((nr + WCOLS - 1) / WCOLS) * groups, phi_us + 4 * (mfma_us + conv_us),
                         esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : 0.8,
                         pl.mt == 4 ? 1024.0 : 2048.0, stream, split_bytes, 2.0, 1, pl.total, pl.in_stat};
-    // (a split with kappa = 1 adds the planes and a launch to a call that streams A once: only for a clear gain)
-    if (old.at(1) < old.at(pl.zsplit) * (p.kappa == 1 ? 1.15 : 1.0)) pl.zsplit = 1;
+    // Which split mfma_kernel is priced with: the one picked above, or none where this model expects that
+    // to be faster -- but an input-stationary split that divides the block evenly stands, since the model lets
+    // too few waves stream A at the full rate (us per call, taken back -> kept: half 42819 x 4980 with 19 blocks
+    // 103 -> 93, half 62208 x 2368 with 27 blocks 68 -> 62, bf16 17280 x 4911 with 15 blocks 57 -> 49).
+    // (A split with kappa = 1 adds the planes and a launch to a call that streams A once: only for a clear gain.)
+    if ((!pl.in_stat || zs != zs_even) && old.at(1) < old.at(pl.zsplit) * (p.kappa == 1 ? 1.15 : 1.0)) pl.zsplit = 1;
     const double t_old = old.at(pl.zsplit);
     double t_ks = 0;
     int cpl = 0, z = 1;

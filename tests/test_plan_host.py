@@ -94,6 +94,16 @@ def test_orbit_runs_of_128_stacked_rows_stay_within_the_grid(n, mode):
     assert plan((512, 128, 64, 16, 8, 4), n, torch.bfloat16)["mode"] == mode
 
 
+@pytest.mark.parametrize("params,n,dtype", [
+    ((62208, 432, 2304, 16, 2, 2), 2368, torch.float16),
+    ((17280, 240, 1152, 16, 3, 2), 4911, torch.bfloat16),
+    ((184431, 524, 1408, 4, 4, 2), 513, torch.float16),
+])
+def test_few_blocks_keep_their_even_row_split(params, n, dtype):
+    p = plan(params, n, dtype)
+    assert p["mode"] == IN and p["flags"] & SP, p
+
+
 def test_plan_honours_the_forced_variant_and_reports_errors():
     sk = B.Sketch(4096, 256, 512, 32, 2, 4)
     assert sk.plan(64, torch.float32)["variant"] == MFMA
