@@ -47,8 +47,13 @@
  *              nearest-even.
  *   Errors     every call returns fs_status; nothing throws, aborts or prints.
  *              Argument errors are detected before any HIP call is made.
- *   Determinism FS_KIND_BLOCKPERM uses no atomics on data: the same inputs give
- *              bit-identical outputs.  FS_KIND_SJLT_SCATTER sums with global
+ *   Determinism FS_KIND_BLOCKPERM uses no atomics on data: the same call gives
+ *              bit-identical outputs.  The order in which a column is summed, and so its last bits,
+ *              may depend on n, on the alignment of A and on how large a workspace the call
+ *              finds.  It does not depend on n among 256, 512, 768 and 1024 columns when
+ *              M <= 8, k < 256 and the call runs input-stationary (fs_sketch_plan) with planes that at
+ *              1024 columns fit FS_STATIC_SCRATCH_BYTES: such a call equals the calls for its
+ *              256-column chunks bit for bit.  FS_KIND_SJLT_SCATTER sums with global
  *              float atomics and is order-nondeterministic by construction.
  */
 #ifndef FLASHSKETCH_H

@@ -120,8 +120,11 @@ struct SplitCost {
   }
 };
 
-// `limit`: bytes of workspace the call can have at most.
-Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt,
+constexpr uint32_t kChunkBlocks = 8;  // plan_mfma's chunk rule: blocks of a sketch it holds for
+
+// `nc`: columns an input-stationary call's kernel and row split are priced for; n, but for plan_mfma's
+// chunk rule.  `limit`: bytes of workspace the call can have at most.
+Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int64_t nc, fs_dtype dt,
                bool have_orbit, size_t limit) {
   Plan pl;
   const size_t esz = dt == FS_F32 ? 4 : 2;
@@ -162,25 +165,27 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   // split adds kappa partial planes.  Pick the split with the smallest modelled time: A streamed at
   // ~6 TB/s once there is a wave per SIMD (1024 of them), planes written at ~3.4 TB/s and read back at
   // ~6 TB/s (rates measured on this kernel pair).
-  int zs = 1, zs_even = 1;  // zs_even: only splits that divide the block evenly
-  {
-    const double a_bytes = (double)p.d * (double)n * esz * groups;
+  auto pick_split = [&](int64_t cols, int* any, int* even) {  // even: only splits that divide the block evenly
+    const double a_bytes = (double)p.d * (double)cols * esz * groups;
+    const double tiles = (double)((cols + WCOLS * pl.ncg - 1) / (WCOLS * pl.ncg));
     const double waves_per_wg = pl.ncg * (can_in ? nrg_i : 1);
     double best = 0, best_even = 0;
     bool divides = true;
     for (int zc = 1; zc <= 16; zc *= 2) {
-      const double waves = (double)p.M * col_tiles * zc * waves_per_wg * groups;
-      const double plane_bytes = (double)zc * p.kappa * (double)p.k * (double)n * 4.0;
+      const double waves = (double)p.M * tiles * zc * waves_per_wg * groups;
+      const double plane_bytes = (double)zc * p.kappa * (double)p.k * (double)cols * 4.0;
       const double t = a_bytes / (6e12 * (waves < 1024 ? waves / 1024 : 1.0)) + plane_bytes / 3.4e12 +
                        plane_bytes / 6e12;
       if (zc == 1 || (divides && p.Bc % (uint32_t)(zc * KC) == 0)) {
-        if (zc == 1 || t < best_even) { best_even = t; zs_even = zc; }
+        if (zc == 1 || t < best_even) { best_even = t; *even = zc; }
       } else {
         divides = false;
       }
-      if (zc == 1 || (zc <= blk_stages && t < best)) { best = t; zs = zc; }
+      if (zc == 1 || (zc <= blk_stages && t < best)) { best = t; *any = zc; }
     }
-  }
+  };
+  int zs = 1, zs_even = 1;
+  pick_split(n, &zs, &zs_even);
   // workspace traffic (write + read of the partial planes) relative to reading A once
   const double rho = 2.0 * zs_even * p.kappa * (double)p.k * 4.0 / ((double)p.d * esz);
   const bool out_starved = (int64_t)p.M * col_tiles < 256;  // fewer output tiles than CUs
@@ -239,9 +244,19 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   if (limit < pl.ws_floor) limit = pl.ws_floor;  // (the call is refused before it gets here)
   double max_bytes = (double)(pl.ws_floor > kSplitScratch ? pl.ws_floor : kSplitScratch);
   if ((double)limit < max_bytes) max_bytes = (double)limit;
-  const double per_split = pl.in_stat ? plane * p.kappa : plane;
+  const double per_split = pl.in_stat ? plane * p.kappa : plane;  // bytes of the planes of one split
+  // the same for nc columns
+  double per_priced = per_split, max_priced = max_bytes;
+  if (!pl.in_stat) nc = n;
+  if (nc != n) {
+    pick_split(nc, &zs, &zs_even);
+    pl.zsplit = zs;
+    per_priced = (double)p.k * (double)((nc + 3) & ~(int64_t)3) * 4.0 * p.kappa;
+    max_priced = zs_even * per_priced > (double)kSplitScratch ? zs_even * per_priced : (double)kSplitScratch;
+    if ((double)limit < max_priced) max_priced = (double)limit;
+  }
   if (pl.run == 1)
-    while (pl.zsplit > 1 && per_split * pl.zsplit > max_bytes) pl.zsplit /= 2;
+    while (pl.zsplit > 1 && per_priced * pl.zsplit > max_priced) pl.zsplit /= 2;
 
   // Shapes the kernel with several output blocks per wave takes go there (it loads A from L2
   // (kappa+S-1)/S times per output block, not kappa times; measured on "mid": kappa = 4, 0.365
@@ -258,6 +273,13 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
     pl.stages = pairs ? (int)outs_stages(pl.total, pl.zsplit) : (pl.total + pl.zsplit - 1) / pl.zsplit;
     pl.zsplit = (pl.total + pl.stages - 1) / pl.stages;
   };
+  auto settle_within = [&](bool pairs) {  // the split that was priced, or the finest below it whose planes fit
+    settle(pairs);
+    pl.z_priced = pl.zsplit;
+    if (pl.run > 1 || pl.zsplit == 1 || per_split * pl.zsplit <= max_bytes) return;
+    while (pl.zsplit > 1 && per_split * pl.zsplit > max_bytes) --pl.zsplit;
+    settle(pairs);
+  };
   // 16-bit output-stationary shapes without slices go to the kernel whose work-group
   // shares its Phi tiles (measured on the "wide" workload: 0.445 against 0.52 ms)
   if (shared_shape) settle(true);
@@ -272,22 +294,19 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   // 17856 x 168: 38 -> 14, half 11253 x 729: 31 -> 9.6.  Where the 128-column waves fill the chip they stay.
   // (Decided without looking at the alignment when n is a multiple of 4, so that an unaligned view sums in the
   // same order as a packed copy of it; rows of another length have no aligned packed copy, and the calls that would be
-  // the shared-Phi kernel's if they were aligned are priced too.  Input-stationary calls of up to four 256-column
-  // chunks, where one chunk leaves CUs without a work-group, are planned as if n were 256: they sum in the
-  // same order as their chunks.)
+  // the shared-Phi kernel's if they were aligned are priced too.)
   if (!(shared_shape && (pl.vec4 || n % 4 == 0)) && nsub == 1 && pl.run == 1) {
     const int kap = pl.in_stat ? (group_slots < (int)p.kappa ? group_slots : (int)p.kappa) : 1;
     const double phi_us = 0.12 + 0.07 * kap;
     const double mfma_us = pl.mt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0;  // per 32 columns and stage
     const double conv_us = esz == 4 ? 0.16 : 0.03;
-    const int64_t nr = pl.in_stat && n % 256 == 0 && n <= 1024 && (int64_t)p.M * groups * 2 < 256 ? 256 : n;
-    const double a_us = (double)p.d * (double)nr * esz / 5.5e6, split_bytes = per_split * (double)nr / (double)n;
+    const double a_us = (double)p.d * (double)nc * esz / 5.5e6;
     const double stream = pl.in_stat ? a_us * groups : a_us * (1 + 0.3 * (p.kappa - 1));
     const int zmax = 65535 / groups;
     // (the waves of mfma_kernel are column groups: they do not share the stages)
-    const SplitCost old{(double)p.M * ((nr + WCOLS - 1) / WCOLS) * groups, phi_us + 4 * (mfma_us + conv_us),
+    const SplitCost old{(double)p.M * ((nc + WCOLS - 1) / WCOLS) * groups, phi_us + 4 * (mfma_us + conv_us),
                         esz == 4 ? (pl.in_stat || p.kappa == 1 ? 1.6 : 2.4) : 0.8,
-                        pl.mt == 4 ? 1024.0 : 2048.0, stream, split_bytes, 2.0, 1, pl.total, pl.in_stat};
+                        pl.mt == 4 ? 1024.0 : 2048.0, stream, per_priced, 2.0, 1, pl.total, pl.in_stat};
     // Which split mfma_kernel is priced with: the one picked above, or none where this model expects that
     // to be faster -- but an input-stationary split that divides the block evenly stands, since the model lets
     // too few waves stream A at the full rate (us per call, taken back -> kept: half 42819 x 4980 with 19 blocks
@@ -302,11 +321,11 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
       int per_cu = (int)(kLdsBudget / ks_lds_bytes(pl.mt, c));
       const int by_regs = 4 * ks_waves_per_simd(pl.mt, c) / nw;
       if (by_regs < per_cu) per_cu = by_regs;
-      const SplitCost ks{(double)p.M * ((nr + 32 * c - 1) / (32 * c)) * groups, phi_us + c * (mfma_us + conv_us),
+      const SplitCost ks{(double)p.M * ((nc + 32 * c - 1) / (32 * c)) * groups, phi_us + c * (mfma_us + conv_us),
                          esz == 4 && c == 4 && pl.mt <= 2 ? 1.6 : 0.8, 256.0 * per_cu * nw,
-                         stream, split_bytes, 1.0 + 0.25 * pl.mt * c, nw, pl.total, pl.in_stat};
+                         stream, per_priced, 1.0 + 0.25 * pl.mt * c, nw, pl.total, pl.in_stat};
       double t = 0;
-      const int zc = ks.best(max_bytes, zmax, &t);
+      const int zc = ks.best(max_priced, zmax, &t);
       if ((n + 32 * c - 1) / (32 * c) <= 65535 && (cpl == 0 || t < 0.9 * t_ks)) { t_ks = t; cpl = c; z = zc; }
     }
     // 128 stacked rows under a few columns: what a wave does per stage is mostly making Phi, and its tile
@@ -323,7 +342,7 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
         if (by_regs < per_cu) per_cu = by_regs;
         const SplitCost hs{(double)p.M * ((n + 32 * cpl - 1) / (32 * cpl)) * 2,
                            0.12 + 0.07 * half_slots + cpl * (hmt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0 + conv_us), 0.8,
-                           256.0 * per_cu * nw, 2 * a_us, split_bytes, 1.0 + 0.25 * hmt * cpl, nw, pl.total, true};
+                           256.0 * per_cu * nw, 2 * a_us, per_priced, 1.0 + 0.25 * hmt * cpl, nw, pl.total, true};
         double t = 0;
         const int zc = hs.best(max_bytes, 65535 / 2, &t);
         if (t < 1.5 * t_ks) {
@@ -332,12 +351,11 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
         }
       }
     }
-    while (z > 1 && per_split * z > max_bytes) --z;
     if (cpl && (n <= 64 || t_ks < 0.8 * t_old)) {
       pl.ks = true;
       pl.cpl = cpl; pl.lds = ks_lds_bytes(pl.mt, cpl);
       pl.zsplit = z;
-      settle(false);
+      settle_within(false);
       pl.planes = pl.in_stat ? pl.zsplit * (int)p.kappa : pl.zsplit > 1 ? pl.zsplit : 0;
       pl.ok = true;
       return pl;
@@ -345,7 +363,7 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_
   }
 
   const bool pairs = pl.mt == 4 && dt != FS_F32 && pl.total % 2 == 0 && !pl.unal;
-  settle(pairs || shared_shape);
+  settle_within(pairs || shared_shape);
   if (pl.run == 1) pl.planes = pl.in_stat ? pl.zsplit * (int)p.kappa : pl.zsplit > 1 ? pl.zsplit : 0;
   // bf16 with one wave per SIMD (128-row tiles) has the registers for a ring twice as deep, and
   // with a single wave nothing else hides the latency of A; the two-stage ring needs an even
@@ -365,7 +383,23 @@ size_t plan_bytes(const SketchParams& p, const Plan& pl) {
 
 mm::Plan plan_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit,
                    size_t ws_bytes) {
-  return make_plan(p, A, lda, n, dt, have_orbit, ws_bytes);
+  // Calls of a few blocks and 512, 768 or 1024 columns that run input-stationary (all of these widths do, or
+  // none: their output tiles never cover the CUs) take the kernel and the row split of 256 columns, so
+  // that each column is summed in the order in which a call for its 256-column chunk sums it.  Where
+  // the planes of that split would, at 1024 columns, go beyond kSplitScratch or be added in another order than
+  // at 256, each width has the split that is best for it instead, and the last bits may differ; as
+  // they may with an attached workspace that is smaller than the planes.  The price of it is 7 % on
+  // average against each width's own split (60 random calls of up to 8 blocks; 0.62 to 1.54 times), so more blocks
+  // have none: held for up to 127 blocks it made bf16 281454 x 512 with 51 blocks take 122 us, not 68.
+  const bool as_chunks = p.M <= kChunkBlocks && n > 256 && n <= 1024 && n % 256 == 0;
+  Plan pl = make_plan(p, A, lda, n, as_chunks ? 256 : n, dt, have_orbit, ws_bytes);
+  if (as_chunks && pl.ok && pl.in_stat) {
+    const int planes = pl.z_priced * (int)p.kappa;
+    if ((double)planes * (double)p.k * 1024.0 * sizeof(float) > (double)kSplitScratch ||
+        reduce_in_parts(planes, p.k, 256) != reduce_in_parts(planes, p.k, 1024))
+      pl = make_plan(p, A, lda, n, n, dt, have_orbit, ws_bytes);
+  }
+  return pl;
 }
 
 Workspace mfma_workspace(const SketchParams& p, const mm::Plan& pl) {
@@ -395,7 +429,7 @@ size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt) {
   const int64_t ld = (n + 7) & ~(int64_t)7;
   size_t most = 0;
   for (int i = 0; i < 4; ++i) {
-    const Workspace w = mfma_workspace(p, make_plan(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0, SIZE_MAX));
+    const Workspace w = mfma_workspace(p, plan_mfma(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0, SIZE_MAX));
     if (w.want > most) most = w.want;
   }
   return most;

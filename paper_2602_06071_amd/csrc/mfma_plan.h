@@ -36,6 +36,7 @@ struct Plan {
   bool outs = false;                // OUT, 16-bit: the kernel of k_outs.hip (work-group-shared Phi tiles)
   bool ks = false;                  // the kernel of k_ksplit_kernel.h (waves of a work-group share the columns)
   int total = 0;                    // ... its stages of a block (IN) or of the kappa blocks (OUT)
+  int z_priced = 1;                 // the row split before the call's workspace bounded it
   int64_t ldw = 0;
   int planes = 0;
   size_t lds = 0;

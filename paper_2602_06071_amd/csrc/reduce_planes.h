@@ -81,6 +81,9 @@ __global__ __launch_bounds__(256) void reduce_planes_kernel(const float* __restr
   }
 }
 
+// Whether a call's planes are added in shares.  (65536 threads are one per lane of a SIMD on every SIMD.)
+inline bool reduce_in_parts(int planes, int64_t k, int64_t ldw) { return planes >= 16 && k * (ldw / 4) < 65536; }
+
 // Enqueues it for element type T.  run / blk2pos / Br / kappa: the orbit-run layout of the planes, or
 // run = 1.
 template <typename T>
@@ -89,8 +92,7 @@ hipError_t launch_reduce_planes(const float* ws, int planes, int64_t k, int64_t 
                                 hipStream_t st) {
   const int out_vec = ((uintptr_t)out % (4 * sizeof(T)) == 0 && ldo % 4 == 0) ? 1 : 0;
   const int64_t work = k * (ldw / 4);
-  // (65536 threads are one per lane of a SIMD on every SIMD)
-  const bool parts = planes >= 16 && work < 65536;
+  const bool parts = reduce_in_parts(planes, k, ldw);
   const int64_t opw = parts ? 32 : 256;
   const dim3 grid((unsigned)((work + opw - 1) / opw));
   if (parts)

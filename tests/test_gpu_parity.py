@@ -535,6 +535,24 @@ def test_chunked_equals_monolithic_bitwise(dtype, variant):
     assert torch.equal(whole, parts)
 
 
+@DTYPES
+@pytest.mark.parametrize("params", [
+    (16000, 128, 2000, 16, 4, 4),     # 64 stacked rows
+    (23997, 48, 3000, 6, 3, 5),       # Br not a power of two
+    (40001, 224, 5715, 32, 4, 4),     # seven blocks, odd length, 128 stacked rows
+    (60000, 24, 20000, 8, 1, 2),      # kappa = 1
+])
+def test_few_blocks_sum_a_column_as_in_its_256_column_chunk(params, dtype):
+    """Up to 8 blocks: the columns of a call of 512, 768 or 1024 have the bits of the call for their chunk."""
+    print("chunks of few blocks", params, dtype, flush=True)
+    A = torch.randn((params[0], 1024), generator=torch.Generator(device=DEV).manual_seed(8), device=DEV).to(dtype)
+    sk = B.Sketch(*params, seed=4)
+    parts = torch.cat([sk.apply(A[:, c:c + 256]) for c in range(0, 1024, 256)], dim=1)
+    check(parts[:, :32], O.apply(oracle_csc(params, 4), host64(A[:, :32])), dtype)
+    for n in (512, 768, 1024):
+        assert torch.equal(sk.apply(A[:, :n]), parts[:, :n]), n
+
+
 @pytest.mark.parametrize("variant", VARIANTS, ids=lambda v: VNAME[v])
 def test_linearity(variant):
     params = (8192, 512, 1024, 64, 4, 4)

@@ -109,3 +109,43 @@ for room, status, splits in ((matrix + (128 << 20), 0, True), (matrix + (1 << 20
         assert s.destroy() == 0
     assert rec.rec_live() == 0
 """)
+
+
+SPLIT = """
+def split(s, n, dtype, ld=None):              # the kernels of a call and their row split
+    rec.rec_clear()
+    assert s.apply(n, dtype, ld) == 0
+    run = [l for l in launches() if "orbit" not in l.kernel]
+    return [l.kernel for l in run], run[0].z
+"""
+
+
+def test_a_multiple_of_256_columns_is_planned_like_its_neighbours(recorded):
+    recorded(SPLIT + """
+for params, n, dtype in [((281454, 1632, 5598, 32, 3, 2), 512, BF16), ((388370, 2464, 5057, 32, 3, 2), 768, BF16),
+                         ((37820, 792, 384, 8, 2, 2), 512, BF16), ((102472, 2048, 3264, 64, 2, 2), 512, F16),
+                         ((30686, 192, 1313, 8, 8, 2), 768, F32)]:
+    assert split(Sketch(*params), n, dtype) == split(Sketch(*params), n - 4, dtype), params
+""")
+
+
+def test_few_blocks_split_a_call_as_its_256_column_chunks(recorded):
+    """Up to 8 blocks: same kernels and row split at 256, 512, 768 and 1024 columns, wherever the planes fit
+    32 MiB at 1024 columns and the reduction adds them in the same way at all widths."""
+    recorded(SPLIT + """
+import random
+rng, held = random.Random(1), 0
+for i in range(600):
+    M, Br = rng.randrange(1, 9), rng.choice([1, 4, 6, 8, 16, 32, 64])
+    kappa, Bc = rng.randrange(1, M + 1), rng.choice([rng.randrange(1, 29000), 64 * rng.randrange(1, 140)])
+    s = Sketch(Bc * M - rng.randrange(Bc), Br * M, Bc, Br, kappa, 1)
+    dtype, ld = rng.randrange(3), 1024 + rng.choice([0, 0, 1, 2, 4])
+    chunk = split(s, 256, dtype, ld)
+    planes = chunk[1] * kappa
+    if s.info().last_mode == 2 and planes * s.k * 4096 <= 32 << 20 and (planes < 16 or s.k < 256 or s.k >= 1024):
+        held += 1
+        for n in (512, 768, 1024):
+            assert split(s, n, dtype, ld) == chunk, (s.d, s.k, Bc, Br, kappa, dtype, ld, n)
+    s.destroy()
+assert held > 300
+""")
