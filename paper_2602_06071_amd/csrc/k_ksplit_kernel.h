@@ -50,8 +50,10 @@ void ksplit_kernel(MfmaArgs a) {
   constexpr int TILE = RWV * PHI_LD;
   constexpr int TILES = ks_tiles(CPL);  // Phi tiles per wave
   constexpr int NR = KsRow<T, CPL, UNAL>::NR;
-  // ring depth in k-steps
-  constexpr int PFD = (NR >= 4 && MT <= 2) || MT * CPL == 8 ? 2 : 4;
+  // Ring depth in k-steps.  UNAL holds three registers per row: four k-steps of them spilled 72 to 89 registers
+  // with MT = 1 and 27 to 33 with MT = 4 (us per call, 4 -> 2 k-steps: half 8712 x 953, kappa = 3, 52.6 -> 24.7;
+  // bf16 213206 x 73, kappa = 2, 70.1 -> 26.7; 55 random calls: 1.5 times as fast with MT = 1, 1.04 with MT = 4, none slower).
+  constexpr int PFD = UNAL || (NR >= 4 && MT <= 2) || MT * CPL == 8 ? 2 : 4;
   static_assert(!UNAL || (sizeof(T) == 2 && CPL == 4), "");
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];

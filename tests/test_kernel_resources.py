@@ -1,0 +1,36 @@
+"""Register use of compiled kernels, from the metadata of the objects the build leaves: no GPU."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+BUILD = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2602_06071_amd", "_build")
+LLVM = "/opt/rocm/llvm/bin"
+
+
+def spills(obj, tmp_path):
+    """{mangled kernel name: spilled vector registers} of a compiled translation unit."""
+    tools = [os.path.join(LLVM, t) for t in ("llvm-objcopy", "clang-offload-bundler", "llvm-readelf")]
+    src = os.path.join(BUILD, obj)
+    if not os.path.exists(src) or not all(shutil.which(t) for t in tools):
+        pytest.skip("no build or no tools")
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    subprocess.run([tools[0], f"--dump-section=.hip_fatbin={fat}", src, str(tmp_path / "copy.o")], check=True)
+    subprocess.run([tools[1], "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={fat}",
+                    f"--output={code}"], check=True)
+    notes = subprocess.run([tools[2], "--notes", code], check=True, capture_output=True, text=True).stdout
+    out = {}
+    for kernel in re.split(r"\n  - \.agpr_count", notes)[1:]:
+        name = re.search(r"\.name:\s+(\S+)", kernel)
+        out[name.group(1)] = int(re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel).group(1))
+    return out
+
+
+@pytest.mark.parametrize("obj", ["k_ksplit_f16.o", "k_ksplit_bf16.o"])
+def test_ksplit_kernels_of_unaligned_rows_spill_nothing_at_tiles_of_32_and_128_rows(obj, tmp_path):
+    """(64 rows: two waves per SIMD leave too few registers at any ring depth.)"""
+    unaligned = {k: v for k, v in spills(obj, tmp_path).items()
+                 if re.search(r"ksplit_kernelI\w+Li[14]ELi4ELb[01]ELb1E", k)}
+    assert len(unaligned) == 4 and set(unaligned.values()) == {0}, unaligned
