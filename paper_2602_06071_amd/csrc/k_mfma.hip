@@ -40,6 +40,7 @@
 //
 // Inputs must be finite: a dense product multiplies every element by the zeros of
 // Phi as well, so an Inf/NaN in A spreads to all rows of the blocks that read it.
+#include <math.h>
 #include <stdio.h>
 
 #include "k_mfma_kernel.h"
@@ -83,7 +84,8 @@ size_t lds_bytes(int mt, int nrg, int ncg, int run, size_t merge) {
 // Modelled time (us) of a launch in which `units` work-groups of `nw` waves share `total` stages each
 // in `z` row splits: the longest of (1) what the waves issue, spread over the 1024 SIMDs, (2) rounds of
 // resident waves, where each stage of a wave costs most of a memory latency on top of its
-// instructions (two where the ring holds half a stage), (3) the stream of A; then the merge of the waves' shares, the partial planes (written
+// instructions (two where the ring holds half a stage), (3) the stream of A; then the merge of the waves' shares, once and
+// again with the start of a work-group for every further round of work-groups, the partial planes (written
 // at 3.4, read back at 6 TB/s: rates measured on this kernel pair; about half that price while they stay in
 // the Infinity Cache) and, where only the split makes
 // one necessary, the launch of the reduction.
@@ -99,6 +101,11 @@ struct SplitCost {
     if (work > t) t = work;
     if (stream_us > t) t = stream_us;
     t += merge_us;
+    // (Without the price of further rounds, of work-groups with one or two stages per wave above all, the K-split
+    // kernel took calls it is slower on: 161 random calls that it moves are 1.19 times as fast with it, 125 of
+    // them by over 5 %, and none slower than mfma_kernel was before.  fp32 28288 x 448 with 221 blocks 48.8 -> 33.3 us,
+    // half 135660 x 394 with 193 blocks 170 -> 97; the other way fp32 40576 x 128 with 317 blocks 20.6 -> 27.0.)
+    if (nw > 1 && waves > slots) t += (ceil(waves / slots) - 1) * (merge_us + 2.0);
     if (has_reduce || z > 1) t += plane_bytes * z * (1 / 3.4e6 + 1 / 6e6) * (plane_bytes * z < 40e6 ? 0.5 : 1.0);
     if (!has_reduce && z > 1) t += 4.0;
     return t;

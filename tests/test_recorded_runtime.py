@@ -149,3 +149,13 @@ for i in range(600):
     s.destroy()
 assert held > 300
 """)
+
+
+@pytest.mark.parametrize("params,n,dtype", [
+    ((28288, 14144, 128, 64, 3, 2), 448, "F32"),      # 884 work-groups, one per CU, of one stage per wave
+    ((2760, 960, 184, 64, 2, 2), 6592, "F32"),
+    ((4925, 308, 64, 4, 2, 2), 256, "F32"),
+    ((135660, 24704, 704, 128, 4, 2), 394, "F16"),
+])
+def test_many_short_rounds_of_work_groups_stay_with_one_wave_per_column_tile(recorded, params, n, dtype):
+    assert "mfma_kernel" in recorded(f"s = Sketch(*{params}); assert s.apply({n}, {dtype}) == 0; print(s.kernel())")
