@@ -343,15 +343,15 @@ def test_shared_phi_kernel_one_hot_columns_are_exact():
 
 # ------------------- waves of a work-group that split the rows ------------
 KSPLIT = [
-    # params (d,k,Bc,Br,kappa,s), n, lda pad, first column of the view: few columns or few blocks.  Tiles of
-    # 32, 64 and 128 columns, each stacked height, uneven shares (63 stages), rows that start inside a dword.
+    # params (d,k,Bc,Br,kappa,s), n, lda pad, first column of the view: few columns or few blocks.  Mostly tiles of
+    # 32 columns (128-column ones: KSPLIT_WIDE), each stacked height, uneven shares (63 stages), odd strides.
     ((15990, 128, 4000, 32, 2, 4), 1, 0, 0),       # 64 stacked rows, one packed column, a partly filled last block
     ((15990, 128, 4000, 32, 2, 4), 32, 1, 1),      # one full 32-column tile, odd stride, odd first element
-    ((15990, 128, 4000, 32, 2, 4), 33, 0, 0),      # 64-column tile
+    ((15990, 128, 4000, 32, 2, 4), 33, 0, 0),      # a column more than the tile
     ((15990, 128, 4000, 32, 2, 4), 64, 3, 0),
-    ((15990, 128, 4000, 32, 2, 4), 65, 0, 0),      # 128-column tile, odd packed rows: three dwords per four columns
+    ((15990, 128, 4000, 32, 2, 4), 65, 0, 0),      # odd packed rows
     ((15990, 128, 4000, 32, 2, 4), 127, 0, 1),
-    ((15991, 128, 4001, 32, 2, 4), 129, 0, 1),     # two column tiles; odd Bc: blocks start in either half of a dword
+    ((15991, 128, 4001, 32, 2, 4), 129, 0, 1),     # odd Bc: blocks start in either half of a dword
     ((15990, 128, 4000, 32, 2, 4), 130, 2, 0),     # dword-aligned, not aligned to four columns
     ((16000, 64, 4000, 16, 2, 4), 100, 0, 0),      # 32 stacked rows
     ((16000, 256, 2000, 32, 4, 4), 30, 0, 0),      # 128 stacked rows
@@ -368,10 +368,28 @@ KSPLIT = [
 ]
 
 
-@DTYPES
-@pytest.mark.parametrize("case", KSPLIT, ids=lambda c: f"{c[0]}-n{c[1]}")
-def test_ksplit_kernel_matches_oracle(case, dtype):
-    params, n, pa, first = case
+# The same with tiles of 128 columns: each stacked height, input- and output-stationary, with and without a row split,
+# rows that start inside a dword ("unal": odd strides, blocks of odd length, partly filled last blocks) and rows
+# that are dword-aligned only.  Last: the kernel expected for 16-bit types and for fp32 ("" = not of interest).
+KSPLIT_WIDE = [
+    ((14467, 112, 1038, 8, 4, 4), 392, 2, 2, "1,4,in,-", ""),
+    ((13944, 208, 543, 8, 4, 4), 309, 4, 0, "1,4,in,unal", ""),
+    ((23971, 120, 1617, 8, 4, 4), 415, 0, 1, "", "1,4,in,-"),
+    ((4348, 384, 393, 32, 8, 4), 353, 1, 0, "1,4,out,-", "1,4,out,-"),
+    ((3937, 160, 897, 32, 5, 4), 349, 4, 0, "1,4,out,unal", ""),
+    ((14223, 104, 1118, 8, 8, 4), 404, 4, 2, "2,4,in,-", ""),
+    ((12207, 192, 523, 8, 8, 4), 377, 2, 1, "2,4,in,unal", "2,2,in,-"),
+    ((6766, 1248, 177, 32, 2, 4), 417, 0, 1, "2,4,in,unal", "2,4,in,-"),       # no row split
+    ((5849, 512, 789, 64, 8, 4), 418, 2, 2, "2,4,out,-", "2,4,out,-"),
+    ((8911, 384, 1553, 64, 6, 4), 409, 0, 0, "2,4,out,unal", ""),
+    ((8602, 448, 1417, 64, 7, 4), 335, 2, 2, "2,4,out,unal", "2,4,out,-"),
+    ((8079, 1248, 209, 32, 4, 4), 405, 0, 1, "4,4,in,unal", "4,4,in,-"),
+    ((4331, 4864, 115, 128, 3, 4), 394, 1, 0, "4,4,out,unal", ""),
+    ((5379, 4736, 147, 128, 1, 4), 386, 0, 1, "", "4,4,out,-"),                # kappa = 1, no planes
+]
+
+
+def check_ksplit(params, n, pa, first, dtype, kernel):
     print("ksplit", params, n, dtype, flush=True)
     d, k = params[0], params[1]
     g = torch.Generator(device=DEV).manual_seed(n + d)
@@ -385,8 +403,7 @@ def test_ksplit_kernel_matches_oracle(case, dtype):
     out = sk.apply(A, obuf[:, :n])
     torch.cuda.synchronize()
     i = sk.info()
-    if n <= 64:
-        assert i.last_kernel.decode().startswith("ksplit_kernel"), i.last_kernel
+    assert i.last_kernel.decode().startswith(kernel), i.last_kernel
     assert (plan["variant"], plan["mode"]) == (i.last_variant, i.last_mode)
     ref = O.apply(oracle_csc(params, 9), host64(A))
     check(out, ref, dtype, "K-split kernel")
@@ -394,6 +411,20 @@ def test_ksplit_kernel_matches_oracle(case, dtype):
     assert (diff <= ETOL[dtype] * (np.abs(ref) + np.sqrt((ref ** 2).mean()))).all()
     assert torch.isnan(obuf[:, n:].float()).all(), "wrote outside the n output columns"
     assert torch.equal(sk.apply(A), out)          # fixed summation order
+
+
+@DTYPES
+@pytest.mark.parametrize("case", KSPLIT, ids=lambda c: f"{c[0]}-n{c[1]}")
+def test_ksplit_kernel_matches_oracle(case, dtype):
+    check_ksplit(*case, dtype, "ksplit_kernel")
+
+
+@DTYPES
+@pytest.mark.parametrize("case", KSPLIT_WIDE, ids=lambda c: f"{c[0]}-n{c[1]}")
+def test_ksplit_kernel_of_128_column_tiles_matches_oracle(case, dtype):
+    want = case[5] if dtype == torch.float32 else case[4]
+    name = {torch.float32: "f32", torch.bfloat16: "bf16", torch.float16: "f16"}[dtype]
+    check_ksplit(*case[:4], dtype, f"ksplit_kernel<{name},{want}>" if want else "")
 
 
 def test_smaller_workspace_takes_a_coarser_split():
