@@ -559,10 +559,10 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restric
 // without a split there would be no reduction, its launch.  Measured (fp32, 24 examples of 1000003
 // entries, kappa*Br = 64, M = 256): 1 split 94 us, 8 splits 36 us.
 int pick_rows_split(double units, int total, double stage_us, double slots, double stream_us,
-                    double set_bytes, bool has_reduce, double max_bytes) {
+                    double set_bytes, bool has_reduce, double max_bytes, int zmax) {
   int best_z = 1;
   double best = 0;
-  for (int zc = 1, st; zc <= total && zc <= 256; zc = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
+  for (int zc = 1, st; zc <= total && zc <= zmax; zc = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
     st = (total + zc - 1) / zc;  // (the next split is the first one with fewer stages per work-group)
     if (zc > 1 && set_bytes * zc > max_bytes) break;
     const double waves = units * zc;
@@ -664,10 +664,9 @@ RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64
   const double stream_us = pl.out_stat ? g_us * (1.0 + 0.3 * (p.kappa - 1)) : g_us * pl.groups;
   double max_bytes = (double)(pl.ws_floor > kSplitScratch ? pl.ws_floor : kSplitScratch);
   if ((double)limit < max_bytes) max_bytes = (double)limit;
-  const int zmax = 65535 / pl.groups;
+  const int zmax = 65535 / pl.groups < 256 ? 65535 / pl.groups : 256;  // grid.z numbers (group, split)
   pl.zsplit = pick_rows_split((double)p.M * ex_tiles * pl.nsub * pl.groups, pl.total, phi_us + pl.et * tile_us, slots,
-                              stream_us, set_bytes, !pl.out_stat, max_bytes);
-  if (pl.zsplit > zmax) pl.zsplit = 1;
+                              stream_us, set_bytes, !pl.out_stat, max_bytes, zmax);
   pl.stages = (pl.total + pl.zsplit - 1) / pl.zsplit;
   if (!pl.out_stat || pl.zsplit > 1) pl.ws = (size_t)set_bytes * pl.zsplit;
   pl.ok = true;

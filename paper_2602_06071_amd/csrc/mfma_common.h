@@ -32,16 +32,6 @@ __device__ __forceinline__ uint32_t perm(uint32_t hi_src, uint32_t lo_src, uint3
   return __builtin_amdgcn_perm(hi_src, lo_src, sel);
 }
 
-// 4 consecutive columns of one row, element by element; columns >= n read as 0.
-template <typename T, int CPL = 4>
-__device__ __forceinline__ typename LdN<T, CPL>::V load4_guarded(const T* p4, int col0, int n) {
-  using V = typename LdN<T, CPL>::V;
-  T e[CPL];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) e[c] = (col0 + c < n) ? p4[c] : (T)0;
-  return *reinterpret_cast<V*>(e);
-}
-
 // MFMA B operands of the four column residues from 8 rows x 4 columns (bf16).
 __device__ __forceinline__ void make_ops(const uint2 (&r)[8], uint4 (&op)[4]) {
   uint32_t* o0 = reinterpret_cast<uint32_t*>(&op[0]);
