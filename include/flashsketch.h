@@ -33,11 +33,10 @@
  *              padding, or the start of the next row; behind the last row only
  *              inside the aligned 4-element group, or without such alignment the
  *              dword, of its last valid element) and up to one before the first
- *              element, inside its dword, are loaded and discarded; their values, NaN
- *              included, never reach the result.  Calls of up to 64 columns load
- *              element by element and read nothing beyond column n-1.  Stores to
- *              out are vectors when out and ldo are
- *              aligned to 4 elements, else element by element.
+ *              element, inside its dword, may be loaded and discarded; their values, NaN
+ *              included, never reach the result.  (Some calls of few columns load element by
+ *              element instead; which ones is not part of this interface.)  Stores to out are
+ *              vectors when out and ldo are aligned to 4 elements, else element by element.
  *   Streams    `stream` is a hipStream_t passed as void* (NULL = default
  *              stream).  Calls enqueue work and return; they never synchronise.
  *              A handle must not be used from two streams at the same time
@@ -239,7 +238,7 @@ typedef enum {
   FS_PLAN_SLOT_GROUPS = 4,   /* input read once per group of wiring slots: more than 128 stacked
                                 rows of small blocks, or more than 64 under at most 64 columns */
   FS_PLAN_SPLIT = 8,         /* the rows of a work-group's input are split over grid.z, or over
-                                all its waves                                                  */
+                                its waves with at least as many stages as waves                */
   FS_PLAN_STACKED = 16       /* output-stationary with several output blocks, consecutive on
                                 the orbit of the wiring, per wave (mode 1, no workspace)       */
 } fs_plan_flags;

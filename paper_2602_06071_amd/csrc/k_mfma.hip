@@ -293,15 +293,17 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
   pl.outs = shared_shape && pl.vec4 && outs_supported(p, A, lda, n, dt, pl.zsplit);
 
   // The K-split kernel: few columns, or too few (block, column tile) pairs (k_ksplit_kernel.h).  Up to 64
-  // columns always; beyond, both kernels are priced by the model above, and the K-split one has to
+  // columns always (but for blocks above 128 rows, and for the shared-Phi kernel's shapes); beyond, both kernels
+  // are priced by the model above, and the K-split one has to
   // promise a fifth less.  Measured (us per call, mfma_kernel with its evenly dividing splits -> this plan):
-  // fp32 262144 x 1, k = 4096, kappa = 4: 40 -> 17; fp32 1923840 x 48, kappa = 8: 632 -> 118; half
+  // fp32 262144 x 1, k = 4096, kappa = 4: 40 -> 16 (with the two slot groups below); fp32 1923840 x 48, kappa = 8: 632 -> 118; half
   // 1575567 x 7 with 98473-row blocks: 3166 -> 107; fp32 262144 x 256 ("tall"): 86 -> 75; half 1728
   // columns of eight 3520-row blocks: 104 -> 32; in 64-column tiles fp32 4096 x 512 ("tiny"): 14 -> 11.6, fp32
   // 17856 x 168: 38 -> 14, half 11253 x 729: 31 -> 9.6.  Where the 128-column waves fill the chip they stay.
-  // (Decided without looking at the alignment when n is a multiple of 4, so that an unaligned view sums in the
-  // same order as a packed copy of it; rows of another length have no aligned packed copy, and the calls that would be
-  // the shared-Phi kernel's if they were aligned are priced too.)
+  // (The choice does not look at the alignment when n is a multiple of 4: an unaligned view of a matrix stays on the
+  // kernel that its packed copy would take, and sums in its order where that is one of these two without orbit
+  // runs.  Rows of another length have no aligned packed copy, and the calls that would be the shared-Phi kernel's
+  // if they were aligned are priced too.)
   if (!(shared_shape && (pl.vec4 || n % 4 == 0)) && nsub == 1 && pl.run == 1) {
     const int kap = pl.in_stat ? (group_slots < (int)p.kappa ? group_slots : (int)p.kappa) : 1;
     const double phi_us = 0.12 + 0.07 * kap;
@@ -338,8 +340,9 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
     // 128 stacked rows under a few columns: what a wave does per stage is mostly making Phi, and its tile
     // leaves room for one work-group per CU.  Two groups of half the slots read A twice, but are twice as
     // many work-groups of half the work: taken unless the model, which does not see the idle slots of a
-    // lone work-group, prices them far higher (fp32 262144 columns of 1 and 40, kappa = 4, 32-row blocks:
-    // 18.9 -> 17.6 and 26.1 -> 24.0 us; bf16 65536 x 64: 14.4 -> 13.6).
+    // lone work-group, prices them far higher (fp32 262144 x 1 and x 40, k = 4096, kappa = 4,
+    // 32-row blocks: 18.4 -> 17.3 and 25.7 -> 23.0 us in a loop over one input; bf16 65536 x 64, k = 4096: 13.7 -> 12.8;
+    // 46 calls, most of up to 64 columns: 0.87 times the time on average, the worst 1.35).
     if (n <= 64 && pl.in_stat && pl.mt == 4 && groups == 1 && p.kappa >= 2) {
       const int half_slots = ((int)p.kappa + 1) / 2, hmt = half_slots * (int)brp <= 32 ? 1 : 2;
       if (half_slots * (int)brp <= 64) {
@@ -421,7 +424,8 @@ Workspace mfma_workspace(const SketchParams& p, const mm::Plan& pl) {
 int mfma_mode(const mm::Plan& pl) { return !pl.in_stat ? 1 : pl.run > 1 ? 3 : 2; }
 
 int mfma_flags(const mm::Plan& pl) {
-  const bool split = pl.zsplit > 1 || (pl.ks && pl.stages >= ks_waves(pl.mt, pl.cpl));  // every wave has a share
+  // (with fewer stages than waves, what the K-split kernel's waves share is hardly a split)
+  const bool split = pl.zsplit > 1 || (pl.ks && pl.stages >= ks_waves(pl.mt, pl.cpl));
   return (pl.vec4 ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
          (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (split ? FS_PLAN_SPLIT : 0) |
          (pl.stacked ? FS_PLAN_STACKED : 0);
