@@ -159,3 +159,13 @@ assert held > 300
 ])
 def test_many_short_rounds_of_work_groups_stay_with_one_wave_per_column_tile(recorded, params, n, dtype):
     assert "mfma_kernel" in recorded(f"s = Sketch(*{params}); assert s.apply({n}, {dtype}) == 0; print(s.kernel())")
+
+
+@pytest.mark.parametrize("params,n,loads", [
+    ((89856, 2808, 128, 4, 1, 2), 213, 4),       # one addend
+    ((10864, 484, 90, 4, 2, 2), 1024, 4),        # two
+    ((65536, 8192, 64, 8, 8, 2), 256, 8),        # eight
+])
+def test_the_rows_reduction_loads_no_more_than_it_needs_together(recorded, params, n, loads):
+    out = recorded(f"s = Sketch(*{params}); assert s.apply_rows({n}, BF16) == 0; print(launches()[-1].kernel)")
+    assert f"reduce_rows_kernelItLi4ELi1ELi{loads}E" in out, out
