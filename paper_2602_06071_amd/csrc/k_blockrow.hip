@@ -1,13 +1,14 @@
 // FlashBlockRow (paper Appendix D, Alg. 2): the gather-only block-row sampling sketch.
 // Output row (g, r) adds s signed rows of A from each of the kappa input blocks its block
-// row samples and scales by sqrt(d/k)/sqrt(kappa*s).  No accumulation conflicts at all:
-// one wave owns one output row of a column tile, every index and sign is wave-uniform
-// (scalar ALU), every load is a contiguous row segment.  It reads k*kappa*s rows of A,
-// not all d: the paper's "fast but fragile" point (some input coordinates are never read).
+// row samples and scales by sqrt(d/k)/sqrt(kappa*s).  No accumulation conflicts at all.  It reads
+// k*kappa*s rows of A, not all d: the paper's "fast but fragile" point (some input coordinates are
+// never read).
 //
 // Where the paper is silent: the kappa blocks of block row g are the wiring neighbours
 // f^l(g); update t of row r in block (g, h) uses w1 = mix32(BK(g,h) ^ C1 ^ (r*32 + t)),
 // index w1 mod Bc, sign = low bit of mix32(w1 ^ C2).  Rows beyond d read as zero.
+#include <type_traits>
+
 #include "convert.h"
 #include "handle.h"
 #include "spec.h"
@@ -23,69 +24,134 @@ __device__ __forceinline__ RowPick pick(uint32_t bk, uint32_t r, uint32_t t, uin
   return {w1 % Bc, (mix32(w1 ^ kC2) & 1u) != 0u};
 }
 
-// VEC: 4 columns per lane through one vector load (aligned A, lda % 4 == 0); else 1 column.
-template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void blockrow_kernel(SketchParams p, const T* __restrict__ A,
-                                                       int64_t lda, int n, T* __restrict__ out,
-                                                       int64_t ldo, int out_vec) {
-  constexpr int CPL = VEC ? 4 : 1;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t row = (int64_t)blockIdx.x * 4 + wave;
-  if (row >= p.k) return;
-  const int lane = threadIdx.x & 63;
-  const int col0 = ((int)blockIdx.y * 64 + lane) * CPL;
-  const uint32_t g = (uint32_t)(row / p.Br), r = (uint32_t)(row % p.Br);
-  const bool full = col0 + CPL <= n;
+// p mod M for p < 2^49 and M <= 2^24 (exact: every value is a whole number below 2^53).
+__device__ __forceinline__ uint32_t mod_wire(double v, double M, double inv_M) {
+  const double q = trunc(v * inv_M);
+  double r = fma(-q, M, v);
+  if (r < 0.0) r += M;
+  if (r >= M) r -= M;
+  return (uint32_t)r;
+}
 
-  float acc[CPL];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
+// Four columns of one row at any element alignment (global memory is read at any address), and back.
+template <typename T> struct Quad {
+  typedef uint32_t V __attribute__((ext_vector_type(2), aligned(2)));
+  static __device__ __forceinline__ void get(V w, float (&v)[4]) { unpack4<T>(make_uint2(w[0], w[1]), v); }
+  static __device__ __forceinline__ V put(const float (&v)[4]) { const uint2 w = pack4<T>(v); return V{w.x, w.y}; }
+};
+template <> struct Quad<float> {
+  typedef float V __attribute__((ext_vector_type(4), aligned(4)));
+  static __device__ __forceinline__ void get(V w, float (&v)[4]) { v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3]; }
+  static __device__ __forceinline__ V put(const float (&v)[4]) { return V{v[0], v[1], v[2], v[3]}; }
+};
+template <typename T> struct One {
+  typedef T V;
+  static __device__ __forceinline__ void get(T w, float (&v)[1]) { v[0] = Elt<T>::load(&w); }
+};
 
-  uint32_t h = g;
-  for (uint32_t l = 0; l < p.kappa; ++l) {
-    h = wire_next(h, p.a, p.b, p.M);
-    const uint32_t bk = block_key(p.key1, g, h, p.M);
-    for (uint32_t t = 0; t < p.s; ++t) {
-      const RowPick pk = pick(bk, r, t, p.Bc);
-      const int64_t src = (int64_t)h * p.Bc + pk.idx;
-      if (src >= p.d) continue;  // zero padding of a partly filled last block
-      const T* sp = A + src * lda + col0;
-      float v[CPL];
-      if constexpr (VEC) {
-        if (full) {
-          if constexpr (sizeof(T) == 2) {
-            unpack4<T>(*reinterpret_cast<const uint2*>(sp), v);
-          } else {
-            const float4 w = *reinterpret_cast<const float4*>(sp);
-            v[0] = w.x; v[1] = w.y; v[2] = w.z; v[3] = w.w;
-          }
-        } else {
+constexpr int kPicks = 2048;    // picks of a work-group in LDS at a time
+constexpr int kRowPicks = 512;  // ... of one output row
+
+// A thread owns V columns of one output row; a work-group `rows_wg` rows of a column tile of up to 256
+// such groups, so that narrow inputs fill the lanes too.  The picks of the rows are hashed by all threads
+// side by side into LDS, as byte offsets (bit 0: the sign, elements being at least two bytes; bit 63: a row
+// of the zero padding); then every thread walks its row's picks, UN loads at a time, in order.
+// What bounds it is the latency of dependent loads and, in large calls, the stream of picked rows.
+// (Hashing each pick on the scalar unit in front of its load, one wave per row, made a call wait for memory
+// once per pick and left the lanes beyond n/4 idle.  us per call, then -> now: fp32 65536 x 1024, k = 4096, 8 picks
+// 30.0 -> 24.5, 5.0 TB/s of unrepeated rows; bf16 951847 x 597, k = 4096, 16 picks 91 -> 19.5; bf16 167730 x 9978,
+// k = 1024, 32 picks 524 -> 127; 24 random calls 1.29 times as fast, those above the host's 8 us 2.2 times.)
+template <typename T, int V, int UN>
+__global__ __launch_bounds__(256) void blockrow_kernel(SketchParams p, const T* __restrict__ A, int64_t lda, int n,
+                                                       T* __restrict__ out, int64_t ldo, int rows_wg, int groups,
+                                                       int picks) {
+  using Ld = std::conditional_t<V == 4, Quad<T>, One<T>>;
+  using Vec = typename Ld::V;
+  __shared__ int64_t s_off[kPicks];
+  __shared__ uint32_t s_a[kRowPicks + 1], s_b[kRowPicks + 1];
+  const uint32_t tid = threadIdx.x;
+  const int64_t wg_row = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * rows_wg;
+  if (wg_row >= p.k) return;
+  const uint32_t row0 = (uint32_t)wg_row;
+  const uint32_t rows = (uint32_t)min((int64_t)rows_wg, p.k - wg_row);
+  const uint32_t grp0 = blockIdx.y * 256u, width = min(256u, (uint32_t)groups - grp0);
+  const uint32_t my_row = tid / width;
+  const bool active = my_row < rows;
+  const int col0 = (int)(grp0 + tid % width) * V;
+  // The last group of a row starts V columns before its end: it repeats columns of the group before it
+  // rather than reading past the row, and does not store them.
+  const int first = min(col0, n - V);
+  const char* base = reinterpret_cast<const char*>(A + first);
+
+  float acc[V];
 #pragma unroll
-          for (int c = 0; c < CPL; ++c) v[c] = col0 + c < n ? Elt<T>::load(sp + c) : 0.f;
-        }
-      } else {
-        v[0] = col0 < n ? Elt<T>::load(sp) : 0.f;
+  for (int c = 0; c < V; ++c) acc[c] = 0.f;
+
+  const double Md = (double)p.M, inv_M = 1.0 / Md;
+  const uint32_t nnz = p.kappa * p.s;
+  uint32_t ca = 1u % p.M, cb = 0;  // f^l0(x) = ca x + cb mod M
+  for (uint32_t t0 = 0; t0 < nnz; t0 += (uint32_t)picks) {
+    const uint32_t cnt = min((uint32_t)picks, nnz - t0);
+    const uint32_t l0 = t0 / p.s, slots = (t0 + cnt - 1) / p.s - l0 + 1;
+    if (t0) __syncthreads();  // the picks before have been read
+    for (uint32_t j = tid; j < slots; j += 256) {
+      uint32_t xa = ca, xb = cb;
+      for (uint32_t i = 0; i <= j; ++i) {
+        xa = mod_wire((double)p.a * (double)xa, Md, inv_M);
+        xb = mod_wire((double)p.a * (double)xb + (double)p.b, Md, inv_M);
       }
+      s_a[j] = xa;
+      s_b[j] = xb;
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < rows * cnt; i += 256) {
+      const uint32_t rl = i / cnt, t = t0 + (i - rl * cnt), l = t / p.s;
+      const uint32_t row = row0 + rl, g = row / p.Br;
+      const uint32_t h = mod_wire((double)s_a[l - l0] * (double)g + (double)s_b[l - l0], Md, inv_M);
+      const RowPick pk = pick(block_key(p.key1, g, h, p.M), row - g * p.Br, t - l * p.s, p.Bc);
+      const int64_t src = (int64_t)h * p.Bc + pk.idx;
+      s_off[rl * cnt + (t - t0)] = src < p.d ? (src * lda * (int64_t)sizeof(T)) | (int64_t)pk.neg : INT64_MIN;
+    }
+    __syncthreads();
+    if (active) {
+      const int64_t* off = s_off + my_row * cnt;
+      for (uint32_t t = 0; t < cnt; t += UN) {
+        Vec w[UN];
+        int64_t o[UN];
 #pragma unroll
-      for (int c = 0; c < CPL; ++c) acc[c] += pk.neg ? -v[c] : v[c];
+        for (int j = 0; j < UN; ++j) o[j] = off[min(t + j, cnt - 1)];  // (past the last pick: it again, not added)
+#pragma unroll
+        for (int j = 0; j < UN; ++j)
+          w[j] = *reinterpret_cast<const Vec*>(base + (o[j] & (INT64_MAX - 1)));  // (padding: row 0, not added)
+#pragma unroll
+        for (int j = 0; j < UN; ++j) {
+          if (t + j >= cnt || o[j] < 0) continue;
+          float v[V];
+          Ld::get(w[j], v);
+#pragma unroll
+          for (int c = 0; c < V; ++c) acc[c] += (o[j] & 1) ? -v[c] : v[c];
+        }
+      }
+    }
+    if (t0 + cnt < nnz) {
+      const uint32_t next = (t0 + cnt) / p.s - l0;
+      if (next) { ca = s_a[next - 1]; cb = s_b[next - 1]; }
     }
   }
+  if (!active) return;
 
-  T* dst = out + row * ldo + col0;
-  if (VEC && full && out_vec) {
-    if constexpr (sizeof(T) == 2) {
-      const float sc[4] = {acc[0] * p.scale, acc[CPL > 1 ? 1 : 0] * p.scale, acc[CPL > 2 ? 2 : 0] * p.scale,
-                           acc[CPL > 3 ? 3 : 0] * p.scale};
-      *reinterpret_cast<uint2*>(dst) = pack4<T>(sc);
-    } else {
-      *reinterpret_cast<float4*>(dst) = make_float4(acc[0] * p.scale, acc[CPL > 1 ? 1 : 0] * p.scale,
-                                                    acc[CPL > 2 ? 2 : 0] * p.scale, acc[CPL > 3 ? 3 : 0] * p.scale);
-    }
-  } else {
+  T* dst = out + (int64_t)(row0 + my_row) * ldo + first;
 #pragma unroll
-    for (int c = 0; c < CPL; ++c)
-      if (col0 + c < n) Elt<T>::store(dst + c, acc[c] * p.scale);
+  for (int c = 0; c < V; ++c) acc[c] *= p.scale;
+  if constexpr (V == 4) {
+    if (first == col0) {
+      *reinterpret_cast<Vec*>(dst) = Ld::put(acc);
+      return;
+    }
   }
+#pragma unroll
+  for (int c = 0; c < V; ++c)
+    if (first + c >= col0) Elt<T>::store(dst + c, acc[c]);
 }
 
 // cols[row*kappa*s + l*s + t] = global column index (may lie in the padding), signs = +-1
@@ -110,19 +176,31 @@ __global__ __launch_bounds__(256) void blockrow_export_kernel(SketchParams p, in
 
 hipError_t launch_blockrow(const SketchParams& p, const void* A, int64_t lda, int64_t n, void* out,
                            int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev) {
-  const size_t esz = dt == FS_F32 ? 4 : 2;
-  const bool vec = (uintptr_t)A % (4 * esz) == 0 && lda % 4 == 0;
-  const int out_vec = ((uintptr_t)out % (4 * esz) == 0 && ldo % 4 == 0) ? 1 : 0;
-  const int64_t cols_per_wg = vec ? 256 : 64;
-  const int64_t col_tiles = (n + cols_per_wg - 1) / cols_per_wg;
-  const int64_t row_groups = (p.k + 3) / 4;
-  if (col_tiles > 65535 || row_groups > 0x7fffffff) return hipErrorInvalidValue;
-  dim3 grid((unsigned)row_groups, (unsigned)col_tiles), block(256);
+  if ((n + 255) / 256 > 65535) return hipErrorInvalidValue;
+  const int v = n >= 4 ? 4 : 1;
+  const int64_t groups = (n + v - 1) / v;
+  const uint32_t nnz = p.kappa * p.s;
+  // Rows of a work-group: what its threads hold, but no fewer than 512 work-groups for it (half 61120 x 1, k = 256
+  // in one work-group of 256 rows: 11.2 us).
+  const int64_t share = (p.k + 511) / 512, fit = groups >= 256 ? 1 : 256 / groups;
+  const int rows_wg = (int)(fit < share ? fit : share);
+  int picks = kPicks / rows_wg < kRowPicks ? kPicks / rows_wg : kRowPicks;
+  if ((uint32_t)picks > nnz) picks = (int)nnz;
+  const int64_t row_wgs = (p.k + rows_wg - 1) / rows_wg;
+  const int64_t gx = row_wgs < (1 << 23) ? row_wgs : 1 << 23;  // (a grid dimension spans fewer than 2^32 threads)
+  dim3 grid((unsigned)gx, (unsigned)((groups + 255) / 256), (unsigned)((row_wgs + gx - 1) / gx)), block(256);
   if (ev.start) (void)hipEventRecord(ev.start, st);
-#define FS_GO(T, V) hipLaunchKernelGGL((blockrow_kernel<T, V>), grid, block, 0, st, p, (const T*)A, lda, (int)n, (T*)out, ldo, out_vec)
-  if (dt == FS_F32)       { if (vec) FS_GO(float, true); else FS_GO(float, false); }
-  else if (dt == FS_BF16) { if (vec) FS_GO(uint16_t, true); else FS_GO(uint16_t, false); }
-  else                    { if (vec) FS_GO(f16, true); else FS_GO(f16, false); }
+#define FS_GO(T, V, UN)                                                                                       \
+  hipLaunchKernelGGL((blockrow_kernel<T, V, UN>), grid, block, 0, st, p, (const T*)A, lda, (int)n, (T*)out, ldo, \
+                     rows_wg, (int)groups, picks)
+#define FS_T(T)                                                              \
+  do {                                                                       \
+    if (v == 1) FS_GO(T, 1, 16);                                             \
+    else if (nnz > 8) FS_GO(T, 4, 16);                                       \
+    else FS_GO(T, 4, 8);                                                     \
+  } while (0)
+  if (dt == FS_F32) FS_T(float); else if (dt == FS_BF16) FS_T(uint16_t); else FS_T(f16);
+#undef FS_T
 #undef FS_GO
   if (ev.stop) (void)hipEventRecord(ev.stop, st);
   return hipGetLastError();

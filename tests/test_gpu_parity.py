@@ -1412,3 +1412,31 @@ def test_blockrow_matches_oracle(case, dtype):
     assert np.array_equal(signs.cpu().numpy(), want_s)
     assert abs(sk.info().scale - R.scale(p)) <= 1e-7 * R.scale(p)
     check(out, R.apply(R.build_csr(p, seed), host64(A)), dtype, "blockrow")
+
+
+@DTYPES
+@pytest.mark.parametrize("params,n,pad,first", [
+    ((4000, 256, 512, 32, 2, 4), 2, 1, 0),            # fewer columns than a thread's vector: one each
+    ((4000, 256, 512, 32, 2, 4), 4, 0, 1),            # one vector, rows that start anywhere in a dword
+    ((4000, 256, 512, 32, 3, 3), 7, 0, 1),            # two that overlap; 9 picks, 128 rows per work-group
+    ((7000, 300, 1167, 50, 5, 2), 333, 2, 0),         # 84 vectors, 3 rows per work-group; six blocks, odd lengths
+    ((4001, 72, 501, 9, 8, 1), 1025, 0, 0),           # one column beyond the 256 vectors of a column tile
+    ((4096, 2048, 64, 32, 64, 32), 2, 0, 0),          # 2048 picks a row, 8 at a time: less than a slot's 32
+    ((4096, 2048, 64, 32, 64, 31), 1024, 0, 0),       # 512 at a time: more than a slot, no whole number of them
+])
+def test_blockrow_of_every_width_matches_oracle(params, n, pad, first, dtype):
+    from oracle import blockrow as R
+    print("blockrow widths", params, n, dtype, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    flat = torch.full((params[0] * (n + pad) + 8,), float("nan"), device=DEV, dtype=dtype)
+    A = flat[first:first + params[0] * (n + pad)].view(params[0], n + pad)   # NaN behind, and in the padding
+    A[:, :n] = torch.randn((params[0], n), generator=g, device=DEV).to(dtype)
+    if pad:
+        A[:, n:] = float("nan")
+    sk = B.Sketch(*params, seed=5, kind=B.KIND_BLOCKROW)
+    buf = torch.full((params[1], n + 1), float("nan"), device=DEV, dtype=dtype)
+    out = sk.apply(A[:, :n], buf[:, :n])
+    torch.cuda.synchronize()
+    check(out, R.apply(R.build_csr(O.Params(*params), 5), host64(A[:, :n])), dtype, "blockrow")
+    assert torch.isnan(buf[:, n:].float()).all(), "wrote outside the n output columns"
+    assert torch.equal(sk.apply(A[:, :n]), out)
