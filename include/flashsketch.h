@@ -101,7 +101,9 @@ typedef enum {
 
 /* Kernel variants of the BLOCKPERM apply (fs_sketch_set_variant). */
 typedef enum {
-  FS_VARIANT_AUTO = 0,    /* pick by shape/dtype/alignment                          */
+  FS_VARIANT_AUTO = 0,    /* pick by shape/dtype/alignment (calls of up to four vectors
+                             that FS_VARIANT_MFMA would take may run, and are reported as
+                             that variant, on a kernel that sums without matrix cores)  */
   FS_VARIANT_GENERIC = 1, /* one lane per column, LDS-private output tile, any Br   */
   FS_VARIANT_MFMA = 2     /* +-1 operand on the matrix cores: any power-of-two Br
                              (other Br while its kappa slots, each padded to the next

@@ -385,7 +385,7 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
     rc = other_kind(h, A, lda, n, dt, &need);
     if (rc != FS_OK) return rc;
   } else if (h->variant != FS_VARIANT_GENERIC) {
-    plan = fs::plan_mfma(h->p, A, lda, n, dt, with_orbit, SIZE_MAX);
+    plan = fs::plan_mfma(h->p, A, lda, n, dt, with_orbit, SIZE_MAX, h->variant == FS_VARIANT_AUTO);
     if (h->variant == FS_VARIANT_MFMA && !plan.ok) return FS_ERR_UNSUPPORTED;
     if (plan.ok) {
       variant = FS_VARIANT_MFMA;
@@ -402,7 +402,7 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
     ws_bytes = h->ws_bytes;
   }
   if (variant == FS_VARIANT_MFMA && need.want > ws_bytes)  // less than it would like: a split that fits
-    plan = fs::plan_mfma(h->p, A, lda, n, dt, with_orbit, ws_bytes);
+    plan = fs::plan_mfma(h->p, A, lda, n, dt, with_orbit, ws_bytes, h->variant == FS_VARIANT_AUTO);
   const ProfSet prof = next_events(h, st);
   const fs::EventPair ev = prof.kernel;
   if (src.external) {
@@ -475,7 +475,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   if ((uintptr_t)G % esz || (uintptr_t)out % esz) return FS_ERR_INVALID_ARG;
   if (h->kind != FS_KIND_BLOCKPERM) return FS_ERR_UNSUPPORTED;
   fs::mm::RowsPlan plan;
-  if (h->variant != FS_VARIANT_GENERIC) plan = fs::plan_rows(h->p, G, ldg, n, dt, SIZE_MAX);
+  if (h->variant != FS_VARIANT_GENERIC) plan = fs::plan_rows(h->p, G, ldg, n, dt, SIZE_MAX, h->variant == FS_VARIANT_AUTO);
   if (h->variant == FS_VARIANT_MFMA && !plan.ok) return FS_ERR_UNSUPPORTED;
   const bool use_mfma = plan.ok;
   hipStream_t st = (hipStream_t)stream;
@@ -483,7 +483,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   if (use_mfma) {
     rc = ensure_workspace(h, fs::Workspace{plan.ws_floor, rows_want(plan)}, st);
     if (rc != FS_OK) return rc;
-    if (plan.ws > h->ws_bytes) plan = fs::plan_rows(h->p, G, ldg, n, dt, h->ws_bytes);  // a split that fits
+    if (plan.ws > h->ws_bytes) plan = fs::plan_rows(h->p, G, ldg, n, dt, h->ws_bytes, h->variant == FS_VARIANT_AUTO);  // a split that fits
   }
   const ProfSet prof = next_events(h, st);
   const fs::EventPair ev = prof.kernel;
@@ -500,7 +500,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   if (rc != FS_OK) return rc;
   const hipError_t e = fs::launch_rows(plan, h->p, G, ldg, n, out, ldo, dt, h->ws, h->ws_bytes, h->orbit, st, ev);
   if (prof.end) (void)hipEventRecord(prof.end, st);
-  snprintf(h->last_kernel, sizeof(h->last_kernel), "rows_kernel");
+  snprintf(h->last_kernel, sizeof(h->last_kernel), "%s", plan.few.ok ? "vector_kernel" : "rows_kernel");
   h->last_variant = FS_VARIANT_MFMA;
   h->last_mode = 2;
   if (e != hipSuccess) return hip_fail(h, e);
@@ -514,7 +514,10 @@ fs_status fs_sketch_rows_workspace_bytes(fs_sketch_t h, int64_t n, fs_dtype dt, 
   const size_t esz = dt == FS_F32 ? 4 : 2;
   const int64_t ld = (h->p.d + 7) & ~(int64_t)7;  // a well-aligned call: packed rows rounded to 16 bytes
   if (34 * ld * (int64_t)esz >= ((int64_t)1 << 31)) return FS_OK;
-  *bytes = rows_want(fs::plan_rows(h->p, (const void*)(uintptr_t)256, ld, n, dt, SIZE_MAX));
+  for (const bool vector : {false, true}) {
+    const size_t want = rows_want(fs::plan_rows(h->p, (const void*)(uintptr_t)256, ld, n, dt, SIZE_MAX, vector));
+    if (want > *bytes) *bytes = want;
+  }
   return FS_OK;
 }
 
@@ -529,7 +532,7 @@ fs_status fs_sketch_plan(fs_sketch_t h, const void* A, int64_t ld, int64_t n, fs
   size_t ws = 0;
   if (n > 0 && h->kind == FS_KIND_BLOCKPERM) {
     if (rows) {
-      const fs::mm::RowsPlan pl = fs::plan_rows(h->p, A, ld, n, dt, SIZE_MAX);
+      const fs::mm::RowsPlan pl = fs::plan_rows(h->p, A, ld, n, dt, SIZE_MAX, h->variant == FS_VARIANT_AUTO);
       if (h->variant == FS_VARIANT_MFMA && !pl.ok) return FS_ERR_UNSUPPORTED;
       if (pl.ok && h->variant != FS_VARIANT_GENERIC) {
         v = FS_VARIANT_MFMA;
@@ -539,7 +542,7 @@ fs_status fs_sketch_plan(fs_sketch_t h, const void* A, int64_t ld, int64_t n, fs
         ws = rows_want(pl);
       }
     } else {
-      const fs::mm::Plan pl = fs::plan_mfma(h->p, A, ld, n, dt, fs::mfma_wants_orbit(h->p), SIZE_MAX);
+      const fs::mm::Plan pl = fs::plan_mfma(h->p, A, ld, n, dt, fs::mfma_wants_orbit(h->p), SIZE_MAX, h->variant == FS_VARIANT_AUTO);
       if (h->variant == FS_VARIANT_MFMA && !pl.ok) return FS_ERR_UNSUPPORTED;
       if (pl.ok && h->variant != FS_VARIANT_GENERIC) {
         v = FS_VARIANT_MFMA;

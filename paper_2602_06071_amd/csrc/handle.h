@@ -97,13 +97,17 @@ hipError_t launch_generic_rows(const SketchParams& p, const void* G, int64_t ldg
 // handed to the launch.  ws_bytes: workspace the call can have; the row split is the best one that fits.
 // orbit: device array of 2*M words (block at each orbit position of the wiring map
 // starting from block 0, then the inverse), or NULL; have_orbit: whether the launch will get it.
+// vector: whether up to four vectors may go to the kernel that needs no matrix cores (k_vector.hip; they need the
+// workspace that the matrix-core kernel would, so that the same calls are refused).
 namespace mm {
 struct Plan;
 struct RowsPlan;
+struct VecPlan;
+struct VecIo;
 }
 bool mfma_wants_orbit(const SketchParams& p);
 mm::Plan plan_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit,
-                   size_t ws_bytes);
+                   size_t ws_bytes, bool vector);
 Workspace mfma_workspace(const SketchParams& p, const mm::Plan& pl);
 // mode 1 output-stationary, 2 input-stationary, 3 the same with orbit runs; flags as in fs_plan_flags
 int mfma_mode(const mm::Plan& pl);
@@ -135,10 +139,16 @@ hipError_t launch_stacked(const SketchParams& p, const void* A, int64_t lda, int
                           size_t desc_cap);
 
 // Matrix-core path for inputs held examples-as-rows: G is n x d (ld = ldg), out is n x k.
-mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes);
+mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes,
+                       bool vector);
 hipError_t launch_rows(const mm::RowsPlan& pl, const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
                        int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev);
+
+// One or a few vectors: sums in LDS instead of a +-1 operand.
+mm::VecPlan plan_vector(const SketchParams& p, int64_t n, fs_dtype dt, double max_bytes);
+hipError_t launch_vector(const mm::VecPlan& pl, const SketchParams& p, const mm::VecIo& io, int64_t n, fs_dtype dt, float* ws,
+                         const uint32_t* orbit, hipStream_t st, EventPair ev);
 
 // Plain SJLT, global float atomics.  ws: k*n floats for bf16 output, unused for fp32.
 size_t scatter_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt);

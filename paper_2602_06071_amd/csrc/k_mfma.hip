@@ -392,7 +392,7 @@ size_t plan_bytes(const SketchParams& p, const Plan& pl) {
 }  // namespace
 
 mm::Plan plan_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, bool have_orbit,
-                   size_t ws_bytes) {
+                   size_t ws_bytes, bool vector) {
   // Calls of a few blocks and 512, 768 or 1024 columns that run input-stationary (all of these widths do, or
   // none: their output tiles never cover the CUs) take the kernel and the row split of 256 columns, so
   // that each column is summed in the order in which a call for its 256-column chunk sums it.  Where
@@ -408,6 +408,19 @@ mm::Plan plan_mfma(const SketchParams& p, const void* A, int64_t lda, int64_t n,
     if ((double)planes * (double)p.k * 1024.0 * sizeof(float) > (double)kSplitScratch ||
         reduce_in_parts(planes, p.k, 256) != reduce_in_parts(planes, p.k, 1024))
       pl = make_plan(p, A, lda, n, n, dt, have_orbit, ws_bytes);
+  }
+  // Up to four vectors on the kernel without matrix cores.  Three or four stay where the matrix-core kernel
+  // stores the result itself (fp32 54632 x 4, kappa = 1: 7.2 against 8.4 us) and where the other would split the rows
+  // (bf16 122176 x 3, 32 blocks, kappa = 8: 11.8 against 14.5).
+  if (vector && pl.ok && (n <= 2 || pl.in_stat || pl.planes > 0)) {
+    const double room = ws_bytes < kSplitScratch ? (double)ws_bytes : (double)kSplitScratch;
+    pl.few = plan_vector(p, n, dt, room);
+    if (n > 2 && pl.few.zsplit > 1) pl.few.ok = false;
+    if (pl.few.ok) {
+      pl.in_stat = false; pl.ks = pl.outs = pl.stacked = false;
+      pl.run = pl.groups = pl.nsub = 1; pl.zsplit = pl.few.zsplit;
+      pl.planes = pl.zsplit > 1 ? pl.zsplit : 0;
+    }
   }
   return pl;
 }
@@ -439,8 +452,8 @@ size_t mfma_workspace_bytes(const SketchParams& p, int64_t n, fs_dtype dt) {
   // the largest over aligned and odd row strides, with and without the orbit table
   const int64_t ld = (n + 7) & ~(int64_t)7;
   size_t most = 0;
-  for (int i = 0; i < 4; ++i) {
-    const Workspace w = mfma_workspace(p, plan_mfma(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0, SIZE_MAX));
+  for (int i = 0; i < 8; ++i) {  // (and of both kernels of a few vectors)
+    const Workspace w = mfma_workspace(p, plan_mfma(p, (const void*)(uintptr_t)256, ld + (i & 1), n, dt, (i & 2) != 0, SIZE_MAX, (i & 4) != 0));
     if (w.want > most) most = w.want;
   }
   return most;
@@ -459,6 +472,17 @@ hipError_t launch_mfma(const mm::Plan& pl, const SketchParams& p, const void* A,
                        int64_t ldo, fs_dtype dt, void* ws, size_t ws_bytes, const uint32_t* orbit, hipStream_t st,
                        EventPair ev, char* desc, size_t desc_cap) {
   if (!pl.ok || plan_bytes(p, pl) > ws_bytes) return hipErrorInvalidValue;
+  if (pl.few.ok) {
+    if (desc && desc_cap)
+      snprintf(desc, desc_cap, "vector_kernel<%s,%d>%s", dt == FS_F32 ? "f32" : dt == FS_BF16 ? "bf16" : "f16", pl.few.nv,
+               pl.planes ? "+reduce_planes" : "");
+    VecIo io;
+    io.A = A; io.out = out; io.step = lda; io.next = 1; io.ostep = ldo; io.onext = 1;
+    io.plane = p.k * pl.ldw; io.pstep = pl.ldw; io.pnext = 1;
+    const hipError_t ve = launch_vector(pl.few, p, io, n, dt, (float*)ws, orbit, st, ev);
+    if (ve != hipSuccess || pl.planes == 0) return ve;
+    return launch_reduce(p, pl, n, out, ldo, dt, (float*)ws, orbit, st);
+  }
   if (pl.stacked) return launch_stacked(p, A, lda, n, out, ldo, dt, orbit, st, ev, desc, desc_cap);
   hipError_t e;
   if (pl.outs) {

@@ -719,8 +719,19 @@ void launch_reduce(int64_t outputs, uint32_t addends, hipStream_t st, const Rows
 
 }  // namespace
 
-mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes) {
-  return make_rows_plan(p, G, ldg, n, dt, ws_bytes);
+mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes,
+                       bool vector) {
+  RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, ws_bytes);
+  if (vector && pl.ok && (n <= 2 || pl.ws > 0)) {  // (three or four: not where it stores the result itself)
+    const double room = ws_bytes < kSplitScratch ? (double)ws_bytes : (double)kSplitScratch;
+    pl.few = plan_vector(p, n, dt, room);
+    if (pl.few.ok) {
+      pl.out_stat = true;
+      pl.groups = pl.nsub = 1; pl.zsplit = pl.few.zsplit;
+      pl.ws = pl.zsplit > 1 ? (size_t)n * (size_t)p.k * 4 * pl.zsplit : 0;
+    }
+  }
+  return pl;
 }
 
 hipError_t launch_rows(const mm::RowsPlan& pl, const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,
@@ -735,13 +746,17 @@ hipError_t launch_rows(const mm::RowsPlan& pl, const SketchParams& p, const void
   while ((1u << a.log2_br) < p.Br) ++a.log2_br;
   a.zsplit = pl.zsplit; a.group_slots = pl.group_slots; a.nsub = pl.nsub;
   const dim3 grid(p.M, (unsigned)((n + 32 * pl.et - 1) / (32 * pl.et)) * pl.nsub, pl.zsplit * pl.groups);
+  VecIo io;
+  io.A = G; io.out = out; io.step = 1; io.next = ldg; io.ostep = 1; io.onext = ldo;
+  io.plane = n * p.k; io.pstep = 1; io.pnext = p.k; io.by_orbit = 1;
 
-  if (ev.start) (void)hipEventRecord(ev.start, st);
+  if (!pl.few.ok && ev.start) (void)hipEventRecord(ev.start, st);
   hipError_t e;
-  if (dt == FS_F32) e = launch_mt<float, false>(pl, grid, st, a);
+  if (pl.few.ok) e = launch_vector(pl.few, p, io, n, dt, (float*)ws, orbit, st, ev);
+  else if (dt == FS_F32) e = launch_mt<float, false>(pl, grid, st, a);
   else if (dt == FS_BF16) e = pl.unal ? launch_mt<uint16_t, true>(pl, grid, st, a) : launch_mt<uint16_t, false>(pl, grid, st, a);
   else e = pl.unal ? launch_mt<f16, true>(pl, grid, st, a) : launch_mt<f16, false>(pl, grid, st, a);
-  if (ev.stop) (void)hipEventRecord(ev.stop, st);
+  if (!pl.few.ok && ev.stop) (void)hipEventRecord(ev.stop, st);
   if (e != hipSuccess || (pl.out_stat && pl.zsplit == 1)) return e;
   const int vec = p.Br % 4 == 0 ? 4 : 1;
   const int64_t outputs = n * (p.k / vec);

@@ -1,0 +1,276 @@
+// BlockPerm-SJLT apply for up to four vectors, in either layout: sums in LDS, no matrix cores.
+//
+// A +-1 operand Phi for the matrix cores costs, per 64 input rows and wiring slot, a cleared and re-read tile
+// of LDS beside the s writes that fill it, and a wave loads and splits 32 columns of which n exist.  For a few
+// vectors that is more than the sums themselves: here a lane owns one input row of a stage and a private
+// column of the accumulators [Br][64] (fp32, the vectors of a lane side by side) in LDS, hashes its row (Appendix
+// E, "Within-block hashing") and adds +-a[u] to the s rows it names.  No address is touched by two lanes or two
+// waves, and the LDS operations of a wave complete in order: no atomics, one order of summation.
+// (ds_add_f32 instead of read, add and write took ten times as long.)
+//
+// Decomposition: output-stationary as in Alg. 1 (work-group = output block g, its waves share the kappa*Bc
+// input rows stage by stage; A is read kappa times, which for a few vectors is little), so that a call is one
+// launch; grid.y splits the rows further where blocks are few and leaves unscaled partial sums to the
+// fixed-order reductions of the matrix-core kernels.  The 64 columns and the waves' tiles are added at the end.
+//
+// What bounds it: vector and LDS instructions (a hash, 6 + n per nonzero) and the latency of a stage, about 0.28 us
+// of a SIMD with one wave, 0.14 with eight; then the start of the kernel.  us per call, matrix-core kernel -> this:
+// fp32 262144 x 1, k = 4096, kappa = 4 18.8 -> 10.1; bf16 1634432 x 2, kappa = 8 143 -> 55; fp32 498176 x 1 as a
+// row, two blocks of 128 rows 37 -> 17; 65 random calls of one to four vectors 1.4 times as fast.
+// Sparse semantics are exact: an Inf or NaN reaches only the outputs that its input row feeds.
+#include <type_traits>
+
+#include "convert.h"
+#include "handle.h"
+#include "lds_limit.h"
+#include "mfma_plan.h"
+#include "spec.h"
+
+namespace fs {
+namespace {
+
+struct VecArgs {
+  SketchParams p;
+  const void* A;   // element (input row u, vector c) at u*step + c*next
+  void* out;       // element (output row r, vector c) at r*ostep + c*onext
+  float* ws;
+  const uint32_t* pos2blk;  // orbit order of the blocks, or NULL
+  int64_t step, next, ostep, onext;
+  int64_t plane, pstep, pnext;  // partial sums: split z of (row, c) at z*plane + row*pstep + c*pnext
+  int n, total, stages, zsplit, by_orbit;  // by_orbit: partial sums are stored by orbit position (rows layout)
+};
+
+constexpr int kVecTables = 2 * 128 * 4;  // behind the accumulators: key and input block per slot
+
+// NV: vectors of a lane, whose sums of one output row lie side by side.
+template <typename T, int NV>
+__global__ __launch_bounds__(1024) void vector_kernel(VecArgs a) {
+  typedef float Sum __attribute__((ext_vector_type(NV)));
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const SketchParams& p = a.p;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr uint32_t row_bytes = NV * 256;  // a row of the accumulators: 64 lanes' NV sums
+  const uint32_t tile = p.Br * row_bytes;   // ... of a wave
+  uint32_t* s_bk = reinterpret_cast<uint32_t*>(smem + nw * tile);
+  uint32_t* s_blk = s_bk + 128;
+
+  const uint32_t blk = blockIdx.x, z = blockIdx.y;
+  const int wg_lo = (int)z * a.stages, wg_n = min(a.stages, a.total - wg_lo);
+  const int per = (wg_n + (int)nw - 1) / (int)nw;
+  const int t_lo = wg_lo + (int)wave * per, t_n = max(0, min(per, wg_lo + wg_n - t_lo));
+  const uint32_t spb = (p.Bc + 63) / 64;  // stages per block
+
+  for (uint32_t sl = tid; sl < p.kappa; sl += 64 * nw) {
+    uint32_t x = blk;
+    if (a.pos2blk) {
+      x = a.pos2blk[p.M + blk] + 1 + sl;  // kappa <= M
+      x = a.pos2blk[x >= p.M ? x - p.M : x];
+    } else {
+      for (uint32_t l = 0; l <= sl; ++l) x = wire_next(x, p.a, p.b, p.M);
+    }
+    s_blk[sl] = x;
+    s_bk[sl] = block_key(p.key1, blk, x, p.M);
+  }
+  for (uint32_t i = tid; i < nw * tile / 16; i += 64 * nw) reinterpret_cast<float4*>(smem)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  __syncthreads();
+
+  // A cursor over the stages: slot, stage in the block.  `f` of the loads, with the rows of the block as one buffer per
+  // vector (rows at or beyond Bc or d lie outside its range and read as 0); `h` of the hashes, with the block's key.
+  const T* base = reinterpret_cast<const T*>(a.A);
+  __amdgpu_buffer_rsrc_t rs[NV];
+  auto open = [&](uint32_t l) {
+    const int64_t first = (int64_t)__builtin_amdgcn_readfirstlane(s_blk[min(l, p.kappa - 1)]) * p.Bc;
+    const int64_t valid = min((int64_t)p.Bc, p.d - first);
+    const int bytes = valid > 0 ? (int)(((valid - 1) * a.step + 1) * (int64_t)sizeof(T)) : 0;
+#pragma unroll
+    for (int c = 0; c < NV; ++c)
+      rs[c] = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base + first * a.step + c * a.next), 0,
+                                                c < a.n ? bytes : 0, 0x00020000);
+  };
+  uint32_t f_l = (uint32_t)t_lo / spb, f_us = (uint32_t)t_lo - f_l * spb;
+  uint32_t h_l = f_l, h_us = f_us, key = __builtin_amdgcn_readfirstlane(s_bk[min(h_l, p.kappa - 1)]);
+  open(f_l);
+  const uint32_t lane_off = lane * (uint32_t)(a.step * (int64_t)sizeof(T)), stage_off = 64 * (uint32_t)(a.step * (int64_t)sizeof(T));
+  auto fetch = [&](uint32_t (&x)[NV]) {  // (behind the wave's last stage: the one after it, or the last block again; not used)
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      if constexpr (sizeof(T) == 4)
+        x[c] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs[c], lane_off, f_us * stage_off, 0);
+      else
+        x[c] = (uint32_t)(unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs[c], lane_off, f_us * stage_off, 0);
+    }
+    if (++f_us == spb) { f_us = 0; open(++f_l); }
+  };
+  auto value = [](uint32_t bits) -> float {
+    if constexpr (sizeof(T) == 4) {
+      return __uint_as_float(bits);
+    } else {
+      const T v = __builtin_bit_cast(T, (uint16_t)bits);
+      return Elt<T>::load(&v);
+    }
+  };
+  unsigned char* const tile_at = smem + wave * tile;
+  const uint32_t mask = (p.Br - 1) * row_bytes + (row_bytes - 1);
+  auto add = [&](const uint32_t (&x)[NV]) {
+    const RowHash rh = row_hash_pow2(key, h_us * 64 + lane, p.Br);
+    float v[NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) v[c] = value(x[c]);
+    uint32_t o = rh.shift * row_bytes + lane * (NV * 4), signs = rh.signs;
+    const uint32_t stride = rh.stride * row_bytes;
+    // G of the row's s sums (distinct ones) together: read, added, written back
+    auto some = [&](auto g_tag) {
+      constexpr int G = decltype(g_tag)::value;
+      Sum* at[G];
+      Sum sum[G];
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        at[i] = reinterpret_cast<Sum*>(tile_at + (o & mask));
+        o += stride;
+        sum[i] = *at[i];
+      }
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        const float sign = __uint_as_float(((signs << (31 - i)) & 0x80000000u) | 0x3F800000u);
+#pragma unroll
+        for (int c = 0; c < NV; ++c) sum[i][c] = fmaf(sign, v[c], sum[i][c]);
+        *at[i] = sum[i];
+      }
+      signs >>= G;
+    };
+    uint32_t left = p.s;
+    for (; left >= 4; left -= 4) some(std::integral_constant<int, 4>{});
+    if (left & 2) some(std::integral_constant<int, 2>{});
+    if (left & 1) some(std::integral_constant<int, 1>{});
+    if (++h_us == spb) {
+      h_us = 0; ++h_l;
+      key = __builtin_amdgcn_readfirstlane(s_bk[min(h_l, p.kappa - 1)]);
+    }
+  };
+  // the elements of four stages are under way while a stage is added
+  uint32_t x[4][NV];
+  if (t_n > 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fetch(x[i]);
+  }
+  for (int t = 0; t < t_n; t += 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (t + i < t_n) {
+        add(x[i]);
+        fetch(x[i]);
+      }
+    }
+  }
+  __syncthreads();
+
+  // Four rows per wave at a time, 16 lanes a row: the waves' tiles in order, then the row's 64 columns.
+  const uint32_t active = (uint32_t)((wg_n + per - 1) / per);
+  for (uint32_t r0 = wave * 4; r0 < p.Br; r0 += 4 * nw) {
+    const uint32_t r = r0 + (lane >> 4);
+    double s[NV];  // (in fp32 this chain of 4 adds per wave held most of the error: fp32 262144 x 1 1.4e-7, in fp64 see there)
+#pragma unroll
+    for (int c = 0; c < NV; ++c) s[c] = 0.0;
+    if (r < p.Br) {
+      const Sum* src = reinterpret_cast<const Sum*>(smem + r * row_bytes) + (lane & 15);
+      for (uint32_t w = 0; w < active; ++w)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const Sum v = src[w * (tile / sizeof(Sum)) + q * 16];
+#pragma unroll
+          for (int c = 0; c < NV; ++c) s[c] += (double)v[c];
+        }
+    }
+#pragma unroll
+    for (int m = 8; m >= 1; m /= 2)
+#pragma unroll
+      for (int c = 0; c < NV; ++c) s[c] += __shfl_xor(s[c], m);
+    if (r >= p.Br || (lane & 15)) continue;
+    uint32_t rec = blk;
+    if (a.zsplit > 1 && a.by_orbit) {
+      rec = a.pos2blk ? a.pos2blk[p.M + blk] + 1 : wire_next(blk, p.a, p.b, p.M);
+      if (rec == p.M) rec = 0;
+    }
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      if (c >= a.n) break;
+      if (a.zsplit > 1)
+        a.ws[z * a.plane + ((int64_t)rec * p.Br + r) * a.pstep + c * a.pnext] = (float)s[c];
+      else
+        Elt<T>::store(reinterpret_cast<T*>(a.out) + ((int64_t)blk * p.Br + r) * a.ostep + c * a.onext, (float)s[c] * p.scale);
+    }
+  }
+}
+
+template <auto kernel>
+hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const VecArgs& a) {
+  const hipError_t e = allow_lds<kernel>(lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_t(const mm::VecPlan& pl, dim3 grid, hipStream_t st, const VecArgs& a) {
+  return pl.nv == 1   ? go<vector_kernel<T, 1>>(grid, 64 * pl.nw, pl.lds, st, a)
+         : pl.nv == 2 ? go<vector_kernel<T, 2>>(grid, 64 * pl.nw, pl.lds, st, a)
+                      : go<vector_kernel<T, 4>>(grid, 64 * pl.nw, pl.lds, st, a);
+}
+
+}  // namespace
+
+// Waves of a work-group and row splits by the smallest modelled time (us): the start, then the stages of the SIMDs
+// in use, each cheaper the more waves a SIMD holds (measured: about 0.28 with one, 0.2 with four, 0.14 with eight, at
+// s = 8), or the stream of A; the start and end of further work-groups; partial sums add a reduction.
+mm::VecPlan plan_vector(const SketchParams& p, int64_t n, fs_dtype dt, double max_bytes) {
+  mm::VecPlan pl;
+  pl.nv = n == 1 ? 1 : n == 2 ? 2 : 4;
+  if (n > pl.nv || !p.br_pow2 || p.kappa > 128 || pl.nv * (uint64_t)p.Br > 128) return pl;
+  const size_t tile = (size_t)pl.nv * p.Br * 256;
+  const int64_t spb = ((int64_t)p.Bc + 63) / 64;
+  if (spb * 64 * 4 >= ((int64_t)1 << 31)) return pl;  // 32-bit offsets in a block held as a row
+  pl.total = (int)(p.kappa * spb);
+  pl.split_bytes = (size_t)p.k * ((n + 3) & ~(int64_t)3) * 4;
+  const double scale = (0.8 + 0.025 * p.s) * (1 + 0.1 * (pl.nv - 1));
+  const double stream_us = (double)p.kappa * (double)p.d * (double)n * (dt == FS_F32 ? 4 : 2) / 5.5e6;
+  double best = 0;
+  for (int nw = 4; nw <= 16; nw *= 2) {
+    const size_t lds = nw * tile + kVecTables;
+    if (lds > kLdsMost) break;
+    const int fit = (int)(kLdsMost / lds) * nw;
+    const double cap = (fit < 32 ? fit : 32) / 4.0;  // waves a SIMD holds
+    for (int z = 1; z <= pl.total && z <= 64; z = z < 8 ? z + 1 : z * 5 / 4) {
+      if (z > 1 && (double)pl.split_bytes * z > max_bytes) break;
+      const int stages = (pl.total + z - 1) / z, per = (stages + nw - 1) / nw;
+      const double wgs = (double)p.M * z, simds = 4.0 * (wgs < 256 ? wgs : 256);
+      const double waves = wgs * nw / simds;  // >= 1
+      double t = per * waves * scale * (0.12 + 0.16 / (waves < cap ? waves : cap));
+      if (stream_us > t) t = stream_us;
+      if (z > 1) t += 3.5 + 0.04 * z;
+      if (wgs > 256) t += 0.4 * (wgs / 256 - 1);
+      if (!pl.ok || t < best * 0.98) {
+        best = t; pl.ok = true; pl.nw = nw; pl.zsplit = (pl.total + stages - 1) / stages; pl.stages = stages; pl.lds = lds;
+      }
+    }
+  }
+  return pl;
+}
+
+hipError_t launch_vector(const mm::VecPlan& pl, const SketchParams& p, const mm::VecIo& io, int64_t n, fs_dtype dt, float* ws,
+                         const uint32_t* orbit, hipStream_t st, EventPair ev) {
+  VecArgs a;
+  a.p = p; a.A = io.A; a.out = io.out; a.ws = ws; a.pos2blk = orbit;
+  a.step = io.step; a.next = io.next; a.ostep = io.ostep; a.onext = io.onext;
+  a.plane = io.plane; a.pstep = io.pstep; a.pnext = io.pnext;
+  a.n = (int)n; a.total = pl.total; a.stages = pl.stages; a.zsplit = pl.zsplit; a.by_orbit = io.by_orbit;
+  const dim3 grid(p.M, (unsigned)pl.zsplit);
+  if (ev.start) (void)hipEventRecord(ev.start, st);
+  const hipError_t e = dt == FS_F32    ? launch_t<float>(pl, grid, st, a)
+                       : dt == FS_BF16 ? launch_t<uint16_t>(pl, grid, st, a)
+                                       : launch_t<f16>(pl, grid, st, a);
+  if (ev.stop) (void)hipEventRecord(ev.stop, st);
+  return e;
+}
+
+}  // namespace fs

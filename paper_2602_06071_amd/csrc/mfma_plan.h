@@ -23,8 +23,25 @@ struct MfmaArgs {
   uint32_t log2_br;
 };
 
+// One or a few vectors of either layout on the kernel of k_vector.hip (not ok: it does not take the call).
+struct VecPlan {
+  bool ok = false;
+  int nv = 1, nw = 4;                     // vectors of a lane, waves of a work-group
+  int zsplit = 1, stages = 0, total = 0;  // row splits, stages of one and of all
+  size_t lds = 0, split_bytes = 0;                        // split_bytes: of the partial sums of one row split
+};
+// Where it finds its elements: strides, in elements, between rows (step) and vectors (next) of A, the result
+// and the partial sums (`plane` between row splits; by_orbit: their blocks as the rows reduction looks for them).
+struct VecIo {
+  const void* A = nullptr;
+  void* out = nullptr;
+  int64_t step = 0, next = 0, ostep = 0, onext = 0, plane = 0, pstep = 0, pnext = 0;
+  int by_orbit = 0;
+};
+
 // What the host decided for one launch (make_plan in k_mfma.hip).
 struct Plan {
+  VecPlan few;
   bool ok = false;
   bool in_stat = false;
   int mt = 0, nrg = 0, ncg = 0, zsplit = 1, stages = 0, run = 1, cpl = 4, pfx = 1;
@@ -45,6 +62,7 @@ struct Plan {
 
 // The same for the examples-as-rows layout (k_rows.hip).
 struct RowsPlan {
+  VecPlan few;
   bool ok = false;
   int mt = 0, et = 4, zsplit = 1, stages = 0, total = 0, groups = 1, group_slots = 0;
   bool out_stat = false;

@@ -1440,3 +1440,65 @@ def test_blockrow_of_every_width_matches_oracle(params, n, pad, first, dtype):
     check(out, R.apply(R.build_csr(O.Params(*params), 5), host64(A[:, :n])), dtype, "blockrow")
     assert torch.isnan(buf[:, n:].float()).all(), "wrote outside the n output columns"
     assert torch.equal(sk.apply(A[:, :n]), out)
+
+
+# ------------------------ up to four vectors: sums without matrix cores ---
+FEW = [
+    # params (d,k,Bc,Br,kappa,s), row or column padding, first element of the view, kernel expected for n = 1, 2 / 3, 4
+    ((15990, 128, 4000, 32, 2, 4), 0, 0, True, True),       # a partly filled last block, 63 stages
+    ((15991, 128, 4001, 32, 3, 7), 3, 1, True, True),       # odd everything; s = 4 + 2 + 1
+    ((16000, 256, 4001, 64, 4, 1), 1, 0, True, False),      # 64 rows: one or two vectors
+    ((9000, 512, 2250, 128, 4, 32), 2, 1, False, False),    # 128 rows: one vector; s = 32
+    ((5000, 128, 2500, 64, 1, 4), 0, 0, True, False),       # M = 2: no orbit table
+    ((1024, 64, 1024, 64, 1, 8), 0, 0, True, False),        # M = 1
+    ((5120, 256, 640, 32, 8, 2), 4, 0, True, True),         # kappa = M
+    ((4096, 64, 64, 1, 4, 1), 0, 0, True, True),            # Br = 1, one stage per block
+    ((100000, 16, 50000, 8, 2, 8), 5, 1, True, True),       # two blocks of 782 stages: row splits, s = Br
+    ((20480, 512, 640, 16, 16, 3), 0, 0, True, True),
+]
+
+
+@DTYPES
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+@pytest.mark.parametrize("case", FEW, ids=lambda c: f"{c[0]}")
+def test_few_vectors_match_oracle_in_both_layouts(case, n, dtype):
+    params, pad, first, two, four = case
+    print("few vectors", params, n, dtype, flush=True)
+    d, k = params[0], params[1]
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    S = oracle_csc(params, 9)
+    tol = ETOL[dtype]
+    for rows in (False, True):
+        shape, ld = ((n, d), d + pad) if rows else ((d, n), n + pad)
+        flat = torch.full(((shape[0] + 1) * ld + 8,), float("nan"), device=DEV, dtype=dtype)
+        X = flat[first:first + shape[0] * ld].view(shape[0], ld)[:, :shape[1]]   # NaN in the padding and behind
+        X.copy_(torch.randn(shape, generator=g, device=DEV))
+        sk = make_sketch(params, 9, B.VARIANT_AUTO)
+        obuf = torch.full((n, k + 1) if rows else (k, n + 1), float("nan"), device=DEV, dtype=dtype)
+        out = obuf[:, :-1]
+        (sk.apply_rows if rows else sk.apply)(X, out)
+        torch.cuda.synchronize()
+        i = sk.info()
+        plan = sk.plan(n, dtype, ld=ld, rows=rows, address=X.data_ptr())
+        few = i.last_kernel.decode().startswith("vector_kernel")
+        if n == 1 or (n == 2 and two):
+            assert few, i.last_kernel
+        elif not four:
+            assert not few, i.last_kernel
+        if few:
+            assert (plan["variant"], plan["mode"]) == (B.VARIANT_MFMA, 1)
+        ref = O.apply_rows(S, host64(X)) if rows else O.apply(S, host64(X))
+        check(out, ref, dtype, "few vectors")
+        diff = np.abs(host64(out) - ref)
+        assert (diff <= tol * (np.abs(ref) + np.sqrt((ref ** 2).mean()))).all()
+        assert torch.isnan(obuf[:, -1].float()).all(), "wrote outside the output"
+        assert torch.equal((sk.apply_rows if rows else sk.apply)(X), out)
+        if few and plan["flags"] & B.PLAN_SPLIT and not rows and plan["workspace_bytes"]:
+            whole = B.Sketch(*params, seed=9)      # less workspace: fewer row splits
+            ws = torch.empty(plan["workspace_bytes"] + 256, dtype=torch.uint8, device=DEV)
+            off = (-ws.data_ptr()) % 256
+            whole.set_workspace(ws[off:off + plan["workspace_bytes"] // 2])
+            try:
+                check(whole.apply(X), ref, dtype, "few vectors, half the workspace")
+            except B.FlashSketchError as e:        # below what the matrix-core kernel must find: refused, as ever
+                assert e.status == 3
