@@ -27,7 +27,7 @@
  *              owned by the caller.  Handles and fs_info are HOST objects.
  *   Alignment  A and out must be aligned to their element size.  The matrix-core
  *              kernels load 4 columns per lane as one vector; rows of a 16-bit
- *              type that start inside a dword (A or lda odd) as the three dwords
+ *              type that start inside a dword (A or lda odd) as the dwords
  *              that hold them, which is slower (never an error).  With n not
  *              a multiple of 4, up to 3 elements behind column n-1 (the row's
  *              padding, or the start of the next row; behind the last row only
@@ -35,8 +35,8 @@
  *              dword, of its last valid element) and up to one before the first
  *              element, inside its dword, may be loaded and discarded; their values, NaN
  *              included, never reach the result.  (Some calls of few columns load element by
- *              element instead; which ones is not part of this interface.)  Stores to out are
- *              vectors when out and ldo are aligned to 4 elements, else element by element.
+ *              element instead; which ones is not part of this interface.)  Stores to out
+ *              touch the k x n elements only.
  *   Streams    `stream` is a hipStream_t passed as void* (NULL = default
  *              stream).  Calls enqueue work and return; they never synchronise.
  *              A handle must not be used from two streams at the same time

@@ -200,9 +200,10 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
   // re-reads of A that mostly hit L2 (about 0.3 of an HBM read each): measured cross-over
   // rho ~ 0.23 (kappa - 1).  With kappa = 1 there is nothing to re-read and OUT stores directly.
   pl.in_stat = can_in && (!can_out || (p.kappa > 1 && (out_starved || rho <= 0.23 * (p.kappa - 1))));
-  // 16-bit shapes of the kernel with work-group-shared Phi tiles, were the rows aligned for it
-  const bool shared_shape = !pl.in_stat && nsub == 1 &&
-                            outs_supported(p, (const void*)(uintptr_t)256, (lda + 3) & ~(int64_t)3, n, dt, 1);
+  // 16-bit shapes of the kernel with work-group-shared Phi tiles
+  const bool shared_shape = !pl.in_stat && nsub == 1 && outs_supported(p, A, lda, n, dt, 1);
+  // its work-groups: 512 columns of an output block, a CU each
+  const int64_t shared_wgs = (int64_t)p.M * ((n + 511) / 512);
   int floor_planes = 0;  // what a call must be able to hold whatever the split
   if (pl.in_stat) {
     pl.mt = mt_i; pl.nrg = nrg_i; pl.zsplit = zs;
@@ -233,7 +234,6 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
     // columns and hold a CU each, so it wants a row split that brings their number to between
     // five eighths of the CUs and all of them (measured on wide: n = 2560 and 3072 whole, 0.20 ms
     // against 0.25 and 0.26 ms split; n = 1536 in 2 splits, n = 1024 in 4)
-    const int64_t shared_wgs = (int64_t)p.M * ((n + 511) / 512);
     auto enough = [&](int z) {
       return shared_shape ? shared_wgs * z >= 160 : (int64_t)p.M * col_tiles * nsub * z >= 512;
     };
@@ -290,10 +290,17 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
   // 16-bit output-stationary shapes without slices go to the kernel whose work-group
   // shares its Phi tiles (measured on the "wide" workload: 0.445 against 0.52 ms)
   if (shared_shape) settle(true);
-  pl.outs = shared_shape && pl.vec4 && outs_supported(p, A, lda, n, dt, pl.zsplit);
+  // Rows that are not aligned to 4 columns cost it nothing (half 65536 x 1531, 64 blocks: 82 us on mfma_kernel, 45 at 1532
+  // columns here); it is taken for them where its work-groups are whole and enough without a split.
+  pl.outs = shared_shape && outs_supported(p, A, lda, n, dt, pl.zsplit) &&
+            (pl.vec4 || (n >= 512 && shared_wgs >= 160));
+
+  // Sketches that hardly compress and sketches of a few blocks keep the shared-Phi kernel, and with it, for whole and for
+  // 256-column calls alike, its order of summation.
+  const bool flat = p.d <= 4 * p.k || p.M <= kChunkBlocks;
 
   // The K-split kernel: few columns, or too few (block, column tile) pairs (k_ksplit_kernel.h).  Up to 64
-  // columns always (but for blocks above 128 rows, and for the shared-Phi kernel's shapes); beyond, both kernels
+  // columns always (but for blocks above 128 rows); beyond, both kernels
   // are priced by the model above, and the K-split one has to
   // promise a fifth less.  Measured (us per call, mfma_kernel with its evenly dividing splits -> this plan):
   // fp32 262144 x 1, k = 4096, kappa = 4: 40 -> 16 (with the two slot groups below); fp32 1923840 x 48, kappa = 8: 632 -> 118; half
@@ -302,9 +309,9 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
   // 17856 x 168: 38 -> 14, half 11253 x 729: 31 -> 9.6.  Where the 128-column waves fill the chip they stay.
   // (The choice does not look at the alignment when n is a multiple of 4: an unaligned view of a matrix stays on the
   // kernel that its packed copy would take, and sums in its order where that is one of these two without orbit
-  // runs.  Rows of another length have no aligned packed copy, and the calls that would be the shared-Phi kernel's
-  // if they were aligned are priced too.)
-  if (!(shared_shape && (pl.vec4 || n % 4 == 0)) && nsub == 1 && pl.run == 1) {
+  // runs.  Rows of another length have no aligned packed copy: the shared-Phi kernel's calls of that kind are
+  // priced too.)
+  if (!(shared_shape && (pl.vec4 || n % 4 == 0) && flat) && nsub == 1 && pl.run == 1) {
     const int kap = pl.in_stat ? (group_slots < (int)p.kappa ? group_slots : (int)p.kappa) : 1;
     const double phi_us = 0.12 + 0.07 * kap;
     const double mfma_us = pl.mt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0;  // per 32 columns and stage
@@ -361,8 +368,12 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
         }
       }
     }
-    if (cpl && (n <= 64 || t_ks < 0.8 * t_old)) {
-      pl.ks = true;
+    // (t_old is the price of mfma_kernel; the shared-Phi kernel is faster than that where its work-groups fill the chip.
+    // us per call, shared-Phi -> K-split, t_ks / t_old: bf16 5728 x 768, 32 blocks of 64 rows 22.3 -> 11.2, 0.30; bf16
+    // 5120 x 176, 64 of 128 rows 28.2 -> 10.7, 0.25; half 19632 x 232, 16 of 64 rows 14.4 -> 8.4, 0.34; bf16 353920 x 208,
+    // 128 of 64 rows 31.8 -> 40.7, 0.69; half 238432 x 1120, 32 of 32 rows 590 -> 600, 0.49)
+    if (cpl && (n <= 64 || t_ks < (pl.outs || (shared_shape && n % 4 == 0) ? 0.45 : 0.8) * t_old)) {
+      pl.ks = true; pl.outs = false;
       pl.cpl = cpl; pl.lds = ks_lds_bytes(pl.mt, cpl);
       pl.zsplit = z;
       settle_within(false);

@@ -23,6 +23,12 @@
 //    an output block, work-group z takes the stages [z*stages, (z+1)*stages) and stores unscaled
 //    fp32 sums to plane z; the fixed-order reduction kernel scales, converts and stores.
 //
+//  * Rows of any alignment (UNAL below: rows that start inside a dword).
+//  * The end of the kernel counts in short calls (8 to 16 stages of about 1 us): stored row by row from the accumulation
+//    registers with one conversion instruction per two values.  us per call, before -> now: bf16 60416 x 6152, 32 blocks
+//    of 128 rows, kappa = 1 197 -> 180; bf16 66048 x 344, 256 blocks 48.8 -> 41.8; bf16 5728 x 768, 32 of 64 rows
+//    22.2 -> 17.8; "wide" 442 -> 434.
+//
 // A goes HBM -> registers -> v_perm transpose -> MFMA B operand exactly as in mfma_kernel.
 // Inputs must be finite (a dense product also multiplies by the zeros of Phi).
 //
@@ -49,7 +55,7 @@ struct OutsArgs {
   int64_t lda, ldo;
   int n;
   int spb;      // stages per input block: ceil(Bc / KC)
-  int out_vec;  // out rows allow 4-column vector stores
+  int vec4;     // rows of A are aligned to 4 columns
   // row split: work-group z (grid.z) takes the stages [z*stages, min((z+1)*stages, kappa*spb)) of
   // its output block (an even number of them) and, when there is more than one, stores its unscaled fp32 sums to
   // plane z of ws (k x ldw floats each) for the fixed-order reduction kernel
@@ -58,7 +64,12 @@ struct OutsArgs {
   int64_t ldw;
 };
 
-template <typename T, int MT, int NW>
+// UNAL: rows may start inside a dword.  The loads stay on dwords (8-byte loads at odd elements reach 12.4 of the 18 TB/s
+// that this loop reads from L1): a lane holds the two dwords from the one its first column lies in, takes the third
+// from the lane above it (one DPP move) and shifts.  The last lane of a half-wave has none above it and is that lane for
+// its neighbour only: a wave covers 124 columns.  us per call with inputs that change from call to call, mfma_kernel (three
+// dwords per row, half the ring) -> here: half 65536 x 1531, 64 blocks of 64 rows, kappa = 2 82.6 -> 65.6; 1532 columns 63.9.
+template <typename T, int MT, int NW, bool UNAL>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(MT > 2 ? 1 : 2)))
 void outs_kernel(OutsArgs a) {
   static_assert(sizeof(T) == 2, "16-bit element types");
@@ -77,7 +88,8 @@ void outs_kernel(OutsArgs a) {
   uint16_t* s_phi = reinterpret_cast<uint16_t*>(smem + 2 * MAX_KAPPA * 4);  // two tiles
 
   const SketchParams& p = a.p;
-  const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, kg = lane >> 5;
+  const int tid = (int)threadIdx.x, lane = tid & 63, kg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // Which (output block, column tile) this work-group takes.  With the orbit table, work-groups
   // are renumbered so that the ones an XCD runs side by side (linear ids are dealt round-robin
@@ -109,27 +121,35 @@ void outs_kernel(OutsArgs a) {
   __syncthreads();
 
   // ---- addressing of A ------------------------------------------------------------------
-  const int col0 = (int)jt * (WCOLS * NW) + wave * WCOLS + 4 * (lane & 31);
+  constexpr int WC = UNAL ? WCOLS - 4 : WCOLS;  // columns per wave
+  const int col0 = (int)jt * (WC * NW) + wave * WC + 4 * (lane & 31);
+  const bool stores = col0 < a.n && (!UNAL || (lane & 31) < 31);
   const char* Abase = reinterpret_cast<const char*>(a.A);
   const int64_t row_bytes = a.lda * (int64_t)sizeof(T);
   // a lane whose columns all lie at or beyond n gets an offset outside every descriptor range:
-  // its loads return 0 and move no data
-  const uint32_t voff0 = col0 < a.n ? (uint32_t)(((int64_t)(kg * 8) * a.lda + col0) * (int64_t)sizeof(T))
-                                    : 0x80000000u;
-  uint32_t soff[8];  // loop-invariant scalar offsets of the 8 rows of a k-step
+  // its loads return 0 and move no data (UNAL: the lane above the last column may hold half of it)
+  const uint32_t voff0 = col0 < a.n + (UNAL ? 4 : 0) ? (uint32_t)(((int64_t)(kg * 8) * a.lda + col0) * (int64_t)sizeof(T))
+                                                     : 0x80000000u;
+  // scalar offsets of the 8 rows of a k-step: loop-invariant, but for the dword that an unaligned row starts in
+  uint32_t soff[8];
+  auto set_soff = [&](uint32_t odd) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) soff[j] = (uint32_t)j * (uint32_t)row_bytes;
+    for (int j = 0; j < 8; ++j) soff[j] = ((uint32_t)j * (uint32_t)row_bytes + odd) & (UNAL ? ~3u : ~0u);
+  };
   const uint32_t kstep_bytes = 16u * (uint32_t)row_bytes;
-  // Descriptor over the rows of one input block; rows at or beyond d (zero padding of a partly
-  // filled last block) and rows of a block's last stage at or beyond Bc lie outside its range and
-  // read as 0.  The range ends with the last valid row's columns rounded up to the 4-column vector.
-  auto make_rsrc = [&](uint32_t hb) {
+  // Descriptor over the rows of one input block, from the dword that holds its first element (`odd`: the byte of that
+  // element inside it); rows at or beyond d (zero padding of a partly filled last block) and rows of a block's last
+  // stage at or beyond Bc lie outside its range and read as 0 (UNAL: the first of them may share a dword with the last
+  // valid row; they are zeroed where they are used).  The range ends with the last valid row's columns, rounded up to
+  // the 4-column vector or, where rows are not aligned to that, to the dword of column n-1.
+  auto make_rsrc = [&](uint32_t hb, uint32_t* odd) {
     const int64_t first_row = (int64_t)hb * p.Bc;
     const int64_t valid = min((int64_t)p.Bc, p.d - first_row);
-    const int64_t ncols = ((int64_t)a.n + 3) & ~(int64_t)3;
-    const int64_t bytes = valid > 0 ? (valid - 1) * row_bytes + ncols * (int64_t)sizeof(T) : 0;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Abase + first_row * row_bytes), 0, (int)bytes,
-                                             0x00020000);
+    const char* first = Abase + first_row * row_bytes;
+    *odd = UNAL ? (uint32_t)(uintptr_t)first & 2u : 0u;
+    const int64_t ncols = a.vec4 ? ((int64_t)a.n + 3) & ~(int64_t)3 : (int64_t)a.n;
+    const int64_t bytes = valid > 0 ? (*odd + (valid - 1) * row_bytes + ncols * (int64_t)sizeof(T) + 3) & ~(int64_t)3 : 0;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first - *odd), 0, (int)bytes, 0x00020000);
   };
 
   f32x16 acc[MT][4];
@@ -145,8 +165,10 @@ void outs_kernel(OutsArgs a) {
   const uint32_t spb = (uint32_t)a.spb;
   const uint32_t t0 = blockIdx.z * (uint32_t)a.stages;  // first stage of this work-group
   uint32_t f_us = t0 % spb, f_l = t0 / spb;
+  uint32_t f_odd;
+  __amdgpu_buffer_rsrc_t f_rs = make_rsrc(__builtin_amdgcn_readfirstlane(s_hblk[f_l]), &f_odd);
+  set_soff(f_odd);
   uint32_t f_voff = voff0 + f_us * (uint32_t)KSTEPS * kstep_bytes;
-  __amdgpu_buffer_rsrc_t f_rs = make_rsrc(__builtin_amdgcn_readfirstlane(s_hblk[f_l]));
   V ld[PFD][8];
 #ifdef FS_ABLATE_LOADS
   bool loads_on = true;  // ablation build: only the prologue loads A, the ring keeps that data
@@ -164,7 +186,10 @@ void outs_kernel(OutsArgs a) {
     if (++f_us == spb) {
       f_us = 0;
       f_voff = voff0;
-      if (++f_l < p.kappa) f_rs = make_rsrc(__builtin_amdgcn_readfirstlane(s_hblk[f_l]));
+      if (++f_l < p.kappa) {
+        f_rs = make_rsrc(__builtin_amdgcn_readfirstlane(s_hblk[f_l]), &f_odd);
+        if constexpr (UNAL) set_soff(f_odd);
+      }
     }
   };
   // Phi (one stage ahead): key of the block, stage in block
@@ -220,11 +245,41 @@ void outs_kernel(OutsArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
   };
 
-  // Ragged last column tile: a lane's 4-column vector may straddle column n.  What it then loads
-  // beyond n is the row's own padding (lda is a multiple of 4, so the memory is the caller's), and
-  // it needs no masking: column c of the lane feeds only the accumulators of column col0 + c (a
-  // column of a matrix product depends on that column of the right operand alone), and columns at
-  // or beyond n are never stored.
+  // Ragged last column tile: what a lane loads beyond column n-1 is the row's own padding, or the start of the next row,
+  // and needs no masking: column c of the lane feeds only the accumulators of column col0 + c (a column of a matrix
+  // product depends on that column of the right operand alone), and columns at or beyond n are never stored.
+
+  // UNAL, of the stage being used: stage in its block, block number, the byte of the block's first element in its dword,
+  // its rows left before the end of the block or row d
+  uint32_t c_us = t0 % spb, c_l = t0 / spb, c_odd = 0;
+  int c_rows = KC;
+  auto stage_begin = [&]() {
+    if constexpr (UNAL) {
+      const int64_t first_row = (int64_t)__builtin_amdgcn_readfirstlane(s_hblk[c_l]) * p.Bc;
+      c_odd = (uint32_t)(uintptr_t)(Abase + first_row * row_bytes) & 2u;
+      c_rows = (int)min((int64_t)KC, min((int64_t)p.Bc, p.d - first_row) - (int64_t)c_us * KC);
+      if (++c_us == spb) { c_us = 0; ++c_l; }
+    }
+  };
+  auto align_rows = [&](V (&cur)[8], V (&r)[8], int ks) {
+    if constexpr (UNAL) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t sh = ((c_odd + (uint32_t)j * (uint32_t)row_bytes) & 2u) << 3;
+        const uint32_t above = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)cur[j].x, 0x130, 0xf, 0xf, true);  // wave_shl:1
+        r[j].x = __builtin_amdgcn_alignbit(cur[j].y, cur[j].x, sh);
+        r[j].y = __builtin_amdgcn_alignbit(above, cur[j].y, sh);
+      }
+      if (c_rows < KC) {  // wave-uniform: the last stage of a partly filled block
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (ks * 16 + kg * 8 + j >= c_rows) r[j].x = r[j].y = 0u;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) r[j] = cur[j];
+    }
+  };
 
   uint4 pa2[2][MT];  // Phi operands of the current and of the next k-step
   auto read_pa = [&](const uint16_t* tile, int ks, uint4 (&dst)[MT]) {
@@ -241,6 +296,7 @@ void outs_kernel(OutsArgs a) {
     constexpr bool FILL = decltype(fill_tag)::value;
     uint16_t* cur_tile = s_phi + PAR * TILE;
     uint16_t* fill_tile = s_phi + (1 - PAR) * TILE;
+    stage_begin();
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
       V(&cur)[8] = ld[(PFS > 1 ? PAR * KSTEPS : 0) + ks];
@@ -252,7 +308,9 @@ void outs_kernel(OutsArgs a) {
       if (ks + 1 < KSTEPS) read_pa(cur_tile, ks + 1, pn);
       else if constexpr (FILL) read_pa(fill_tile, 0, pn);
       uint4 op[4];
-      make_ops(cur, op);
+      V rows[8];
+      align_rows(cur, rows, ks);
+      make_ops(rows, op);
       if constexpr (FETCH) issue(cur);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
@@ -314,11 +372,17 @@ void outs_kernel(OutsArgs a) {
   // ---- epilogue: scale, convert, store ------------------------------------------------------------
   // accumulator register i of tile (mt, c) holds block row mt*32 + 8*(i/4) + 4*kg + i%4 of column
   // col0 + c
-  if (col0 >= a.n) return;
+  if (!stores) return;
+  // (MT = 4: keeps these tiles in the accumulation registers until they are used.  Left to itself the compiler moves all
+  // of them, by the sixteen and for every way out of the kernel at once, and spills a hundred.)
+  auto hold = [&](int mt) {
+    if constexpr (MT == 4) asm volatile("" : "+a"(acc[mt][0]), "+a"(acc[mt][1]), "+a"(acc[mt][2]), "+a"(acc[mt][3]));
+  };
   if (a.zsplit > 1) {  // a partial sum: plane blockIdx.z (ldw is a multiple of 4 and col0 + 3 < ldw)
     float* plane = a.ws + (int64_t)blockIdx.z * p.k * a.ldw;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
+      hold(mt);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const uint32_t row = (uint32_t)(mt * 32 + 8 * (i >> 2) + 4 * kg + (i & 3));
@@ -328,23 +392,34 @@ void outs_kernel(OutsArgs a) {
     }
     return;
   }
+  // (the choice is the wave's, once; a scale of its own per copy and rows kept apart, or the 256 products of both copies
+  // are formed ahead of the choice and spill)
+  auto store = [&](auto whole_tag) {
+    float scale = p.scale;
+    asm volatile("" : "+v"(scale));
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
+      hold(mt);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t row = (uint32_t)(mt * 32 + 8 * (i >> 2) + 4 * kg + (i & 3));
-      float v[4] = {acc[mt][0][i] * p.scale, acc[mt][1][i] * p.scale, acc[mt][2][i] * p.scale,
-                    acc[mt][3][i] * p.scale};
-      T* dst = reinterpret_cast<T*>(a.out) + ((int64_t)blk * p.Br + row) * a.ldo + col0;
-      if (a.out_vec && col0 + 3 < a.n) {
-        *reinterpret_cast<uint2*>(dst) = pack4<T>(v);
-      } else {
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t row = (uint32_t)(mt * 32 + 8 * (i >> 2) + 4 * kg + (i & 3));
+        const float v[4] = {acc[mt][0][i] * scale, acc[mt][1][i] * scale, acc[mt][2][i] * scale, acc[mt][3][i] * scale};
+        T* dst = reinterpret_cast<T*>(a.out) + ((int64_t)blk * p.Br + row) * a.ldo + col0;
+        if constexpr (decltype(whole_tag)::value) {  // (global memory is written at any address)
+          typedef uint32_t U2 __attribute__((ext_vector_type(2), aligned(2)));
+          const uint2 w = pack4<T>(v);
+          *reinterpret_cast<U2*>(dst) = U2{w.x, w.y};
+        } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (col0 + c < a.n) Elt<T>::store(dst + c, v[c]);
+          for (int c = 0; c < 4; ++c)
+            if (col0 + c < a.n) Elt<T>::store(dst + c, v[c]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-  }
+  };
+  if ((int)jt * (WC * NW) + (wave + 1) * WC <= a.n) store(std::true_type{});
+  else store(std::false_type{});
 }
 
 template <auto kernel>
@@ -354,21 +429,22 @@ hipError_t go(dim3 grid, unsigned threads, size_t lds, hipStream_t st, const Out
 }
 
 template <typename T, int MT>
-hipError_t launch_t(int nw, dim3 grid, size_t lds, hipStream_t st, const OutsArgs& a) {
-  if (nw == 4) return go<outs_kernel<T, MT, 4>>(grid, 256, lds, st, a);
-  return go<outs_kernel<T, MT, 2>>(grid, 128, lds, st, a);
+hipError_t launch_t(int nw, bool unal, dim3 grid, size_t lds, hipStream_t st, const OutsArgs& a) {
+  if (nw == 4)
+    return unal ? go<outs_kernel<T, MT, 4, true>>(grid, 256, lds, st, a) : go<outs_kernel<T, MT, 4, false>>(grid, 256, lds, st, a);
+  return unal ? go<outs_kernel<T, MT, 2, true>>(grid, 128, lds, st, a) : go<outs_kernel<T, MT, 2, false>>(grid, 128, lds, st, a);
 }
 
 }  // namespace
 
 // Shapes this kernel takes (the caller has already chosen the output-stationary decomposition
-// without slices, and the row split): 16-bit type, Br = 32, 64 or 128, vector-aligned A, an even
+// without slices, and the row split): 16-bit type, Br = 32, 64 or 128, any alignment, an even
 // number >= 4 of stages, more than one wave of columns, offsets that fit 32 bits.
 bool outs_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n, fs_dtype dt, int zsplit) {
   if (dt == FS_F32) return false;
   if (p.Br != 32 && p.Br != 64 && p.Br != 128) return false;
   if (p.kappa > (uint32_t)MAX_KAPPA || n <= WCOLS) return false;
-  if ((uintptr_t)A % 8 || (lda * 2) % 8) return false;
+  if ((uintptr_t)A % 2) return false;
   const int64_t spb = ((int64_t)p.Bc + KC - 1) / KC;
   const int64_t T = spb * p.kappa;
   if (T < 4 || T % 2) return false;
@@ -380,7 +456,7 @@ bool outs_supported(const SketchParams& p, const void* A, int64_t lda, int64_t n
   if ((16 * lda + n) * 2 >= ((int64_t)1 << 31)) return false;
   if (spb * KC * lda * 2 >= ((int64_t)1 << 31)) return false;
   const int nw = n > 2 * WCOLS ? 4 : 2;
-  if ((n + WCOLS * nw - 1) / (WCOLS * nw) > 65535) return false;
+  if ((n + (WCOLS - 4) * nw - 1) / ((WCOLS - 4) * nw) > 65535) return false;
   return true;
 }
 
@@ -391,12 +467,13 @@ hipError_t launch_outs(const SketchParams& p, const void* A, int64_t lda, int64_
   a.p = p; a.A = A; a.out = out; a.pos2blk = orbit;
   a.lda = lda; a.ldo = ldo; a.n = (int)n;
   a.spb = (int)(((int64_t)p.Bc + KC - 1) / KC);
-  a.out_vec = ((uintptr_t)out % 8 == 0 && (ldo * 2) % 8 == 0) ? 1 : 0;
   a.zsplit = zsplit; a.stages = (int)outs_stages((int64_t)a.spb * p.kappa, zsplit); a.ws = ws; a.ldw = ldw;
   if (zsplit > 1 && (!ws || ldw % 4 || ldw < n)) return hipErrorInvalidValue;
   const int nw = n > 2 * WCOLS ? 4 : 2;
   const int mt = (int)p.Br / 32;
-  const int tnw = WCOLS * nw;
+  a.vec4 = !((uintptr_t)A % 8 || (lda * 2) % 8);
+  const bool unal = (uintptr_t)A % 4 || (lda * 2) % 4;
+  const int tnw = (unal ? WCOLS - 4 : WCOLS) * nw;
   const unsigned col_tiles = (unsigned)((n + tnw - 1) / tnw);
   const size_t lds = 2 * MAX_KAPPA * 4 + 2 * (size_t)(32 * mt) * PHI_LD * 2;
   dim3 grid(p.M, col_tiles, zsplit);
@@ -406,9 +483,9 @@ hipError_t launch_outs(const SketchParams& p, const void* A, int64_t lda, int64_
   if (ev.start) (void)hipEventRecord(ev.start, st);
   hipError_t e;
 #define FS_T(T)                                                           \
-  (mt == 4 ? launch_t<T, 4>(nw, grid, lds, st, a)                         \
-   : mt == 2 ? launch_t<T, 2>(nw, grid, lds, st, a)                       \
-             : launch_t<T, 1>(nw, grid, lds, st, a))
+  (mt == 4 ? launch_t<T, 4>(nw, unal, grid, lds, st, a)                         \
+   : mt == 2 ? launch_t<T, 2>(nw, unal, grid, lds, st, a)                       \
+             : launch_t<T, 1>(nw, unal, grid, lds, st, a))
   if (dt == FS_BF16) e = FS_T(uint16_t); else e = FS_T(f16);
 #undef FS_T
   if (ev.stop) (void)hipEventRecord(ev.stop, st);

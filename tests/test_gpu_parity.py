@@ -1502,3 +1502,36 @@ def test_few_vectors_match_oracle_in_both_layouts(case, n, dtype):
                 check(whole.apply(X), ref, dtype, "few vectors, half the workspace")
             except B.FlashSketchError as e:        # below what the matrix-core kernel must find: refused, as ever
                 assert e.status == 3
+
+
+# --------------- shared Phi tiles: rows that start at any element ---------
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16], ids=["bf16", "f16"])
+@pytest.mark.parametrize("params,n,pad,first,kernel", [
+    ((65536, 4096, 1024, 64, 2, 4), 1531, 0, 1, "2,4>"),                       # five whole column tiles and three columns
+    ((65536, 4096, 1024, 64, 2, 4), 1028, 1, 0, "2,4>"),                       # the packed copy takes the same kernel
+    ((65501, 2048, 1024, 32, 6, 2), 1537, 0, 0, "1,4>"),                       # one column in the last tile, a partly filled last block
+    ((32000, 4096, 1001, 128, 3, 8), 4099, 2, 1, "4,4>"),                      # odd Bc: blocks start in either half of a dword
+    ((20480, 10240, 256, 128, 4, 8), 516, 1, 0, "4,4>"),                       # 80 blocks, one vector in the last tile
+])
+def test_shared_phi_kernel_takes_rows_of_any_alignment(params, n, pad, first, kernel, dtype):
+    print("shared Phi, unaligned", params, n, dtype, flush=True)
+    d, k = params[0], params[1]
+    flat = torch.full((d * (n + pad) + 8,), float("nan"), device=DEV, dtype=dtype)
+    A = flat[first:first + d * (n + pad)].view(d, n + pad)[:, :n]
+    A.copy_(torch.randn((d, n), generator=torch.Generator(device=DEV).manual_seed(n), device=DEV))
+    sk = B.Sketch(*params, seed=8)
+    buf = torch.full((k, n + 1), float("nan"), device=DEV, dtype=dtype)
+    out = sk.apply(A, buf[:, :n])
+    torch.cuda.synchronize()
+    name = "bf16" if dtype == torch.bfloat16 else "f16"
+    assert sk.info().last_kernel.decode() == f"outs_kernel<{name},{kernel}"
+    assert torch.isnan(buf[:, n:].float()).all(), "wrote outside the n output columns"
+    cols = np.unique(np.r_[0, 3, 127, 128, 511, 512, np.arange(n - 9, n), np.random.default_rng(1).integers(0, n, 8)])
+    idx = torch.from_numpy(cols).to(DEV)
+    ref = O.apply(oracle_csc(params, 8), host64(A[:, idx]))
+    check(out[:, idx], ref, dtype, "shared Phi kernel, unaligned")
+    diff = np.abs(host64(out[:, idx]) - ref)
+    assert (diff <= ETOL[dtype] * (np.abs(ref) + np.sqrt((ref ** 2).mean()))).all()
+    aligned = torch.zeros((d, (n + 3) // 4 * 4), device=DEV, dtype=dtype)[:, :n]
+    aligned.copy_(A)
+    assert torch.equal(sk.apply(aligned), out)      # same order of summation
