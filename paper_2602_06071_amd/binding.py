@@ -1,4 +1,5 @@
-"""ctypes binding of include/flashsketch.h: same names, argument marshalling only.
+"""Binding of include/flashsketch.h: same names, argument marshalling only (ctypes; the two apply calls through a
+native module where it is built).
 
 PyTorch supplies device memory (``tensor.data_ptr()``) and the HIP stream
 (``torch.cuda.current_stream().cuda_stream``); nothing is computed here.
@@ -114,6 +115,22 @@ def _stream_ptr(stream) -> int:
     return int(stream.cuda_stream)
 
 
+def _native_call():
+    """The native form of Sketch.apply and apply_rows (csrc/torch_call.cpp: same checks, same calls), or None where
+    it has not been built; the Python code below then does the same through ctypes."""
+    try:
+        from . import _torch_call
+    except ImportError:
+        return None
+    if _raw_stream is None or _current_device is None:
+        return None
+    _torch_call.setup(C.cast(lib.fs_sketch_apply_ld, C.c_void_p).value, C.cast(lib.fs_sketch_apply_rows, C.c_void_p).value,
+                      _current_device, _raw_stream)
+    return _torch_call.call
+
+
+_call = _native_call()
+
 _deferred: list = []  # handles whose destruction was postponed (see Sketch.__del__)
 
 
@@ -206,6 +223,12 @@ class Sketch:
 
     def apply(self, A: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
         """out = S @ A for a 2-D row-major view A (unit column stride)."""
+        if stream is None and _call is not None:
+            r = _call(False, self._h.value, self.d, self.k, A, out)
+            if r is not None:
+                if r.__class__ is int:
+                    _check(r, "fs_sketch_apply_ld")
+                return r
         if A.dim() != 2 or A.shape[0] != self.d or A.stride(1) != 1 and A.shape[1] > 1:
             raise ValueError("A must be d x n with contiguous rows")
         n = A.shape[1]
@@ -233,6 +256,12 @@ class Sketch:
     def apply_rows(self, G: torch.Tensor, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
         """out (n x k) = G @ S^T for a 2-D row-major G (n x d, unit column stride): every row of G
         is one vector to sketch."""
+        if stream is None and _call is not None:
+            r = _call(True, self._h.value, self.d, self.k, G, out)
+            if r is not None:
+                if r.__class__ is int:
+                    _check(r, "fs_sketch_apply_rows")
+                return r
         if G.dim() != 2 or G.shape[1] != self.d or G.stride(1) != 1:
             raise ValueError("G must be n x d with contiguous rows")
         n = G.shape[0]

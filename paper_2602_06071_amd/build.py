@@ -1,4 +1,5 @@
-"""Builds libflashsketch.so for gfx950 with hipcc, in-tree, next to this file.
+"""Builds libflashsketch.so for gfx950 with hipcc, and _torch_call.so (the binding's apply calls, host code) with the
+C++ compiler, in-tree, next to this file.
 
     python -m paper_2602_06071_amd.build [--force] [--define NAME]... [--output PATH]
 
@@ -22,6 +23,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libflashsketch.so")
+CALL_SRC, CALL = os.path.join(CSRC, "torch_call.cpp"), os.path.join(HERE, "_torch_call.so")
 
 ARCH = "gfx950"
 # Packed-fp32 VALU forms are kept off for every device translation unit.
@@ -44,6 +46,28 @@ def _stale(src: str, obj: str, headers: list[str]) -> bool:
         return True
     t = os.path.getmtime(obj)
     return any(os.path.getmtime(f) > t for f in [src, __file__] + headers)
+
+
+def build_call(force: bool = False, verbose: bool = True) -> None:
+    """The CPython module of csrc/torch_call.cpp, against the headers of the installed torch."""
+    import sysconfig
+
+    import torch
+    header = os.path.join(HERE, "..", "include", "flashsketch.h")
+    if not force and not _stale(CALL_SRC, CALL, [header]):
+        return
+    base = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(base, "include"), "-I" + os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], CALL_SRC, "-o", CALL,
+           "-L" + os.path.join(base, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode:
+        sys.stderr.write(r.stderr)
+        raise RuntimeError(f"{cmd[0]} failed on {CALL_SRC}")
+    if verbose:
+        print(f"[build] linked {CALL}")
 
 
 def build(force: bool = False, verbose: bool = True, defines: tuple = (), output: str | None = None) -> str:
@@ -89,6 +113,8 @@ def build(force: bool = False, verbose: bool = True, defines: tuple = (), output
             raise RuntimeError("link failed")
         if verbose:
             print(f"[build] linked {LIB}")
+    if not output:
+        build_call(force, verbose)
     return LIB
 
 

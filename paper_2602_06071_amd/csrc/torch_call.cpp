@@ -1,0 +1,118 @@
+// The two apply calls of binding.py without ctypes: a CPython module that reads the tensors' sizes, strides and
+// addresses, allocates the result and calls the C ABI.  It takes plain CUDA (HIP) tensors that the call
+// accepts and hands everything else -- subclasses, active torch modes, other devices, types and
+// layouts, and every argument error -- back to the Python code, which then raises what it always did.
+//
+// Why: argument marshalling in Python and ctypes was half of what a small call costs the host.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "../../include/flashsketch.h"
+
+namespace {
+
+using Apply = fs_status (*)(fs_sketch_t, const void*, int64_t, int64_t, void*, int64_t, fs_dtype, void*);
+
+// fs_sketch_apply_ld, fs_sketch_apply_rows; torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+Apply g_apply[2];
+PyObject *g_device, *g_stream;
+
+bool dtype_code(at::ScalarType t, fs_dtype* code) {
+  switch (t) {
+    case at::kFloat: *code = FS_F32; return true;
+    case at::kBFloat16: *code = FS_BF16; return true;
+    case at::kHalf: *code = FS_F16; return true;
+    default: return false;
+  }
+}
+
+bool plain(PyObject* o) {
+  if (!THPVariable_CheckExact(o)) return false;
+  const at::Tensor& t = THPVariable_Unpack(o);
+  return t.is_cuda() && t.layout() == at::kStrided && t.has_storage() && t.dim() == 2 && !t.is_conj() && !t.is_neg();
+}
+
+PyObject* setup(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  if (n != 4) {
+    PyErr_SetString(PyExc_TypeError, "setup(apply_ld, apply_rows, get_device, get_stream)");
+    return nullptr;
+  }
+  for (int i = 0; i < 2; ++i) {
+    g_apply[i] = reinterpret_cast<Apply>(PyLong_AsVoidPtr(args[i]));
+    if (PyErr_Occurred()) return nullptr;
+  }
+  Py_INCREF(args[2]);
+  Py_INCREF(args[3]);
+  Py_XSETREF(g_device, args[2]);
+  Py_XSETREF(g_stream, args[3]);
+  Py_RETURN_NONE;
+}
+
+// call(rows, handle, d, k, X, out or None) -> the result, None (not a call for this module) or an fs_status
+PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
+  HANDLE_TH_ERRORS
+  if (nargs != 6 || !plain(args[4]) || (args[5] != Py_None && !plain(args[5])) || at::impl::torch_function_mode_enabled() ||
+      c10::impl::TorchDispatchModeTLS::any_modes_set())
+    Py_RETURN_NONE;
+  const int rows = args[0] == Py_True;
+  fs_sketch_t h = reinterpret_cast<fs_sketch_t>(args[1] == Py_None ? nullptr : PyLong_AsVoidPtr(args[1]));
+  const int64_t d = PyLong_AsLongLong(args[2]), k = PyLong_AsLongLong(args[3]);
+  if (PyErr_Occurred()) return nullptr;
+  const at::Tensor& x = THPVariable_Unpack(args[4]);
+  fs_dtype dt;
+  if (!dtype_code(x.scalar_type(), &dt)) Py_RETURN_NONE;
+  const int64_t n = rows ? x.size(0) : x.size(1);
+  if ((rows ? x.size(1) : x.size(0)) != d) Py_RETURN_NONE;
+  if (x.stride(1) != 1 && (rows || n > 1)) Py_RETURN_NONE;
+  const int64_t o0 = rows ? n : k, o1 = rows ? k : n;
+  at::Tensor out;
+  if (args[5] != Py_None) {
+    out = THPVariable_Unpack(args[5]);
+    if (out.size(0) != o0 || out.size(1) != o1 || out.scalar_type() != x.scalar_type() || (out.stride(1) != 1 && (rows || n > 1)))
+      Py_RETURN_NONE;
+  }
+  // the current device's current stream, as the calls through Python take it
+  PyObject* dev = PyObject_CallNoArgs(g_device);
+  if (!dev) return nullptr;
+  PyObject* raw = PyObject_CallOneArg(g_stream, dev);
+  Py_DECREF(dev);
+  if (!raw) return nullptr;
+  void* stream = PyLong_AsVoidPtr(raw);
+  Py_DECREF(raw);
+  if (PyErr_Occurred()) return nullptr;
+
+  fs_status st;
+  {
+    struct NoGil {  // (ctypes let go of it too; restored where at::empty throws)
+      PyThreadState* s = PyEval_SaveThread();
+      ~NoGil() { PyEval_RestoreThread(s); }
+    } no_gil;
+    if (!out.defined()) out = at::empty({o0, o1}, x.options());
+    // (a single row may have any stride)
+    const int64_t ldx = rows && n == 1 && x.stride(0) < d ? d : x.stride(0);
+    const int64_t ldo = rows && n == 1 && out.stride(0) < k ? k : out.stride(0);
+    st = g_apply[rows](h, x.const_data_ptr(), ldx, n, out.mutable_data_ptr(), ldo, dt, stream);
+  }
+  if (st != FS_OK) return PyLong_FromLong((long)st);
+  if (args[5] != Py_None) {
+    Py_INCREF(args[5]);
+    return args[5];
+  }
+  return THPVariable_Wrap(std::move(out));
+  END_HANDLE_TH_ERRORS
+}
+
+PyMethodDef methods[] = {
+    {"setup", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(setup)), METH_FASTCALL, nullptr},
+    {"call", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(call)), METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_torch_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__torch_call() { return PyModule_Create(&module); }

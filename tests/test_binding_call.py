@@ -1,0 +1,97 @@
+"""The native form of the binding's apply calls against its Python form (through ctypes)."""
+import pytest
+import torch
+
+from paper_2602_06071_amd import binding as B
+
+native = pytest.mark.skipif(B._call is None, reason="the native call module is not built")
+PARAMS = (4001, 256, 501, 32, 2, 4)
+
+
+class Sub(torch.Tensor):
+    pass
+
+
+@native
+def test_what_is_not_a_plain_device_tensor_is_left_to_python():
+    sk = B.Sketch(*PARAMS)
+    for x in (torch.zeros(4001, 3), torch.zeros(4001, 3).as_subclass(Sub), torch.zeros(3), "x", None,
+              torch.zeros(4001, 3, device="meta"), torch.zeros(4001, 3).to_sparse()):
+        assert B._call(False, sk._h.value, sk.d, sk.k, x, None) is None
+    with pytest.raises(ValueError):
+        sk.apply(torch.zeros(10, 3))
+    with pytest.raises(ValueError):
+        sk.apply_rows(torch.zeros(3, 10))
+
+
+@native
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [False, True], ids=["columns", "rows"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16], ids=["f32", "bf16", "f16"])
+def test_native_and_python_calls_do_the_same(rows, dtype, monkeypatch):
+    sk = B.Sketch(*PARAMS, seed=3)
+    apply = sk.apply_rows if rows else sk.apply
+    turn = (lambda t: t) if rows else (lambda t: t.t())
+    shape = (lambda n, m: (n, m)) if rows else (lambda n, m: (m, n))
+    big = torch.randn(shape(9, 4004), device="cuda").to(dtype)
+    whole = big[:, 1:4002] if rows else big[1:4002]
+    inputs = [whole, whole[2:5] if rows else whole[:, 2:5], whole[:1] if rows else whole[:, :1], whole[:0] if rows else whole[:, :0],
+              whole.contiguous()]
+    side = torch.cuda.Stream()
+
+    def results():
+        got = []
+        for x in inputs:
+            n = x.shape[0] if rows else x.shape[1]
+            got.append(apply(x))
+            wide = torch.full(shape(n, 256 + 3) if rows else (256, n + 3), float("nan"), device="cuda", dtype=dtype)
+            out = wide[:, :256] if rows else wide[:, :n]
+            assert apply(x, out) is out
+            got.append(wide)
+            with torch.cuda.stream(side):
+                got.append(apply(x))
+            side.synchronize()
+        with torch.device("cpu"):                   # a torch function mode
+            got.append(apply(inputs[0]))
+        got.append(apply(inputs[0].requires_grad_()).detach())
+        inputs[0].requires_grad_(False)
+        return got
+
+    a = results()
+    assert all(t.device.type == "cuda" and t.dtype == dtype for t in a)
+    bad = [(turn(whole)[..., :7], ValueError), (whole.double(), TypeError), (whole[None], ValueError)]
+    outs = [(torch.empty(shape(9, 255), device="cuda", dtype=dtype), ValueError),
+            (torch.empty(shape(9, 256), device="cuda", dtype=torch.float64), ValueError),
+            (torch.empty(shape(9, 256)[::-1], device="cuda", dtype=dtype).t(), ValueError)]
+
+    def errors():
+        kinds = []
+        for args in [(x, None) for x, _ in bad] + [(whole, o) for o, _ in outs]:
+            with pytest.raises((ValueError, TypeError)) as e:
+                apply(*args)
+            kinds.append((type(e.value), str(e.value)))
+        return kinds
+
+    native_errors = errors()
+    assert [k for k, _ in native_errors] == [k for _, k in bad + outs]
+    monkeypatch.setattr(B, "_call", None)
+    assert errors() == native_errors
+    b = results()
+    assert all(torch.equal(x.nan_to_num(), y.nan_to_num()) and x.shape == y.shape and x.stride() == y.stride() for x, y in zip(a, b))
+    monkeypatch.undo()
+    sk.close()
+    with pytest.raises(B.FlashSketchError) as e:
+        apply(whole)
+    assert e.value.status == 1
+
+
+@native
+@pytest.mark.gpu
+def test_native_call_under_vmap_is_left_to_python():
+    sk = B.Sketch(*PARAMS)
+    x = torch.randn(2, 4001, 3, device="cuda")
+
+    def f(a):
+        assert B._call(False, sk._h.value, sk.d, sk.k, a, None) is None
+        return a
+    torch.vmap(f)(x)
