@@ -380,15 +380,28 @@ void ksplit_kernel(MfmaArgs a) {
       if (col >= a.n) continue;
       const float4* src = reinterpret_cast<const float4*>(mbuf) + e;
       float4 v = src[0];
-      for (int w = 1; w < active; ++w) {
-        const float4 o = src[(size_t)w * UNITS];
-        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+      if (!IN_STAT && p.kappa > 1) {
+        // (the kappa blocks' sums meet here, not in planes added one by one: in fp64, which keeps the error at
+        // that of the input-stationary form)
+        double x = v.x, y = v.y, z4 = v.z, q = v.w;
+        for (int w = 1; w < active; ++w) {
+          const float4 o = src[(size_t)w * UNITS];
+          x += (double)o.x; y += (double)o.y; z4 += (double)o.z; q += (double)o.w;
+        }
+        v = make_float4((float)x, (float)y, (float)z4, (float)q);
+      } else {
+        for (int w = 1; w < active; ++w) {
+          const float4 o = src[(size_t)w * UNITS];
+          v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+        }
       }
       if (IN_STAT) {
         const uint32_t slot = row_s >> lbr, r = row_s & ((1u << lbr) - 1u);
         if (slot >= kap || r >= p.Br) continue;  // idle rows: above the stacked slots, or above Br in a slot
         float* dst = a.ws + (((int64_t)z * p.kappa + slot0 + slot) * p.k + (int64_t)s_blk[slot] * p.Br + r) * a.ldw + col;
         *reinterpret_cast<float4*>(dst) = v;
+      } else if (row_s >= p.Br) {  // idle rows of a block below the tile height
+        continue;
       } else if (a.zsplit > 1) {
         float* dst = a.ws + ((int64_t)z * p.k + (int64_t)blk * p.Br + row_s) * a.ldw + col;
         *reinterpret_cast<float4*>(dst) = v;

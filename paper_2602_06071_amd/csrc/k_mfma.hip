@@ -372,6 +372,39 @@ Plan make_plan(const SketchParams& p, const void* A, int64_t lda, int64_t n, int
     // us per call, shared-Phi -> K-split, t_ks / t_old: bf16 5728 x 768, 32 blocks of 64 rows 22.3 -> 11.2, 0.30; bf16
     // 5120 x 176, 64 of 128 rows 28.2 -> 10.7, 0.25; half 19632 x 232, 16 of 64 rows 14.4 -> 8.4, 0.34; bf16 353920 x 208,
     // 128 of 64 rows 31.8 -> 40.7, 0.69; half 238432 x 1120, 32 of 32 rows 590 -> 600, 0.49)
+    // Few columns of a small input-stationary call: output-stationary it reads A kappa times and makes one block's Phi at a
+    // time, but stores the result itself, which spares the planes and the reduction's launch.  Taken while its time is at
+    // most 2 us above the other's without that launch, and short (beyond, the price of making Phi and converting
+    // A kappa times is not seen well enough).  us per call, one launch against two, by that difference: bf16 62421 x 8, 512
+    // blocks, kappa = 4 9.7 -> 6.6 (-1.6 us); fp32 5056 x 19, 16 blocks 9.3 -> 6.5 (0.8); fp32 46952 x 39, 64 blocks 10.0 -> 8.2 (1.9);
+    // half 30055 x 74, 32 blocks 9.6 -> 11.3 (3.1); bf16 680653 x 11, 512 blocks 22.4 -> 30.0 (5.0).  (fp32 up to kappa s = 8: one
+    // chain over more terms has a larger error than the blocks' planes added one by one, 1.06 times at 16, 1.2 at 32.)
+    if (n <= 128 && pl.in_stat && cpl && p.br_pow2 && p.Br <= 128 && p.kappa <= (uint32_t)MAX_KAPPA &&
+        (esz == 2 || (uint64_t)p.kappa * p.s <= 8)) {
+      const int omt = p.Br <= 32 ? 1 : (int)p.Br / 32, ototal = (int)((int64_t)p.kappa * blk_stages);
+      const double omfma = omt * 4 * (esz == 4 ? 3 : 1) * 32 / 2400.0;
+      double to = 0;
+      int oc = 0;
+      for (int c = n <= 32 ? 1 : n <= 64 ? 2 : 4; c >= 1; c /= 2) {
+        const int nw = ks_waves(omt, c);
+        int per_cu = (int)(kLdsBudget / ks_lds_bytes(omt, c));
+        const int by_regs = 4 * ks_waves_per_simd(omt, c) / nw;
+        if (by_regs < per_cu) per_cu = by_regs;
+        const SplitCost os{(double)p.M * ((n + 32 * c - 1) / (32 * c)), 0.19 + c * (omfma + conv_us),
+                           esz == 4 && c == 4 && omt <= 2 ? 1.6 : 0.8, 256.0 * per_cu * nw, a_us * (1 + 0.3 * (p.kappa - 1)), 0.0,
+                           1.0 + 0.25 * omt * c, nw, ototal, false};
+        const double t = os.at(1);
+        if (oc == 0 || t < 0.9 * to) { to = t; oc = c; }
+      }
+      if (to < t_ks + 2.0 && to < 6.0) {
+        pl.in_stat = false; pl.ks = true;
+        pl.mt = omt; pl.cpl = oc; pl.lds = ks_lds_bytes(omt, oc);
+        pl.groups = 1; pl.group_slots = (int)p.kappa;
+        pl.total = pl.stages = ototal; pl.zsplit = pl.z_priced = 1; pl.planes = 0;
+        pl.ok = true;
+        return pl;
+      }
+    }
     if (cpl && (n <= 64 || t_ks < (pl.outs || (shared_shape && n % 4 == 0) ? 0.45 : 0.8) * t_old)) {
       pl.ks = true; pl.outs = false;
       pl.cpl = cpl; pl.lds = ks_lds_bytes(pl.mt, cpl);

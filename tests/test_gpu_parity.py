@@ -1535,3 +1535,24 @@ def test_shared_phi_kernel_takes_rows_of_any_alignment(params, n, pad, first, ke
     aligned = torch.zeros((d, (n + 3) // 4 * 4), device=DEV, dtype=dtype)[:, :n]
     aligned.copy_(A)
     assert torch.equal(sk.apply(aligned), out)      # same order of summation
+
+
+# ---- few columns of small calls: one launch, blocks below the tile height, every kappa ----
+@DTYPES
+@pytest.mark.parametrize("params,n,pa,first", [
+    ((10105, 1024, 79, 8, 8, 2), 38, 0, 0),       # 8-row blocks in a 32-row tile, odd Bc, a partly filled last block
+    ((10105, 1024, 79, 8, 8, 2), 5, 1, 1),
+    ((11264, 512, 352, 16, 4, 8), 33, 0, 0),      # a column more than the tile
+    ((7803, 256, 122, 4, 2, 3), 64, 2, 1),
+    ((6144, 256, 48, 2, 16, 2), 20, 0, 0),        # one stage per block
+    ((4222, 128, 33, 1, 2, 1), 32, 0, 0),         # Br = 1
+    ((19901, 4096, 311, 64, 2, 2), 16, 0, 0),     # 64-row blocks
+    ((10105, 1024, 79, 8, 8, 2), 127, 0, 0),
+    ((5056, 512, 316, 32, 4, 5), 65, 3, 0),
+])
+def test_few_columns_of_a_small_call_are_stored_by_one_launch(params, n, pa, first, dtype):
+    check_ksplit(params, n, pa, first, dtype, "ksplit_kernel")
+    sk = B.Sketch(*params)
+    sk.apply(torch.zeros((params[0], n), device=DEV, dtype=dtype))
+    if dtype != torch.float32 or params[4] * params[5] <= 8:
+        assert sk.info().last_kernel.decode().endswith("out,->") and sk.info().last_mode == 1
