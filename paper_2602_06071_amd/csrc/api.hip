@@ -538,7 +538,7 @@ fs_status fs_sketch_plan(fs_sketch_t h, const void* A, int64_t ld, int64_t n, fs
         v = FS_VARIANT_MFMA;
         m = pl.out_stat ? 1 : 2;
         f = (pl.vec ? 0 : FS_PLAN_ELEMENT_LOADS) | (pl.nsub > 1 ? FS_PLAN_ROW_SLICES : 0) |
-            (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (pl.zsplit > 1 ? FS_PLAN_SPLIT : 0);
+            (pl.groups > 1 ? FS_PLAN_SLOT_GROUPS : 0) | (pl.zsplit > 1 || pl.nw > 1 ? FS_PLAN_SPLIT : 0);
         ws = rows_want(pl);
       }
     } else {

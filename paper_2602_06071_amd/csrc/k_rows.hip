@@ -12,7 +12,7 @@
 // probe -- and each 32-example tile is passed through a small padded LDS tile of the wave to
 // reach the operand order (LDS operations of one wave complete in order: no barrier).
 //
-//  * input-stationary (one wave = one work-group): (input block h, 32*ET examples, row split z)
+//  * input-stationary: (input block h, 32*ET examples, row split z)
 //    reads its K-range of G once and accumulates the kappa stacked destination blocks
 //    g_l = f^{-l}(h) (kappa*Br <= 32*MT MFMA columns); fp32 partial results stored by input
 //    block and a fixed-order gather-reduction give `out` without atomics on data;
@@ -21,14 +21,23 @@
 //    into the wave's own LDS tile [stacked row][64 + 8] (one tile: a stage reads all its
 //    operands first, then the tile is cleared and refilled behind those reads);
 //  * fp32 inputs: exact three-way bf16 split of the 8 values a lane holds, three MFMAs;
-//  * the prefetch ring holds whole example tiles (all lines of a tile are requested together).
+//  * the prefetch ring holds whole example tiles (all lines of a tile are requested together);
+//  * up to 64 examples: 1 to 8 waves of a work-group share (block, examples) and split its stages,
+//    each with tiles of its own, and their sums meet in LDS at the end (fp64, in wave order).  What
+//    bounds these calls is not memory but what a wave issues per stage (the hashes, the MFMAs of
+//    32 rows whatever n is) with few waves to overlap: fp32 24 x 1000003, kappa = 8 38.9 -> 32.5 us, of
+//    which the hashes of four slots side by side are 4; 60 random calls of 5 to 64 examples 1.16
+//    times as fast (0.92 to 2.0).
+//    Larger calls have waves enough without: one wave = one work-group.
 //
 // Shapes: power-of-two Br (kappa*Br <= 128: tile height 32, 64 or 128, rows above kappa*Br idle;
 // more: Br < 32 in groups of wiring slots, Br in {32, 64, 128} output-stationary), any Bc and
 // alignment.  Inputs must be finite (a dense product also multiplies by the zeros).
+#include <cmath>
 #include <type_traits>
 
 #include "handle.h"
+#include "lds_limit.h"
 #include "mfma_common.h"
 #include "mfma_plan.h"
 #include "spec.h"
@@ -47,9 +56,9 @@ struct RowsArgs {
   void* out;              // OUT mode: the result itself
   int64_t ldg, ldo;
   int n;        // examples
-  int stages;       // 64-entry stages per work-group (the last row split may have fewer)
+  int stages;       // 64-entry stages per wave (the last ones may have fewer or none)
   int total;        // stages of an input block (IN) or of the kappa blocks an output block reads (OUT)
-  int zsplit;       // row splits: split z takes the stages [z*stages, min((z+1)*stages, total))
+  int zsplit;       // row splits: wave w of nw in split z takes `stages` of them from (z*nw + w)*stages on
   int group_slots;  // IN: wiring slots one work-group stacks (grid.z = zsplit * slot groups)
   int nsub;         // OUT, Br > 128: 128-row slices of an output block (grid.y = example tiles * nsub)
   uint32_t log2_br;
@@ -76,12 +85,21 @@ struct RowsArgs {
 // descriptor per 32-example tile instead of one per wave (2 % slower on the gradient workload).
 constexpr int rows_waves_per_simd(int esz, int mt, int et) {
   if (et == 4) return (esz == 4 && mt >= 2) || mt == 4 ? 1 : 2;
-  if (et == 2) return esz == 4 && mt == 4 ? 1 : 2;
-  return mt == 4 ? 2 : mt == 2 ? (esz == 4 ? 2 : 3) : 3;
+  return et == 2 && esz == 4 && mt == 4 ? 1 : 2;
 }
+// Waves of a work-group at most, each with rows_lds_wave bytes behind the slot tables.
+constexpr int rows_waves(int esz, int mt, int et) { return et == 4 ? 1 : 4 * rows_waves_per_simd(esz, mt, et); }
+constexpr int kRowsTables = 2 * MAX_KAPPA * 4;
+constexpr size_t rows_lds_wave(int esz, int mt) { return (size_t)(32 * mt) * PHI_LD * 2 + 32 * (KC * esz + 16); }
+// fp32: the sum of a stage is made apart from the others (128 stacked rows leave no registers for it).
+constexpr bool rows_apart(int esz, int mt, int et) { return esz == 4 && mt < 4 && et == 1; }
+// ET = 1: stages in flight.  A handful of waves per SIMD with one stage each wait for memory most of the time;
+// with two waves per SIMD the registers hold four 16-bit stages, or two of fp32 or beside 128 stacked rows, or one
+// of fp32 beside 128.
+constexpr int rows_ahead(int esz, int mt) { return esz == 2 ? (mt == 4 ? 2 : 4) : mt == 4 ? 1 : 2; }
 enum RowsMode { kIn, kOut, kOutSplit };
 template <typename T, int MT, int ET, RowsMode MODE, bool UNAL = false, bool BIG = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(rows_waves_per_simd(sizeof(T), MT, ET))))
+__global__ __launch_bounds__(64 * rows_waves(sizeof(T), MT, ET)) __attribute__((amdgpu_waves_per_eu(rows_waves_per_simd(sizeof(T), MT, ET))))
 void rows_kernel(RowsArgs a) {
   constexpr bool OUT = MODE != kIn;
   constexpr int RWV = 32 * MT;         // tile height: kappa * Br stacked output rows, rounded up
@@ -95,12 +113,16 @@ void rows_kernel(RowsArgs a) {
   static_assert(NLD == KSTEPS * NV, "what a lane loads of a tile is what it uses as operands of a stage");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const SketchParams& p = a.p;
-  const int lane = (int)threadIdx.x;
+  const int lane = ET == 4 ? (int)threadIdx.x : (int)threadIdx.x & 63;
+  const int wave = ET == 4 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nw = ET == 4 ? 1 : (int)(blockDim.x >> 6);
   const int m = lane & 31, kg = lane >> 5;
   uint32_t* s_bk = reinterpret_cast<uint32_t*>(smem);   // [MAX_KAPPA] block keys per slot
   uint32_t* s_blk = s_bk + MAX_KAPPA;                   // [MAX_KAPPA] destination block g_l
-  uint16_t* s_phi = reinterpret_cast<uint16_t*>(smem + 2 * MAX_KAPPA * 4);
-  unsigned char* s_g = smem + 2 * MAX_KAPPA * 4 + TILE * 2;  // transposition tile: [32][GLD] bytes
+  constexpr int WAVE_LDS = TILE * 2 + 32 * GLD;         // of one wave
+  static_assert(WAVE_LDS == (int)rows_lds_wave(sizeof(T), MT), "what the host reserves");
+  uint16_t* s_phi = reinterpret_cast<uint16_t*>(smem + kRowsTables + wave * WAVE_LDS);
+  unsigned char* s_g = smem + kRowsTables + wave * WAVE_LDS + TILE * 2;  // transposition tile: [32][GLD] bytes
 
   // Which (block, example tile) this wave takes.  OUT with an orbit table: work-groups are
   // renumbered so that the ones an XCD runs side by side (the hardware deals linear ids
@@ -130,12 +152,14 @@ void rows_kernel(RowsArgs a) {
   const int z = OUT ? (int)blockIdx.z : (int)(blockIdx.z % (uint32_t)a.zsplit);
   const uint32_t slot0 = OUT ? 0u : (blockIdx.z / (uint32_t)a.zsplit) * (uint32_t)a.group_slots;
   const uint32_t kap = OUT ? p.kappa : min(p.kappa - slot0, (uint32_t)a.group_slots);
-  const int t_first = z * a.stages;
-  const int T_stages = min(a.stages, a.total - t_first);  // >= 1: the host picks zsplit = ceil(total / stages)
+  // (the host picks zsplit = ceil(total / (nw * stages)): only waves other than the first can find nothing left)
+  const int t_own = (z * nw + wave) * a.stages;
+  const int T_stages = ET == 4 ? min(a.stages, a.total - t_own) : max(0, min(a.stages, a.total - t_own));
+  const int t_first = T_stages > 0 || ET == 4 ? t_own : 0;
   const uint32_t lbr = a.log2_br;
 
   // slot tables and an empty tile
-  for (int sl = lane; sl < (int)kap; sl += 64) {
+  for (int sl = (int)threadIdx.x; sl < (int)kap; sl += 64 * nw) {
     uint32_t x = blk;
     if (remap) {
       const uint32_t l = (sl + p.kappa - (opos + 1) % p.kappa) % p.kappa;  // 0 .. kappa-1
@@ -153,7 +177,7 @@ void rows_kernel(RowsArgs a) {
       if (TILE / 8 % 64 == 0 || lane + i * 64 < TILE / 8) z4[lane + i * 64] = make_uint4(0, 0, 0, 0);
   };
   clear_tile();
-  __syncthreads();  // one wave: orders the table writes before the reads by other lanes
+  __syncthreads();  // orders the table writes before the reads by other lanes and waves
 
   // ---- loads ---------------------------------------------------------------------------
   // One descriptor per wave (BIG: per 32-example tile): base = its first example row; the range
@@ -209,8 +233,9 @@ void rows_kernel(RowsArgs a) {
   // back to back, once.  (Requesting them one k-step at a time, a stage apart, re-fetched every
   // line four times.)
   // (UNAL pieces are five dwords each: with 64 or more stacked rows a full ring would spill)
-  constexpr int R = ET == 1 ? 1 : sizeof(T) == 2 ? (UNAL && MT >= 2 ? ET / 2 : ET) : 2;
-  static_assert(ET % R == 0, "the ring divides a stage");
+  // ET = 1: slot q holds the stages t = q (mod R).
+  constexpr int R = ET == 1 ? rows_ahead(sizeof(T), MT) : sizeof(T) == 2 ? (UNAL && MT >= 2 ? ET / 2 : ET) : 2;
+  static_assert(ET == 1 || ET % R == 0, "the ring divides a stage");
   static_assert(!UNAL || sizeof(T) == 2, "only 16-bit entries can start inside a dword");
   uint4 ld[R][NLD];
   uint32_t ld5[UNAL ? R : 1][UNAL ? NLD : 1];  // UNAL: the fifth dword of each piece
@@ -218,16 +243,17 @@ void rows_kernel(RowsArgs a) {
   // row offset kb.  RPI rows further on (an even number) they start in the same half.
   static_assert(RPI % 2 == 0, "rows of one lane share their parity");
   auto odd = [&](uint32_t kb) -> uint32_t { return (voff + kb) & 2u; };
-  auto issue_tile = [&](uint32_t kb, int slot, int c) {
+  // (not wanted, ET = 1: an offset outside the descriptor's range, for which nothing is read)
+  auto issue_tile = [&](uint32_t kb, int slot, int c, bool wanted = true) {
     uint4(&dst)[NLD] = ld[slot];
     // (UNAL: the half-dword of kb, if any, moves from the scalar to the lane offset, which is then
     // rounded down to a dword)
-    const uint32_t vo = UNAL ? (voff + (kb & 2u)) & ~3u : voff;
+    const uint32_t vo = !wanted ? 0x80000000u : UNAL ? (voff + (kb & 2u)) & ~3u : voff;
     const uint32_t kq = UNAL ? kb & ~2u : kb;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const __amdgpu_buffer_rsrc_t rs = rs_t[BIG ? c : 0];
-      const uint32_t so = (uint32_t)((BIG ? 0 : c * 32) + i * RPI) * (uint32_t)row_bytes + kq;
+      const uint32_t so = wanted ? (uint32_t)((BIG ? 0 : c * 32) + i * RPI) * (uint32_t)row_bytes + kq : 0u;
       dst[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, vo, so, 0));
       if constexpr (UNAL) ld5[slot][i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, vo + 16u, so, 0);
     }
@@ -241,8 +267,8 @@ void rows_kernel(RowsArgs a) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[c][rt][i] = 0.f;
 
-  // ---- Phi^T of the stage (sl_n, st_n) / t: IN: part `part` takes every 4th slot; OUT: the one
-  // block of the stage, in part 0 -----------------------------------------------------------
+  // ---- Phi^T of the stage (sl_n, st_n) / t: IN: part `part` takes every 4th slot (up to 64 examples: part 0 all
+  // of them); OUT: the one block of the stage, in part 0 -----------------------------------------------------------
   auto produce = [&](int t, int part) {
     if constexpr (OUT) {
       if (part != 0) return;
@@ -280,14 +306,43 @@ void rows_kernel(RowsArgs a) {
       }
       return;
     }
-    for (uint32_t slot = part; slot < kap; slot += KSTEPS) {
-      const RowHash rh = row_hash_pow2(s_bk[slot], u, p.Br);
-      uint32_t r = rh.shift;
-      const uint32_t base = slot << lbr;
-      for (uint32_t i = 0; i < p.s; ++i) {
-        s_phi[__umul24(base + r, (uint32_t)PHI_LD) + lane] = (uint16_t)(((rh.signs >> i) << 15) | Fmt<T>::one);
-        r = (r + rh.stride) & (p.Br - 1);
+    // G slots from `slot` on, side by side: one hash is a chain of some thirty dependent instructions, and with
+    // one or two waves per SIMD nothing else fills its gaps.
+    auto some = [&](uint32_t slot, auto g_tag) {
+      constexpr int G = decltype(g_tag)::value;
+      RowHash rh[G];
+      uint32_t r[G];
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        rh[q] = row_hash_pow2(s_bk[slot + q], u, p.Br);
+        r[q] = rh[q].shift;
       }
+      for (uint32_t i = 0; i < p.s; ++i) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+          s_phi[__umul24(((slot + q) << lbr) + r[q], (uint32_t)PHI_LD) + lane] =
+              (uint16_t)(((rh[q].signs >> i) << 15) | Fmt<T>::one);
+          r[q] = (r[q] + rh[q].stride) & (p.Br - 1);
+        }
+      }
+    };
+    if constexpr (ET == 4) {
+      for (uint32_t slot = part; slot < kap; slot += KSTEPS) {
+        const RowHash rh = row_hash_pow2(s_bk[slot], u, p.Br);
+        uint32_t r = rh.shift;
+        const uint32_t base = slot << lbr;
+        for (uint32_t i = 0; i < p.s; ++i) {
+          s_phi[__umul24(base + r, (uint32_t)PHI_LD) + lane] = (uint16_t)(((rh.signs >> i) << 15) | Fmt<T>::one);
+          r = (r + rh.stride) & (p.Br - 1);
+        }
+      }
+    } else if (part == 0) {
+      constexpr bool ROOM = MT < 4 || ET == 1;  // (128 rows of two example tiles spill with four slots)
+      uint32_t slot = 0;
+      if constexpr (ROOM)
+        for (; slot + 4 <= kap; slot += 4) some(slot, std::integral_constant<int, 4>{});
+      for (; slot + 2 <= kap; slot += 2) some(slot, std::integral_constant<int, 2>{});
+      if (kap & 1) some(slot, std::integral_constant<int, 1>{});
     }
   };
 
@@ -301,8 +356,20 @@ void rows_kernel(RowsArgs a) {
   auto dword_mask = [](int rem) -> uint32_t {  // rem = valid bytes from this dword on
     return rem >= 4 ? 0xFFFFFFFFu : rem >= 2 ? 0x0000FFFFu : 0u;
   };
-  auto stage = [&](int t, auto last_tag) {
+  // ET = 1: the cursor of the loads runs R stages ahead of the stage in use, that of Phi^T (step_next) one.
+  uint32_t sl_f = sl_n, st_f = st_n, kb_f = kb_c;
+  auto step_fetch = [&]() {
+    if constexpr (OUT) {
+      if (++st_f == spb) { st_f = 0; ++sl_f; }
+      const uint32_t hb = __builtin_amdgcn_readfirstlane(s_blk[min(sl_f, p.kappa - 1)]);
+      kb_f = (hb * p.Bc + st_f * KC) * (uint32_t)sizeof(T);
+    } else {
+      kb_f += ROWB;
+    }
+  };
+  auto stage = [&](int t, auto last_tag, auto slot_tag) {
     constexpr bool LAST = decltype(last_tag)::value;
+    constexpr int SLOT = decltype(slot_tag)::value;  // ET = 1: the ring slot of this stage
     const int tail_bytes = d_bytes - (int)kb_c;  // bytes of this stage's K-range that lie before entry d
     const bool tail = tail_bytes < ROWB;
     uint4 pb[KSTEPS][MT];  // stacked row rt*32 + m, the K-values of (k-step j, half kg)
@@ -315,11 +382,13 @@ void rows_kernel(RowsArgs a) {
     if constexpr (!LAST) { clear_tile(); step_next(); }
 #pragma unroll
     for (int c = 0; c < ET; ++c) {
-      if constexpr (!LAST) {
+      if (!LAST && (ET > 1 || t + 1 < T_stages)) {
 #pragma unroll
         for (int part = c * KSTEPS / ET; part < (c + 1) * KSTEPS / ET; ++part) produce(t + 1, part);
       }
-      uint4(&cur)[NLD] = ld[c % R];
+      constexpr int PLACES = ET == 1 ? 1 : R;
+      const int slot = SLOT + c % PLACES;
+      uint4(&cur)[NLD] = ld[slot];
       if constexpr (UNAL) {
         const uint32_t sh = odd(kb_c) << 3;  // 0 or 16 bits
 #pragma unroll
@@ -327,7 +396,7 @@ void rows_kernel(RowsArgs a) {
           cur[i].x = __builtin_amdgcn_alignbit(cur[i].y, cur[i].x, sh);
           cur[i].y = __builtin_amdgcn_alignbit(cur[i].z, cur[i].y, sh);
           cur[i].z = __builtin_amdgcn_alignbit(cur[i].w, cur[i].z, sh);
-          cur[i].w = __builtin_amdgcn_alignbit(ld5[c % R][i], cur[i].w, sh);
+          cur[i].w = __builtin_amdgcn_alignbit(ld5[slot][i], cur[i].w, sh);
         }
       }
       if (tail) {  // wave-uniform: only the stages of a partly filled last block that reach entry d
@@ -345,9 +414,14 @@ void rows_kernel(RowsArgs a) {
 #pragma unroll
       for (int i = 0; i < NLD; ++i) *reinterpret_cast<uint4*>(g_wr + i * RPI * GLD) = cur[i];
       // refill the slot with the tile R places further on: same stage, or the next one
-      const int CN = (c + R) % ET;  // compile-time after unrolling
-      const bool wrap = c + R >= ET;
-      if (!(LAST && wrap)) issue_tile(wrap ? kb_n : kb_c, c % R, CN);
+      if constexpr (ET == 1) {
+        issue_tile(kb_f, slot, 0, t + R < T_stages);
+        step_fetch();
+      } else {
+        const int CN = (c + R) % ET;  // compile-time after unrolling
+        const bool wrap = c + R >= ET;
+        if (!(LAST && wrap)) issue_tile(wrap ? kb_n : kb_c, slot, CN);
+      }
 #pragma unroll
       for (int i = 0; i < NLD; ++i)
         g[i] = *reinterpret_cast<const uint4*>(g_rd + (i / NV) * (16 * (int)sizeof(T)) + (i % NV) * 16);
@@ -357,6 +431,16 @@ void rows_kernel(RowsArgs a) {
 #pragma unroll
           for (int rt = 0; rt < MT; ++rt) acc[c][rt] = mfma<T>(g[j], pb[j][rt], acc[c][rt]);
       } else {
+        // (a sum of its own per stage, added once: one rounding at the size of the whole sum instead of twelve.
+        // A wave of few examples has longer sums than the row splits it takes the place of.)
+        constexpr bool APART = rows_apart(sizeof(T), MT, ET);
+        f32x16 part[APART ? MT : 1];
+        if constexpr (APART) {
+#pragma unroll
+          for (int rt = 0; rt < MT; ++rt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) part[rt][i] = 0.f;
+        }
 #pragma unroll
         for (int jj = 0; jj < KSTEPS; jj += 2) {
           uint4 pc[2][3];
@@ -371,8 +455,16 @@ void rows_kernel(RowsArgs a) {
 #pragma unroll
             for (int cc = 0; cc < 2; ++cc)
 #pragma unroll
-              for (int rt = 0; rt < MT; ++rt)
-                acc[c][rt] = mfma<T>(pc[cc][piece], pb[jj + cc][rt], acc[c][rt]);
+              for (int rt = 0; rt < MT; ++rt) {
+                f32x16& to = APART ? part[rt] : acc[c][rt];
+                to = mfma<T>(pc[cc][piece], pb[jj + cc][rt], to);
+              }
+        }
+        if constexpr (APART) {
+#pragma unroll
+          for (int rt = 0; rt < MT; ++rt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[c][rt][i] += part[rt][i];
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -380,17 +472,95 @@ void rows_kernel(RowsArgs a) {
     kb_c = kb_n;
   };
 
-  if (rows_valid > 0) {
+  if (rows_valid > 0 && (ET == 4 || T_stages > 0)) {
+    using Slot0 = std::integral_constant<int, 0>;
 #pragma unroll
-    for (int c = 0; c < R; ++c) issue_tile(kb_c, c, c);
+    for (int c = 0; c < R; ++c) {
+      issue_tile(ET == 1 ? kb_f : kb_c, c, ET == 1 ? 0 : c, ET > 1 || c < T_stages);
+      if constexpr (ET == 1) step_fetch();
+    }
 #pragma unroll
     for (int part = 0; part < KSTEPS; ++part) produce(0, part);
-    for (int t = 0; t + 1 < T_stages; ++t) stage(t, std::false_type{});
-    stage(T_stages - 1, std::true_type{});
+    if constexpr (ET == 1) {
+      // (whole turns of the ring, then what is left; Phi^T made behind the last stage is not used)
+      int t = 0;
+      for (; t + R <= T_stages; t += R) {
+        stage(t, std::false_type{}, Slot0{});
+        if constexpr (R >= 2) stage(t + 1, std::false_type{}, std::integral_constant<int, 1>{});
+        if constexpr (R >= 4) {
+          stage(t + 2, std::false_type{}, std::integral_constant<int, 2>{});
+          stage(t + 3, std::false_type{}, std::integral_constant<int, 3>{});
+        }
+      }
+      if (R >= 2 && t < T_stages) stage(t, std::false_type{}, Slot0{});
+      if constexpr (R >= 4) {
+        if (t + 1 < T_stages) stage(t + 1, std::false_type{}, std::integral_constant<int, 1>{});
+        if (t + 2 < T_stages) stage(t + 2, std::false_type{}, std::integral_constant<int, 2>{});
+      }
+    } else {
+      for (int t = 0; t + 1 < T_stages; ++t) stage(t, std::false_type{}, Slot0{});
+      stage(T_stages - 1, std::true_type{}, Slot0{});
+    }
   }
 
   // ---- epilogue: accumulator v of tile (c, rt) is example ex0 + 32 c + 8 (v/4) + 4 kg + v%4,
   // stacked row 32 rt + m.
+  const bool merge = ET < 4 && (nw > 1 || (MODE == kOut && (int)p.Br < RWV));
+  if (merge) {
+    // The waves' tiles meet in LDS, one example tile at a time, over the Phi^T and transposition tiles.
+    constexpr int MERGE = 32 * RWV;  // floats of a wave
+    static_assert(MERGE * 4 <= WAVE_LDS, "a merged tile fits where the wave's own tiles were");
+    float* const mine = reinterpret_cast<float*>(s_phi);
+    const float4* const all = reinterpret_cast<const float4*>(smem + kRowsTables);
+    uint32_t rec = blk;
+    if constexpr (MODE == kIn) {
+      if (a.orbit) rec = a.orbit[p.M + blk];
+    } else if constexpr (MODE == kOutSplit) {
+      rec = a.orbit ? a.orbit[p.M + blk] + 1u : wire_next(blk, p.a, p.b, p.M);
+      if (rec == p.M) rec = 0;
+    }
+    const int width = OUT ? min((int)p.Br, RWV) : RWV;  // (OUT, Br < 32: the rows above Br idle)
+#pragma unroll
+    for (int c = 0; c < ET; ++c) {
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+#pragma unroll
+        for (int rt = 0; rt < MT; ++rt)
+          mine[(8 * (v >> 2) + 4 * kg + (v & 3)) * RWV + rt * 32 + m] = acc[c][rt][v];
+      __syncthreads();
+      const int valid = min(32, rows_valid - 32 * c);
+      for (int e = (int)threadIdx.x; e < valid * (RWV / 4); e += 64 * nw) {
+        const int ex = ex0 + 32 * c + e / (RWV / 4), col = e % (RWV / 4) * 4;
+        if (col >= width) continue;
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+        for (int w = 0; w < nw; ++w) {
+          const float4 v = all[w * (WAVE_LDS / 16) + e];
+          sum[0] += (double)v.x; sum[1] += (double)v.y; sum[2] += (double)v.z; sum[3] += (double)v.w;
+        }
+        if constexpr (MODE == kOut) {
+          float r[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) r[q] = (float)(sum[q] * (double)p.scale);
+          T* dst = reinterpret_cast<T*>(a.out) + (int64_t)ex * a.ldo + (int64_t)blk * p.Br + row_lo + col;
+          if (width >= 4 && (uintptr_t)dst % (4 * sizeof(T)) == 0) {
+            if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2*>(dst) = pack4<T>(r);
+            else *reinterpret_cast<float4*>(dst) = make_float4(r[0], r[1], r[2], r[3]);
+          } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (col + q < width) Elt<T>::store(dst + q, r[q]);
+          }
+        } else {
+          const int64_t at = MODE == kOutSplit ? (((int64_t)z * a.n + ex) * p.M + rec) * p.Br + row_lo + col
+                                               : (((int64_t)blockIdx.z * a.n + ex) * p.M + rec) * RWV + col;
+          *reinterpret_cast<float4*>(a.ws + at) = make_float4((float)sum[0], (float)sum[1], (float)sum[2], (float)sum[3]);
+        }
+      }
+    }
+    return;
+  }
   if constexpr (OUT) {
     if constexpr (MODE == kOutSplit) {  // a partial sum: the record of the block, at the place the reduction looks for
       const uint32_t pos = a.orbit ? __builtin_amdgcn_readfirstlane(a.orbit[p.M + blk]) : 0u;
@@ -559,11 +729,14 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float* __restric
 // waves, each stage of a wave costing a memory latency on top, (3) the stream of G, plus the
 // records written at 3.4 and read back at 6 TB/s (rates measured on this kernel pair) and, where
 // without a split there would be no reduction, its launch.  Measured (fp32, 24 examples of 1000003
-// entries, kappa*Br = 64, M = 256): 1 split 94 us, 8 splits 36 us.
-int pick_rows_split(double units, int total, double stage_us, double slots, double stream_us,
-                    double set_bytes, bool has_reduce, double max_bytes, int zmax) {
-  int best_z = 1;
-  double best = 0;
+// entries, kappa*Br = 64, M = 256, one wave per work-group): 1 split 94 us, 8 splits 36 us.
+struct RowsSplit {
+  int z = 1, nw = 1, stages = 0;
+  double us = 0;
+};
+RowsSplit pick_rows_split(double units, int total, double stage_us, double slots, double stream_us, double set_bytes,
+                          bool has_reduce, double max_bytes, int zmax) {
+  RowsSplit best;
   for (int zc = 1, st; zc <= total && zc <= zmax; zc = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
     st = (total + zc - 1) / zc;  // (the next split is the first one with fewer stages per work-group)
     if (zc > 1 && set_bytes * zc > max_bytes) break;
@@ -574,13 +747,67 @@ int pick_rows_split(double units, int total, double stage_us, double slots, doub
     if (stream_us > t) t = stream_us;
     if (has_reduce || zc > 1) t += set_bytes * zc * (1 / 3.4e6 + 1 / 6e6);
     if (!has_reduce && zc > 1) t += 4.0;
-    if (zc == 1 || t < best) { best = t; best_z = zc; }
+    if (zc == 1 || t < best.us) { best.z = zc; best.stages = st; best.us = t; }
   }
-  return best_z;
+  return best;
 }
 
-// `limit`: bytes of workspace the call can have at most.
-RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t limit) {
+// The same for up to 64 examples, where the waves of a work-group split the stages first: that many fewer sets of
+// records for as many waves.  Fitted to some 350 timed (waves, splits) of 21 calls.  A stage of a lone wave on a
+// SIMD takes `stage_us` (what it issues and its dependent chains), two there together `pair` times as long; equal
+// work-groups run in whole rounds; 4.6 us from launch to the first stage and from the last one to the end, and at
+// least what the host needs for one launch or two.  The reduction: its launch, the records, and a latency per 8
+// addends of a thread (65536 outputs or fewer than 16 addends: of all).
+struct RowsFew {
+  double units;           // work-groups without a split
+  int total;              // stages of one
+  double stage_us, pair;
+  int per_simd;           // waves a SIMD's registers hold
+  size_t lds_wave;
+  double stream_us, set_bytes;
+  int set_addends;        // addends of an output in one set of records
+  bool many_outputs, has_reduce;
+  int nw_max;
+  int most;               // stages of a wave at most (0: any number)
+};
+RowsSplit pick_few_split(const RowsFew& c, double max_bytes, int zmax) {
+  RowsSplit best;
+  for (int nw = 1; nw <= c.nw_max && nw <= c.total; nw *= 2) {
+    const size_t lds = kRowsTables + nw * c.lds_wave;
+    if (nw > 1 && lds > kLdsMost) break;
+    const int by_lds = (int)(kLdsMost / lds), by_regs = 4 * c.per_simd / nw;
+    const double fit = by_lds < by_regs ? by_lds : by_regs;  // work-groups of a CU
+    int st = 0;
+    for (int zc = 1; zc <= zmax; zc = (c.total + nw * (st - 1) - 1) / (nw * (st - 1))) {
+      st = (c.total + nw * zc - 1) / (nw * zc);  // (the next split is the first one with fewer stages per wave)
+      if (zc > 1 && c.set_bytes * zc > max_bytes) break;
+      if (c.most > 0 && st > c.most) continue;
+      const double here = std::ceil(c.units * zc / 256), rounds = std::ceil(here / fit);
+      const double on_simd = std::ceil((here < fit ? here : fit) * nw / 4);
+      double t = rounds * st * c.stage_us * (on_simd > 1 ? on_simd * c.pair / 2 : 1.0);
+      const double cus = c.units * zc < 256 ? c.units * zc : 256, share = 185 / cus;  // fewer CUs stream less
+      const double stream = share > 1 ? share * c.stream_us : c.stream_us;
+      t = stream > t ? stream + 0.15 * t : t + 0.15 * stream;  // (neither hides all of the other)
+      t += 4.6 + 0.05 * nw;
+      double least = 4.5;
+      if (c.has_reduce || zc > 1) {
+        const int addends = c.set_addends * zc;
+        t += 3.5 + c.set_bytes * zc * (1 / 3.4e6 + 1 / 6e6);
+        t += addends >= 16 && !c.many_outputs ? 1.0 + 0.05 * addends : 1.0 * ((addends + 7) / 8);
+        least = 7.5;
+      }
+      if (t < least) t = least;
+      if (best.stages == 0 || t < best.us) { best.us = t; best.z = zc; best.nw = nw; best.stages = st; }
+      if (st == 1) break;
+    }
+  }
+  if (best.stages > 0) best.z = (c.total + best.nw * best.stages - 1) / (best.nw * best.stages);  // (no split without a stage)
+  return best;
+}
+
+// `limit`: bytes of workspace the call can have at most.  `one_launch`: output-stationary may take the place of two launches.
+RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t limit,
+                        bool one_launch) {
   RowsPlan pl;
   const size_t esz = dt == FS_F32 ? 4 : 2;
   if (n < 1) return pl;
@@ -656,40 +883,83 @@ RowsPlan make_rows_plan(const SketchParams& p, const void* G, int64_t ldg, int64
   const int64_t ex_tiles = (n + 32 * pl.et - 1) / (32 * pl.et);
   if (ex_tiles * pl.nsub > 65535) return pl;
 
-  // slot tables, the Phi^T tile and the transposition tile
-  pl.lds = 2 * MAX_KAPPA * 4 + (size_t)(32 * pl.mt) * PHI_LD * 2 + 32 * (KC * esz + 16);
   pl.waves_per_simd = rows_waves_per_simd((int)esz, pl.mt, pl.et);
-  const int by_lds = (int)((160 * 1024) / pl.lds);
-  const double slots = 256.0 * (4 * pl.waves_per_simd < by_lds ? 4 * pl.waves_per_simd : by_lds);
   pl.total = pl.out_stat ? (int)(p.kappa * blk_stages) : (int)blk_stages;
   const double g_us = (double)p.d * (double)n * esz / 5.5e6;
   const double stream_us = pl.out_stat ? g_us * (1.0 + 0.3 * (p.kappa - 1)) : g_us * pl.groups;
   double max_bytes = (double)(pl.ws_floor > kSplitScratch ? pl.ws_floor : kSplitScratch);
   if ((double)limit < max_bytes) max_bytes = (double)limit;
   const int zmax = 65535 / pl.groups < 256 ? 65535 / pl.groups : 256;  // grid.z numbers (group, split)
-  pl.zsplit = pick_rows_split((double)p.M * ex_tiles * pl.nsub * pl.groups, pl.total, phi_us + pl.et * tile_us, slots,
-                              stream_us, set_bytes, !pl.out_stat, max_bytes, zmax);
-  pl.stages = (pl.total + pl.zsplit - 1) / pl.zsplit;
-  if (!pl.out_stat || pl.zsplit > 1) pl.ws = (size_t)set_bytes * pl.zsplit;
+  const size_t lds = kRowsTables + rows_lds_wave((int)esz, pl.mt);
+  const int by_lds = (int)(kLdsMost / lds);
+  const double slots = 256.0 * (4 * pl.waves_per_simd < by_lds ? 4 * pl.waves_per_simd : by_lds);
+  RowsSplit sp = pick_rows_split((double)p.M * ex_tiles * pl.nsub * pl.groups, pl.total, phi_us + pl.et * tile_us, slots,
+                                 stream_us, set_bytes, !pl.out_stat, max_bytes, zmax);
+  // us of a stage of a lone wave: example tiles, then a hash per slot and its nonzeros
+  auto few = [&](bool out_stat, int mt, int et, int total, double set, bool has_reduce) {
+    const int slots = out_stat ? 1 : pl.group_slots < (int)p.kappa ? pl.group_slots : (int)p.kappa;
+    const double tile = esz == 4 ? 0.6 + 0.2 * mt : 0.35 + 0.1 * mt;
+    RowsFew c;
+    c.units = (double)p.M * (double)((n + 32 * et - 1) / (32 * et)) * (out_stat && p.Br > 128 ? (int)(p.Br / 128) : 1) * pl.groups;
+    c.total = total;
+    c.stage_us = tile + (et - 1) * (esz == 4 ? tile : 0.3) + slots * (0.06 + 0.019 * p.s);
+    c.pair = mt == 4 ? 2.0 : 1.5;
+    c.per_simd = rows_waves_per_simd((int)esz, mt, et);
+    c.lds_wave = rows_lds_wave((int)esz, mt);
+    c.stream_us = out_stat ? g_us * (1.0 + 0.3 * (p.kappa - 1)) : g_us * pl.groups;
+    c.set_bytes = set;
+    c.set_addends = out_stat ? 1 : (int)p.kappa;
+    c.many_outputs = (double)n * (double)p.k / (p.Br % 4 == 0 ? 4 : 1) >= 65536;
+    c.has_reduce = has_reduce;
+    c.nw_max = rows_waves((int)esz, mt, et);
+    // (an fp32 sum in one piece is no longer than where one wave has a split to itself, or ten stages: its error grows
+    // with the root of its length, 3208704 x 7 held as rows 2.1e-7 with 40 stages, 2.7e-7 with 49)
+    c.most = esz == 4 && !rows_apart(4, mt, et) ? (sp.stages > 10 ? sp.stages : 10) : 0;
+    return c;
+  };
+  if (pl.et < 4) {
+    const RowsSplit f = pick_few_split(few(pl.out_stat, pl.mt, pl.et, pl.total, set_bytes, !pl.out_stat), max_bytes, zmax);
+    if (f.stages > 0) sp = f;
+  }
+  pl.ws = !pl.out_stat || sp.z > 1 ? (size_t)set_bytes * sp.z : 0;
+  auto take = [&](const RowsSplit& from) {
+    pl.zsplit = from.z; pl.nw = from.nw; pl.stages = from.stages;
+    pl.lds = kRowsTables + pl.nw * rows_lds_wave((int)esz, pl.mt);
+  };
+  take(sp);
   pl.ok = true;
+  // Up to 32 examples: output-stationary in one launch where that is shorter by the model.  us per
+  // call, before -> one launch: bf16 84215 x 26, 128 blocks, kappa = 2 11.4 -> 7.7; half 8768 x 8, 128 blocks, kappa = 8
+  // 10.5 -> 6.6; where the model says two, one took longer (fp32 10048 x 8, 32 blocks of 64, kappa = 8 13.8 against 9.5).
+  if (one_launch && pl.ws > 0 && pl.et == 1 && n <= 32 && pl.groups == 1 && p.br_pow2 && p.Br <= 128 && p.kappa <= (uint32_t)MAX_KAPPA) {
+    const int mt = p.Br <= 32 ? 1 : (int)p.Br / 32, total = (int)(p.kappa * blk_stages);
+    const RowsSplit one = pick_few_split(few(true, mt, 1, total, 0.0, false), 0.0, 1);
+    if (one.stages > 0 && one.us + 0.5 <= sp.us) {
+      pl.out_stat = true; pl.big = false; pl.et = 1; pl.mt = mt; pl.nsub = 1; pl.total = total; pl.ws = 0;
+      pl.waves_per_simd = rows_waves_per_simd((int)esz, mt, 1);
+      take(one);
+    }
+  }
   return pl;
 }
 
-template <typename K>
-hipError_t go(K kernel, dim3 grid, size_t lds, hipStream_t st, const RowsArgs& a) {
-  hipLaunchKernelGGL(kernel, grid, dim3(64), lds, st, a);
+template <auto kernel>
+hipError_t go(const RowsPlan& pl, dim3 grid, hipStream_t st, const RowsArgs& a) {
+  const hipError_t e = allow_lds<kernel>(pl.lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * pl.nw), pl.lds, st, a);
   return hipGetLastError();
 }
 
 template <typename T, int MT, int ET, bool UNAL>
 hipError_t launch_mode(const RowsPlan& pl, dim3 grid, hipStream_t st, const RowsArgs& a) {
   if (pl.out_stat)
-    return pl.zsplit > 1 ? go(rows_kernel<T, MT, ET, kOutSplit, UNAL>, grid, pl.lds, st, a)
-                         : go(rows_kernel<T, MT, ET, kOut, UNAL>, grid, pl.lds, st, a);
+    return pl.zsplit > 1 ? go<rows_kernel<T, MT, ET, kOutSplit, UNAL>>(pl, grid, st, a)
+                         : go<rows_kernel<T, MT, ET, kOut, UNAL>>(pl, grid, st, a);
   if constexpr (ET == 4) {
-    if (pl.big) return go(rows_kernel<T, MT, ET, kIn, UNAL, true>, grid, pl.lds, st, a);
+    if (pl.big) return go<rows_kernel<T, MT, ET, kIn, UNAL, true>>(pl, grid, st, a);
   }
-  return go(rows_kernel<T, MT, ET, kIn, UNAL>, grid, pl.lds, st, a);
+  return go<rows_kernel<T, MT, ET, kIn, UNAL>>(pl, grid, st, a);
 }
 
 template <typename T, int MT, bool UNAL>
@@ -721,17 +991,18 @@ void launch_reduce(int64_t outputs, uint32_t addends, hipStream_t st, const Rows
 
 mm::RowsPlan plan_rows(const SketchParams& p, const void* G, int64_t ldg, int64_t n, fs_dtype dt, size_t ws_bytes,
                        bool vector) {
-  RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, ws_bytes);
+  RowsPlan pl = make_rows_plan(p, G, ldg, n, dt, ws_bytes, false);
   if (vector && pl.ok && (n <= 2 || pl.ws > 0)) {  // (three or four: not where it stores the result itself)
     const double room = ws_bytes < kSplitScratch ? (double)ws_bytes : (double)kSplitScratch;
     pl.few = plan_vector(p, n, dt, room);
     if (pl.few.ok) {
       pl.out_stat = true;
-      pl.groups = pl.nsub = 1; pl.zsplit = pl.few.zsplit;
+      pl.groups = pl.nsub = pl.nw = 1; pl.zsplit = pl.few.zsplit;
       pl.ws = pl.zsplit > 1 ? (size_t)n * (size_t)p.k * 4 * pl.zsplit : 0;
+      return pl;
     }
   }
-  return pl;
+  return pl.ok && pl.ws > 0 && n <= 32 ? make_rows_plan(p, G, ldg, n, dt, ws_bytes, true) : pl;
 }
 
 hipError_t launch_rows(const mm::RowsPlan& pl, const SketchParams& p, const void* G, int64_t ldg, int64_t n, void* out,

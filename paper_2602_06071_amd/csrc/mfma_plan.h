@@ -69,6 +69,7 @@ struct RowsPlan {
   bool vec = true;       // every piece starts on 16 bytes
   bool unal = false;     // some pieces start inside a dword (16-bit types)
   int nsub = 1;          // OUT: 128-row slices of an output block
+  int nw = 1;            // waves of a work-group (they split the stages)
   bool big = false;      // IN: one descriptor per 32-example tile (very long rows)
   int waves_per_simd = 1;
   size_t lds = 0;

@@ -1556,3 +1556,42 @@ def test_few_columns_of_a_small_call_are_stored_by_one_launch(params, n, pa, fir
     sk.apply(torch.zeros((params[0], n), device=DEV, dtype=dtype))
     if dtype != torch.float32 or params[4] * params[5] <= 8:
         assert sk.info().last_kernel.decode().endswith("out,->") and sk.info().last_mode == 1
+
+
+# Up to 64 examples held as rows: the waves of a work-group split the stages and add their tiles in LDS.  Fewer stages
+# than waves, a remainder, rings of one, two and four stages that end in every place, output blocks lower than a
+# vector store, one launch and two.
+ROWS_FEW = [
+    # params (d,k,Bc,Br,kappa,s), n, ldg pad, ldo pad
+    ((64, 8, 64, 8, 1, 2), 5, 0, 0),               # one block, one stage, one wave
+    ((1000, 4, 500, 2, 2, 1), 9, 1, 1),            # two rows per block, no orbit table
+    ((4000, 16, 250, 1, 4, 1), 32, 2, 3),          # one row per block
+    ((4000, 32, 500, 4, 8, 3), 31, 1, 2),          # 32 stacked rows, a slot's row group of three
+    ((6400, 96, 800, 12, 3, 5), 17, 0, 1),         # Br not a power of two: two launches
+    ((5000, 256, 625, 32, 7, 2), 33, 0, 0),        # a second example tile with one example; seven slots: 4 + 2 + 1
+    ((9000, 512, 1125, 64, 1, 4), 64, 3, 1),       # stored directly, two full tiles
+    ((6144, 1024, 768, 128, 3, 8), 6, 0, 0),       # 128 rows, output-stationary
+    ((70000, 64, 8750, 8, 8, 4), 12, 1, 0),        # 137 stages, 64 stacked rows
+    ((70000, 128, 8750, 16, 8, 4), 50, 0, 2),      # 128 stacked rows of two example tiles
+    ((30690, 512, 60, 1, 1, 1), 8, 0, 0),          # blocks of less than a stage, the last one half filled
+]
+
+
+@DTYPES
+@pytest.mark.parametrize("case", ROWS_FEW, ids=lambda c: f"{c[0]}-n{c[1]}")
+def test_few_examples_held_as_rows_match_oracle(case, dtype):
+    params, n, pg, po = case
+    print("few rows", params, n, dtype, flush=True)
+    d, k = params[0], params[1]
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    Gbuf = torch.full((n + 1, d + pg), float("nan"), device=DEV, dtype=dtype)  # the padding never reaches the result
+    Gbuf[:n, :d] = torch.randn((n, d), generator=g, device=DEV).to(dtype)
+    G = Gbuf[:n, :d]
+    sk = make_sketch(params, 21, B.VARIANT_MFMA)
+    out = torch.full((n + 1, k + po), 7.0, device=DEV, dtype=dtype)
+    sk.apply_rows(G, out[:n, :k])
+    ref = O.apply_rows(oracle_csc(params, 21), host64(G))
+    check(out[:n, :k], ref, dtype, "apply_rows, few examples")
+    assert (out[n:] == 7.0).all() and (out[:, k:] == 7.0).all()
+    again = sk.apply_rows(G)
+    assert torch.equal(again, out[:n, :k])  # fixed summation order
