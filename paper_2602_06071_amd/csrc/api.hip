@@ -228,20 +228,21 @@ fs_status fs_sketch_create_kind(fs_sketch_t* out, fs_kind kind, int64_t d, int64
   h->last_kernel[0] = 0;
   h->device = -1;
   h->ws = nullptr; h->ws_bytes = 0; h->ws_owned = true; h->ws_refused = false; h->ws_captured = false;
-  h->dense = nullptr; h->dense_scratch = 0;
+  h->dense = nullptr; h->dense_scratch = 0; h->dense_half = false;
   h->profiling = false; h->prof_used = 0; h->prof_scope = 0;
   h->orbit = nullptr;
 
   if (kind == FS_KIND_GAUSS_DENSE) {
     if ((double)k * (double)d > 2.0e9) { delete h; return FS_ERR_UNSUPPORTED; }
-    h->dense_scratch = fs::kGaussScratch;
-    hipError_t e = hipMalloc(&h->dense, fs::gauss_bytes(k, d) + h->dense_scratch);
-    if (e == hipErrorOutOfMemory) {  // the matrix alone: applies then do not split d
+    hipError_t e = hipErrorOutOfMemory;
+    // what the device has room for: all of it, no half pieces, or the matrix alone (applies then do not split d)
+    for (int have = 2; have >= 0 && e == hipErrorOutOfMemory; --have) {
       (void)hipGetLastError();
-      h->dense_scratch = 0;
-      e = hipMalloc(&h->dense, fs::gauss_bytes(k, d));
+      h->dense_half = have == 2;
+      h->dense_scratch = have ? fs::kGaussScratch : 0;
+      e = hipMalloc(&h->dense, fs::gauss_bytes(k, d) + (h->dense_half ? fs::gauss_half_bytes(k, d) : 0) + h->dense_scratch);
     }
-    if (e == hipSuccess) e = fs::gauss_fill(h->dense, k, d, p.key1, nullptr);
+    if (e == hipSuccess) e = fs::gauss_fill(h->dense, h->dense_half, k, d, p.key1, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
       (void)hipGetLastError();
@@ -431,7 +432,7 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
     e = fs::launch_scatter(h->p, A, lda, n, out, ldo, dt, ws, st, ev);
     what = "scatter_kernel";
   } else if (h->kind == FS_KIND_GAUSS_DENSE) {
-    e = fs::launch_gauss(h->dense, h->dense_scratch, h->p.k, h->p.d, A, lda, n, out, ldo, dt, st, ev);
+    e = fs::launch_gauss(h->dense, h->dense_half, h->dense_scratch, h->p.k, h->p.d, A, lda, n, out, ldo, dt, st, ev);
     what = "gauss_kernel";
   } else if (h->kind == FS_KIND_BLOCKROW) {
     e = fs::launch_blockrow(h->p, A, lda, n, out, ldo, dt, st, ev);

@@ -45,6 +45,7 @@ struct fs_sketch_s {
   // GAUSS_DENSE: the k x d matrix in its fp32 and 16-bit forms and room for partial planes (one allocation)
   void* dense;
   size_t dense_scratch;  // bytes of that room
+  bool dense_half;       // whether the half pieces of fp32 applies are among them
 };
 
 namespace fs {
@@ -163,14 +164,16 @@ hipError_t launch_blockrow(const SketchParams& p, const void* A, int64_t lda, in
 hipError_t launch_blockrow_export(const SketchParams& p, int32_t* cols, int8_t* signs, hipStream_t st);
 
 // Dense Gaussian sketch.  `storage` holds the k x d matrix as fp32, then five 16-bit copies (bf16
-// rounded, the exact bf16 split hi / mid / lo, half): gauss_bytes(k, d) bytes; behind them `scratch` bytes for
-// the partial planes of applies that split d, kGaussScratch or none.  (Room of its own, so that the applies of
+// rounded, the exact bf16 split hi / mid / lo, half): gauss_bytes(k, d) bytes; behind them, if `half`, the two half
+// pieces of larger fp32 applies (gauss_half_bytes) and `scratch` bytes for the partial planes of applies that split d,
+// kGaussScratch or none.  (Room of its own, so that the applies of
 // this kind need no workspace, under capture and through fs_sketch_apply_static alike.)
 constexpr size_t kGaussScratch = (size_t)64 << 20;
 size_t gauss_bytes(int64_t k, int64_t d);
-hipError_t gauss_fill(void* storage, int64_t k, int64_t d, uint32_t key1, hipStream_t st);
+size_t gauss_half_bytes(int64_t k, int64_t d);
+hipError_t gauss_fill(void* storage, bool half, int64_t k, int64_t d, uint32_t key1, hipStream_t st);
 bool gauss_supported(int64_t k, int64_t d, const void* A, int64_t lda, int64_t n, fs_dtype dt);
-hipError_t launch_gauss(void* storage, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
+hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
                         int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev);
 
 }  // namespace fs

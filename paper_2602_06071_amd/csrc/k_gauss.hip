@@ -15,13 +15,18 @@
 // MFMA operand (4 columns x 8 rows per lane, transposed with v_perm_b32), S tiles of
 // 128 rows x 64 columns are staged in LDS (double buffered, one barrier per stage that orders LDS
 // traffic only: the loads of A stay in flight).
-// fp32 applies use six bf16 MFMAs per tile (hi*hi, hi*mid, mid*hi, hi*lo, lo*hi,
-// mid*mid); the dropped cross terms are below 2^-23 relative.
+// Small fp32 applies use six bf16 MFMAs per tile (hi*hi, hi*mid, mid*hi, hi*lo, lo*hi,
+// mid*mid); the dropped cross terms are below 2^-23 relative.  Larger ones use three half MFMAs (hi*hi, hi*lo, lo*hi) on
+// x*2^e = hi + lo with 11 significant bits and a sign each, so that 2^-23 relative is left and lo*lo is below 2^-23;
+// the range of half is no limit, since each column of A has an e of its own (gauss_colmax_kernel: its largest entry
+// comes to lie between 2^14 and 2^15, half's subnormals reach 2^-39 below that) and S has one for all.
 //
 // What bounds it: the matrix cores, if a wave has enough of them per element it loads and (fp32)
-// splits: a 128 x 128 wave tile (all 512 registers of a lane) has 96 MFMAs per 208 vector instructions of a
-// k-step, a 32 x 128 one 24.  Such tiles are few (256 for k = 4096, n = 1024), so the d columns of S are
-// split over grid.z into fp32 planes that a second kernel adds in order.
+// splits: a 128 x 128 wave tile (all 512 registers of a lane) has 48 MFMAs per 80 vector instructions of a
+// k-step, a 32 x 128 one 12.  Such tiles are few (256 for k = 4096, n = 1024), so the d columns of S are
+// split over grid.z into fp32 planes that a second kernel adds in order.  fp32 65536 x 1024, k = 4096: 1.38 ms, of which 75 us the
+// column maxima, 1.26 PFLOP/s of half products (a library bf16 product of 8192^3 on random data: 1.22), i.e. what the
+// matrix cores do at the clock that power leaves them.
 #include <math.h>
 
 #include <type_traits>
@@ -40,6 +45,7 @@ using namespace mm;
 __global__ __launch_bounds__(256) void gauss_fill_kernel(float* __restrict__ S32, uint16_t* __restrict__ Sbf,
                                                          uint16_t* __restrict__ Shi, uint16_t* __restrict__ Smid,
                                                          uint16_t* __restrict__ Slo, uint16_t* __restrict__ Sh,
+                                                         f16* __restrict__ H, f16* __restrict__ L, int es,
                                                          int64_t k, int64_t d, uint32_t key1, int tiled, double sqrt_k) {
   // `at`: place in the 16-bit copies, idx: in the matrix by rows.  Tiled: the threads walk the tiles, whose
   // 64-column rows are whole lines of S32 too (shapes no apply takes are left in rows).
@@ -66,6 +72,64 @@ __global__ __launch_bounds__(256) void gauss_fill_kernel(float* __restrict__ S32
   Shi[at] = (uint16_t)(sb >> 16);
   Smid[at] = (uint16_t)(r1b >> 16);
   Slo[at] = (uint16_t)(__float_as_uint(r2) >> 16);
+  if (H) {
+    const float t = ldexpf(s, es);
+    const f16 h = (f16)t;
+    H[at] = h;
+    L[at] = (f16)(t - (float)h);
+  }
+}
+
+// The largest magnitude of every column over the rows [c*rows, (c+1)*rows), c = blockIdx.y, as the bits of a
+// float: part[c][column].  NaN is above infinity.  A work-group takes 4*2^sh columns, its lanes 4 each.
+__global__ __launch_bounds__(1024) void gauss_colmax_kernel(const float* __restrict__ A, int64_t d, int64_t lda, int n,
+                                                            int64_t rows, int sh, uint32_t* __restrict__ part, int64_t ldw) {
+  __shared__ uint4 s_max[1024];
+  const int tid = threadIdx.x, lanes = 1 << sh, sub = tid >> sh, nsub = 1024 >> sh;
+  const int col0 = ((int)blockIdx.x * lanes + (tid & (lanes - 1))) * 4;
+  const int64_t first = (int64_t)blockIdx.y * rows, last = min(first + rows, d);
+  uint4 m = make_uint4(0, 0, 0, 0);
+  if (col0 < n) {
+    constexpr int UN = 8;  // loads in flight
+    for (int64_t r0 = first + sub; r0 < last; r0 += UN * nsub) {
+      uint4 v[UN];
+#pragma unroll
+      for (int j = 0; j < UN; ++j)  // (past the end the last row again: a hit)
+        v[j] = *reinterpret_cast<const uint4*>(A + min(r0 + j * nsub, last - 1) * lda + col0);
+#pragma unroll
+      for (int j = 0; j < UN; ++j) {
+        m.x = max(m.x, v[j].x & 0x7fffffffu); m.y = max(m.y, v[j].y & 0x7fffffffu);
+        m.z = max(m.z, v[j].z & 0x7fffffffu); m.w = max(m.w, v[j].w & 0x7fffffffu);
+      }
+    }
+  }
+  s_max[tid] = m;
+  __syncthreads();
+  for (int h = 512; h >= lanes; h >>= 1) {
+    if (tid < h) {
+      const uint4 o = s_max[tid + h];
+      m.x = max(m.x, o.x); m.y = max(m.y, o.y); m.z = max(m.z, o.z); m.w = max(m.w, o.w);
+      s_max[tid] = m;
+    }
+    __syncthreads();
+  }
+  if (tid < lanes && col0 < n) *reinterpret_cast<uint4*>(part + (int64_t)blockIdx.y * ldw + col0) = m;
+}
+
+// x (8 rows of one column) * m as two half pieces each, rounded to nearest: what is left is below 2^-23 of x*m.
+__device__ __forceinline__ void split_half(const uint32_t (&x)[8], float m, uint4& hi, uint4& lo) {
+  typedef f16 h2 __attribute__((ext_vector_type(2)));
+  uint32_t* h = reinterpret_cast<uint32_t*>(&hi);
+  uint32_t* l = reinterpret_cast<uint32_t*>(&lo);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float x0 = __uint_as_float(x[2 * q]), x1 = __uint_as_float(x[2 * q + 1]);
+    h[q] = __builtin_bit_cast(uint32_t, h2{(f16)(x0 * m), (f16)(x1 * m)});
+    asm("" : "+v"(h[q]));  // (or each half is made a second time for the difference)
+    const h2 v = __builtin_bit_cast(h2, h[q]);
+    // m is a power of two: exact before it is rounded
+    l[q] = __builtin_bit_cast(uint32_t, h2{(f16)fmaf(x0, m, -(float)v.x), (f16)fmaf(x1, m, -(float)v.y)});
+  }
 }
 
 struct GaussArgs {
@@ -75,16 +139,25 @@ struct GaussArgs {
   float* ws;  // zsplit > 1: planes of k x ldw floats
   int64_t k, d, lda, ldo, ldw;
   int n, total, stages, zsplit, out_vec;
+  // two half pieces: largest magnitudes of the columns, `parts` rows of ldw, and the exponent S was scaled by
+  const uint32_t* colmax;
+  int parts, es;
+  int cgroup;  // column tiles (of grid.y, which it divides) that consecutive work-groups take in turn
 };
 
 // Work-group: 128 = 32*MT*NRG rows of S x 128*NCG columns of A, stages [z*stages, min((z+1)*stages, total)) of
 // the d/64; wave: 32*MT rows x 128 columns.
-template <typename T, int MT, int NRG, int NCG>
+// HALF (fp32): two half pieces of both operands instead of three bf16 ones.
+template <typename T, int MT, int NRG, int NCG, bool HALF = false>
 __global__ __launch_bounds__(64 * NRG * NCG) __attribute__((amdgpu_waves_per_eu(MT > 2 || (MT == 2 && sizeof(T) == 4) ? 1 : 2)))
 void gauss_kernel(GaussArgs a) {
   using V = typename Ld<T>::V;
-  constexpr int PFD = Ld<T>::PFD * (MT > 2 ? 2 : 1) > KSTEPS ? KSTEPS : Ld<T>::PFD * (MT > 2 ? 2 : 1);
-  constexpr int PARTS = sizeof(T) == 4 ? 3 : 1;
+  using P = std::conditional_t<HALF, f16, T>;  // type of the pieces (as mfma() names them)
+  // DEEP (one wave per SIMD, many stages): two stages a pass, S tiles and operands fetched earlier, one barrier a stage where
+  // it is not waited for.  Short calls of the small tiles are 1.1 to 1.2 times slower with it (its start, its code).
+  constexpr bool DEEP = MT == 4;
+  constexpr int PFD = Ld<T>::PFD;  // k-steps that the loads of A run ahead
+  constexpr int PARTS = sizeof(T) == 4 ? (HALF ? 2 : 3) : 1;
   constexpr int NW = NRG * NCG, NT = 64 * NW;
   constexpr int RW = 32 * MT * NRG;
   static_assert(RW == 128, "the 16-bit copies of S are stored in tiles of 128 rows");
@@ -97,10 +170,26 @@ void gauss_kernel(GaussArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rg = wave / NCG, cg = wave % NCG, kg = lane >> 5;
-  const int col0 = (int)blockIdx.y * (WCOLS * NCG) + cg * WCOLS + 4 * (lane & 31);
-  const int64_t row_base = (int64_t)blockIdx.x * RW;
-  const int t0 = (int)blockIdx.z * a.stages;
-  const int T_stages = min(a.stages, a.total - t0);  // >= 1
+  // Which (rows, columns, split) this work-group takes: linear ids are dealt round-robin over the 8 XCDs; renumbered, an
+  // XCD's work-groups are consecutive, and consecutive ones share a split and few column tiles (a.cgroup), so that what
+  // they read of A and of S they read from one L2.
+  uint32_t bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  if constexpr (DEEP) {  // (the divisions would be a good part of a short call)
+    const uint32_t gx = gridDim.x, gy = gridDim.y, total = gx * gy * gridDim.z;
+    const uint32_t id = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+    const uint32_t q = total / 8, r = total % 8;
+    uint32_t nid = (id % 8) * q + min(id % 8, r) + id / 8;
+    const uint32_t C = (uint32_t)a.cgroup;
+    by = nid % C; nid /= C;
+    bx = nid % gx; nid /= gx;
+    by += nid % (gy / C) * C;
+    bz = nid / (gy / C);
+  }
+  const int col0 = (int)by * (WCOLS * NCG) + cg * WCOLS + 4 * (lane & 31);
+  const int64_t row_base = (int64_t)bx * RW;
+  const int t0 = (int)bz * a.stages;
+  // DEEP: even; behind the last row of A (only the last split can reach there) the loads give zeros
+  const int T_stages = DEEP ? (min(a.stages, a.total - t0) + 1) & ~1 : min(a.stages, a.total - t0);
   const int64_t row_bytes = a.lda * (int64_t)sizeof(T);
   // The whole of A is one buffer (offsets fit 32 bits: checked on the host).  A lane whose columns all
   // lie at or beyond n gets an offset outside its range; a vector that straddles n loads the row's own
@@ -117,23 +206,52 @@ void gauss_kernel(GaussArgs a) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[mt][c][i] = 0.f;
 
+  // HALF: the power of two that takes the largest entry of each of the lane's columns to [2^14, 2^15), or as near as
+  // the exponents of a float go (columns of subnormals); 1 for columns with an infinity or a NaN
+  float colm[4];
+  if constexpr (HALF) {
+    uint4 m = make_uint4(0, 0, 0, 0);
+    if (col0 < a.n) {  // (n is rounded up to 4 in the rows of the maxima)
+      constexpr int UN = 16;  // loads in flight (past the end the last one again)
+      for (int i = 0; i < a.parts; i += UN) {
+        uint4 v[UN];
+#pragma unroll
+        for (int j = 0; j < UN; ++j)
+          v[j] = *reinterpret_cast<const uint4*>(a.colmax + (int64_t)min(i + j, a.parts - 1) * a.ldw + col0);
+#pragma unroll
+        for (int j = 0; j < UN; ++j) {
+          m.x = max(m.x, v[j].x); m.y = max(m.y, v[j].y); m.z = max(m.z, v[j].z); m.w = max(m.w, v[j].w);
+        }
+      }
+    }
+    const uint32_t mx[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t e = mx[c] >> 23;
+      colm[c] = __uint_as_float((e == 255 ? 127u : min(268u - e, 254u)) << 23);
+    }
+  }
+
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));  // (an array of uint4 lands in scratch memory here)
-  u4 sreg[PARTS * SREG];
-  const int64_t s_first = ((int64_t)blockIdx.x * a.total + t0) * (RW * KC) + tid * 8;
-  auto s_fetch = [&](int t) {
+  // S tiles on their way: SA stages are between the fetch of one and its place in LDS (tile t in sreg[t % SA])
+  constexpr int SA = DEEP && sizeof(T) == 2 ? 2 : 1;
+  u4 sreg[SA][PARTS * SREG];
+  const int64_t s_first = ((int64_t)bx * a.total + t0) * (RW * KC) + tid * 8;
+  auto s_fetch = [&](int t, u4 (&dst)[PARTS * SREG]) {
+    if constexpr (DEEP) t = min(t, a.total - 1 - t0);
 #pragma unroll
     for (int pt = 0; pt < PARTS; ++pt)
 #pragma unroll
       for (int i = 0; i < SREG; ++i)
-        sreg[pt * SREG + i] = *reinterpret_cast<const u4*>((pt == 0 ? a.S[0] : pt == 1 ? a.S[1] : a.S[2]) + s_first + (int64_t)t * (RW * KC) + i * NT * 8);
+        dst[pt * SREG + i] = *reinterpret_cast<const u4*>((pt == 0 ? a.S[0] : pt == 1 ? a.S[1] : a.S[2]) + s_first + (int64_t)t * (RW * KC) + i * NT * 8);
   };
-  auto s_store = [&](int buf) {
+  auto s_store = [&](int buf, u4 (&src)[PARTS * SREG]) {
 #pragma unroll
     for (int pt = 0; pt < PARTS; ++pt)
 #pragma unroll
       for (int i = 0; i < SREG; ++i) {
         const int e = tid + i * NT, row = e >> 3, c16 = e & 7;
-        *reinterpret_cast<u4*>(s_tile + (buf * PARTS + pt) * TILE + row * PHI_LD + c16 * 8) = sreg[pt * SREG + i];
+        *reinterpret_cast<u4*>(s_tile + (buf * PARTS + pt) * TILE + row * PHI_LD + c16 * 8) = src[pt * SREG + i];
       }
   };
   auto lds_barrier = [&]() {
@@ -144,6 +262,7 @@ void gauss_kernel(GaussArgs a) {
 
   V ld[PFD][8];
   auto issue = [&](int kk, V (&dst)[8]) {
+    if constexpr (DEEP) kk = min(kk, (a.total - t0) * KSTEPS);  // (16 rows behind the last one read zeros; offsets of more could wrap)
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t soj = (uint32_t)((t0 * KSTEPS + kk) * 16 + j) * (uint32_t)row_bytes;
@@ -154,22 +273,35 @@ void gauss_kernel(GaussArgs a) {
     }
   };
 
-  auto stage = [&](int t, auto last_tag) {
+  // S operands of a k-step.  AHEAD: read one k-step before they are used (three pieces of a 128-row tile leave no registers for it).
+  constexpr bool AHEAD = DEEP && PARTS <= 2;
+  uint4 pa2[AHEAD ? 2 : 1][PARTS][MT];
+  auto read_pa = [&](const uint16_t* tile, int ks, uint4 (&pa)[PARTS][MT]) {
+#pragma unroll
+    for (int pt = 0; pt < PARTS; ++pt)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        pa[pt][mt] = *reinterpret_cast<const uint4*>(
+            tile + pt * TILE + ((rg * MT + mt) * 32 + (lane & 31)) * PHI_LD + ks * 16 + kg * 8);
+  };
+
+  // One stage; DEEP: t % 2 == PAR.  Tile t+1 is written behind its third k-step (DEEP) or its last into the buffer that held tile
+  // t-1, and one barrier behind that, when this wave has read its last operands of tile t, gives it free.
+  auto stage = [&](int t, auto par_tag, auto last_tag) {
+    constexpr int PAR = decltype(par_tag)::value;
     constexpr bool LAST = decltype(last_tag)::value;
-    lds_barrier();  // tile t is complete, tile t+1's buffer has been read
-    if constexpr (!LAST) s_fetch(t + 1);
-    const uint16_t* tile = s_tile + (t & 1) * PARTS * TILE;
+    const int buf = DEEP ? PAR : t & 1;
+    const uint16_t* tile = s_tile + buf * PARTS * TILE;
+    const uint16_t* next = s_tile + (1 - buf) * PARTS * TILE;
+    if constexpr (!LAST && SA == 1) s_fetch(t + 1, sreg[0]);
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
-      uint4 pa[PARTS][MT];
-#pragma unroll
-      for (int pt = 0; pt < PARTS; ++pt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          pa[pt][mt] = *reinterpret_cast<const uint4*>(
-              tile + pt * TILE + ((rg * MT + mt) * 32 + (lane & 31)) * PHI_LD + ks * 16 + kg * 8);
-      V(&cur)[8] = ld[ks % PFD];
-      const bool fetch = !LAST || ks + PFD < KSTEPS;
+      uint4(&pa)[PARTS][MT] = pa2[AHEAD ? ks & 1 : 0];
+      if constexpr (!AHEAD) read_pa(tile, ks, pa);
+      else if (ks + 1 < KSTEPS) read_pa(tile, ks + 1, pa2[(ks + 1) & 1]);
+      else if constexpr (!LAST) read_pa(next, 0, pa2[0]);
+      V(&cur)[8] = ld[(PAR * KSTEPS + ks) % PFD];
+      const bool fetch = !LAST || ks + PFD < KSTEPS;  // (behind the last row they read zeros)
       if constexpr (sizeof(T) == 2) {
         uint4 op[4];
         make_ops(cur, op);
@@ -179,52 +311,104 @@ void gauss_kernel(GaussArgs a) {
 #pragma unroll
           for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[0][mt], op[c], acc[mt][c]);
       } else {
+        // product by product over the row tiles: with MT = 4 an accumulator is reused only after three other MFMAs
+        // (back-to-back dependent MFMAs stall the matrix pipe); smaller tiles of half pieces take two columns together
+        constexpr int CG = HALF && MT < 4 ? 2 : 1;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          uint32_t xs[8];
+        for (int c0 = 0; c0 < 4; c0 += CG) {
+          uint4 x[CG][PARTS];
 #pragma unroll
-          for (int j = 0; j < 8; ++j)
-            xs[j] = c == 0 ? cur[j].x : c == 1 ? cur[j].y : c == 2 ? cur[j].z : cur[j].w;
-          uint4 hi, mid, lo;
-          split_ops(xs, hi, mid, lo);
-          // product by product over the row tiles: with MT = 4 an accumulator is reused only
-          // after three other MFMAs (back-to-back dependent MFMAs stall the matrix pipe)
+          for (int c = 0; c < CG; ++c) {
+            uint32_t xs[8];
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[0][mt], hi, acc[mt][c]);
+            for (int j = 0; j < 8; ++j)
+              xs[j] = c0 + c == 0 ? cur[j].x : c0 + c == 1 ? cur[j].y : c0 + c == 2 ? cur[j].z : cur[j].w;
+            if constexpr (HALF) split_half(xs, colm[c0 + c], x[c][0], x[c][1]);
+            else split_ops(xs, x[c][0], x[c][1], x[c][PARTS - 1]);
+          }
+          auto product = [&](auto ps, auto px) {
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[0][mt], mid, acc[mt][c]);
+            for (int c = 0; c < CG; ++c)
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[1][mt], hi, acc[mt][c]);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[0][mt], lo, acc[mt][c]);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[2][mt], hi, acc[mt][c]);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) acc[mt][c] = mfma<T>(pa[1][mt], mid, acc[mt][c]);
+              for (int mt = 0; mt < MT; ++mt)
+                acc[mt][c0 + c] = mfma<P>(pa[decltype(ps)::value][mt], x[c][decltype(px)::value], acc[mt][c0 + c]);
+          };
+          using I0 = std::integral_constant<int, 0>;
+          using I1 = std::integral_constant<int, 1>;
+          using I2 = std::integral_constant<int, PARTS - 1>;
+          product(I0{}, I0{});
+          product(I0{}, I1{});
+          product(I1{}, I0{});
+          if constexpr (!HALF) {
+            product(I0{}, I2{});
+            product(I2{}, I0{});
+            product(I1{}, I1{});
+          }
         }
         if (fetch) issue(t * KSTEPS + ks + PFD, cur);
       }
+      if constexpr (!LAST) {
+        if (ks == (DEEP ? KSTEPS - 2 : KSTEPS - 1)) {
+          s_store(1 - buf, sreg[(1 - PAR) % SA]);
+          if constexpr (SA == 2) s_fetch(t + 3, sreg[1 - PAR]);
+        }
+      }
+      if constexpr (AHEAD) {  // one wave per SIMD: everything else between the MFMAs
+        constexpr int NM = 4 * MT * (HALF ? 3 : 1);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+          __builtin_amdgcn_sched_group_barrier(0x090, 1, 0);
+        }
+      }
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!LAST) {
+        if (ks == (AHEAD ? KSTEPS - 2 : KSTEPS - 1)) lds_barrier();
+      }
     }
-    if constexpr (!LAST) s_store((t + 1) & 1);
   };
 
 #pragma unroll
   for (int i = 0; i < PFD; ++i) issue(i, ld[i]);
-  s_fetch(0);
-  s_store(0);
-  for (int t = 0; t + 1 < T_stages; ++t) stage(t, std::false_type{});
-  stage(T_stages - 1, std::true_type{});
+  s_fetch(0, sreg[0]);
+  if constexpr (SA == 2) s_fetch(1, sreg[1]);
+  s_store(0, sreg[0]);
+  if constexpr (SA == 2) s_fetch(2, sreg[0]);
+  lds_barrier();
+  if constexpr (AHEAD) read_pa(s_tile, 0, pa2[0]);
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  if constexpr (DEEP) {
+    for (int t = 0; t + 2 < T_stages; t += 2) {
+      stage(t, P0{}, std::false_type{});
+      stage(t + 1, P1{}, std::false_type{});
+    }
+    stage(T_stages - 2, P0{}, std::false_type{});
+    stage(T_stages - 1, P1{}, std::true_type{});
+  } else {
+    for (int t = 0; t + 1 < T_stages; ++t) stage(t, P0{}, std::false_type{});
+    stage(T_stages - 1, P0{}, std::true_type{});
+  }
 
   if (col0 >= a.n) return;
+  int unscale[4];
+  if constexpr (HALF) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) unscale[c] = 127 - (int)(__float_as_uint(colm[c]) >> 23) - a.es;
+  }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int64_t row = row_base + (rg * MT + mt) * 32 + 8 * (i >> 2) + 4 * kg + (i & 3);
-      const float v[4] = {acc[mt][0][i], acc[mt][1][i], acc[mt][2][i], acc[mt][3][i]};
-      if (a.zsplit > 1) {  // a partial sum: plane blockIdx.z (col0 + 3 < ldw)
-        *reinterpret_cast<float4*>(a.ws + ((int64_t)blockIdx.z * a.k + row) * a.ldw + col0) = make_float4(v[0], v[1], v[2], v[3]);
+      float v[4] = {acc[mt][0][i], acc[mt][1][i], acc[mt][2][i], acc[mt][3][i]};
+      if constexpr (HALF) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = ldexpf(v[c], unscale[c]);
+      }
+      if (a.zsplit > 1) {  // a partial sum: plane bz (col0 + 3 < ldw)
+        *reinterpret_cast<float4*>(a.ws + ((int64_t)bz * a.k + row) * a.ldw + col0) = make_float4(v[0], v[1], v[2], v[3]);
         continue;
       }
       T* dst = reinterpret_cast<T*>(a.out) + row * a.ldo + col0;
@@ -244,33 +428,59 @@ void gauss_kernel(GaussArgs a) {
   }
 }
 
+// half: fp32 on two half pieces; its column maxima, in up to 64 shares of the rows, have kColmaxRoom bytes in front of the planes.
+struct GaussPlan { int ncg = 4, zsplit = 1, stages = 1; bool half = false; double us = 0; };
+constexpr size_t kColmaxRoom = (size_t)4 << 20;
+int64_t colmax_parts(int64_t ldw) {
+  const int64_t p = (int64_t)kColmaxRoom / (ldw * 4);
+  return p > 64 ? 64 : p;
+}
+
 // Columns per work-group (128, 256 or 512) and splits of the d/64 stages.  128-column waves that own all 128
 // rows (512 columns per work-group) do the most matrix work per loaded element; fewer columns leave
 // waves without any, so narrower work-groups divide the rows among the waves instead.  The smallest
-// modelled time: rounds of resident work-groups times stages, plus the planes (written at 3.4, read at
-// 6 TB/s, half that price while they stay in the Infinity Cache) and the reduction's launch.  Measured
-// (us per call, one 128 x 512 or 128 x 256 work-group per tile before): fp32 65536 x 1024, k = 4096: 4390 -> 2350
-// (1.4 PFLOP/s of bf16 products); fp32 41152 x 672, k = 1792: 5190 -> 614; half 42816 x 148, k = 384 (three
-// work-groups with element loads before): 11030 -> 26.
-struct GaussPlan { int ncg = 4, zsplit = 1, stages = 1; };
-GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratch) {
+// modelled time: rounds of resident work-groups (two on a CU take 1.7 times as long as one) times stages, plus the planes
+// (written at 3.4, read at 6 TB/s, half that price while they stay in the Infinity Cache) and the reduction's launch.  The
+// rates are a fit to the timed plans of 60 shapes (to 8 %; what it takes of the fp32 ones is slower than the best by 0.8 % in
+// the geometric mean, 7 % at most).
+GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratch, bool half) {
   GaussPlan pl;
+  pl.half = half;
   const int total = (int)(d / KC);
   const double plane = (double)k * (double)((n + 3) & ~(int64_t)3) * 4.0;
   double best = 0;
   for (int ncg = 4; ncg >= 1; ncg /= 2) {
     const int64_t wgs = (k / 128) * ((n + 128 * ncg - 1) / (128 * ncg));
     // us per stage of a work-group that has its CU to itself
-    const double stage_us = dt == FS_F32 ? (ncg == 4 ? 9.2 : ncg == 2 ? 5.2 : 4.0) : (ncg == 4 ? 2.0 : ncg == 2 ? 1.3 : 0.9);
-    const int per_cu = dt == FS_F32 || ncg == 4 ? 1 : 2;
-    for (int z = 1, st; z <= total && z <= 128; z = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
-      st = (total + z - 1) / z;
+    const double stage_us = half           ? (ncg == 4 ? 3.8 : ncg == 2 ? 2.6 : 1.87)
+                            : dt == FS_F32 ? (ncg == 4 ? 7.0 : ncg == 2 ? 4.4 : 3.28)
+                                           : (ncg == 4 ? 1.75 : ncg == 2 ? 1.3 : 0.9);
+    const int per_cu = ncg == 1 || (ncg == 2 && dt != FS_F32) ? 2 : 1;
+    const int unit = ncg == 4 ? 2 : 1;  // (an even number of stages where the kernel needs it)
+    for (int z = 1, st; z <= total && z <= 128; z = st > unit ? (total + st - unit - 1) / (st - unit) : total + 1) {
+      st = ((total + z - 1) / z + unit - 1) / unit * unit;
+      if ((total + st - 1) / st != z) continue;
       if (z > 1 && plane * z > (double)scratch) break;
-      const double w = (double)wgs * z, rounds = ceil(w / (256 * per_cu));
-      double t = rounds * (w > 256 && per_cu > 1 ? 1.7 : 1.0) * (st * stage_us + 3.0);
+      const double w = (double)wgs * z, rounds = per_cu == 2 && w > 256 ? 1.7 * ceil(w / 512) : ceil(w / 256);
+      double t = rounds * (st * stage_us + (dt == FS_F32 ? 4.4 : 3.0));
       if (z > 1) t += 4.0 + plane * z * (1 / 3.4e6 + 1 / 6e6) * (plane * z < 40e6 ? 0.5 : 1.0);
       if ((ncg == 4 && z == 1) || t < 0.98 * best) { best = t; pl.ncg = ncg; pl.zsplit = z; pl.stages = st; }
     }
+  }
+  pl.us = best + (half ? 8.0 + (double)d * (double)n * 4.0 / 4.5e6 : 0.0);
+  return pl;
+}
+
+// fp32: two half pieces of both operands are three products where three bf16 pieces are six, behind a pass over A for the
+// largest entry of each column.  Small calls cannot win back that pass's launch and its read (us, six products against
+// three: 4608 x 44, k = 384 13 / 19; 8192 x 280, k = 384 32.0 / 32.4; 4992 x 152, k = 2816 55 / 48; 8192 x 1024, k = 4096
+// 331 / 213; 65536 x 1024, k = 4096 2335 / 1383).  Error against 64 bits: 4608 x 44 1.7e-7 / 1.5e-7, 29952 x 840 9.8e-7 / 6.5e-7, 65536 x
+// 1024 2.7e-6 / 1.6e-6 (half as many additions are rounded).
+GaussPlan gauss_choose(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratch, bool pieces) {
+  GaussPlan pl = gauss_plan(k, d, n, dt, scratch, false);
+  if (dt == FS_F32 && pieces && colmax_parts((n + 3) & ~(int64_t)3) > 0) {
+    const GaussPlan h = gauss_plan(k, d, n, dt, scratch, true);
+    if (h.us < 0.92 * pl.us) pl = h;
   }
   return pl;
 }
@@ -290,15 +500,29 @@ hipError_t go(K kernel, dim3 grid, unsigned threads, size_t lds, hipStream_t st,
 
 // fp32, bf16, three pieces of the exact split, half.
 size_t gauss_bytes(int64_t k, int64_t d) { return ((size_t)k * (size_t)d * (4 + 5 * 2) + 255) & ~(size_t)255; }
+// The two half pieces and the room of the column maxima, behind them.
+size_t gauss_half_bytes(int64_t k, int64_t d) { return (((size_t)k * (size_t)d * 4 + 255) & ~(size_t)255) + kColmaxRoom; }
 
-hipError_t gauss_fill(void* storage, int64_t k, int64_t d, uint32_t key1, hipStream_t st) {
+namespace {
+// S is scaled by 2^es before it is cut into half pieces: no entry is above 5.77 / sqrt(k) (24-bit Box-Muller), so the
+// largest come to lie between 2^13 and 2^15.
+int half_exponent(int64_t k) {
+  int e = 0;
+  while ((k >> (2 * e + 2)) > 0) ++e;  // floor(log2(k) / 2)
+  return 12 + e;
+}
+}  // namespace
+
+hipError_t gauss_fill(void* storage, bool half, int64_t k, int64_t d, uint32_t key1, hipStream_t st) {
   float* S32 = (float*)storage;
   uint16_t* b = (uint16_t*)(S32 + k * d);
   const int64_t blocks = (k * d + 255) / 256;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   const int tiled = d % KC == 0 && k % 128 == 0;
+  f16* h = half ? (f16*)((char*)storage + gauss_bytes(k, d)) : nullptr;
   hipLaunchKernelGGL(gauss_fill_kernel, dim3((unsigned)blocks), dim3(256), 0, st, S32, b, b + k * d,
-                     b + 2 * k * d, b + 3 * k * d, b + 4 * k * d, k, d, key1, tiled, sqrt((double)k));
+                     b + 2 * k * d, b + 3 * k * d, b + 4 * k * d, h, half ? h + k * d : nullptr, half_exponent(k), k, d,
+                     key1, tiled, sqrt((double)k));
   return hipGetLastError();
 }
 
@@ -310,30 +534,48 @@ bool gauss_supported(int64_t k, int64_t d, const void* A, int64_t lda, int64_t n
   return (n + 255) / 256 <= 65535;
 }
 
-hipError_t launch_gauss(void* storage, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
+hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
                         int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev) {
   const float* S32 = (const float*)storage;
   const uint16_t* b = (const uint16_t*)(S32 + k * d);
   const size_t esz = dt == FS_F32 ? 4 : 2;
-  const GaussPlan pl = gauss_plan(k, d, n, dt, scratch);
+  const GaussPlan pl = gauss_choose(k, d, n, dt, scratch, half);
   GaussArgs a;
   a.A = A; a.out = out; a.k = k; a.d = d; a.lda = lda; a.ldo = ldo; a.n = (int)n;
   a.total = (int)(d / KC); a.stages = pl.stages; a.zsplit = pl.zsplit;
   a.ldw = (n + 3) & ~(int64_t)3;
-  a.ws = (float*)((char*)storage + gauss_bytes(k, d));
+  a.ws = (float*)((char*)storage + gauss_bytes(k, d) + (half ? gauss_half_bytes(k, d) : 0));
   a.out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
   a.S[1] = a.S[2] = nullptr;
-  if (dt == FS_F32) { a.S[0] = b + k * d; a.S[1] = b + 2 * k * d; a.S[2] = b + 3 * k * d; }
+  a.colmax = nullptr; a.parts = 0; a.es = half_exponent(k);
+  if (pl.half) {
+    a.S[0] = (const uint16_t*)((char*)storage + gauss_bytes(k, d));
+    a.S[1] = a.S[0] + k * d;
+    const int sh = n > 128 ? 6 : n > 64 ? 5 : n > 32 ? 4 : 3;
+    const int64_t tiles = (n + (4 << sh) - 1) / (4 << sh);
+    int64_t parts = (256 + tiles - 1) / tiles;  // about 4096 waves
+    parts = parts > colmax_parts(a.ldw) ? colmax_parts(a.ldw) : parts;
+    uint32_t* maxima = (uint32_t*)((char*)a.ws - kColmaxRoom);
+    a.colmax = maxima;
+    const int64_t rows = (d + parts - 1) / parts;
+    a.parts = (int)((d + rows - 1) / rows);
+    hipLaunchKernelGGL(gauss_colmax_kernel, dim3((unsigned)tiles, (unsigned)a.parts), dim3(1024), 0, st, (const float*)A, d,
+                       lda, (int)n, rows, sh, maxima, a.ldw);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  } else if (dt == FS_F32) { a.S[0] = b + k * d; a.S[1] = b + 2 * k * d; a.S[2] = b + 3 * k * d; }
   else a.S[0] = dt == FS_BF16 ? b : b + 4 * k * d;
   const dim3 grid((unsigned)(k / 128), (unsigned)((n + 128 * pl.ncg - 1) / (128 * pl.ncg)), (unsigned)pl.zsplit);
-  const size_t lds = (size_t)2 * (dt == FS_F32 ? 3 : 1) * 128 * PHI_LD * 2;
+  a.cgroup = 1;
+  while (2 * a.cgroup * 128 * pl.ncg <= 1024 && grid.y % (2 * a.cgroup) == 0) a.cgroup *= 2;
+  const size_t lds = (size_t)2 * (pl.half ? 2 : dt == FS_F32 ? 3 : 1) * 128 * PHI_LD * 2;
   if (ev.start) (void)hipEventRecord(ev.start, st);
   hipError_t e;
-#define FS_G(T)                                                          \
-  (pl.ncg == 4   ? go(gauss_kernel<T, 4, 1, 4>, grid, 256, lds, st, a)   \
-   : pl.ncg == 2 ? go(gauss_kernel<T, 2, 2, 2>, grid, 256, lds, st, a)   \
-                 : go(gauss_kernel<T, 1, 4, 1>, grid, 256, lds, st, a))
-  e = dt == FS_F32 ? FS_G(float) : dt == FS_BF16 ? FS_G(uint16_t) : FS_G(f16);
+#define FS_G(T, H)                                                          \
+  (pl.ncg == 4   ? go(gauss_kernel<T, 4, 1, 4, H>, grid, 256, lds, st, a)   \
+   : pl.ncg == 2 ? go(gauss_kernel<T, 2, 2, 2, H>, grid, 256, lds, st, a)   \
+                 : go(gauss_kernel<T, 1, 4, 1, H>, grid, 256, lds, st, a))
+  e = pl.half ? FS_G(float, true) : dt == FS_F32 ? FS_G(float, false) : dt == FS_BF16 ? FS_G(uint16_t, false) : FS_G(f16, false);
 #undef FS_G
   if (ev.stop) (void)hipEventRecord(ev.stop, st);
   if (e != hipSuccess || pl.zsplit == 1) return e;

@@ -695,6 +695,40 @@ def test_dense_gaussian_split_over_few_tiles(k, d, n, pad, dtype):
     assert torch.equal(again, out) and torch.equal(sk.apply(A), out)
 
 
+@pytest.mark.parametrize("k,d,n,pad", [(2816, 4992, 152, 0), (1536, 64 * 157, 321, 3), (4096, 4096, 1030, 2), (512, 32768, 300, 4)])
+def test_dense_gaussian_fp32_columns_of_any_magnitude(k, d, n, pad):
+    """fp32 calls large enough for the half pieces (by the planner; an odd number of stages, a last column tile of few columns):
+    columns from the smallest normal number to near the largest, zeros, subnormals, one large entry among small ones, NaN in the
+    padding; a NaN or an infinity stays in its column."""
+    print("gauss fp32 magnitudes", k, d, n, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(11)
+    buf = torch.full((d + 1, n + pad), float("nan"), device=DEV)
+    A = buf[:d, :n]
+    e = torch.linspace(-125.0, 110.0, n, dtype=torch.float64, device=DEV)
+    A.copy_((torch.randn((d, n), generator=g, device=DEV).double() * torch.exp2(e)).float())
+    A[:, 0] = 0.0
+    A[:, 1] = torch.randn((d,), generator=g, device=DEV) * 2.0 ** -126 * 0.01  # subnormals
+    A[3, 2] = 1.0e30
+    A[5, 7], A[6, 8] = float("nan"), float("inf")
+    sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
+    out = sk.apply(A)
+    torch.cuda.synchronize()
+    S = sk.export_dense().double()
+    ref = S @ A.double()
+    bad = torch.zeros(n, dtype=torch.bool, device=DEV)
+    bad[7:9] = True
+    assert not torch.isfinite(out[:, bad]).any() and torch.isfinite(out[:, ~bad]).all()
+    assert (out[:, 0] == 0).all()
+    # each column by itself: sums of d terms, whose operands and products are off by at most 2^-22 relative before they are added;
+    # column 1 lies below the normal numbers, where results are whole multiples of 2^-149
+    err = (out.double() - ref).norm(dim=0) / ref.norm(dim=0).clamp(min=1e-300)
+    rest = ~bad
+    rest[:2] = False
+    assert err[rest].max() <= 1e-5, err[rest].max()
+    assert (out[:, 1].double() - ref[:, 1]).abs().max() <= 2.0 ** -149 + 1e-5 * ref[:, 1].abs().max()
+    assert torch.equal(sk.apply(A)[:, rest], out[:, rest])
+
+
 # ------------------------------------------------ full-size configs -------
 def _sampled_parity(cfg, A, out, seed=0):
     """Oracle on a sample of columns of the full-size problem: one column, at a random place, from
