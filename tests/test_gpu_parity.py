@@ -427,6 +427,34 @@ def test_ksplit_kernel_of_128_column_tiles_matches_oracle(case, dtype):
     check_ksplit(*case[:4], dtype, f"ksplit_kernel<{name},{want}>" if want else "")
 
 
+@DTYPES
+@pytest.mark.parametrize("params,n,pad,first", [
+    ((10683, 2048, 84, 16, 4, 2), 136, 0, 0),     # 128 blocks, a last stage of 20 rows, a partly filled last block
+    ((4248, 1024, 67, 16, 4, 2), 227, 0, 1),      # odd packed rows from an odd element, blocks of odd length
+    ((10176, 2048, 159, 32, 2, 4), 161, 2, 2),    # dword-aligned rows of a view
+    ((6720, 1024, 210, 32, 2, 2), 1031, 1, 0),    # many column tiles, the last one of 7
+    ((7424, 1024, 58, 8, 8, 1), 200, 0, 0),       # blocks of 8 rows in a tile of 32, less than a stage each
+])
+def test_small_calls_of_over_128_columns_are_stored_in_one_launch(params, n, pad, first, dtype):
+    print("one launch", params, n, dtype, flush=True)
+    d, k = params[0], params[1]
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    flat = torch.full(((d + 2) * (n + pad) + 8,), float("nan"), device=DEV, dtype=dtype)
+    A = flat[4 + first:4 + first + d * (n + pad)].view(d, n + pad)  # NaN right before and behind
+    A[:, :n] = torch.randn((d, n), generator=g, device=DEV).to(dtype)
+    A = A[:, :n]
+    sk = make_sketch(params, 9, B.VARIANT_AUTO)
+    obuf = torch.full((k, n + 3), float("nan"), device=DEV, dtype=dtype)
+    out = sk.apply(A, obuf[:, :n])
+    torch.cuda.synchronize()
+    i = sk.info()
+    assert i.last_kernel.decode().startswith("ksplit_kernel") and i.last_mode == 1, i.last_kernel
+    assert "reduce" not in i.last_kernel.decode()
+    assert torch.isnan(obuf[:, n:].float()).all(), "wrote outside the n output columns"
+    check(out, O.apply(oracle_csc(params, 9), host64(A)), dtype, "one launch")
+    assert torch.equal(sk.apply(A), out)
+
+
 def test_smaller_workspace_takes_a_coarser_split():
     """A call that wants a finer row split than the workspace attached to its handle has room for
     runs with a coarser one; output-stationary calls run with none at all."""
