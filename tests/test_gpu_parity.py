@@ -389,6 +389,39 @@ KSPLIT_WIDE = [
 ]
 
 
+ROWS_MANY = [
+    # params (d,k,Bc,Br,kappa,s), n, pad: over 32 examples in tiles of 32 or 64 whose waves share the stages, or in one launch
+    ((9486, 2048, 149, 32, 4, 8), 312, 64),       # 64 blocks of three stages, a partly filled last block
+    ((4288, 512, 268, 32, 2, 4), 970, 0),         # many example tiles, the last one of 10 examples
+    ((20160, 1280, 1008, 64, 1, 8), 129, 1),      # kappa = 1, rows that start inside a dword
+    ((6142, 1024, 384, 64, 1, 8), 113, 0),
+    ((16384, 2048, 256, 32, 4, 2), 65, 3),
+    ((11200, 2048, 88, 16, 4, 2), 200, 0),        # blocks of 16 rows
+    ((31930, 1280, 3193, 128, 2, 4), 97, 2),      # blocks of 128 rows
+    ((13548, 288, 424, 9, 3, 2), 161, 0),         # Br not a power of two
+]
+
+
+@DTYPES
+@pytest.mark.parametrize("params,n,pad", ROWS_MANY)
+def test_rows_of_more_than_32_examples_by_price(params, n, pad, dtype):
+    print("rows by price", params, n, pad, dtype, flush=True)
+    d, k = params[0], params[1]
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    buf = torch.full((n + 1, d + pad), float("nan"), device=DEV, dtype=dtype)
+    buf[:n, :d] = torch.randn((n, d), generator=g, device=DEV).to(dtype)
+    G = buf[:n, :d]
+    ref = O.apply_rows(oracle_csc(params, 9), host64(G))
+    for variant in (B.VARIANT_AUTO, B.VARIANT_MFMA, B.VARIANT_GENERIC):
+        sk = make_sketch(params, 9, variant)
+        obuf = torch.full((n, k + 5), float("nan"), device=DEV, dtype=dtype)
+        out = sk.apply_rows(G, obuf[:, :k])
+        torch.cuda.synchronize()
+        assert torch.isnan(obuf[:, k:].float()).all(), "wrote outside the k output columns"
+        check(out, ref, dtype, f"rows by price, variant {variant}")
+        assert torch.equal(sk.apply_rows(G), out)
+
+
 def check_ksplit(params, n, pa, first, dtype, kernel):
     print("ksplit", params, n, dtype, flush=True)
     d, k = params[0], params[1]
