@@ -237,7 +237,7 @@ fs_status fs_sketch_create_kind(fs_sketch_t* out, fs_kind kind, int64_t d, int64
     hipError_t e = hipErrorOutOfMemory;
     // what the device has room for: all of it, no half pieces, or the matrix alone (applies then do not split d)
     for (int have = 2; have >= 0 && e == hipErrorOutOfMemory; --have) {
-      (void)hipGetLastError();
+      if (have < 2) (void)hipGetLastError();  // of the attempt before; what the caller left stays to be seen
       h->dense_half = have == 2;
       h->dense_scratch = have ? fs::kGaussScratch : 0;
       e = hipMalloc(&h->dense, fs::gauss_bytes(k, d) + (h->dense_half ? fs::gauss_half_bytes(k, d) : 0) + h->dense_scratch);

@@ -12,13 +12,14 @@ enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2 };
 
 /* ---- what a test sets and reads ---- */
 static size_t budget = SIZE_MAX, live;
-static int capturing, device;
+static int capturing, device, pending;
 static char log_text[1 << 16];
 static size_t log_len;
 
 void rec_budget(size_t bytes) { budget = bytes; }
 void rec_capturing(int on) { capturing = on; }
 void rec_device(int id) { device = id; }
+void rec_pending(int error) { pending = error; }  /* what an earlier call of the program left behind */
 size_t rec_live(void) { return live; }
 const char* rec_log(void) { return log_text; }
 void rec_clear(void) { log_len = 0; log_text[0] = 0; }
@@ -41,7 +42,7 @@ int hipMalloc(void** p, size_t n) {
   while (slot < n_blocks && blocks[slot].n) ++slot;
   if (n > budget - (live < budget ? live : budget) || slot == 4096) {
     note("malloc-failed %zu\n", n);
-    return hipErrorOutOfMemory;
+    return pending = hipErrorOutOfMemory;
   }
   if (slot == n_blocks) ++n_blocks;
   *p = next_address;
@@ -108,7 +109,7 @@ int hipFuncSetAttribute(const void* f, int attr, int value) {
 }
 
 /* ---- the rest ---- */
-int hipGetLastError(void) { return hipSuccess; }
+int hipGetLastError(void) { const int e = pending; pending = hipSuccess; return e; }
 int hipGetDeviceCount(int* n) { *n = 128; return hipSuccess; }
 int hipGetDevice(int* id) { *id = device; return hipSuccess; }
 int hipGetSymbolAddress(void** p, const void* symbol) { (void)symbol; *p = (void*)(uintptr_t)(1ull << 36); return hipSuccess; }

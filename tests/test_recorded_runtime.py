@@ -111,6 +111,20 @@ for room, status, splits in ((matrix + (128 << 20), 0, True), (matrix + (1 << 20
 """)
 
 
+def test_creating_a_dense_sketch_does_not_swallow_an_error_of_the_program(recorded):
+    recorded("""
+rec.rec_pending(700)
+s = Sketch(4096, 256, kind=2)
+assert s.status == 4 or rec.hipGetLastError() == 700      # reported, or still there
+if s.status:
+    assert not s.h.value and rec.rec_live() == 0
+rec.rec_budget(rec.rec_live() + (16 << 20))               # out of memory is create's own: it leaves nothing
+rec.rec_pending(0)
+s = Sketch(4096, 256, kind=2)
+assert s.status == 0 and rec.hipGetLastError() == 0
+""")
+
+
 SPLIT = """
 def split(s, n, dtype, ld=None):              # the kernels of a call and their row split
     rec.rec_clear()
