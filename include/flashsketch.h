@@ -295,7 +295,8 @@ fs_status fs_sketch_set_variant(fs_sketch_t h, fs_variant v);
 
 /* Kernel timing for benchmarks.  After profile_begin, each apply records HIP events on its
  * stream, up to max_launches applies: with FS_PROFILE_KERNEL in `scope` one pair around its
- * dominant kernel (the one that streams A), with FS_PROFILE_APPLY one pair around everything
+ * dominant kernel (the one that streams A; for FS_KIND_GAUSS_DENSE with the pass over A for its
+ * column maxima, where the call makes one), with FS_PROFILE_APPLY one pair around everything
  * the apply enqueues (zero-fills, table builds, the dominant kernel, plane reductions,
  * conversions).  Every recorded event costs a few microseconds on the stream, so with both
  * scopes the inner pair lengthens what the outer pair measures: ask for one scope at a time

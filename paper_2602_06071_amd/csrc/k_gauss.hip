@@ -548,6 +548,7 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
   a.out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
   a.S[1] = a.S[2] = nullptr;
   a.colmax = nullptr; a.parts = 0; a.es = half_exponent(k);
+  if (ev.start) (void)hipEventRecord(ev.start, st);  // (both passes over A lie between the events)
   if (pl.half) {
     a.S[0] = (const uint16_t*)((char*)storage + gauss_bytes(k, d));
     a.S[1] = a.S[0] + k * d;
@@ -569,7 +570,6 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
   a.cgroup = 1;
   while (2 * a.cgroup * 128 * pl.ncg <= 1024 && grid.y % (2 * a.cgroup) == 0) a.cgroup *= 2;
   const size_t lds = (size_t)2 * (pl.half ? 2 : dt == FS_F32 ? 3 : 1) * 128 * PHI_LD * 2;
-  if (ev.start) (void)hipEventRecord(ev.start, st);
   hipError_t e;
 #define FS_G(T, H)                                                          \
   (pl.ncg == 4   ? go(gauss_kernel<T, 4, 1, 4, H>, grid, 256, lds, st, a)   \

@@ -119,8 +119,9 @@ int hipMemcpyAsync(void* d, const void* s, size_t n, int kind, void* stream) {
   (void)d; (void)s; (void)n; (void)kind; (void)stream;
   return hipSuccess;
 }
-int hipEventCreate(void** e) { *e = (void*)(uintptr_t)1; return hipSuccess; }
+static uintptr_t next_event = 1;
+int hipEventCreate(void** e) { *e = (void*)next_event++; return hipSuccess; }
 int hipEventDestroy(void* e) { (void)e; return hipSuccess; }
-int hipEventRecord(void* e, void* stream) { (void)e; (void)stream; return hipSuccess; }
+int hipEventRecord(void* e, void* stream) { (void)stream; note("event %p\n", e); return hipSuccess; }
 int hipEventSynchronize(void* e) { (void)e; return hipSuccess; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 0.f; return hipSuccess; }

@@ -125,6 +125,21 @@ assert s.status == 0 and rec.hipGetLastError() == 0
 """)
 
 
+def test_the_kernel_scope_of_a_profile_holds_every_pass_over_the_input(recorded):
+    """A larger fp32 call of the dense sketch reads A twice: for the column maxima and for the product."""
+    recorded("""
+s = Sketch(16384, 2048, kind=2)
+assert lib.fs_sketch_profile_begin(s.h, 1, 1) == 0
+rec.rec_clear()
+assert s.apply(512) == 0
+log = [ln[1] if ln[0] == "launch" else ln[0] for ln in lines() if ln[0] in ("launch", "event")]
+maxima, product = ([i for i, w in enumerate(log) if name in w] for name in ("gauss_colmax", "gauss_kernel"))
+assert len(maxima) == 1 and product, log      # (the half pieces are taken here)
+events = [i for i, w in enumerate(log) if w == "event"]
+assert len(events) == 2 and events[0] < maxima[0] and max(product) < events[1], log
+""")
+
+
 SPLIT = """
 def split(s, n, dtype, ld=None):              # the kernels of a call and their row split
     rec.rec_clear()
