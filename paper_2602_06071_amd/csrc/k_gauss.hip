@@ -32,6 +32,7 @@
 #include <type_traits>
 
 #include "handle.h"
+#include "lds_limit.h"
 #include "mfma_common.h"
 #include "reduce_planes.h"
 #include "spec.h"
@@ -436,6 +437,9 @@ int64_t colmax_parts(int64_t ldw) {
   return p > 64 ? 64 : p;
 }
 
+// LDS of a work-group: two stages of the pieces of S.
+size_t gauss_lds(fs_dtype dt, bool half) { return (size_t)2 * (half ? 2 : dt == FS_F32 ? 3 : 1) * 128 * PHI_LD * 2; }
+
 // Columns per work-group (128, 256 or 512) and splits of the d/64 stages.  128-column waves that own all 128
 // rows (512 columns per work-group) do the most matrix work per loaded element; fewer columns leave
 // waves without any, so narrower work-groups divide the rows among the waves instead.  The smallest
@@ -455,7 +459,9 @@ GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratc
     const double stage_us = half           ? (ncg == 4 ? 3.8 : ncg == 2 ? 2.6 : 1.87)
                             : dt == FS_F32 ? (ncg == 4 ? 7.0 : ncg == 2 ? 4.4 : 3.28)
                                            : (ncg == 4 ? 1.75 : ncg == 2 ? 1.3 : 0.9);
-    const int per_cu = ncg == 1 || (ncg == 2 && dt != FS_F32) ? 2 : 1;
+    // (one wave per SIMD: one; else what the LDS holds, which with three pieces is one too: us per call of a handle without
+    // half pieces, priced as two -> as one: 17664 x 52, k = 1280 52.2 -> 48.4; of 40 such calls 10 0.93 to 0.98 times, one 1.03)
+    const int per_cu = ncg == 4 || (ncg == 2 && dt == FS_F32) || 2 * gauss_lds(dt, half) > kLdsMost ? 1 : 2;
     const int unit = ncg == 4 ? 2 : 1;  // (an even number of stages where the kernel needs it)
     for (int z = 1, st; z <= total && z <= 128; z = st > unit ? (total + st - unit - 1) / (st - unit) : total + 1) {
       st = ((total + z - 1) / z + unit - 1) / unit * unit;
@@ -569,7 +575,7 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
   const dim3 grid((unsigned)(k / 128), (unsigned)((n + 128 * pl.ncg - 1) / (128 * pl.ncg)), (unsigned)pl.zsplit);
   a.cgroup = 1;
   while (2 * a.cgroup * 128 * pl.ncg <= 1024 && grid.y % (2 * a.cgroup) == 0) a.cgroup *= 2;
-  const size_t lds = (size_t)2 * (pl.half ? 2 : dt == FS_F32 ? 3 : 1) * 128 * PHI_LD * 2;
+  const size_t lds = gauss_lds(dt, pl.half);
   hipError_t e;
 #define FS_G(T, H)                                                          \
   (pl.ncg == 4   ? go(gauss_kernel<T, 4, 1, 4, H>, grid, 256, lds, st, a)   \

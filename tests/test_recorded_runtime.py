@@ -140,6 +140,22 @@ assert len(events) == 2 and events[0] < maxima[0] and max(product) < events[1], 
 """)
 
 
+@pytest.mark.parametrize("k,d,n,splits", [
+    (3200, 37504, 64, 10),    # 25 row tiles: 250 work-groups in one round (20 splits would be two rounds of 30 stages for one of 59)
+])
+def test_dense_fp32_work_groups_that_fill_the_lds_alone_are_priced_in_whole_rounds(recorded, k, d, n, splits):
+    """Three pieces of 128 x 64 of S, twice, are 108 KiB: a CU of 160 KiB holds one such work-group."""
+    recorded(f"""
+rec.rec_budget(rec.rec_live() + 14 * {k} * {d} + (65 << 20))   # no room for the half pieces
+s = Sketch({d}, {k}, kind=2)
+rec.rec_clear()
+assert s.status == 0 and s.apply({n}) == 0
+run = launches()[0]
+assert "gauss_kernel" in run.kernel and 2 * run.lds > 160 << 10, run
+assert run.x * run.y * run.z <= 256 and run.z == {splits}, run
+""")
+
+
 SPLIT = """
 def split(s, n, dtype, ld=None):              # the kernels of a call and their row split
     rec.rec_clear()
