@@ -149,7 +149,10 @@ struct GaussArgs {
 // Work-group: 128 = 32*MT*NRG rows of S x 128*NCG columns of A, stages [z*stages, min((z+1)*stages, total)) of
 // the d/64; wave: 32*MT rows x 128 columns.
 // HALF (fp32): two half pieces of both operands instead of three bf16 ones.
-template <typename T, int MT, int NRG, int NCG, bool HALF = false>
+// ODD: whether a.stages is (only the kernel that walks two stages a pass has to know: a last stage of its own for either
+// parity costs the accumulators of a wave their registers, 370 to 930 spilled.  Splits rounded up to an even number
+// took longer (us per call): bf16 47808 x 436, k = 2048 121 -> 113, half 7424 x 392, k = 3584 47.2 -> 45.6.
+template <typename T, int MT, int NRG, int NCG, bool HALF = false, bool ODD = false>
 __global__ __launch_bounds__(64 * NRG * NCG) __attribute__((amdgpu_waves_per_eu(MT > 2 || (MT == 2 && sizeof(T) == 4) ? 1 : 2)))
 void gauss_kernel(GaussArgs a) {
   using V = typename Ld<T>::V;
@@ -189,15 +192,16 @@ void gauss_kernel(GaussArgs a) {
   const int col0 = (int)by * (WCOLS * NCG) + cg * WCOLS + 4 * (lane & 31);
   const int64_t row_base = (int64_t)bx * RW;
   const int t0 = (int)bz * a.stages;
-  // DEEP: even; behind the last row of A (only the last split can reach there) the loads give zeros
-  const int T_stages = DEEP ? (min(a.stages, a.total - t0) + 1) & ~1 : min(a.stages, a.total - t0);
+  const int mine = min(a.stages, a.total - t0);  // >= 1
+  // DEEP: odd or even as a.stages; a shorter last split may have one more, of zeros
+  const int T_stages = !DEEP ? mine : ODD ? mine | 1 : (mine + 1) & ~1;
   const int64_t row_bytes = a.lda * (int64_t)sizeof(T);
-  // The whole of A is one buffer (offsets fit 32 bits: checked on the host).  A lane whose columns all
-  // lie at or beyond n gets an offset outside its range; a vector that straddles n loads the row's own
+  // A up to the split's last row is one buffer (offsets fit 32 bits: checked on the host), behind which loads give
+  // zeros.  A lane whose columns all lie at or beyond n gets an offset outside its range; a vector that straddles n loads the row's own
   // padding too (or nothing, behind the last row), which feeds only columns that are never stored.
   const uint32_t voff = col0 < a.n ? (uint32_t)(((int64_t)(kg * 8) * a.lda + col0) * (int64_t)sizeof(T)) : 0x80000000u;
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<void*>(a.A), 0, (int)((a.d - 1) * row_bytes + ((a.n + 3) & ~3) * (int64_t)sizeof(T)), 0x00020000);
+      const_cast<void*>(a.A), 0, (int)(((int64_t)(t0 + mine) * KC - 1) * row_bytes + ((a.n + 3) & ~3) * (int64_t)sizeof(T)), 0x00020000);
 
   f32x16 acc[MT][4];
 #pragma unroll
@@ -239,7 +243,7 @@ void gauss_kernel(GaussArgs a) {
   u4 sreg[SA][PARTS * SREG];
   const int64_t s_first = ((int64_t)bx * a.total + t0) * (RW * KC) + tid * 8;
   auto s_fetch = [&](int t, u4 (&dst)[PARTS * SREG]) {
-    if constexpr (DEEP) t = min(t, a.total - 1 - t0);
+    if constexpr (DEEP) t = min(t, mine - 1);  // (behind the last tile, for zeros of A or not used)
 #pragma unroll
     for (int pt = 0; pt < PARTS; ++pt)
 #pragma unroll
@@ -263,7 +267,7 @@ void gauss_kernel(GaussArgs a) {
 
   V ld[PFD][8];
   auto issue = [&](int kk, V (&dst)[8]) {
-    if constexpr (DEEP) kk = min(kk, (a.total - t0) * KSTEPS);  // (16 rows behind the last one read zeros; offsets of more could wrap)
+    if constexpr (DEEP) kk = min(kk, mine * KSTEPS);  // (16 rows behind the last one read zeros; offsets of more could wrap)
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t soj = (uint32_t)((t0 * KSTEPS + kk) * 16 + j) * (uint32_t)row_bytes;
@@ -385,8 +389,12 @@ void gauss_kernel(GaussArgs a) {
       stage(t, P0{}, std::false_type{});
       stage(t + 1, P1{}, std::false_type{});
     }
-    stage(T_stages - 2, P0{}, std::false_type{});
-    stage(T_stages - 1, P1{}, std::true_type{});
+    if constexpr (ODD) {
+      stage(T_stages - 1, P0{}, std::true_type{});
+    } else {
+      stage(T_stages - 2, P0{}, std::false_type{});
+      stage(T_stages - 1, P1{}, std::true_type{});
+    }
   } else {
     for (int t = 0; t + 1 < T_stages; ++t) stage(t, P0{}, std::false_type{});
     stage(T_stages - 1, P0{}, std::true_type{});
@@ -462,9 +470,8 @@ GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratc
     // (one wave per SIMD: one; else what the LDS holds, which with three pieces is one too: us per call of a handle without
     // half pieces, priced as two -> as one: 17664 x 52, k = 1280 52.2 -> 48.4; of 40 such calls 10 0.93 to 0.98 times, one 1.03)
     const int per_cu = ncg == 4 || (ncg == 2 && dt == FS_F32) || 2 * gauss_lds(dt, half) > kLdsMost ? 1 : 2;
-    const int unit = ncg == 4 ? 2 : 1;  // (an even number of stages where the kernel needs it)
-    for (int z = 1, st; z <= total && z <= 128; z = st > unit ? (total + st - unit - 1) / (st - unit) : total + 1) {
-      st = ((total + z - 1) / z + unit - 1) / unit * unit;
+    for (int z = 1, st; z <= total && z <= 128; z = st > 1 ? (total + st - 2) / (st - 1) : total + 1) {
+      st = (total + z - 1) / z;
       if ((total + st - 1) / st != z) continue;
       if (z > 1 && plane * z > (double)scratch) break;
       const double w = (double)wgs * z, rounds = per_cu == 2 && w > 256 ? 1.7 * ceil(w / 512) : ceil(w / 256);
@@ -577,9 +584,10 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
   while (2 * a.cgroup * 128 * pl.ncg <= 1024 && grid.y % (2 * a.cgroup) == 0) a.cgroup *= 2;
   const size_t lds = gauss_lds(dt, pl.half);
   hipError_t e;
-#define FS_G(T, H)                                                          \
-  (pl.ncg == 4   ? go(gauss_kernel<T, 4, 1, 4, H>, grid, 256, lds, st, a)   \
-   : pl.ncg == 2 ? go(gauss_kernel<T, 2, 2, 2, H>, grid, 256, lds, st, a)   \
+#define FS_G(T, H)                                                                     \
+  (pl.ncg == 4   ? pl.stages % 2 ? go(gauss_kernel<T, 4, 1, 4, H, true>, grid, 256, lds, st, a) \
+                                 : go(gauss_kernel<T, 4, 1, 4, H>, grid, 256, lds, st, a)       \
+   : pl.ncg == 2 ? go(gauss_kernel<T, 2, 2, 2, H>, grid, 256, lds, st, a)              \
                  : go(gauss_kernel<T, 1, 4, 1, H>, grid, 256, lds, st, a))
   e = pl.half ? FS_G(float, true) : dt == FS_F32 ? FS_G(float, false) : dt == FS_BF16 ? FS_G(uint16_t, false) : FS_G(f16, false);
 #undef FS_G

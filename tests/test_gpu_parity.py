@@ -756,6 +756,33 @@ def test_dense_gaussian_split_over_few_tiles(k, d, n, pad, dtype):
     assert torch.equal(again, out) and torch.equal(sk.apply(A), out)
 
 
+@pytest.mark.parametrize("dtype,k,d,n", [
+    # work-groups of 512 columns: an even and an odd number of stages, and a last split of either
+    (torch.bfloat16, 640, 16384, 264), (torch.bfloat16, 1024, 10944, 295), (torch.bfloat16, 2304, 2176, 514), (torch.bfloat16, 768, 11840, 264),
+    (torch.float16, 768, 14720, 266), (torch.float16, 1920, 5312, 285), (torch.float16, 2432, 3648, 277), (torch.float16, 1152, 8192, 270),
+    (torch.float32, 2816, 1024, 305), (torch.float32, 256, 14528, 260), (torch.float32, 384, 14144, 263), (torch.float32, 2176, 2304, 275),
+    (torch.float32, 1664, 3712, 277), (torch.float32, 1664, 3776, 284), (torch.float32, 2432, 3648, 260), (torch.float32, 2816, 2880, 260),
+])
+def test_dense_gaussian_with_any_number_of_stages_in_a_split(dtype, k, d, n):
+    """Every split of d ends at a row of its own: NaN behind the last row, and what one split adds must not reach the next."""
+    print("gauss stages", k, d, n, dtype, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(k + n)
+    ld = (n + 7) & ~3
+    buf = torch.full((d + 70, ld), float("nan"), device=DEV, dtype=dtype)
+    buf[:d, :n] = torch.randn((d, n), generator=g, device=DEV).to(dtype)
+    A = buf[:d, :n]
+    sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
+    obuf = torch.full((k, n + 1), float("nan"), device=DEV, dtype=dtype)
+    out = sk.apply(A, obuf[:, :n])
+    torch.cuda.synchronize()
+    assert torch.isnan(obuf[:, n:].float()).all(), "wrote outside the n output columns"
+    ref = sk.export_dense().to(dtype).double() @ A.double()
+    # against S as its type holds it: one rounding of the result, and in fp32 sums of at most 14528 terms (2e-6 was seen at 65536)
+    err = float((out.double() - ref).norm() / ref.norm())
+    assert err <= {torch.float32: 4e-6, torch.bfloat16: 4e-3, torch.float16: 5e-4}[dtype], f"dense gaussian: {err:.3e}"
+    assert torch.equal(sk.apply(A), out)
+
+
 @pytest.mark.parametrize("k,d,n,pad", [(2816, 4992, 152, 0), (1536, 64 * 157, 321, 3), (4096, 4096, 1030, 2), (512, 32768, 300, 4)])
 def test_dense_gaussian_fp32_columns_of_any_magnitude(k, d, n, pad):
     """fp32 calls large enough for the half pieces (by the planner; an odd number of stages, a last column tile of few columns):

@@ -156,6 +156,21 @@ assert run.x * run.y * run.z <= 256 and run.z == {splits}, run
 """)
 
 
+@pytest.mark.parametrize("k,d,n,dtype,stages", [
+    (2048, 47808, 436, "BF16", 47),    # 747 stages for 16 row tiles: 16 splits are one whole round of 256 work-groups
+    (3584, 7424, 392, "F16", 17),
+])
+def test_a_dense_call_is_split_by_whole_stages_odd_or_even(recorded, k, d, n, dtype, stages):
+    recorded(f"""
+s = Sketch({d}, {k}, kind=2)
+rec.rec_clear()
+assert s.apply({n}, {dtype}) == 0
+run = launches()[0]
+assert "gauss_kernel" in run.kernel and "Li4ELi1ELi4E" in run.kernel and run.z == -(-({d} // 64) // {stages}), run
+assert "Li4ELi1ELi4ELb0ELb1E" in run.kernel, run      # the variant for an odd number of stages: none is added to a full split
+""")
+
+
 SPLIT = """
 def split(s, n, dtype, ld=None):              # the kernels of a call and their row split
     rec.rec_clear()
