@@ -44,7 +44,13 @@
  *              (its workspace is shared).
  *   Precision  accumulation is always fp32; one fp32 multiply by
  *              (float)(1/sqrt(kappa*s)) follows; bf16 and half outputs are rounded to
- *              nearest-even.
+ *              nearest-even.  FS_KIND_GAUSS_DENSE, fp32: S and A are multiplied in 16-bit pieces, either
+ *              three bf16 ones that hold every entry exactly or (larger calls, by price, on handles
+ *              that have them) two half ones that hold it to 2^-23 relative or 2^-39 of the largest
+ *              entry of its column of A, or of S.  Columns with few terms (some 300, a term counted by the
+ *              fourth root of its share of the largest) are not taken in half pieces, so that the
+ *              sketch of a unit vector is a column of S bit for bit; the error of the others against 64
+ *              bits is below that of the exact pieces, which take twice as many rounded additions.
  *   Errors     every call returns fs_status; nothing throws, aborts or prints.
  *              Argument errors are detected before any HIP call is made.
  *   Determinism FS_KIND_BLOCKPERM uses no atomics on data: the same call gives
@@ -146,7 +152,10 @@ fs_status fs_sketch_create(fs_sketch_t* out, int64_t d, int64_t k, int32_t Bc, i
 
 /* As above for any kind.  SJLT_SCATTER requires Bc == d, Br == k, kappa == 1.
  * GAUSS_DENSE allocates and fills the k x d matrix on the current device
- * (FS_ERR_HIP / FS_ERR_ALLOC without a device); it ignores Bc, Br, kappa, s. */
+ * (FS_ERR_HIP / FS_ERR_ALLOC without a device); it ignores Bc, Br, kappa, s.  It asks for 18 bytes per
+ * entry and 68 MiB; if the device has no room for that, for 14 bytes per entry and 64 MiB (no half
+ * pieces: larger fp32 applies take longer, and their last bits differ), then for the 14 bytes alone
+ * (applies do not split d).  Which of the three a handle got does not change afterwards. */
 fs_status fs_sketch_create_kind(fs_sketch_t* out, fs_kind kind, int64_t d, int64_t k, int32_t Bc,
                                 int32_t Br, int32_t kappa, int32_t s, uint64_t seed);
 

@@ -17,9 +17,12 @@
 // traffic only: the loads of A stay in flight).
 // Small fp32 applies use six bf16 MFMAs per tile (hi*hi, hi*mid, mid*hi, hi*lo, lo*hi,
 // mid*mid); the dropped cross terms are below 2^-23 relative.  Larger ones use three half MFMAs (hi*hi, hi*lo, lo*hi) on
-// x*2^e = hi + lo with 11 significant bits and a sign each, so that 2^-23 relative is left and lo*lo is below 2^-23;
-// the range of half is no limit, since each column of A has an e of its own (gauss_colmax_kernel: its largest entry
-// comes to lie between 2^14 and 2^15, half's subnormals reach 2^-39 below that) and S has one for all.
+// x*2^e = hi + lo, two halfs of 11 significant bits: off by 2^-23 of x at most (a quarter of all numbers of 24 bits are), or,
+// where lo falls under half's normal range (|x*2^e| < 2^-2), by 2^-25; the dropped lo*lo is below 2^-22.  Each column of A has an e of
+// its own, by which its largest entry comes to lie between 2^14 and 2^15 (gauss_colmax_kernel), so that 2^-25 is 2^-39 of that entry;
+// S has one for all.  Summed over a column of many terms that is less than what half as many rounded additions spare;
+// column tiles with a column of few terms, where it would not be (a unit vector's sketch is a column of S), are computed with
+// six products by a second launch (gauss_terms).
 //
 // What bounds it: the matrix cores, if a wave has enough of them per element it loads and (fp32)
 // splits: a 128 x 128 wave tile (all 512 registers of a lane) has 48 MFMAs per 80 vector instructions of a
@@ -81,15 +84,24 @@ __global__ __launch_bounds__(256) void gauss_fill_kernel(float* __restrict__ S32
   }
 }
 
-// The largest magnitude of every column over the rows [c*rows, (c+1)*rows), c = blockIdx.y, as the bits of a
-// float: part[c][column].  NaN is above infinity.  A work-group takes 4*2^sh columns, its lanes 4 each.
+// Fourth root of the magnitude with these bits, to 6 %: a quarter of its exponent, and of its significand linearly.  Zero and
+// subnormal numbers give kRoot0.  (Two of the root instruction made the pass over A wait for them, on 64 work-groups by 5 to 8 us.)
+__device__ __forceinline__ float root4(uint32_t bits) { return __uint_as_float((bits >> 2) + 0x2FA00000u); }
+constexpr float kRoot0 = 0x1.4p-32f;
+
+// Of every column over the rows [c*rows, (c+1)*rows), c = blockIdx.y: the largest magnitude, as the bits of a float
+// (NaN is above infinity), part[c][column], and the sum of the magnitudes' fourth roots, sums[c][column].  A work-group
+// takes 4*2^sh columns, its lanes 4 each.
 __global__ __launch_bounds__(1024) void gauss_colmax_kernel(const float* __restrict__ A, int64_t d, int64_t lda, int n,
-                                                            int64_t rows, int sh, uint32_t* __restrict__ part, int64_t ldw) {
+                                                            int64_t rows, int sh, uint32_t* __restrict__ part,
+                                                            float* __restrict__ sums, int64_t ldw) {
   __shared__ uint4 s_max[1024];
+  __shared__ float4 s_sum[1024];
   const int tid = threadIdx.x, lanes = 1 << sh, sub = tid >> sh, nsub = 1024 >> sh;
   const int col0 = ((int)blockIdx.x * lanes + (tid & (lanes - 1))) * 4;
   const int64_t first = (int64_t)blockIdx.y * rows, last = min(first + rows, d);
   uint4 m = make_uint4(0, 0, 0, 0);
+  float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
   if (col0 < n) {
     constexpr int UN = 8;  // loads in flight
     for (int64_t r0 = first + sub; r0 < last; r0 += UN * nsub) {
@@ -99,25 +111,34 @@ __global__ __launch_bounds__(1024) void gauss_colmax_kernel(const float* __restr
         v[j] = *reinterpret_cast<const uint4*>(A + min(r0 + j * nsub, last - 1) * lda + col0);
 #pragma unroll
       for (int j = 0; j < UN; ++j) {
-        m.x = max(m.x, v[j].x & 0x7fffffffu); m.y = max(m.y, v[j].y & 0x7fffffffu);
-        m.z = max(m.z, v[j].z & 0x7fffffffu); m.w = max(m.w, v[j].w & 0x7fffffffu);
+        const uint32_t mask = r0 + j * nsub < last ? 0x7fffffffu : 0u;
+        v[j].x &= mask; v[j].y &= mask; v[j].z &= mask; v[j].w &= mask;
+        m.x = max(m.x, v[j].x); m.y = max(m.y, v[j].y); m.z = max(m.z, v[j].z); m.w = max(m.w, v[j].w);
+        if (mask) { f.x += root4(v[j].x); f.y += root4(v[j].y); f.z += root4(v[j].z); f.w += root4(v[j].w); }
       }
     }
   }
   s_max[tid] = m;
+  s_sum[tid] = f;
   __syncthreads();
   for (int h = 512; h >= lanes; h >>= 1) {
     if (tid < h) {
       const uint4 o = s_max[tid + h];
       m.x = max(m.x, o.x); m.y = max(m.y, o.y); m.z = max(m.z, o.z); m.w = max(m.w, o.w);
       s_max[tid] = m;
+      const float4 g = s_sum[tid + h];
+      f.x += g.x; f.y += g.y; f.z += g.z; f.w += g.w;
+      s_sum[tid] = f;
     }
     __syncthreads();
   }
-  if (tid < lanes && col0 < n) *reinterpret_cast<uint4*>(part + (int64_t)blockIdx.y * ldw + col0) = m;
+  if (tid < lanes && col0 < n) {
+    *reinterpret_cast<uint4*>(part + (int64_t)blockIdx.y * ldw + col0) = m;
+    *reinterpret_cast<float4*>(sums + (int64_t)blockIdx.y * ldw + col0) = f;
+  }
 }
 
-// x (8 rows of one column) * m as two half pieces each, rounded to nearest: what is left is below 2^-23 of x*m.
+// x (8 rows of one column) * m as two half pieces each, rounded to nearest: what is left is at most 2^-23 of x*m or 2^-25.
 __device__ __forceinline__ void split_half(const uint32_t (&x)[8], float m, uint4& hi, uint4& lo) {
   typedef f16 h2 __attribute__((ext_vector_type(2)));
   uint32_t* h = reinterpret_cast<uint32_t*>(&hi);
@@ -140,8 +161,13 @@ struct GaussArgs {
   float* ws;  // zsplit > 1: planes of k x ldw floats
   int64_t k, d, lda, ldo, ldw;
   int n, total, stages, zsplit, out_vec;
-  // two half pieces: largest magnitudes of the columns, `parts` rows of ldw, and the exponent S was scaled by
+  // two half pieces: largest magnitudes of the columns and sums of their fourth roots, `parts` rows of ldw each, and the
+  // exponent S was scaled by; `few`: for every column tile of grid.y whether one of its columns has fewer than `terms` terms,
+  // written by the kernel of half pieces, which leaves such a tile to the one of three
   const uint32_t* colmax;
+  const float* colsum;
+  int* few;
+  float terms;
   int parts, es;
   int cgroup;  // column tiles (of grid.y, which it divides) that consecutive work-groups take in turn
 };
@@ -150,9 +176,11 @@ struct GaussArgs {
 // the d/64; wave: 32*MT rows x 128 columns.
 // HALF (fp32): two half pieces of both operands instead of three bf16 ones.
 // ODD: whether a.stages is (only the kernel that walks two stages a pass has to know: a last stage of its own for either
-// parity costs the accumulators of a wave their registers, 370 to 930 spilled.  Splits rounded up to an even number
+// parity costs the accumulators of a wave their registers, 370 to 930 spilled).  Splits rounded up to an even number
 // took longer (us per call): bf16 47808 x 436, k = 2048 121 -> 113, half 7424 x 392, k = 3584 47.2 -> 45.6.
-template <typename T, int MT, int NRG, int NCG, bool HALF = false, bool ODD = false>
+// REST (fp32, three pieces): the column tiles that the kernel of half pieces left.  They are scaled too: below 2^-110 an
+// entry's third piece would lie under bf16's range.
+template <typename T, int MT, int NRG, int NCG, bool HALF = false, bool ODD = false, bool REST = false>
 __global__ __launch_bounds__(64 * NRG * NCG) __attribute__((amdgpu_waves_per_eu(MT > 2 || (MT == 2 && sizeof(T) == 4) ? 1 : 2)))
 void gauss_kernel(GaussArgs a) {
   using V = typename Ld<T>::V;
@@ -211,30 +239,74 @@ void gauss_kernel(GaussArgs a) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[mt][c][i] = 0.f;
 
-  // HALF: the power of two that takes the largest entry of each of the lane's columns to [2^14, 2^15), or as near as
+  if constexpr (REST) {
+    if (!a.few[by]) return;  // (uniform)
+  }
+  // SCALE: the power of two that takes the largest entry of each of the lane's columns to [2^14, 2^15), or as near as
   // the exponents of a float go (columns of subnormals); 1 for columns with an infinity or a NaN
+  constexpr bool SCALE = HALF || REST;
   float colm[4];
-  if constexpr (HALF) {
+  if constexpr (SCALE) {
+    // The rows of maxima and sums, dealt to the 2*NRG half-waves of a column group, then through LDS: a chain of a few loads
+    // in front of the first product (all 64 rows by every lane took 3 to 6 us).
+    constexpr int SHARES = 2 * NRG, UN = NCG == 4 ? 16 : 8;  // loads in flight (past the end the last one again)
+    uint4* s_m = reinterpret_cast<uint4*>(smem);              // [NCG][SHARES][32]
+    float4* s_f = reinterpret_cast<float4*>(s_m + NCG * SHARES * 32);
+    int* vote = reinterpret_cast<int*>(s_f + NCG * SHARES * 32);
     uint4 m = make_uint4(0, 0, 0, 0);
-    if (col0 < a.n) {  // (n is rounded up to 4 in the rows of the maxima)
-      constexpr int UN = 16;  // loads in flight (past the end the last one again)
-      for (int i = 0; i < a.parts; i += UN) {
+    float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (col0 < a.n) {  // (n is rounded up to 4 in the rows)
+      for (int i = 2 * rg + kg; i < a.parts; i += UN * SHARES) {
         uint4 v[UN];
+        float4 w[UN];
 #pragma unroll
-        for (int j = 0; j < UN; ++j)
-          v[j] = *reinterpret_cast<const uint4*>(a.colmax + (int64_t)min(i + j, a.parts - 1) * a.ldw + col0);
+        for (int j = 0; j < UN; ++j) {
+          const int64_t at = (int64_t)min(i + j * SHARES, a.parts - 1) * a.ldw + col0;
+          v[j] = *reinterpret_cast<const uint4*>(a.colmax + at);
+          if constexpr (HALF) w[j] = *reinterpret_cast<const float4*>(a.colsum + at);
+        }
 #pragma unroll
         for (int j = 0; j < UN; ++j) {
           m.x = max(m.x, v[j].x); m.y = max(m.y, v[j].y); m.z = max(m.z, v[j].z); m.w = max(m.w, v[j].w);
+          if (HALF && i + j * SHARES < a.parts) { f.x += w[j].x; f.y += w[j].y; f.z += w[j].z; f.w += w[j].w; }
         }
       }
     }
+    s_m[(cg * SHARES + 2 * rg + kg) * 32 + (lane & 31)] = m;
+    if constexpr (HALF) s_f[(cg * SHARES + 2 * rg + kg) * 32 + (lane & 31)] = f;
+    __syncthreads();
+    m = make_uint4(0, 0, 0, 0);
+    f = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int h = 0; h < SHARES; ++h) {
+      const uint4 v = s_m[(cg * SHARES + h) * 32 + (lane & 31)];
+      m.x = max(m.x, v.x); m.y = max(m.y, v.y); m.z = max(m.z, v.z); m.w = max(m.w, v.w);
+      if constexpr (HALF) {
+        const float4 w = s_f[(cg * SHARES + h) * 32 + (lane & 31)];
+        f.x += w.x; f.y += w.y; f.z += w.z; f.w += w.w;
+      }
+    }
     const uint32_t mx[4] = {m.x, m.y, m.z, m.w};
+    const float sum[4] = {f.x, f.y, f.z, f.w};
+    bool few = false;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const uint32_t e = mx[c] >> 23;
       colm[c] = __uint_as_float((e == 255 ? 127u : min(268u - e, 254u)) << 23);
+      // (less what d zeros add; a column of zeros alone has terms enough, one with an infinity or a NaN has not)
+      if (col0 + c < a.n && mx[c]) few |= e == 255 || sum[c] - (float)a.d * kRoot0 < a.terms * root4(mx[c]);
     }
+    if constexpr (HALF) {
+      const bool wave_few = __any(few);
+      if (lane == 0) vote[wave] = wave_few;
+      __syncthreads();
+      bool tile_few = false;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) tile_few |= vote[w] != 0;
+      if (bx == 0 && bz == 0 && tid == 0) a.few[by] = tile_few;
+      if (tile_few) return;  // (uniform)
+    }
+    __syncthreads();  // (all of this lies where tiles of S will)
   }
 
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));  // (an array of uint4 lands in scratch memory here)
@@ -328,6 +400,10 @@ void gauss_kernel(GaussArgs a) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
               xs[j] = c0 + c == 0 ? cur[j].x : c0 + c == 1 ? cur[j].y : c0 + c == 2 ? cur[j].z : cur[j].w;
+            if constexpr (REST) {  // exact, or far below what the column's largest entry leaves of fp32
+#pragma unroll
+              for (int j = 0; j < 8; ++j) xs[j] = __float_as_uint(__uint_as_float(xs[j]) * colm[c0 + c]);
+            }
             if constexpr (HALF) split_half(xs, colm[c0 + c], x[c][0], x[c][1]);
             else split_ops(xs, x[c][0], x[c][1], x[c][PARTS - 1]);
           }
@@ -402,9 +478,9 @@ void gauss_kernel(GaussArgs a) {
 
   if (col0 >= a.n) return;
   int unscale[4];
-  if constexpr (HALF) {
+  if constexpr (SCALE) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) unscale[c] = 127 - (int)(__float_as_uint(colm[c]) >> 23) - a.es;
+    for (int c = 0; c < 4; ++c) unscale[c] = 127 - (int)(__float_as_uint(colm[c]) >> 23) - (HALF ? a.es : 0);
   }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
@@ -412,7 +488,7 @@ void gauss_kernel(GaussArgs a) {
     for (int i = 0; i < 16; ++i) {
       const int64_t row = row_base + (rg * MT + mt) * 32 + 8 * (i >> 2) + 4 * kg + (i & 3);
       float v[4] = {acc[mt][0][i], acc[mt][1][i], acc[mt][2][i], acc[mt][3][i]};
-      if constexpr (HALF) {
+      if constexpr (SCALE) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) v[c] = ldexpf(v[c], unscale[c]);
       }
@@ -437,13 +513,23 @@ void gauss_kernel(GaussArgs a) {
   }
 }
 
-// half: fp32 on two half pieces; its column maxima, in up to 64 shares of the rows, have kColmaxRoom bytes in front of the planes.
+// half: fp32 on two half pieces; the maxima and sums of its columns, in up to 64 shares of the rows, and a word per column
+// tile have kColmaxRoom bytes in front of the planes.
 struct GaussPlan { int ncg = 4, zsplit = 1, stages = 1; bool half = false; double us = 0; };
 constexpr size_t kColmaxRoom = (size_t)4 << 20;
 int64_t colmax_parts(int64_t ldw) {
-  const int64_t p = (int64_t)kColmaxRoom / (ldw * 4);
+  const int64_t p = ((int64_t)kColmaxRoom - 4 * (ldw / 128 + 1)) / (ldw * 8);
   return p > 64 ? 64 : p;
 }
+
+// Terms from which on a column is summed as well from two half pieces as from three: three hold it exactly, so that what
+// counts there is only how many of its additions are rounded; of a column of few terms hardly any.  A term counts by the
+// fourth root of its share of the largest (2^-20 of it as 1/32: such terms are still rounded when they are added).  Error
+// against 64 bits, two pieces / three, for m terms of random sign and place: of magnitude 1 1.77 (m = 2), 1.14 (16), 1.05 (128), 1.01
+// (512) at 65536 x 512, k = 4096 with 8 splits of d, 1.10 (64), 1.05 (256), 1.03 (1024) at 32768 x 300, k = 512 with 64 splits, which are
+// each summed apart; normal ones 1.08 (1), 0.94 (32), 0.80 (256) and 1.14, 1.04, 0.95; one term of magnitude 1 among 65536 of 2^-20 0.91, of
+// 2^-26 1.00.  (A dense column of normal entries has 0.6 d.)
+constexpr int gauss_terms(int zsplit) { return 256 + 16 * zsplit; }
 
 // LDS of a work-group: two stages of the pieces of S.
 size_t gauss_lds(fs_dtype dt, bool half) { return (size_t)2 * (half ? 2 : dt == FS_F32 ? 3 : 1) * 128 * PHI_LD * 2; }
@@ -480,20 +566,21 @@ GaussPlan gauss_plan(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratc
       if ((ncg == 4 && z == 1) || t < 0.98 * best) { best = t; pl.ncg = ncg; pl.zsplit = z; pl.stages = st; }
     }
   }
-  pl.us = best + (half ? 8.0 + (double)d * (double)n * 4.0 / 4.5e6 : 0.0);
+  pl.us = best + (half ? 10.0 + (double)d * (double)n * 4.0 / 4.5e6 : 0.0);
   return pl;
 }
 
-// fp32: two half pieces of both operands are three products where three bf16 pieces are six, behind a pass over A for the
-// largest entry of each column.  Small calls cannot win back that pass's launch and its read (us, six products against
-// three: 4608 x 44, k = 384 13 / 19; 8192 x 280, k = 384 32.0 / 32.4; 4992 x 152, k = 2816 55 / 48; 8192 x 1024, k = 4096
-// 331 / 213; 65536 x 1024, k = 4096 2335 / 1383).  Error against 64 bits: 4608 x 44 1.7e-7 / 1.5e-7, 29952 x 840 9.8e-7 / 6.5e-7, 65536 x
-// 1024 2.7e-6 / 1.6e-6 (half as many additions are rounded).
+// fp32: two half pieces of both operands are three products where three bf16 pieces are six, behind a pass over A for what
+// each column needs and before a launch that finds nothing to do unless a tile was left.  Small calls cannot win back the two
+// launches and the read (us, six products against three: 4416 x 64, k = 3840 40.2 / 38.7; 12672 x 36, k = 1152 34.7 / 35.0; 4992 x 152,
+// k = 2816 53.2 / 48.1; 57856 x 208, k = 640 117 / 94; 65536 x 1024, k = 4096 2283 / 1394).  Error against 64 bits: 4416 x 64 3.8e-7 / 2.8e-7,
+// 57856 x 208 6.7e-7 / 4.4e-7, 65536 x 1024 2.7e-6 / 1.6e-6, 0.45 to 0.76 times in 60 random calls (half as many additions are
+// rounded, each by more than the pieces leave out).
 GaussPlan gauss_choose(int64_t k, int64_t d, int64_t n, fs_dtype dt, size_t scratch, bool pieces) {
   GaussPlan pl = gauss_plan(k, d, n, dt, scratch, false);
   if (dt == FS_F32 && pieces && colmax_parts((n + 3) & ~(int64_t)3) > 0) {
     const GaussPlan h = gauss_plan(k, d, n, dt, scratch, true);
-    if (h.us < 0.92 * pl.us) pl = h;
+    if (h.us < 0.95 * pl.us && d >= 4 * gauss_terms(h.zsplit)) pl = h;  // (where a dense column has the terms)
   }
   return pl;
 }
@@ -560,12 +647,13 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
   a.ws = (float*)((char*)storage + gauss_bytes(k, d) + (half ? gauss_half_bytes(k, d) : 0));
   a.out_vec = ((uintptr_t)out % (4 * esz) == 0 && (ldo * esz) % (4 * esz) == 0) ? 1 : 0;
   a.S[1] = a.S[2] = nullptr;
-  a.colmax = nullptr; a.parts = 0; a.es = half_exponent(k);
+  a.colmax = nullptr; a.colsum = nullptr; a.few = nullptr; a.parts = 0; a.es = half_exponent(k);
+  a.terms = (float)gauss_terms(pl.zsplit);
   if (ev.start) (void)hipEventRecord(ev.start, st);  // (both passes over A lie between the events)
   if (pl.half) {
     a.S[0] = (const uint16_t*)((char*)storage + gauss_bytes(k, d));
     a.S[1] = a.S[0] + k * d;
-    const int sh = n > 128 ? 6 : n > 64 ? 5 : n > 32 ? 4 : 3;
+    const int sh = n > 512 ? 6 : n > 256 ? 5 : n > 128 ? 4 : 3;  // (three tiles or more: 64 work-groups do not read at the full rate)
     const int64_t tiles = (n + (4 << sh) - 1) / (4 << sh);
     int64_t parts = (256 + tiles - 1) / tiles;  // about 4096 waves
     parts = parts > colmax_parts(a.ldw) ? colmax_parts(a.ldw) : parts;
@@ -573,8 +661,11 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
     a.colmax = maxima;
     const int64_t rows = (d + parts - 1) / parts;
     a.parts = (int)((d + rows - 1) / rows);
+    float* sums = (float*)(maxima + a.parts * a.ldw);
+    a.colsum = sums;
+    a.few = (int*)(sums + a.parts * a.ldw);
     hipLaunchKernelGGL(gauss_colmax_kernel, dim3((unsigned)tiles, (unsigned)a.parts), dim3(1024), 0, st, (const float*)A, d,
-                       lda, (int)n, rows, sh, maxima, a.ldw);
+                       lda, (int)n, rows, sh, maxima, sums, a.ldw);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else if (dt == FS_F32) { a.S[0] = b + k * d; a.S[1] = b + 2 * k * d; a.S[2] = b + 3 * k * d; }
@@ -582,14 +673,23 @@ hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int
   const dim3 grid((unsigned)(k / 128), (unsigned)((n + 128 * pl.ncg - 1) / (128 * pl.ncg)), (unsigned)pl.zsplit);
   a.cgroup = 1;
   while (2 * a.cgroup * 128 * pl.ncg <= 1024 && grid.y % (2 * a.cgroup) == 0) a.cgroup *= 2;
-  const size_t lds = gauss_lds(dt, pl.half);
   hipError_t e;
-#define FS_G(T, H)                                                                     \
-  (pl.ncg == 4   ? pl.stages % 2 ? go(gauss_kernel<T, 4, 1, 4, H, true>, grid, 256, lds, st, a) \
-                                 : go(gauss_kernel<T, 4, 1, 4, H>, grid, 256, lds, st, a)       \
-   : pl.ncg == 2 ? go(gauss_kernel<T, 2, 2, 2, H>, grid, 256, lds, st, a)              \
-                 : go(gauss_kernel<T, 1, 4, 1, H>, grid, 256, lds, st, a))
-  e = pl.half ? FS_G(float, true) : dt == FS_F32 ? FS_G(float, false) : dt == FS_BF16 ? FS_G(uint16_t, false) : FS_G(f16, false);
+#define FS_G(T, H, R)                                                                                               \
+  (pl.ncg == 4   ? pl.stages % 2 ? go(gauss_kernel<T, 4, 1, 4, H, true, R>, grid, 256, gauss_lds(dt, H), st, a)     \
+                                 : go(gauss_kernel<T, 4, 1, 4, H, false, R>, grid, 256, gauss_lds(dt, H), st, a)    \
+   : pl.ncg == 2 ? go(gauss_kernel<T, 2, 2, 2, H, false, R>, grid, 256, gauss_lds(dt, H), st, a)                    \
+                 : go(gauss_kernel<T, 1, 4, 1, H, false, R>, grid, 256, gauss_lds(dt, H), st, a))
+  if (pl.half) {
+    e = FS_G(float, true, false);
+    if (e == hipSuccess) {  // the column tiles that it left, into the same planes
+      a.S[0] = b + k * d; a.S[1] = b + 2 * k * d; a.S[2] = b + 3 * k * d;
+      e = FS_G(float, false, true);
+    }
+  } else {
+    e = dt == FS_F32    ? FS_G(float, false, false)
+        : dt == FS_BF16 ? FS_G(uint16_t, false, false)
+                        : FS_G(f16, false, false);
+  }
 #undef FS_G
   if (ev.stop) (void)hipEventRecord(ev.stop, st);
   if (e != hipSuccess || pl.zsplit == 1) return e;

@@ -817,6 +817,62 @@ def test_dense_gaussian_fp32_columns_of_any_magnitude(k, d, n, pad):
     assert torch.equal(sk.apply(A)[:, rest], out[:, rest])
 
 
+@pytest.mark.parametrize("k,d,n", [(3840, 4416, 31), (1664, 44096, 44), (1152, 48960, 68), (2816, 4992, 152), (1536, 64 * 157, 321), (4096, 4096, 1030)])
+def test_dense_gaussian_fp32_dense_columns_of_any_magnitude_in_half_pieces(k, d, n):
+    """Columns of many terms only, so that no tile is left to the kernel of three pieces: from 2^-120 to 2^110, one of zeros,
+    NaN in the padding and behind the last row."""
+    print("gauss fp32 half pieces", k, d, n, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(13)
+    buf = torch.full((d + 66, (n + 7) & ~3), float("nan"), device=DEV)
+    A = buf[:d, :n]
+    e = torch.linspace(-120.0, 110.0, n, dtype=torch.float64, device=DEV)
+    A.copy_((torch.randn((d, n), generator=g, device=DEV).double() * torch.exp2(e)).float())
+    A[:, n // 2] = 0.0
+    sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
+    out = sk.apply(A)
+    torch.cuda.synchronize()
+    ref = sk.export_dense().double() @ A.double()
+    assert (out[:, n // 2] == 0).all()
+    err = (out.double() - ref).norm(dim=0) / ref.norm(dim=0).clamp(min=1e-300)
+    # each column by itself: d products off by 2^-22 relative at most, in sums that were seen off by 2.7e-6 at d = 65536
+    assert err.max() <= 4e-6, err.max()
+    assert torch.equal(sk.apply(A), out)
+
+
+@pytest.mark.parametrize("k,d,n", [(1664, 44096, 44), (2816, 4992, 152), (1536, 64 * 157, 321), (4096, 4096, 1030), (512, 32768, 300)])
+def test_dense_gaussian_fp32_columns_of_few_terms_are_exact_in_larger_calls(k, d, n):
+    """Unit vectors, scaled by powers of two: their sketch is a column of S, bit for bit, in calls that hold dense columns in two
+    half pieces; the other column tiles stay as they are.  A large entry among many small ones: an absolute bound from it."""
+    print("gauss fp32 few terms", k, d, n, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(12)
+    dense, A = (torch.randn((d, (n + 3) & ~3), generator=g, device=DEV)[:, :n] for _ in range(2))
+    sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
+    S = sk.export_dense()
+    before = sk.apply(dense)
+    A.copy_(dense)
+    cols = list(range(max(0, n - 20), n, 2))    # the last column tile
+    hot = [(i * 7919) % d for i in range(len(cols))]
+    for i, (c, r) in enumerate(zip(cols, hot)):
+        A[:, c] = 0.0
+        A[r, c] = (-1.0) ** i * 2.0 ** [0, 0, 1, -1, 20, -20, 60, -60, 90, -90][i % 10]
+    out = sk.apply(A)
+    for c, r in zip(cols, hot):
+        assert torch.equal(out[:, c], S[:, r] * A[r, c]), (c, r)
+    same = cols[0] // 512 * 512                 # no work-group has more columns
+    assert torch.equal(out[:, :same], before[:, :same])
+    assert torch.equal(sk.apply(dense), before) and torch.equal(sk.apply(A), out)   # nothing stays behind
+    every = torch.arange(n, device=DEV)
+    for small in (-20, -26, -30):
+        A.copy_(dense * 2.0 ** small)
+        A[every * 31 % d, every] = 1.0
+        out = sk.apply(A)
+        ref = S.double() @ A.double()
+        # a result is S_ri and small terms: 2^-22 of S_ri from the pieces at most, and the sum of a split is rounded once per
+        # product of 16 rows, 3 d / 16 times at most, by 2^-25 of S_ri in the root mean square (six times that as the largest)
+        bound = 2.0 ** -22 + 6 * 2.0 ** -25 * (3 * d / 16) ** 0.5
+        assert (out.double() - ref).abs().max() <= bound * float(S.abs().max()), small
+
+
 # ------------------------------------------------ full-size configs -------
 def _sampled_parity(cfg, A, out, seed=0):
     """Oracle on a sample of columns of the full-size problem: one column, at a random place, from

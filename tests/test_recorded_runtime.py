@@ -171,6 +171,24 @@ assert "Li4ELi1ELi4ELb0ELb1E" in run.kernel, run      # the variant for an odd n
 """)
 
 
+def test_a_dense_call_on_half_pieces_is_followed_by_the_kernel_for_columns_of_few_terms(recorded):
+    """(It takes the column tiles that the other left: same grid, same planes.)"""
+    recorded("""
+for k, d, n, half in ((4096, 4096, 1030, True), (2816, 4992, 152, True), (1664, 44096, 44, True), (384, 4608, 44, False),
+                      (4096, 512, 4096, False)):          # (512 rows: a dense column has hardly the terms)
+    s = Sketch(d, k, kind=2)
+    rec.rec_clear()
+    assert s.apply(n, ld=(n + 3) & ~3) == 0
+    run = [l for l in launches() if "reduce" not in l.kernel]
+    assert len(run) == (3 if half else 1), run
+    pieces = [2 if "ELb1ELb" in l.kernel else 3 for l in run if "12gauss_kernel" in l.kernel]
+    assert pieces == ([2, 3] if half else [3]), run
+    if half:
+        assert "gauss_colmax" in run[0].kernel and run[1][1:5] == run[2][1:5], run
+    s.destroy()
+""")
+
+
 SPLIT = """
 def split(s, n, dtype, ld=None):              # the kernels of a call and their row split
     rec.rec_clear()
