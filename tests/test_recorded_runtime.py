@@ -290,3 +290,48 @@ for params in [(15990, 128, 4000, 32, 2, 4), (16000, 256, 4001, 64, 4, 1), (1000
                 accepted += got[0][:2].count(0)
 assert refused > 100 and accepted > 100
 """)
+
+
+ROWS_FORM = """
+import re
+def form(s, n, dtype, ld=None):               # of a rows call: (stacked rows / 32, examples / 32, mode, splits, waves, chains of the reduction)
+    rec.rec_clear()
+    assert s.apply_rows(n, dtype, ld=ld) == 0
+    run = [l for l in launches() if "orbit" not in l.kernel]
+    mt, et, mode = map(int, re.search(r"rows_kernelI\\w+?Li(\\d)ELi(\\d)ELNS0_8RowsModeE(\\d)E", run[0].kernel).groups())
+    chains = int(re.search(r"reduce_rows_kernelI\\w+?Li\\dELi(\\d)E", run[1].kernel).group(1)) if len(run) > 1 else 0
+    return mt, et, mode, run[0].z, run[0].threads // 64, chains
+"""
+
+
+def test_rows_forms_that_are_taken_by_price_are_no_less_exact_in_fp32(recorded):
+    """Against the form of FS_VARIANT_MFMA, by what the two leave to fp32: twelve roundings per stage of a wave at the size of its
+    sum (or of the stage, where that is made apart), one per merged record, the reduction's chains."""
+    recorded(ROWS_FORM + """
+import math, random
+rng, moved = random.Random(2), 0
+def error(f, Bc, Br, kappa, sk):
+    mt, et, mode, z, nw, chains = f
+    total = -(-Bc // 64) * (kappa if mode else 1)
+    stages, apart = -(-total // (z * nw)), et == 1 and mt < 4
+    dense = 1 - (1 - sk / Br) ** 16           # of a product's 16 input rows some meet an output row
+    e = 1.7 + (3.9 * dense + 0.42 * stages if apart else 2.9 * dense * stages)
+    if chains:
+        addends = z * (1 if mode else kappa)
+        e += 1.1 + (0.5 if nw > 1 else 0) + (3.0 + 1.4 * addends / 16 if chains > 1 else 0)
+    return e / 0.93 if apart else e
+cases = [(23637, 4096, 185, 32, 4, 4, 156), (88448, 8192, 173, 16, 4, 8, 64), (10316, 1024, 645, 64, 1, 8, 198), (8585, 2048, 135, 32, 8, 8, 99)]
+for i in range(400):
+    M, Br, kappa = rng.choice([16, 32, 64, 128, 256]), rng.choice([8, 16, 32, 64, 128]), rng.choice([1, 2, 4, 8])
+    Bc = round(math.exp(rng.uniform(math.log(64), math.log(20000))))
+    cases.append((Bc * M - rng.randrange(Bc), Br * M, Bc, Br, kappa, rng.choice([2, 4, 8]), round(math.exp(rng.uniform(math.log(33), math.log(1024))))))
+for d, k, Bc, Br, kappa, sk, n in cases:
+    s = Sketch(d, k, Bc, Br, kappa, sk)
+    new = form(s, n, F32)
+    assert lib.fs_sketch_set_variant(s.h, 2) == 0
+    old = form(s, n, F32)
+    s.destroy()
+    moved += new != old
+    assert error(new, Bc, Br, kappa, sk) <= error(old, Bc, Br, kappa, sk) * 1.0001, (d, k, Bc, Br, kappa, sk, n, old, new)
+assert moved > 100
+""")
