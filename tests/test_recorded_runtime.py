@@ -335,3 +335,38 @@ for d, k, Bc, Br, kappa, sk, n in cases:
     assert error(new, Bc, Br, kappa, sk) <= error(old, Bc, Br, kappa, sk) * 1.0001, (d, k, Bc, Br, kappa, sk, n, old, new)
 assert moved > 100
 """)
+
+
+@pytest.mark.parametrize("params,n,dtype,pad", [
+    # us per call in this form and in the one the models preferred
+    ((26348, 4096, 103, 16, 4, 8), 823, "F16", 0),         # 34.7, 42.1: thirteen rounds of waves with one stage each
+    ((145573, 8192, 1138, 64, 1, 4), 538, "F16", 64),      # 38.5, 47.4
+    ((520256, 1024, 32516, 64, 1, 2), 336, "BF16", 0),     # 111, 134: bound by the stream of G
+    ((511868, 1024, 15996, 32, 1, 4), 524, "F16", 0),      # 138, 164
+    ((397504, 4096, 1553, 16, 4, 2), 328, "F16", 0),       # 66.6, 76.4
+    ((100544, 4096, 786, 32, 2, 4), 528, "F32", 0),        # 60.8, 75.2
+    ((1597598, 2048, 49925, 64, 1, 8), 66, "F16", 0),      # 57, 86
+    ((751817, 8192, 11748, 128, 8, 8), 68, "BF16", 64),    # 242, 327
+])
+def test_rows_calls_that_other_forms_would_slow_down_keep_theirs(recorded, params, n, dtype, pad):
+    recorded(ROWS_FORM + f"""
+s = Sketch(*{params})
+new = form(s, {n}, {dtype}, s.d + {pad})
+assert lib.fs_sketch_set_variant(s.h, 2) == 0
+assert new == form(s, {n}, {dtype}, s.d + {pad}), new
+""")
+
+
+@pytest.mark.parametrize("params,n,dtype,pad,want", [
+    ((9486, 2048, 149, 32, 4, 8), 312, "F16", 64, "one launch"),      # 24.6 -> 9.7 us
+    ((5696, 1024, 178, 32, 2, 8), 936, "F16", 0, "one launch"),
+    ((23132, 4096, 362, 64, 1, 2), 222, "BF16", 0, "one launch"),     # (kappa = 1: stored by tiles of 64 examples)
+    ((93968, 8192, 1472, 128, 8, 8), 529, "F16", 0, "one launch"),    # 356 -> 199
+    ((1090981, 2048, 68187, 128, 1, 2), 104, "BF16", 0, "two"),       # 79.6 -> 68.1
+])
+def test_rows_calls_that_other_forms_speed_up_take_them(recorded, params, n, dtype, pad, want):
+    recorded(ROWS_FORM + f"""
+s = Sketch(*{params})
+mt, et, mode, z, nw, chains = form(s, {n}, {dtype}, s.d + {pad})
+assert et < 4 and nw > 1 and (chains == 0) == ({want!r} == "one launch"), (mt, et, mode, z, nw, chains)
+""")
