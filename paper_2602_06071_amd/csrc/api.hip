@@ -503,7 +503,7 @@ fs_status fs_sketch_apply_rows(fs_sketch_t h, const void* G, int64_t ldg, int64_
   if (prof.end) (void)hipEventRecord(prof.end, st);
   snprintf(h->last_kernel, sizeof(h->last_kernel), "%s", plan.few.ok ? "vector_kernel" : "rows_kernel");
   h->last_variant = FS_VARIANT_MFMA;
-  h->last_mode = 2;
+  h->last_mode = plan.out_stat ? 1 : 2;
   if (e != hipSuccess) return hip_fail(h, e);
   return FS_OK;
 }

@@ -370,3 +370,18 @@ s = Sketch(*{params})
 mt, et, mode, z, nw, chains = form(s, {n}, {dtype}, s.d + {pad})
 assert et < 4 and nw > 1 and (chains == 0) == ({want!r} == "one launch"), (mt, et, mode, z, nw, chains)
 """)
+
+
+def test_a_rows_call_reports_the_mode_that_it_was_planned_in(recorded):
+    recorded("""
+modes = set()
+for params, n, dtype in [((9486, 2048, 149, 32, 4, 8), 312, F16), ((4194304, 8192, 4096, 8, 8, 2), 256, BF16), ((20160, 1280, 1008, 64, 1, 8), 129, F32),
+                         ((8192, 1024, 512, 64, 4, 8), 200, F32), ((262144, 4096, 2048, 32, 4, 4), 1, F32), ((262144, 4096, 2048, 32, 4, 4), 24, F32),
+                         ((256, 384, 64, 96, 2, 4), 70, F32)]:
+    s = Sketch(*params)
+    mode = C.c_int32()
+    assert lib.fs_sketch_plan(s.h, C.c_void_p(1 << 44), C.c_int64(s.d), C.c_int64(n), dtype, 1, None, C.byref(mode), None, None) == 0
+    assert s.apply_rows(n, dtype) == 0 and s.info().last_mode == mode.value, (params, n, s.info().last_mode, mode.value)
+    modes.add(mode.value)
+assert modes == {0, 1, 2}
+""")
