@@ -432,8 +432,8 @@ fs_status fs::apply_cols(fs_sketch_t h, const void* A, int64_t lda, int64_t n, v
     e = fs::launch_scatter(h->p, A, lda, n, out, ldo, dt, ws, st, ev);
     what = "scatter_kernel";
   } else if (h->kind == FS_KIND_GAUSS_DENSE) {
-    e = fs::launch_gauss(h->dense, h->dense_half, h->dense_scratch, h->p.k, h->p.d, A, lda, n, out, ldo, dt, st, ev);
-    what = "gauss_kernel";
+    e = fs::launch_gauss(h->dense, h->dense_half, h->dense_scratch, h->p.k, h->p.d, A, lda, n, out, ldo, dt, st, ev, h->last_kernel,
+                         sizeof(h->last_kernel));
   } else if (h->kind == FS_KIND_BLOCKROW) {
     e = fs::launch_blockrow(h->p, A, lda, n, out, ldo, dt, st, ev);
     what = "blockrow_kernel";

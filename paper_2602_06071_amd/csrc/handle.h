@@ -174,6 +174,7 @@ size_t gauss_half_bytes(int64_t k, int64_t d);
 hipError_t gauss_fill(void* storage, bool half, int64_t k, int64_t d, uint32_t key1, hipStream_t st);
 bool gauss_supported(int64_t k, int64_t d, const void* A, int64_t lda, int64_t n, fs_dtype dt);
 hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
-                        int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev);
+                        int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev, char* desc,
+                        size_t desc_cap);
 
 }  // namespace fs

@@ -31,6 +31,7 @@
 // column maxima, 1.26 PFLOP/s of half products (a library bf16 product of 8192^3 on random data: 1.22), i.e. what the
 // matrix cores do at the clock that power leaves them.
 #include <math.h>
+#include <stdio.h>
 
 #include <type_traits>
 
@@ -635,11 +636,16 @@ bool gauss_supported(int64_t k, int64_t d, const void* A, int64_t lda, int64_t n
 }
 
 hipError_t launch_gauss(void* storage, bool half, size_t scratch, int64_t k, int64_t d, const void* A, int64_t lda,
-                        int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev) {
+                        int64_t n, void* out, int64_t ldo, fs_dtype dt, hipStream_t st, EventPair ev, char* desc,
+                        size_t desc_cap) {
   const float* S32 = (const float*)storage;
   const uint16_t* b = (const uint16_t*)(S32 + k * d);
   const size_t esz = dt == FS_F32 ? 4 : 2;
   const GaussPlan pl = gauss_choose(k, d, n, dt, scratch, half);
+  if (desc && desc_cap)  // (a column tile with a column of few terms: by its counterpart on three pieces)
+    snprintf(desc, desc_cap, "gauss_kernel<%s,%d,%d,%d,%s,%s>%s", dt == FS_F32 ? "f32" : dt == FS_BF16 ? "bf16" : "f16", pl.ncg,
+             4 / pl.ncg, pl.ncg, pl.half ? "half" : "-", pl.ncg == 4 && pl.stages % 2 ? "odd" : "-",
+             pl.zsplit > 1 ? "+reduce_planes" : "");
   GaussArgs a;
   a.A = A; a.out = out; a.k = k; a.d = d; a.lda = lda; a.ldo = ldo; a.n = (int)n;
   a.total = (int)(d / KC); a.stages = pl.stages; a.zsplit = pl.zsplit;

@@ -390,21 +390,28 @@ KSPLIT_WIDE = [
 
 
 ROWS_MANY = [
-    # params (d,k,Bc,Br,kappa,s), n, pad: over 32 examples in tiles of 32 or 64 whose waves share the stages, or in one launch
-    ((9486, 2048, 149, 32, 4, 8), 312, 64),       # 64 blocks of three stages, a partly filled last block
-    ((4288, 512, 268, 32, 2, 4), 970, 0),         # many example tiles, the last one of 10 examples
-    ((20160, 1280, 1008, 64, 1, 8), 129, 1),      # kappa = 1, rows that start inside a dword
-    ((6142, 1024, 384, 64, 1, 8), 113, 0),
-    ((16384, 2048, 256, 32, 4, 2), 65, 3),
-    ((11200, 2048, 88, 16, 4, 2), 200, 0),        # blocks of 16 rows
-    ((31930, 1280, 3193, 128, 2, 4), 97, 2),      # blocks of 128 rows
-    ((13548, 288, 424, 9, 3, 2), 161, 0),         # Br not a power of two
+    # params (d,k,Bc,Br,kappa,s), n, pad, form in fp32, in 16 bits (stacked rows / 32, examples / 32 of a tile, mode; that they are
+    # taken is checked on the host, in test_recorded_runtime.py): over 32 examples in tiles of 32 or 64 whose waves share the
+    # stages, or in one launch
+    ((9486, 2048, 149, 32, 4, 8), 312, 64, "1,1,out", "1,2,out"),      # 64 blocks of three stages, a partly filled last block
+    ((4288, 512, 268, 32, 2, 4), 970, 0, "1,1,out", "1,1,out"),           # many example tiles, the last one of 10 examples
+    ((20160, 1280, 1008, 64, 1, 8), 129, 1, "2,2,out", "2,2,out"),     # kappa = 1, rows that start inside a dword
+    ((6142, 1024, 384, 64, 1, 8), 113, 0, "2,4,outsplit", "2,2,out"),     # (fp32: its sums are shorter as they are)
+    ((16384, 2048, 256, 32, 4, 2), 65, 3, "1,1,out", "1,1,out"),
+    ((11200, 2048, 88, 16, 4, 2), 200, 0, "1,2,out", "1,2,out"),          # blocks of 16 rows
+    ((31930, 1280, 3193, 128, 2, 4), 97, 2, "4,1,outsplit", "4,2,outsplit"),   # blocks of 128 rows
+    ((13548, 288, 424, 9, 3, 2), 161, 0, "2,2,in", "2,2,in"),             # Br not a power of two
+    ((10030, 160, 1020, 16, 4, 8), 232, 0, "2,2,in", "2,2,in"),
+    ((4144, 80, 420, 8, 8, 2), 283, 0, "2,2,in", "2,2,in"),               # blocks of 8 rows
+    ((9482, 160, 1038, 16, 8, 2), 125, 0, "4,2,in", "4,2,in"),            # 128 stacked rows
+    ((8899, 320, 923, 32, 4, 8), 109, 0, "4,2,in", "4,2,in"),
+    ((4354, 2048, 140, 64, 2, 4), 36, 0, "4,2,in", "2,1,out"),
 ]
 
 
 @DTYPES
-@pytest.mark.parametrize("params,n,pad", ROWS_MANY)
-def test_rows_of_more_than_32_examples_by_price(params, n, pad, dtype):
+@pytest.mark.parametrize("params,n,pad,form32,form16", ROWS_MANY)
+def test_rows_of_more_than_32_examples_by_price(params, n, pad, form32, form16, dtype):
     print("rows by price", params, n, pad, dtype, flush=True)
     d, k = params[0], params[1]
     g = torch.Generator(device=DEV).manual_seed(n + d)
@@ -419,6 +426,8 @@ def test_rows_of_more_than_32_examples_by_price(params, n, pad, dtype):
         torch.cuda.synchronize()
         assert torch.isnan(obuf[:, k:].float()).all(), "wrote outside the k output columns"
         check(out, ref, dtype, f"rows by price, variant {variant}")
+        if variant == B.VARIANT_AUTO:
+            assert sk.info().last_mode == sk.plan(n, dtype, ld=G.stride(0), rows=True, address=G.data_ptr())["mode"]
         assert torch.equal(sk.apply_rows(G), out)
 
 
@@ -756,14 +765,18 @@ def test_dense_gaussian_split_over_few_tiles(k, d, n, pad, dtype):
     assert torch.equal(again, out) and torch.equal(sk.apply(A), out)
 
 
-@pytest.mark.parametrize("dtype,k,d,n", [
-    # work-groups of 512 columns: an even and an odd number of stages, and a last split of either
-    (torch.bfloat16, 640, 16384, 264), (torch.bfloat16, 1024, 10944, 295), (torch.bfloat16, 2304, 2176, 514), (torch.bfloat16, 768, 11840, 264),
-    (torch.float16, 768, 14720, 266), (torch.float16, 1920, 5312, 285), (torch.float16, 2432, 3648, 277), (torch.float16, 1152, 8192, 270),
-    (torch.float32, 2816, 1024, 305), (torch.float32, 256, 14528, 260), (torch.float32, 384, 14144, 263), (torch.float32, 2176, 2304, 275),
-    (torch.float32, 1664, 3712, 277), (torch.float32, 1664, 3776, 284), (torch.float32, 2432, 3648, 260), (torch.float32, 2816, 2880, 260),
+@pytest.mark.parametrize("dtype,k,d,n,pieces,stages", [
+    # work-groups of 512 columns: an even and an odd number of stages, and for either a last split of either
+    (torch.bfloat16, 640, 16384, 264, "-", "-"), (torch.bfloat16, 1024, 10944, 295, "-", "-"),
+    (torch.bfloat16, 2304, 2176, 514, "-", "odd"), (torch.bfloat16, 768, 11840, 264, "-", "odd"),
+    (torch.float16, 768, 14720, 266, "-", "-"), (torch.float16, 1920, 5312, 285, "-", "-"),
+    (torch.float16, 2432, 3648, 277, "-", "odd"), (torch.float16, 1152, 8192, 270, "-", "odd"),
+    (torch.float32, 2816, 1024, 305, "-", "-"), (torch.float32, 256, 14528, 260, "-", "-"),
+    (torch.float32, 384, 14144, 263, "-", "odd"), (torch.float32, 2176, 2304, 275, "-", "odd"),
+    (torch.float32, 2560, 2432, 283, "half", "-"), (torch.float32, 2432, 4416, 262, "half", "-"),
+    (torch.float32, 768, 11968, 260, "half", "odd"), (torch.float32, 1408, 5952, 258, "half", "odd"),
 ])
-def test_dense_gaussian_with_any_number_of_stages_in_a_split(dtype, k, d, n):
+def test_dense_gaussian_with_any_number_of_stages_in_a_split(dtype, k, d, n, pieces, stages):
     """Every split of d ends at a row of its own: NaN behind the last row, and what one split adds must not reach the next."""
     print("gauss stages", k, d, n, dtype, flush=True)
     g = torch.Generator(device=DEV).manual_seed(k + n)
@@ -776,6 +789,8 @@ def test_dense_gaussian_with_any_number_of_stages_in_a_split(dtype, k, d, n):
     out = sk.apply(A, obuf[:, :n])
     torch.cuda.synchronize()
     assert torch.isnan(obuf[:, n:].float()).all(), "wrote outside the n output columns"
+    name = {torch.float32: "f32", torch.bfloat16: "bf16", torch.float16: "f16"}[dtype]
+    assert sk.info().last_kernel.decode() == f"gauss_kernel<{name},4,1,4,{pieces},{stages}>+reduce_planes"
     ref = sk.export_dense().to(dtype).double() @ A.double()
     # against S as its type holds it: one rounding of the result, and in fp32 sums of at most 14528 terms (2e-6 was seen at 65536)
     err = float((out.double() - ref).norm() / ref.norm())
@@ -801,6 +816,7 @@ def test_dense_gaussian_fp32_columns_of_any_magnitude(k, d, n, pad):
     sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
     out = sk.apply(A)
     torch.cuda.synchronize()
+    assert ",half," in sk.info().last_kernel.decode(), sk.info().last_kernel
     S = sk.export_dense().double()
     ref = S @ A.double()
     bad = torch.zeros(n, dtype=torch.bool, device=DEV)
@@ -817,8 +833,9 @@ def test_dense_gaussian_fp32_columns_of_any_magnitude(k, d, n, pad):
     assert torch.equal(sk.apply(A)[:, rest], out[:, rest])
 
 
-@pytest.mark.parametrize("k,d,n", [(3840, 4416, 31), (1664, 44096, 44), (1152, 48960, 68), (2816, 4992, 152), (1536, 64 * 157, 321), (4096, 4096, 1030)])
-def test_dense_gaussian_fp32_dense_columns_of_any_magnitude_in_half_pieces(k, d, n):
+@pytest.mark.parametrize("k,d,n,tile", [(3840, 4416, 31, "1,4,1"), (1664, 44096, 44, "1,4,1"), (1152, 48960, 68, "1,4,1"), (2816, 4992, 152, "2,2,2"),
+                                        (1536, 64 * 157, 321, "4,1,4"), (4096, 4096, 1030, "4,1,4")])
+def test_dense_gaussian_fp32_dense_columns_of_any_magnitude_in_half_pieces(k, d, n, tile):
     """Columns of many terms only, so that no tile is left to the kernel of three pieces: from 2^-120 to 2^110, one of zeros,
     NaN in the padding and behind the last row."""
     print("gauss fp32 half pieces", k, d, n, flush=True)
@@ -831,6 +848,7 @@ def test_dense_gaussian_fp32_dense_columns_of_any_magnitude_in_half_pieces(k, d,
     sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
     out = sk.apply(A)
     torch.cuda.synchronize()
+    assert sk.info().last_kernel.decode().startswith(f"gauss_kernel<f32,{tile},half,"), sk.info().last_kernel
     ref = sk.export_dense().double() @ A.double()
     assert (out[:, n // 2] == 0).all()
     err = (out.double() - ref).norm(dim=0) / ref.norm(dim=0).clamp(min=1e-300)
@@ -849,6 +867,7 @@ def test_dense_gaussian_fp32_columns_of_few_terms_are_exact_in_larger_calls(k, d
     sk = B.Sketch(d, k, d, k, 1, 1, seed=2, kind=B.KIND_GAUSS_DENSE)
     S = sk.export_dense()
     before = sk.apply(dense)
+    assert ",half," in sk.info().last_kernel.decode(), sk.info().last_kernel
     A.copy_(dense)
     cols = list(range(max(0, n - 20), n, 2))    # the last column tile
     hot = [(i * 7919) % d for i in range(len(cols))]

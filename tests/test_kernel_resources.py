@@ -52,3 +52,9 @@ def test_kernels_of_few_vectors_of_the_rows_layout_and_of_block_rows_spill_nothi
     assert found
     for name, v in found.items():
         assert v <= (2 if re.search(r"rows_kernelI\w+?Li4ELi4ELNS0_8RowsModeE1E", name) else 0), (name, v)
+
+
+def test_dense_kernels_spill_nothing(tmp_path):
+    """(Those of 512 columns fill 472 to 504 of a lane's 512 registers.)"""
+    found = {k: v for k, v in spills("k_gauss.o", tmp_path).items() if "gauss_kernel" in k}
+    assert len(found) == 20 and set(found.values()) == {0}, found

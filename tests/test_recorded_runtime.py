@@ -140,6 +140,21 @@ assert len(events) == 2 and events[0] < maxima[0] and max(product) < events[1], 
 """)
 
 
+def test_a_dense_sketch_without_room_for_half_pieces_splits_and_keeps_three(recorded):
+    recorded("""
+k, d, n = 2816, 4992, 152                     # taken in half pieces where a handle has them
+for room, half in ((20 * k * d + (128 << 20), True), (14 * k * d + (65 << 20), False)):
+    rec.rec_budget(rec.rec_live() + room)
+    s = Sketch(d, k, kind=2)
+    assert s.status == 0 and len(lines("malloc-failed")) == (0 if half else 1)
+    rec.rec_clear()
+    assert s.apply(n) == 0 and (",half," in s.kernel()) == half and s.kernel().endswith("+reduce_planes"), s.kernel()
+    assert ("gauss_colmax" in launches()[0].kernel) == half and launches()[-2].z > 1
+    assert s.destroy() == 0 and rec.rec_live() == 0
+    rec.rec_clear()
+""")
+
+
 @pytest.mark.parametrize("k,d,n,splits", [
     (3200, 37504, 64, 10),    # 25 row tiles: 250 work-groups in one round (20 splits would be two rounds of 30 stages for one of 59)
 ])
@@ -384,4 +399,18 @@ for params, n, dtype in [((9486, 2048, 149, 32, 4, 8), 312, F16), ((4194304, 819
     assert s.apply_rows(n, dtype) == 0 and s.info().last_mode == mode.value, (params, n, s.info().last_mode, mode.value)
     modes.add(mode.value)
 assert modes == {0, 1, 2}
+""")
+
+
+def test_the_rows_calls_checked_against_the_oracle_take_the_forms_that_they_name(recorded):
+    from test_gpu_parity import ROWS_MANY
+    cases = [(params, n, pad, dtype, form) for params, n, pad, form32, form16 in ROWS_MANY
+             for dtype, form in (("F32", form32), ("BF16", form16), ("F16", form16))]
+    recorded(ROWS_FORM + f"""
+for params, n, pad, dtype, want in {cases!r}:
+    s = Sketch(*params)
+    mt, et, mode, z, nw, chains = form(s, n, globals()[dtype], s.d + pad)
+    assert f"{{mt}},{{et}},{{['in', 'out', 'outsplit'][mode]}}" == want and (chains == 0) == (mode == 1), (params, n, dtype, mt, et, mode, z, nw)
+    assert nw > 1 or et == 4, (params, n, dtype)
+    s.destroy()
 """)
