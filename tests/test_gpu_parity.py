@@ -394,18 +394,18 @@ ROWS_MANY = [
     # taken is checked on the host, in test_recorded_runtime.py): over 32 examples in tiles of 32 or 64 whose waves share the
     # stages, or in one launch
     ((9486, 2048, 149, 32, 4, 8), 312, 64, "1,1,out", "1,2,out"),      # 64 blocks of three stages, a partly filled last block
-    ((4288, 512, 268, 32, 2, 4), 970, 0, "1,1,out", "1,1,out"),           # many example tiles, the last one of 10 examples
-    ((20160, 1280, 1008, 64, 1, 8), 129, 1, "2,2,out", "2,2,out"),     # kappa = 1, rows that start inside a dword
+    ((4288, 512, 268, 32, 2, 4), 970, 0, "1,1,out", "1,2,out"),           # many example tiles, the last one of 10 examples
+    ((20160, 1280, 1008, 64, 1, 8), 129, 1, "2,1,out", "2,2,out"),     # kappa = 1, rows that start inside a dword
     ((6142, 1024, 384, 64, 1, 8), 113, 0, "2,4,outsplit", "2,2,out"),     # (fp32: its sums are shorter as they are)
     ((16384, 2048, 256, 32, 4, 2), 65, 3, "1,1,out", "1,1,out"),
     ((11200, 2048, 88, 16, 4, 2), 200, 0, "1,2,out", "1,2,out"),          # blocks of 16 rows
     ((31930, 1280, 3193, 128, 2, 4), 97, 2, "4,1,outsplit", "4,2,outsplit"),   # blocks of 128 rows
     ((13548, 288, 424, 9, 3, 2), 161, 0, "2,2,in", "2,2,in"),             # Br not a power of two
     ((10030, 160, 1020, 16, 4, 8), 232, 0, "2,2,in", "2,2,in"),
-    ((4144, 80, 420, 8, 8, 2), 283, 0, "2,2,in", "2,2,in"),               # blocks of 8 rows
+    ((4144, 80, 420, 8, 8, 2), 283, 0, "2,2,in", "2,4,in"),               # blocks of 8 rows
     ((9482, 160, 1038, 16, 8, 2), 125, 0, "4,2,in", "4,2,in"),            # 128 stacked rows
     ((8899, 320, 923, 32, 4, 8), 109, 0, "4,2,in", "4,2,in"),
-    ((4354, 2048, 140, 64, 2, 4), 36, 0, "4,2,in", "2,1,out"),
+    ((4354, 2048, 140, 64, 2, 4), 36, 0, "2,1,out", "2,2,out"),
 ]
 
 
