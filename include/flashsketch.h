@@ -108,9 +108,13 @@ typedef enum {
 
 /* Kernel variants of the BLOCKPERM apply (fs_sketch_set_variant). */
 typedef enum {
-  FS_VARIANT_AUTO = 0,    /* pick by shape/dtype/alignment (calls of up to four vectors
-                             that FS_VARIANT_MFMA would take may run, and are reported as
-                             that variant, on a kernel that sums without matrix cores)  */
+  FS_VARIANT_AUTO = 0,    /* pick by shape/dtype/alignment.  Calls that FS_VARIANT_MFMA
+                             would take are reported as that variant, but may run in
+                             another form, with another order of summation: up to four
+                             vectors on a kernel that sums without matrix cores, small
+                             calls of over 128 columns and rows calls of over 32 examples
+                             output-stationary in one launch, and the latter in smaller
+                             tiles                                                     */
   FS_VARIANT_GENERIC = 1, /* one lane per column, LDS-private output tile, any Br   */
   FS_VARIANT_MFMA = 2     /* +-1 operand on the matrix cores: any power-of-two Br
                              (other Br while its kappa slots, each padded to the next
@@ -213,7 +217,9 @@ fs_status fs_sketch_apply_static(fs_sketch_t h, const void* A, int64_t lda, int6
  *    wiring slots (G is read once per group).  Also needs 130*ldg*sizeof(elt) < 2^31 (input-stationary: 34*ldg*sizeof(elt));
  *    any Bc, and d need not be a multiple of it.
  *    When there are too few blocks and examples for the chip, the stages of a work-group are
- *    split over grid.z in both forms.
+ *    split over grid.z in both forms.  FS_VARIANT_AUTO stores calls that are input-stationary by
+ *    this rule output-stationary (16 <= Br <= 128; up to 32 examples any Br <= 128) where one launch is
+ *    priced lower than two, in fp32 beyond 32 examples only if the result is as exact.
  *    Fastest when G, ldg*sizeof(elt) and Bc*sizeof(elt) are multiples of 16
  *    bytes; a piece that starts on an odd 16-bit entry is loaded as the five dwords that hold
  *    it (up to 2 bytes before G's first and after its last entry, inside the same dword, are
