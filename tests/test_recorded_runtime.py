@@ -412,3 +412,13 @@ for params, n, pad, dtype, want in {cases!r}:
     assert nw > 1 or et == 4, (params, n, dtype)
     s.destroy()
 """)
+
+
+@pytest.mark.parametrize("params,n,out", [
+    ((8296, 1024, 260, 32, 2, 4), 197, True),       # two stages a wave, one before: error 8.54e-8, 8.55e-8
+    ((25920, 1024, 832, 32, 2, 4), 312, False),     # four, two before: 1.10e-7, 1.03e-7
+    ((31704, 1024, 991, 32, 2, 4), 257, False),
+])
+def test_wide_fp32_column_calls_are_stored_in_one_launch_only_by_sums_about_as_short(recorded, params, n, out):
+    kernel = recorded(f"s = Sketch(*{params}); assert s.apply({n}, F32) == 0; print(s.kernel())").strip()
+    assert kernel.startswith("ksplit_kernel<f32,") and (",out," in kernel) == out and kernel.endswith("+reduce_planes") != out, kernel
